@@ -329,6 +329,7 @@ int launch_gemm(vlac_ctx* c, int epi, const bf16_t* wp, const float* wscale, int
 bool gemm_can_fuse_norm(int n_rows_host, int decode_pos, int kpad);
 
 // embed.hip
+int embed_init();  // kernel attribute setup; returns hipError_t
 void launch_embed_patches(vlac_ctx* c, const uint8_t* frame, int B, int H, int W, int patch,
                           const bf16_t* w_proj, const int32_t* reuse_order, const int32_t* reuse_count,
                           int stride, const int32_t* layer_count, float* embeds, int L, hipStream_t st);

@@ -6,9 +6,11 @@
 //   e[i, :] = (pixels_i / 127.5 - 1) . W,   pixels_i = patch i as [p rows][p cols][3] bytes.
 //
 // Work: (changed patches) x 3 p^2 x d multiply-adds against a matrix of a few MB that stays
-// in L2: plain fp32 FMAs, 8 patches per workgroup so that a weight is loaded once per 8
-// products; pixels are staged in LDS as fp32.  The patches to do are compacted into a list
-// first, so that the work is proportional to their number.
+// in L2, on the matrix cores: pixels / 127.5 - 1 = (2 pixels - 255) / 255, and 2 pixels - 255
+// is an odd integer of at most 8 bits, which bf16 holds exactly; so with bf16 weights every
+// product is exact and only the fp32 sum rounds, as it did with fp32 multiply-adds.  The
+// patches to do are compacted into a list first, so that the work is proportional to their
+// number.
 #include "common.h"
 
 // list[b][0 .. n_live[b]) = the patches of stream b that are NOT among the first m reuse
@@ -51,66 +53,195 @@ __global__ __launch_bounds__(256) void embed_mark_kernel(const int32_t* __restri
   if (tid == 0) n_live[b] = base;
 }
 
-constexpr int EMB_PB = 8;   // patches per workgroup
-constexpr int EMB_CH = 12;  // values of k per batch of weight loads
-
-// Workgroup (x: 256 output features, y: group of 8 live patches, z: stream).  Pixels of the
-// group go to LDS as fp32 [k][8 patches], so that a thread fetches the 8 values of one k
-// with two 16-byte reads (all lanes the same address) and does 8 multiply-adds per weight.
-__global__ __launch_bounds__(256) void embed_patches_kernel(const uint8_t* __restrict__ frame, int H, int W,
+// Workgroup (x: 512 / KS output features, y: group of 32 RT live patches, z: stream).  The pixels
+// of the group go to LDS as bf16 operands in fragment order ([k/16][lane] of 16 bytes, lane =
+// patch + 32 (k/8 % 2)).  KS = 1: a wave multiplies them by 128 features of its own; KS = 4: the
+// waves share 128 features, take a quarter of the k-tiles each, and their sums meet in LDS, which
+// gives a small call four times the workgroups and a quarter of the chain.
+// A wave's operand tile t (of 4) covers the features 4 j + t, j = lane % 32: a lane then reads
+// 4 neighbouring features of a weight row with one 8-byte load (w_proj is [k][feature], so the 8
+// values of k that an operand wants are 8 loads, 8 rows of it, and two byte permutations per
+// pair), and writes 4 neighbouring features of an embedding row with one 16-byte store.
+// Bound by latency at one stream and by staging the pixels and writing the output at many.
+// Measured at d_model 4096, 14 x 14 patches, kernel alone, against the fp32 multiply-adds of 8
+// patches per workgroup that this replaces: 166 patches of one stream 12 us (42 before),
+// 4800 patches of 8 streams 66 us (537 before; 192 with KS = 4 and two row tiles, which stages
+// the same pixels 32 times).
+// (EMB_D k-tiles of weights in flight per wave: with 2 row tiles only 2, so that a
+// second workgroup fits the CU: 85 -> 72 us per call at 8 x 1024 patches)
+template <int RT, int KS, bool VEC>
+__global__ __launch_bounds__(256, 2) void embed_patches_kernel(const uint8_t* __restrict__ frame, int H, int W,
                                                             int patch, const bf16_t* __restrict__ w_proj,
                                                             int d, const int* __restrict__ list,
                                                             const int* __restrict__ n_live,
                                                             float* __restrict__ embeds, int L) {
-  extern __shared__ float4 px4[];  // [dp][2] float4 = [dp][8] floats
-  float* px = (float*)px4;
-  const int gw = W / patch, dp = 3 * patch * patch;
-  const int b = blockIdx.z, g0 = blockIdx.y * EMB_PB, n = blockIdx.x * 256 + threadIdx.x;
+  extern __shared__ uint4 px[];  // [RT][k-tiles][64]; KS = 4: then, per row tile, the waves' sums
+  constexpr int PB = 32 * RT, EMB_D = RT == 2 ? 2 : 4;
+  const int gw = W / patch, dp = 3 * patch * patch, prow = 3 * patch, n_kt = (dp + 15) >> 4;
+  const int b = blockIdx.z, g0 = blockIdx.y * PB, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int nl = n_live[b];
   if (g0 >= nl) return;
   const int* mine = list + (size_t)b * 4096 + g0;
-  const int cnt = min(EMB_PB, nl - g0);
-  const int prow = 3 * patch;  // bytes of one pixel row of a patch
-  const int dpp = (dp + EMB_CH - 1) / EMB_CH * EMB_CH;  // rows of k past dp hold zeros
-  for (int e = threadIdx.x; e < dpp * EMB_PB; e += 256) {
-    const int j = e / dpp, k = e - j * dpp;  // consecutive threads: consecutive bytes of a patch row
-    float v = 0.f;
-    if (j < cnt && k < dp) {
-      const int i = mine[j], r = i / gw, c = i - r * gw, y = k / prow, x = k - y * prow;
-      v = (float)frame[(((size_t)b * H + (size_t)r * patch + y) * W + (size_t)c * patch) * 3 + x] / 127.5f - 1.0f;
+  const int cnt = min(PB, nl - g0);
+  const int j = lane & 31, g = lane >> 5;
+  const int f0 = (KS == 1 ? blockIdx.x * 512 + 128 * w : blockIdx.x * 128) + 4 * j;  // this lane's 4 features
+  const int fl = min(f0, d - 4);                                                     // (d is a multiple of 32)
+
+  // this wave's k-tiles [kt0, kt1); weight rows past the last one are read again and meet zeros
+  const int kt0 = KS == 1 ? 0 : w * n_kt / 4, kt1 = KS == 1 ? n_kt : (w + 1) * n_kt / 4;
+  uint2 wb[EMB_D][8];
+  auto load_w = [&](int kt, uint2(&x)[8]) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const bf16_t* src = w_proj + (size_t)min(kt * 16 + 8 * g + u, dp - 1) * d + fl;
+      if constexpr (VEC) x[u] = *(const uint2*)src;
+      else x[u] = make_uint2(src[0] | ((uint32_t)src[1] << 16), src[2] | ((uint32_t)src[3] << 16));
     }
-    px[k * EMB_PB + j] = v;
+  };
+#pragma unroll
+  for (int s = 0; s < EMB_D; ++s) load_w(min(kt0 + s, n_kt - 1), wb[s]);
+
+  // pixels: a thread takes pixel row y of one patch, two pixels at a time where the row lies on
+  // an even address and starts at an even k; unused patches of the group stay undefined (an
+  // operand row only reaches its own result row)
+  uint16_t* px16 = (uint16_t*)px;
+  auto odd = [](uint32_t v) { return fmaf(2.f, (float)v, -255.f); };  // exact
+  for (int e = tid; e < PB * patch; e += 256) {
+    const int p = e % PB, y = e / PB;
+    if (p >= cnt) continue;
+    const int i = mine[p], r = i / gw, c = i - r * gw;
+    const uint8_t* src = frame + (((size_t)b * H + (size_t)r * patch + y) * W + (size_t)c * patch) * 3;
+    uint16_t* dst = px16 + (size_t)(p >> 5) * n_kt * 512 + (p & 31) * 8;
+    auto at = [&](int k) { return dst + (k >> 4) * 512 + ((k >> 3) & 1) * 256 + (k & 7); };
+    const int k0 = y * prow;
+    int x = 0;
+    if (((((uintptr_t)src) | (uintptr_t)k0) & 1) == 0) {
+      for (; x + 14 <= prow; x += 14) {
+        uint16_t v[7];
+#pragma unroll
+        for (int u = 0; u < 7; ++u) v[u] = *(const uint16_t*)(src + x + 2 * u);
+#pragma unroll
+        for (int u = 0; u < 7; ++u)
+          *(uint32_t*)at(k0 + x + 2 * u) = __builtin_amdgcn_perm(__float_as_uint(odd((uint32_t)v[u] >> 8)),
+                                                                 __float_as_uint(odd((uint32_t)v[u] & 255u)), 0x07060302u);
+      }
+    }
+    for (; x < prow; ++x) *at(k0 + x) = (uint16_t)(__float_as_uint(odd(src[x])) >> 16);
+  }
+  for (int e = tid; e < PB * (n_kt * 16 - dp); e += 256) {  // k past the last pixel: zeros
+    const int p = e % PB, k = dp + e / PB;
+    px16[(size_t)(p >> 5) * n_kt * 512 + (size_t)(k >> 4) * 512 + ((k >> 3) & 1) * 256 + (p & 31) * 8 + (k & 7)] = 0;
   }
   __syncthreads();
-  if (n >= d) return;
-  float acc[EMB_PB];
+
+  f32x16 acc[RT][4];
 #pragma unroll
-  for (int j = 0; j < EMB_PB; ++j) acc[j] = 0.f;
-  // weights of EMB_CH values of k at a time, the next batch in flight behind the FMAs
-  // (past the end the last row is fetched again and meets the zeros in LDS)
-  uint16_t wa[EMB_CH], wb[EMB_CH];
-  const bf16_t* wcol = w_proj + n;
+  for (int m = 0; m < RT; ++m)
 #pragma unroll
-  for (int u = 0; u < EMB_CH; ++u) wa[u] = wcol[(size_t)min(u, dp - 1) * d];
-  for (int k0 = 0; k0 < dpp; k0 += EMB_CH) {
+    for (int t = 0; t < 4; ++t)
 #pragma unroll
-    for (int u = 0; u < EMB_CH; ++u) wb[u] = wcol[(size_t)min(k0 + EMB_CH + u, dp - 1) * d];
+      for (int i = 0; i < 16; ++i) acc[m][t][i] = 0.f;
+  auto step = [&](int kt, uint2(&x)[8]) {
+    // operand of tile t: the 8 values of k of feature 4 j + t, a half of a dword per weight row
+    uint4 op[4];
 #pragma unroll
-    for (int u = 0; u < EMB_CH; ++u) {
-      const float w = __uint_as_float((uint32_t)wa[u] << 16);  // bf16 -> fp32
-      const float4 a = px4[2 * (k0 + u)], c = px4[2 * (k0 + u) + 1];
-      acc[0] = fmaf(a.x, w, acc[0]); acc[1] = fmaf(a.y, w, acc[1]);
-      acc[2] = fmaf(a.z, w, acc[2]); acc[3] = fmaf(a.w, w, acc[3]);
-      acc[4] = fmaf(c.x, w, acc[4]); acc[5] = fmaf(c.y, w, acc[5]);
-      acc[6] = fmaf(c.z, w, acc[6]); acc[7] = fmaf(c.w, w, acc[7]);
+    for (int t = 0; t < 4; ++t) {
+      const uint32_t sel = (t & 1) ? 0x07060302u : 0x05040100u;
+      uint32_t v[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const uint32_t lo = (t >> 1) ? x[2 * q].y : x[2 * q].x;
+        const uint32_t hi = (t >> 1) ? x[2 * q + 1].y : x[2 * q + 1].x;
+        v[q] = __builtin_amdgcn_perm(hi, lo, sel);
+      }
+      op[t] = make_uint4(v[0], v[1], v[2], v[3]);
     }
+    load_w(min(kt + EMB_D, n_kt - 1), x);
 #pragma unroll
-    for (int u = 0; u < EMB_CH; ++u) wa[u] = wb[u];
+    for (int m = 0; m < RT; ++m) {
+      const uint4 q = px[((size_t)m * n_kt + kt) * 64 + lane];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) acc[m][t] = mfma32<false>(q, op[t], acc[m][t]);
+    }
+  };
+  // (whole groups without a branch inside, so that the loads of EMB_D k-tiles stay in flight)
+  int kt = kt0;
+  for (; kt + EMB_D <= kt1; kt += EMB_D) {
+#pragma unroll
+    for (int s = 0; s < EMB_D; ++s) step(kt + s, wb[s]);
   }
 #pragma unroll
-  for (int j = 0; j < EMB_PB; ++j)
-    if (j < cnt) embeds[((size_t)b * L + mine[j]) * d + n] = acc[j];
+  for (int s = 0; s < EMB_D - 1; ++s)
+    if (kt + s < kt1) step(kt + s, wb[s]);
+
+  auto store = [&](int p, float4 s) {
+    if (p < cnt && f0 < d) {
+      float* out = embeds + ((size_t)b * L + mine[p]) * d + f0;
+      s.x /= 255.f; s.y /= 255.f; s.z /= 255.f; s.w /= 255.f;
+      if constexpr (VEC) {
+        *(float4*)out = s;
+      } else {
+        out[0] = s.x; out[1] = s.y; out[2] = s.z; out[3] = s.w;
+      }
+    }
+  };
+  if constexpr (KS == 1) {
+#pragma unroll
+    for (int m = 0; m < RT; ++m)
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        store(32 * m + 8 * (i >> 2) + 4 * g + (i & 3), make_float4(acc[m][0][i], acc[m][1][i], acc[m][2][i], acc[m][3][i]));
+    return;
+  }
+  // KS = 4: wave w finishes the registers 4 w .. 4 w + 3 of every tile (patches 8 w + 4 g + e), so
+  // that all four waves store; the others' parts go through LDS, [wave][register][lane][tile]
+  float* part = (float*)px;
+#pragma unroll
+  for (int m = 0; m < RT; ++m) {
+    __syncthreads();  // (the pixels, or the sums of the row tile before, are no longer read)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      if ((i >> 2) != w)
+        *(float4*)(part + (((size_t)w * 16 + i) * 64 + lane) * 4) =
+            make_float4(acc[m][0][i], acc[m][1][i], acc[m][2][i], acc[m][3][i]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      if ((i >> 2) != w) continue;
+      float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int ww = 0; ww < 4; ++ww) {  // fixed order
+        const float4 q = ww == w ? make_float4(acc[m][0][i], acc[m][1][i], acc[m][2][i], acc[m][3][i])
+                                 : *(const float4*)(part + (((size_t)ww * 16 + i) * 64 + lane) * 4);
+        s.x += q.x; s.y += q.y; s.z += q.z; s.w += q.w;
+      }
+      store(32 * m + 8 * (i >> 2) + 4 * g + (i & 3), s);
+    }
+  }
 }
+
+// LDS: the pixel operands of the group; KS = 4: or the four waves' sums of one row tile
+static size_t embed_lds(int RT, int KS, int dp) {
+  return std::max((size_t)RT * ((dp + 15) / 16) * 1024, KS == 1 ? (size_t)0 : (size_t)65536);
+}
+
+int embed_init() {
+  hipError_t e;
+#define VLAC_EMB_SET(RT_, KS_, VEC_)                                                                     \
+  if ((e = hipFuncSetAttribute((const void*)embed_patches_kernel<RT_, KS_, VEC_>,                         \
+                               hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)) != hipSuccess) return (int)e;
+  VLAC_EMB_SET(1, 4, true) VLAC_EMB_SET(1, 4, false) VLAC_EMB_SET(2, 1, true) VLAC_EMB_SET(2, 1, false)
+#undef VLAC_EMB_SET
+  return 0;
+}
+
+// Workgroups of 512 features and 64 patches from the size on at which they fill the chip once
+// (256 of them; the number of live patches is known on the device only, so all are counted), and
+// patches of up to 15 x 15 pixels, two groups of which fit the LDS of a CU.  Both sides, per call: at
+// 128 such workgroups (4 x 256 patches, d_model 4096) 29 us against 22 with KS = 4, at 256 (2 x
+// 1024) 33 against 38, at 1024 (8 x 1024) 85 against 117.
+static const long long kEmbWide = 256;
 
 void launch_embed_patches(vlac_ctx* c, const uint8_t* frame, int B, int H, int W, int patch,
                           const bf16_t* w_proj, const int32_t* reuse_order, const int32_t* reuse_count,
@@ -118,8 +249,17 @@ void launch_embed_patches(vlac_ctx* c, const uint8_t* frame, int B, int H, int W
   const int L_v = (H / patch) * (W / patch), d = c->cfg.d_model, dp = 3 * patch * patch;
   hipLaunchKernelGGL(embed_mark_kernel, dim3(B), dim3(256), 0, st, reuse_order, reuse_count, stride,
                      layer_count, c->cfg.n_layers, L_v, c->flags, c->embed_list, c->embed_n);
-  hipLaunchKernelGGL(embed_patches_kernel, dim3((d + 255) / 256, (L_v + EMB_PB - 1) / EMB_PB, B), dim3(256),
-                     (size_t)EMB_PB * ((dp + EMB_CH - 1) / EMB_CH * EMB_CH) * sizeof(float), st, frame, H, W,
-                     patch, w_proj, d, c->embed_list,
-                     c->embed_n, embeds, L);
+  const bool wide = (long long)((d + 511) / 512) * ((L_v + 63) / 64) * B >= kEmbWide && embed_lds(2, 1, dp) <= 80 * 1024;
+  // (8-byte weight loads and 16-byte stores where the caller's buffers allow them)
+  const bool vec = (uintptr_t)w_proj % 8 == 0 && (uintptr_t)embeds % 16 == 0;
+#define VLAC_EMB(RT_, KS_, VEC_)                                                                           \
+  hipLaunchKernelGGL((embed_patches_kernel<RT_, KS_, VEC_>),                                               \
+                     dim3((d + 512 / KS_ - 1) / (512 / KS_), (L_v + 32 * RT_ - 1) / (32 * RT_), B), dim3(256), \
+                     embed_lds(RT_, KS_, dp), st, frame, H, W, patch, w_proj, d, c->embed_list, c->embed_n, embeds, L)
+  if (wide) {
+    if (vec) VLAC_EMB(2, 1, true); else VLAC_EMB(2, 1, false);
+  } else {
+    if (vec) VLAC_EMB(1, 4, true); else VLAC_EMB(1, 4, false);
+  }
+#undef VLAC_EMB
 }

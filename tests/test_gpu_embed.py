@@ -69,6 +69,47 @@ def test_embed_matches_oracle(H, W, patch):
         gm.close()
 
 
+@pytest.mark.parametrize("B,H,W,patch,skew", [
+    (1, 13 * 5, 13 * 7, 13, 0),     # odd rows of pixels, 35 patches: one past a row tile
+    (2, 26 * 2, 26 * 16, 26, 0),    # the largest patch: 127 k-tiles, exactly one row tile
+    (1, 14, 14 * 33, 14, 1),        # buffers that allow no wide loads and stores
+    (4, 256, 256, 4, 0),            # 256 groups of 64 patches: the wide form
+    (4, 256, 256, 4, 1),
+    (7, 3 * 40, 3 * 50, 3, 0),      # odd patches, the wide form with a ragged last group
+])
+def test_embed_at_the_edges_of_its_tiles(B, H, W, patch, skew):
+    """Every product is exact, so what is left is the rounding of an fp32 sum of 3 patch^2 terms
+    of magnitude |w| <= 5 std: n 2^-24 sqrt(n) std-sized terms stay below 1e-5 here."""
+    import torch
+    cfg = synth.CONFIGS["tiny"]
+    gm = GpuModel(cfg, seed=0, max_batch=B, max_seq=32)
+    try:
+        V, dev = gm.V, gm.device
+        rng = np.random.default_rng(B + H + W + patch)
+        L_v, dp, d = (H // patch) * (W // patch), 3 * patch * patch, cfg.d_model
+        frames = rng.integers(0, 256, size=(B, H, W, 3), dtype=np.uint8)
+        w = synth.round_bf16(synth.projection_matrix(d, patch, 9))
+        reuse = [rng.choice(L_v, size=min(b, L_v), replace=False).tolist() for b in range(B)]
+        order = torch.zeros((B, max(1, B)), dtype=torch.int32, device=dev)
+        for b, r in enumerate(reuse):
+            order[b, :len(r)] = torch.tensor(r, dtype=torch.int32)
+        count = torch.tensor([len(r) for r in reuse], dtype=torch.int32, device=dev)
+        wbuf = torch.zeros(dp * d + 8, dtype=torch.bfloat16, device=dev)[skew:skew + dp * d].view(dp, d)
+        wbuf.copy_(torch.tensor(w))
+        fbuf = torch.zeros(frames.size + 8, dtype=torch.uint8, device=dev)[skew:skew + frames.size].view(frames.shape)
+        fbuf.copy_(torch.tensor(frames))
+        out = torch.full((B * L_v * d + 8,), -7.0, device=dev)[skew:skew + B * L_v * d].view(B, L_v, d)
+        V.vlac_embed_patches(gm.ctx, fbuf, B, H, W, patch, wbuf, order, count, order.shape[1], None, out, L_v)
+        got = out.cpu().numpy()
+        for b in range(B):
+            want = O.embed_patches(frames[b], patch, w, reuse[b])
+            keep = ~np.isnan(want[:, 0])
+            assert np.abs(got[b][keep] - want[keep]).max() <= 1e-5
+            assert np.all(got[b][~keep] == -7.0)
+    finally:
+        gm.close()
+
+
 def test_embed_feeds_the_sparse_prefill():
     """Two steps at the tiny configuration: frame -> Alg. 1 -> embeddings of the recomputed
     patches only -> sparse prefill, all on the GPU, against the oracle's chain."""
