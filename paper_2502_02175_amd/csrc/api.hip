@@ -63,7 +63,7 @@ void free_all(vlac_ctx* c) {
   void* dev[] = {c->w_head, c->s_head, c->scale_tmp, c->wdeq, c->embed, c->g_final, c->rope_cos, c->rope_sin, c->h, c->hdec, c->xa, c->xf,
                  c->qbuf, c->partial, c->rpart, c->counters, c->rows, c->prev_slot, c->n_rows, c->slot_off, c->rank,
                  c->m_layer, c->n_rows_bl, c->statp, c->stat_counters, c->logits, c->tokens,
-                 c->dec_rows, c->terms, c->flags, c->embed_list, c->embed_n, c->relevance, c->errword, c->scratch_i,
+                 c->dec_rows, c->terms, c->flags, c->embed_list, c->embed_n, c->relevance, c->entropy, c->ratio_counters, c->errword, c->scratch_i,
                  c->zero_tile};
   for (void* p : dev) (void)hipFree(p);
   for (int i = 0; i < c->prof_cap; ++i) {
@@ -215,12 +215,15 @@ int vlac_create(const vlac_model_cfg* cfg, vlac_ctx** out) {
   A_(embed_list, (size_t)mb * 4096);
   A_(embed_n, mb);
   A_(relevance, (size_t)mb * 4096);
+  A_(entropy, (size_t)mb * nl);
+  A_(ratio_counters, mb);
   A_(errword, 1);
   A_(zero_tile, 512);
   A_(scratch_i, 64);
 #undef A_
   if (e == hipSuccess) e = hipMemset(ctx->counters, 0, ctx->n_counters * sizeof(int));
   if (e == hipSuccess) e = hipMemset(ctx->stat_counters, 0, mb * sizeof(int));
+  if (e == hipSuccess) e = hipMemset(ctx->ratio_counters, 0, mb * sizeof(int));
   if (e == hipSuccess) e = hipMemset(ctx->errword, 0, sizeof(int));
   if (e == hipSuccess) e = hipMemset(ctx->zero_tile, 0, 512 * sizeof(bf16_t));
   // operand padding (rows of the last 32-row tile, K padding) must be finite: zero once
@@ -460,10 +463,10 @@ int vlac_select_static(vlac_ctx* ctx, const uint8_t* frame_prev, const uint8_t* 
     n_rel = nr < 0 ? 0 : (nr > (double)L_v ? (int)L_v : (int)nr);
   }
   hipStream_t st = (hipStream_t)stream;
-  launch_patch_terms(frame_prev, frame_cur, B, H, W, patch, ctx->terms, st);
-  launch_select(ctx->terms, B, (int)L_v, tau_num, tau_den, top_k, attn_mean, ctx->cfg.n_layers,
-                layer_mask, n_rel, ctx->flags, ctx->relevance, out_idx, out_order, out_count,
-                out_relevance, stride, st);
+  launch_patch_terms(frame_prev, frame_cur, B, H, W, patch, ctx->terms, attn_mean, ctx->cfg.n_layers, layer_mask,
+                     ctx->relevance, st);
+  launch_select(ctx->terms, B, (int)L_v, tau_num, tau_den, top_k, n_rel, ctx->flags, ctx->relevance, out_idx, out_order,
+                out_count, out_relevance, stride, st);
   VLAC_HIP(hipGetLastError());
   return VLAC_OK;
 }
@@ -476,7 +479,7 @@ int vlac_layer_ratio(vlac_ctx* ctx, const float* attn_mean, int B, int L_v, floa
   if (B < 1 || B > ctx->cfg.max_batch || L_v < 1 || L_v > 65536) return VLAC_E_RANGE;
   if (gain_k != gain_k) return VLAC_E_RANGE;
   launch_layer_ratio(attn_mean, ctx->cfg.n_layers, B, L_v, gain_k, reuse_count, out_alpha,
-                     out_layer_count, (hipStream_t)stream);
+                     out_layer_count, ctx->entropy, ctx->ratio_counters, (hipStream_t)stream);
   VLAC_HIP(hipGetLastError());
   return VLAC_OK;
 }

@@ -167,6 +167,8 @@ struct vlac_ctx {
   int* embed_list;  // [max_batch][4096] patches to embed
   int* embed_n;     // [max_batch]
   float* relevance; // [max_batch, 4096]
+  unsigned long long* entropy;  // [max_batch, n_layers] fp64 bits, changes hands inside layer_ratio_kernel
+  int* ratio_counters;          // [max_batch] its arrival counters (self-resetting)
   bf16_t* zero_tile; // one operand tile of zeros
   int* errword;     // device error bits
   int* scratch_i;   // small int scratch
@@ -189,16 +191,17 @@ struct vlac_ctx {
 // ---- launchers implemented in the .hip files (all asynchronous on `st`) ----
 
 // select.hip
-void launch_patch_terms(const uint8_t* prev, const uint8_t* cur, int B, int H, int W, int patch,
-                        uint32_t* terms, hipStream_t st);
-void launch_select(const uint32_t* terms, int B, int L_v, int tau_num, int tau_den, int top_k,
-                   const float* attn_mean, int n_layers, const uint8_t* layer_mask_host, int n_rel,
-                   uint8_t* flags, float* relevance_ws, int32_t* out_idx, int32_t* out_order,
+// terms of every patch, and its score: attn_mean averaged over the layers of the mask (0 without attn_mean)
+void launch_patch_terms(const uint8_t* prev, const uint8_t* cur, int B, int H, int W, int patch, uint32_t* terms,
+                        const float* attn_mean, int n_layers, const uint8_t* layer_mask_host, float* score,
+                        hipStream_t st);
+void launch_select(const uint32_t* terms, int B, int L_v, int tau_num, int tau_den, int top_k, int n_rel,
+                   uint8_t* flags, const float* score, int32_t* out_idx, int32_t* out_order,
                    int32_t* out_count, float* out_relevance, int stride, hipStream_t st);
 int select_scratch_init();  // resolves the fixed scratch of vlac_select_static_noalloc on the current device; hipError_t
 void launch_layer_ratio(const float* attn_mean, int n_layers, int B, int L_v, float gain_k,
                         const int32_t* reuse_count, float* out_alpha, int32_t* out_layer_count,
-                        hipStream_t st);
+                        unsigned long long* ent, int* counters, hipStream_t st);
 
 // rows.hip
 void launch_plan(vlac_ctx* c, int B, int L_v, int L_t, const int32_t* reuse_order,

@@ -1,10 +1,11 @@
 // Token selection (Alg. 1 of VLA-Cache) and the layer-adaptive ratio (Sec. 3.4).
 //
-//   patch_terms_kernel   Eq. (sim): per patch the exact integers dot, |P_t|^2, |P_{t-1}|^2
+//   patch_terms_kernel   Eq. (sim): per patch the exact integers dot, |P_t|^2, |P_{t-1}|^2, and
+//                        the task-relevance score (mean over layers)
 //   select_rank_kernel   threshold (Sim >= tau, cross-multiplied in 128-bit integers),
 //                        Top-k by exact rational comparison (Eq. topk), task-relevance
 //                        quantile filter (Eq. ptask, Eq. pfinal)
-//   select_compact_kernel  ascending index list and reuse order
+//   select_order_kernel  ascending index list and reuse order
 //   layer_ratio_kernel   entropy ratio and Eq. (reuse_ratio), in fp64
 //
 // All of this is HBM/latency-bound integer work: 2*H*W*3 bytes of pixels per
@@ -16,17 +17,55 @@
 
 typedef unsigned __int128 u128;
 
+#define SEL_MAX_LV 4096
+struct LayerMask { uint32_t w[16]; };  // bit l set = layer l is averaged over (<= 512 layers)
+
+// The task-relevance score of 256 patches of stream b: the mean over the layers of the mask, fp32,
+// layers in ascending order.  Sixteen layers are asked for at a time, those outside the mask too
+// (their values are dropped, not added).
+__device__ inline void relevance_scores(const float* __restrict__ attn_mean, int n_layers, int B, int b, int L_v,
+                                        const LayerMask& mask, int j, float* __restrict__ score) {
+  if (j >= L_v) return;
+  float s = 0.f;
+  if (attn_mean) {
+    int n = 0;
+    for (int l0 = 0; l0 < n_layers; l0 += 16) {
+      float t[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) t[u] = attn_mean[((size_t)min(l0 + u, n_layers - 1) * B + b) * L_v + j];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        const int l = l0 + u;
+        const bool on = l < n_layers && ((mask.w[(l0 >> 5) & 15] >> (l & 31)) & 1u);
+        s = on ? s + t[u] : s;
+        n += on;
+      }
+    }
+    s = s / (float)(n > 0 ? n : 1);
+  }
+  score[(size_t)b * L_v + j] = s;
+}
+
 // ---------------------------------------------------------------------------
-// Eq. (sim) terms.  One workgroup per (patch row, stream).
+// Eq. (sim) terms.  One workgroup per (patch row, stream); behind them in the grid the workgroups
+// that compute the scores, 256 patches each, beside the pixels instead of once per workgroup of
+// the ranking kernel (64 times per stream at 1024 patches: 59 us of ranking for 8 such streams,
+// 18 us now).
 // ---------------------------------------------------------------------------
 template <int VEC>
 __global__ __launch_bounds__(256) void patch_terms_kernel(const uint8_t* __restrict__ prev,
                                                           const uint8_t* __restrict__ cur, int H,
                                                           int W, int patch,
-                                                          uint32_t* __restrict__ terms) {
+                                                          uint32_t* __restrict__ terms,
+                                                          const float* __restrict__ attn_mean, int n_layers,
+                                                          LayerMask layer_mask, float* __restrict__ score) {
   extern __shared__ uint32_t acc[];  // [gw][3]
   const int gw = W / patch, gh = H / patch;
   const int b = blockIdx.y, pr = blockIdx.x, tid = threadIdx.x;
+  if (pr >= gh) {
+    relevance_scores(attn_mean, n_layers, gridDim.y, b, gw * gh, layer_mask, (pr - gh) * 256 + tid, score);
+    return;
+  }
   const size_t base = ((size_t)b * H + (size_t)pr * patch) * W * 3;
   const int rowbytes = W * 3, pbytes = patch * 3, nbytes = patch * rowbytes;
   for (int i = tid; i < gw * 3; i += 256) acc[i] = 0;
@@ -91,16 +130,23 @@ __global__ __launch_bounds__(256) void patch_terms_kernel(const uint8_t* __restr
 }
 
 void launch_patch_terms(const uint8_t* prev, const uint8_t* cur, int B, int H, int W, int patch,
-                        uint32_t* terms, hipStream_t st) {
+                        uint32_t* terms, const float* attn_mean, int n_layers, const uint8_t* layer_mask_host,
+                        float* score, hipStream_t st) {
   const int gw = W / patch, gh = H / patch;
+  LayerMask lm;
+  for (int i = 0; i < 16; ++i) lm.w[i] = 0;
+  for (int l = 0; l < n_layers && l < 512; ++l)
+    if (!layer_mask_host || layer_mask_host[l]) lm.w[l >> 5] |= 1u << (l & 31);
   const size_t shm = (size_t)gw * 3 * sizeof(uint32_t);
   const bool vec = ((size_t)patch * W * 3) % 16 == 0 && ((size_t)H * W * 3) % 16 == 0 &&
                    ((uintptr_t)prev % 16 == 0) && ((uintptr_t)cur % 16 == 0);
-  dim3 grid(gh, B);
-  if (vec)
-    hipLaunchKernelGGL(patch_terms_kernel<16>, grid, dim3(256), shm, st, prev, cur, H, W, patch, terms);
-  else
-    hipLaunchKernelGGL(patch_terms_kernel<1>, grid, dim3(256), shm, st, prev, cur, H, W, patch, terms);
+  dim3 grid(gh + (gw * gh + 255) / 256, B);
+#define VLAC_TERMS(VEC_)                                                                                        \
+  hipLaunchKernelGGL(patch_terms_kernel<VEC_>, grid, dim3(256), shm, st, prev, cur, H, W, patch, terms, attn_mean, \
+                     n_layers, lm, score)
+  if (vec) VLAC_TERMS(16);
+  else VLAC_TERMS(1);
+#undef VLAC_TERMS
 }
 
 // ---------------------------------------------------------------------------
@@ -115,9 +161,6 @@ __device__ inline Frac sim_fraction(uint32_t dot, uint32_t na, uint32_t nb) {
   return {(uint64_t)dot * dot, (uint64_t)na * nb};
 }
 
-#define SEL_MAX_LV 4096
-struct LayerMask { uint32_t w[16]; };  // bit l set = layer l is averaged over (<= 512 layers)
-
 // grid (ceil(L_v / 16), B).  flags[b, i] = 1 iff patch i is in P_final.
 // A workgroup ranks 256 / SEL_LPT patches, SEL_LPT lanes to a patch: every lane counts, over
 // its share of the other patches, those that come before its patch (by similarity for Top-k,
@@ -129,7 +172,7 @@ struct LayerMask { uint32_t w[16]; };  // bit l set = layer l is averaged over (
 template <int SEL_LPT>
 __global__ __launch_bounds__(256) void select_rank_kernel(
     const uint32_t* __restrict__ terms, int L_v, uint64_t tn2, uint64_t td2, int top_k,
-    const float* __restrict__ attn_mean, int n_layers, int B, LayerMask layer_mask, int n_rel, uint8_t* __restrict__ flags, float* __restrict__ relevance) {
+    const float* __restrict__ relevance, int n_rel, uint8_t* __restrict__ flags) {
   __shared__ double approx[SEL_MAX_LV];
   __shared__ float score[SEL_MAX_LV];
   __shared__ uint8_t pass[SEL_MAX_LV];
@@ -139,17 +182,7 @@ __global__ __launch_bounds__(256) void select_rank_kernel(
     const Frac f = sim_fraction(t[j * 3], t[j * 3 + 1], t[j * 3 + 2]);
     pass[j] = (u128)f.num * td2 >= (u128)tn2 * f.den;
     approx[j] = (double)f.num / (double)f.den;
-    float s = 0.f;
-    if (attn_mean) {
-      int n = 0;
-      for (int l = 0; l < n_layers; ++l)
-        if ((layer_mask.w[l >> 5] >> (l & 31)) & 1u) {
-          s += attn_mean[((size_t)l * B + b) * L_v + j];
-          ++n;
-        }
-      s = s / (float)(n > 0 ? n : 1);
-    }
-    score[j] = s;
+    score[j] = relevance[(size_t)b * L_v + j];
   }
   __syncthreads();
   constexpr int SEL_PPW = 256 / SEL_LPT;
@@ -178,7 +211,7 @@ __global__ __launch_bounds__(256) void select_rank_kernel(
     }
   }
   const float si = score[ii];
-  if (attn_mean && n_rel > 0) {
+  if (n_rel > 0) {
     // rank by score descending, ties -> lower index
     for (int j = sub; j < L_v; j += SEL_LPT) rr += (score[j] > si) || (score[j] == si && j < ii);
   }
@@ -188,142 +221,180 @@ __global__ __launch_bounds__(256) void select_rank_kernel(
     rr += __shfl_xor(rr, o);
   }
   if (!live || sub != 0) return;
-  bool keep = passed && rank < top_k;
-  if (attn_mean) {
-    if (keep && n_rel > 0) keep = rr >= n_rel;
-    relevance[(size_t)b * L_v + i] = si;
-  } else {
-    relevance[(size_t)b * L_v + i] = 0.f;
-  }
-  flags[(size_t)b * L_v + i] = keep;
+  flags[(size_t)b * L_v + i] = passed && rank < top_k && (n_rel <= 0 || rr >= n_rel);
 }
 
-// grid (B).  Ascending list, count, and the list ordered by (score asc, index asc).
-// The kept tokens are compacted first (ascending index, with their scores, in LDS); the
-// place of a kept token in the reuse order is then the number of kept tokens that come
-// before it, counted over the compact list only: its k-th entry precedes the i-th if its
-// score is lower, or equal with k < i (the compact list ascends by index).
-__global__ __launch_bounds__(256) void select_compact_kernel(
+// grid as select_rank_kernel.  Ascending list, count, and the list ordered by (score asc, index
+// asc).  A kept token's place in either list is the number of kept tokens that come before it, which
+// SEL_LPT lanes count together as above: no pass over the stream has to wait for another (one
+// workgroup per stream that compacted first: 5 us at 256 patches, 23 us at 1024; now 3.6 and 7.5 us).
+template <int SEL_LPT>
+__global__ __launch_bounds__(256) void select_order_kernel(
     const uint8_t* __restrict__ flags, const float* __restrict__ relevance, int L_v,
     int32_t* __restrict__ out_idx, int32_t* __restrict__ out_order, int32_t* __restrict__ out_count,
     float* __restrict__ out_relevance, int stride) {
-  __shared__ float cscore[SEL_MAX_LV];
-  __shared__ int cidx[SEL_MAX_LV];
-  __shared__ int wsum[4];
-  __shared__ int base_s;
-  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  if (tid == 0) base_s = 0;
+  __shared__ float score[SEL_MAX_LV];
+  __shared__ uint8_t kept[SEL_MAX_LV];
+  const int b = blockIdx.y, tid = threadIdx.x;
+  for (int k = tid; k < L_v; k += 256) {
+    score[k] = relevance[(size_t)b * L_v + k];
+    kept[k] = flags[(size_t)b * L_v + k];
+  }
   __syncthreads();
-  for (int c0 = 0; c0 < L_v; c0 += 256) {
-    const int i = c0 + tid;
-    int f = 0;
-    float sc = 0.f;
-    if (i < L_v) {
-      f = flags[(size_t)b * L_v + i];
-      sc = relevance[(size_t)b * L_v + i];
-      if (out_relevance) out_relevance[(size_t)b * L_v + i] = sc;
+  constexpr int SEL_PPW = 256 / SEL_LPT;
+  const int sub = tid % SEL_LPT, i = blockIdx.x * SEL_PPW + tid / SEL_LPT;
+  const bool live = i < L_v, count = blockIdx.x == 0 && tid < SEL_LPT;  // the first patch's lanes count all
+  const int ii = live ? i : 0;
+  const bool mine = live && kept[ii];
+  const float si = score[ii];
+  int pos = 0, ord = 0, all = 0;
+  if (mine || count) {
+    for (int k = sub; k < L_v; k += SEL_LPT) {
+      const float sk = score[k];
+      const int f = kept[k];
+      all += f;
+      pos += f & (k < ii);
+      ord += f & ((sk < si) || (sk == si && k < ii));
     }
-    const unsigned long long bal = __ballot(f);
-    const int inwave = __popcll(bal & ((1ull << lane) - 1ull));
-    if (lane == 0) wsum[w] = __popcll(bal);
-    __syncthreads();
-    int off = base_s;
-    for (int k = 0; k < w; ++k) off += wsum[k];
-    if (f) {
-      const int k = off + inwave;
-      cidx[k] = i;
-      cscore[k] = sc;
-      if (k < stride) out_idx[(size_t)b * stride + k] = i;
-    }
-    __syncthreads();
-    if (tid == 0) base_s += wsum[0] + wsum[1] + wsum[2] + wsum[3];
-    __syncthreads();
   }
-  const int n = base_s;
-  if (tid == 0) out_count[b] = n;
-  for (int i = tid; i < n; i += 256) {
-    const float si = cscore[i];
-    int ord = 0;
-    for (int k = 0; k < n; ++k) {
-      const float sk = cscore[k];
-      ord += (sk < si) || (sk == si && k < i);
-    }
-    if (ord < stride) out_order[(size_t)b * stride + ord] = cidx[i];
+#pragma unroll
+  for (int o = SEL_LPT / 2; o > 0; o >>= 1) {
+    pos += __shfl_xor(pos, o);
+    ord += __shfl_xor(ord, o);
+    all += __shfl_xor(all, o);
   }
+  if (!live || sub != 0) return;
+  if (count) out_count[b] = all;
+  if (out_relevance) out_relevance[(size_t)b * L_v + i] = si;
+  if (!mine) return;
+  if (pos < stride) out_idx[(size_t)b * stride + pos] = i;
+  if (ord < stride) out_order[(size_t)b * stride + ord] = i;
 }
 
-void launch_select(const uint32_t* terms, int B, int L_v, int tau_num, int tau_den, int top_k,
-                   const float* attn_mean, int n_layers, const uint8_t* layer_mask_host, int n_rel,
-                   uint8_t* flags, float* relevance_ws, int32_t* out_idx, int32_t* out_order,
+void launch_select(const uint32_t* terms, int B, int L_v, int tau_num, int tau_den, int top_k, int n_rel,
+                   uint8_t* flags, const float* score, int32_t* out_idx, int32_t* out_order,
                    int32_t* out_count, float* out_relevance, int stride, hipStream_t st) {
   const uint64_t tn2 = (uint64_t)tau_num * (uint64_t)tau_num;
   const uint64_t td2 = (uint64_t)tau_den * (uint64_t)tau_den;
-  LayerMask lm;
-  for (int i = 0; i < 16; ++i) lm.w[i] = 0;
-  for (int l = 0; l < n_layers && l < 512; ++l)
-    if (!layer_mask_host || layer_mask_host[l]) lm.w[l >> 5] |= 1u << (l & 31);
   const long long patches = (long long)B * L_v;
 #define VLAC_RANK(LPT_)                                                                            \
-  hipLaunchKernelGGL(select_rank_kernel<LPT_>, dim3((L_v * LPT_ + 255) / 256, B), dim3(256), 0, st, \
-                     terms, L_v, tn2, td2, top_k, attn_mean, n_layers, B, lm, n_rel, flags, relevance_ws)
-  if (patches <= 16384) VLAC_RANK(16);
-  else if (patches <= 65536) VLAC_RANK(4);
-  else VLAC_RANK(1);
+  {                                                                                                \
+    const dim3 grid((L_v * LPT_ + 255) / 256, B);                                                   \
+    hipLaunchKernelGGL(select_rank_kernel<LPT_>, grid, dim3(256), 0, st, terms, L_v, tn2, td2, top_k, score, n_rel, \
+                       flags);                                                                      \
+    hipLaunchKernelGGL(select_order_kernel<LPT_>, grid, dim3(256), 0, st, flags, score, L_v, out_idx, out_order, \
+                       out_count, out_relevance, stride);                                           \
+  }
+  if (patches <= 16384) VLAC_RANK(16)
+  else if (patches <= 65536) VLAC_RANK(4)
+  else VLAC_RANK(1)
 #undef VLAC_RANK
-  hipLaunchKernelGGL(select_compact_kernel, dim3(B), dim3(256), 0, st, flags, relevance_ws, L_v,
-                     out_idx, out_order, out_count, out_relevance, stride);
 }
 
 // ---------------------------------------------------------------------------
-// Sec. 3.4.  grid (B), fp64 throughout; sums are fixed-shape trees, so the
-// result does not depend on scheduling.
+// Sec. 3.4.  grid (layers, B), fp64 throughout: a workgroup per layer and stream, whose sums are
+// fixed-shape trees; the last workgroup of a stream to arrive (atomic counter, no waiting) turns
+// the entropies into the ratios.  So the result does not depend on scheduling.
+// Bound by latency at one stream (two rounds of loads, the hand-over, a short serial sum) and by
+// the fp64 logarithms at many: 7 us at 32 layers x 256 tokens (15 with all layers of a
+// stream in one workgroup and the ratios divided out one after the other), 10 us at 8
+// streams x 1024 tokens (38).
 // ---------------------------------------------------------------------------
-#define RATIO_MAX_LAYERS 512
+__device__ inline double wave_sum_f64(double v) {
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  return v;
+}
 
-__global__ __launch_bounds__(1024) void layer_ratio_kernel(
+__global__ __launch_bounds__(256) void layer_ratio_kernel(
     const float* __restrict__ attn_mean, int n_layers, int B, int L_v, float gain_k,
     const int32_t* __restrict__ reuse_count, float* __restrict__ out_alpha,
-    int32_t* __restrict__ out_layer_count) {
-  __shared__ double ent[RATIO_MAX_LAYERS];
-  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  // a wave per layer (layers w, w + 16, ...): its sums are shuffle trees of fixed shape
-  for (int l = w; l < n_layers; l += 16) {
-    const float* a = attn_mean + ((size_t)l * B + b) * L_v;
-    double s = 0;
-    for (int v = lane; v < L_v; v += 64) s += (double)a[v];
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-    const double tot = s;
-    double e = 0;
-    if (tot > 0)
-      for (int v = lane; v < L_v; v += 64) {
-        const double p = (double)a[v] / tot;
-        if (p > 0) e -= p * log(p);
-      }
-    for (int o = 32; o > 0; o >>= 1) e += __shfl_xor(e, o);
-    if (lane == 0) ent[l] = tot > 0 ? e : 0.0;
+    int32_t* __restrict__ out_layer_count, unsigned long long* ent, int* counters) {
+  __shared__ double red[2][4];
+  __shared__ int s_last;
+  const int l = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const float* a = attn_mean + ((size_t)l * B + b) * L_v;
+  float v[4];  // the first 1024 tokens stay in registers between the two passes
+  double s = 0;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) v[u] = tid + 256 * u < L_v ? a[tid + 256 * u] : 0.f;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) s += (double)v[u];
+  for (int i = tid + 1024; i < L_v; i += 256) s += (double)a[i];
+  s = wave_sum_f64(s);
+  if (lane == 0) red[0][w] = s;
+  __syncthreads();
+  const double tot = red[0][0] + red[0][1] + red[0][2] + red[0][3];
+  double e = 0;
+  if (tot > 0) {
+    auto add = [&](float x) {
+      const double p = (double)x / tot;
+      if (p > 0) e -= p * log(p);
+    };
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (256 * u < L_v) add(v[u]);
+    for (int i = tid + 1024; i < L_v; i += 256) add(a[i]);
   }
+  e = wave_sum_f64(e);
+  if (lane == 0) red[1][w] = e;
   __syncthreads();
   if (tid == 0) {
-    double cum = 0, best = 0;
-    const int cnt = reuse_count ? reuse_count[b] : 0;
-    for (int l = 0; l < n_layers; ++l) {
-      if (l > 0 && ent[l - 1] > 0) cum += (ent[l - 1] - ent[l]) / ent[l - 1];
-      double al = (double)gain_k * cum;
-      al = al < 0 ? 0 : (al > 1 ? 1 : al);
-      best = al > best ? al : best;
-      const float af = (float)best;
-      out_alpha[(size_t)b * n_layers + l] = af;
-      if (out_layer_count)
-        out_layer_count[(size_t)b * n_layers + l] = (int)floorf(af * (float)(cnt > 0 ? cnt : 0));
+    const double E = tot > 0 ? red[1][0] + red[1][1] + red[1][2] + red[1][3] : 0.0;
+    __hip_atomic_store(ent + (size_t)b * n_layers + l, __builtin_bit_cast(unsigned long long, E), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+    stores_done();
+    const int old = atomicAdd(counters + b, 1);
+    s_last = old == n_layers - 1;
+    if (s_last) counters[b] = 0;  // ready for the next call
+  }
+  __syncthreads();
+  if (!s_last || w > 0) return;
+  // One wave: 64 layers at a time, a lane per layer.  The sum over the layers is serial, in
+  // ascending order; the running maximum is exact in any order.
+  double cum = 0, best = 0, e_prev = 0;
+  const int cnt = reuse_count ? max(reuse_count[b], 0) : 0;
+  auto lane_f64 = [](double x, int k) {
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
+    return __builtin_bit_cast(double, (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, k) |
+                                          ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(u >> 32), k) << 32));
+  };
+  for (int l0 = 0; l0 < n_layers; l0 += 64) {
+    const int ll = l0 + lane, n = min(64, n_layers - l0);
+    const double E = __builtin_bit_cast(double, __hip_atomic_load(ent + (size_t)b * n_layers + min(ll, n_layers - 1),
+                                                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    double P = __shfl_up(E, 1);  // the layer before
+    if (lane == 0) P = e_prev;
+    const bool on = ll > 0 && P > 0;
+    const double r = on ? (P - E) / P : 0.0;
+    double mine = 0;
+    const unsigned long long adds = __ballot(on);
+    for (int k = 0; k < n; ++k) {
+      if ((adds >> k) & 1) cum += lane_f64(r, k);
+      mine = lane == k ? cum : mine;
+    }
+    e_prev = lane_f64(E, 63);
+    double al = (double)gain_k * mine;
+    al = al < 0 ? 0 : (al > 1 ? 1 : al);
+    double run = al > best ? al : best;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const double below = __shfl_up(run, o);
+      if (lane >= o && below > run) run = below;
+    }
+    best = lane_f64(run, n - 1);
+    if (ll < n_layers) {
+      const float af = (float)run;
+      out_alpha[(size_t)b * n_layers + ll] = af;
+      if (out_layer_count) out_layer_count[(size_t)b * n_layers + ll] = (int)floorf(af * (float)cnt);
     }
   }
 }
 
 void launch_layer_ratio(const float* attn_mean, int n_layers, int B, int L_v, float gain_k,
                         const int32_t* reuse_count, float* out_alpha, int32_t* out_layer_count,
-                        hipStream_t st) {
-  hipLaunchKernelGGL(layer_ratio_kernel, dim3(B), dim3(1024), 0, st, attn_mean, n_layers, B, L_v,
-                     gain_k, reuse_count, out_alpha, out_layer_count);
+                        unsigned long long* ent, int* counters, hipStream_t st) {
+  hipLaunchKernelGGL(layer_ratio_kernel, dim3(n_layers, B), dim3(256), 0, st, attn_mean, n_layers, B, L_v,
+                     gain_k, reuse_count, out_alpha, out_layer_count, ent, counters);
 }
 
 // ---------------------------------------------------------------------------
@@ -332,8 +403,8 @@ void launch_layer_ratio(const float* attn_mean, int n_layers, int B, int L_v, fl
 // keeps in its context) in a fixed array in device memory.  Every GPU holds its own copy of
 // the array at its own address; host code only ever uses the address that
 // hipGetSymbolAddress returns for the current device, never the array's name.  Nothing in
-// the array has to start at zero: patch_terms_kernel writes all terms of the call's patches,
-// select_rank_kernel all their scores and flags, before anything reads them.
+// the array has to start at zero: patch_terms_kernel writes all terms and scores of the call's
+// patches, select_rank_kernel all their flags, before anything reads them.
 // ---------------------------------------------------------------------------
 namespace {
 
@@ -408,8 +479,9 @@ extern "C" int vlac_select_static_noalloc(const uint8_t* frame_prev, const uint8
   float* score = (float*)(ws + kScoreOff);
   uint8_t* flags = (uint8_t*)(ws + kFlagsOff);
   hipStream_t st = (hipStream_t)stream;
-  launch_patch_terms(frame_prev, frame_cur, B, H, W, patch, terms, st);
-  launch_select(terms, B, (int)L_v, tau_num, tau_den, top_k, attn_mean, attn_mean ? n_layers : 0, layer_mask,
-                n_rel, flags, score, out_idx, out_order, out_count, out_relevance, stride, st);
+  launch_patch_terms(frame_prev, frame_cur, B, H, W, patch, terms, attn_mean, attn_mean ? n_layers : 0, layer_mask,
+                     score, st);
+  launch_select(terms, B, (int)L_v, tau_num, tau_den, top_k, n_rel, flags, score, out_idx, out_order, out_count,
+                out_relevance, stride, st);
   return hipGetLastError() == hipSuccess ? VLAC_OK : VLAC_E_HIP;
 }

@@ -219,3 +219,40 @@ def test_layer_ratio_with_more_layers_than_waves():
             assert np.all(np.diff(lc[b].cpu().numpy()) >= 0)
     finally:
         V.vlac_destroy(ctx)
+
+
+@pytest.mark.parametrize("nl,L_v", [(1, 256), (17, 25), (64, 256), (65, 1024), (130, 1100), (512, 16)])
+def test_layers_in_chunks_and_masks(nl, L_v):
+    """The scores are added up 16 layers at a time and the ratios finished 64 layers at a time by
+    the last workgroup of a stream; 1100 tokens do not stay in registers.  Three calls in a row:
+    the arrival counters start every call at zero."""
+    import torch
+    import paper_2502_02175_amd as V
+    B, side = 3, {256: 16, 25: 5, 1024: 32, 16: 4, 1100: None}[L_v]
+    ctx = V.vlac_create(V.ModelCfg(nl, 32, 4, 4, 64, 16, 32, 1e-6, 1e4, B, 32, V.OPERAND_F16))
+    try:
+        rng = np.random.default_rng(nl + L_v)
+        attn = (rng.random((nl, B, L_v)) ** (1 + 3.0 * np.arange(nl) / nl)[:, None, None]).astype(np.float32)
+        alpha = torch.empty((B, nl), device="cuda")
+        lc = torch.empty((B, nl), dtype=torch.int32, device="cuda")
+        counts = np.array([L_v // 2, 0, 7], dtype=np.int32)
+        for _ in range(3):
+            alpha.fill_(-1)
+            V.vlac_layer_ratio(ctx, torch.tensor(attn, device="cuda"), B, L_v, 1.3,
+                               torch.tensor(counts, device="cuda"), alpha, lc)
+            torch.cuda.synchronize()
+            for b in range(B):
+                np.testing.assert_allclose(alpha[b].cpu().numpy(), O.layer_ratio(attn[:, b], 1.3), atol=1e-6)
+        if side:
+            mask = (rng.random(nl) < 0.5).astype(np.uint8)
+            attn[~mask.astype(bool)] = np.inf                    # a layer outside the mask adds nothing
+            pairs = [synth.frame_pair(side * 4, side * 4, 4, L_v // 4, seed=b) for b in range(B)]
+            prev, cur = np.stack([p[0] for p in pairs]), np.stack([p[1] for p in pairs])
+            idx, order, rel = run_select(dict(V=V, torch=torch, ctx=ctx), prev, cur, 4, 24, 25, L_v, attn, mask, 0.6)
+            for b in range(B):
+                s = O.task_relevance(np.where(np.isinf(attn), 0, attn)[:, b], mask)
+                np.testing.assert_array_equal(rel[b], s)
+                want, want_order = O.filter_task_relevant(O.select_static(prev[b], cur[b], 4, 24, 25, L_v), s, 0.6)
+                assert idx[b] == want and order[b] == want_order
+    finally:
+        V.vlac_destroy(ctx)
