@@ -328,8 +328,8 @@ __global__ __launch_bounds__(256, XMODE == X_NORM8 ? 2 : 3) void gemm_few_kernel
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int cc = max(min(c + u, w_hi - 1), 0);
-      if constexpr (!W8) b[u] = wsrc[(size_t)cc * 64];
-      else if (u < U / 2) b[u] = wsrc[(size_t)max(min((c >> 1) + u, (w_hi >> 1) - 1), 0) * 64];
+      if constexpr (!W8) b[u] = ld_stream(wsrc + (size_t)cc * 64);
+      else if (u < U / 2) b[u] = ld_stream(wsrc + (size_t)max(min((c >> 1) + u, (w_hi >> 1) - 1), 0) * 64);
       if constexpr (XMODE == X_GLOBAL) {
         const uint4* xs = (c + u < w_hi && row_lane) ? xsrc + (size_t)cc * 64 : a.zero_tile + lane;
         x[u] = *xs;
@@ -446,8 +446,10 @@ __global__ __launch_bounds__(256, XMODE == X_NORM8 ? 2 : 3) void gemm_few_kernel
 
   // The batch a compute phase needs must have been issued BEFORE the batch that flies
   // behind it; the fences stop the instruction scheduler from mixing the phases (which
-  // would drain the queue every iteration).
-  for (int c = w_lo; c < w_hi; c += 2 * U) {
+  // would drain the queue every iteration).  The last two batches ask for nothing more: loads
+  // past the end of the range (clamped to its last tile) would be real traffic.
+  int c = w_lo;
+  for (; c + 2 * U < w_hi; c += 2 * U) {
     compute(c, bw[0], ax[0]);
     __builtin_amdgcn_sched_barrier(0);
     load(c + 2 * U, bw[0], ax[0]);
@@ -457,6 +459,8 @@ __global__ __launch_bounds__(256, XMODE == X_NORM8 ? 2 : 3) void gemm_few_kernel
     load(c + 3 * U, bw[1], ax[1]);
     __builtin_amdgcn_sched_barrier(0);
   }
+  compute(c, bw[0], ax[0]);
+  compute(c + U, bw[1], ax[1]);
 
   if (w > 0) {
 #pragma unroll
