@@ -5,8 +5,7 @@
 // Sec. 3.3, Eq. avistext for the statistic; Sec. 3.1 for the attention itself).
 //
 // A workgroup handles 32 query rows of one head; its 4 waves take every 4th tile
-// of 32 cache positions (so a single decode query still spreads over 4 waves,
-// and a head over its own workgroup), flash-style, entirely on the matrix cores,
+// of 32 cache positions, flash-style, entirely on the matrix cores,
 // and merge their (max, sum, output) triples through LDS at the end:
 //   S^T[key, query] = K . Q^T   A operand: K tile (fragment order in the cache),
 //                               B operand: Q tile (fragment order from the QKV epilogue)
@@ -28,7 +27,7 @@
 struct AttnArgs {
   const int* rows;      // this layer's rows (b << 16 | pos)
   const int* slot_off;  // [B + 1] first slot of every stream
-  int decode_pos;       // >= 0: one row per stream at this position; rows / slot_off are not read
+  int decode_pos;       // attn_decode_kernel: one row per stream at this position; rows / slot_off are not read
   const bf16_t* qbuf;
   bf16_t* out;          // attention output, fragment order, KC = kc_out
   int kc_out;
@@ -44,7 +43,6 @@ struct AttnArgs {
   int* stat_counters;   // [B]
   int defer_stats;      // the parked sums are added up by stats_reduce_kernel after the last layer
   int rows4_from;       // > 0: streams with at least this many rows are left to attn_rows4_kernel
-  int dec_pack;         // decode with grouped queries: the query heads of one kv head share a workgroup
 };
 
 template <int HD, bool F16>
@@ -57,24 +55,16 @@ __global__ __launch_bounds__(256) void attn_rows_kernel(AttnArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int j = lane & 31, g = lane >> 5;
   const int b = blockIdx.z;
-  const bool dec = a.decode_pos >= 0;
-  const int off_b = dec ? b : a.slot_off[b];
-  const int n_b = dec ? 1 : a.slot_off[b + 1] - off_b;
+  const int off_b = a.slot_off[b];
+  const int n_b = a.slot_off[b + 1] - off_b;
   const int s0 = blockIdx.x * 32;
   if (s0 >= n_b) return;
   if (a.rows4_from > 0 && n_b >= a.rows4_from) return;
-  // A decode pass has one query per stream and head, 1 column of the 32 a tile has.  With
-  // grouped queries the heads that share a kv head fill the columns of ONE tile (blockIdx.y
-  // is then the kv head, and the head is per lane): one workgroup per stream and kv head
-  // reads the K and V tiles that group-many workgroups would each have read.
-  const bool packed = dec && a.dec_pack;
-  const int group = a.n_q_heads / a.n_kv_heads;
-  const int hk = packed ? blockIdx.y : blockIdx.y / group;
-  const int h = packed ? hk * group + min(j, group - 1) : blockIdx.y;
-  const bool valid = packed ? j < group : s0 + j < n_b;
-  const int sg = off_b + ((valid && !packed) ? s0 + j : n_b - 1);  // this lane's query slot
-  const int pos = dec ? a.decode_pos : (valid ? (a.rows[sg] & 0xffff) : 0);
-  const int pos_last = dec ? a.decode_pos : (a.rows[off_b + min(s0 + 31, n_b - 1)] & 0xffff);
+  const int h = blockIdx.y, hk = h / (a.n_q_heads / a.n_kv_heads);
+  const bool valid = s0 + j < n_b;
+  const int sg = off_b + (valid ? s0 + j : n_b - 1);  // this lane's query slot
+  const int pos = valid ? (a.rows[sg] & 0xffff) : 0;
+  const int pos_last = a.rows[off_b + min(s0 + 31, n_b - 1)] & 0xffff;
   const int n_kt = (pos_last >> 5) + 1;
 
   const size_t head_elems = (size_t)a.max_seq * HD;
@@ -198,7 +188,7 @@ __global__ __launch_bounds__(256) void attn_rows_kernel(AttnArgs a) {
   }
 
   // ---- text-to-vision statistic (all conditions are uniform over the workgroup) ----
-  if (!a.attn_mean || a.L_t <= 0 || a.L_v <= 0 || dec) return;
+  if (!a.attn_mean || a.L_t <= 0 || a.L_v <= 0) return;
   if (pos_last < a.L_v) return;  // no text row in this tile
   __syncthreads();
   const int x_first = (n_b - a.L_t) >> 5;  // first tile that holds a text row
@@ -261,6 +251,142 @@ __global__ __launch_bounds__(256) void attn_rows_kernel(AttnArgs a) {
       for (int i = 0; i < 16; ++i) acc += (p0 + i < n_part) ? t[i] : 0.f;
     }
     a.attn_mean[(size_t)b * a.attn_mean_stride + v] = acc * norm;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// One query per stream and head (a decode pass).  The query heads that share a kv head fill the
+// columns of one tile (at most 32 of them), so a workgroup per stream and kv head reads K and V
+// once for all of them.  Bound by latency: a stream's cache slice of a layer is a few MB, read by
+// as many workgroups as there are kv heads.  So every wave takes key tiles of its own (one each up
+// to 16 tiles, 512 positions), asks for its query, K and V at once, and the waves meet once, in
+// LDS, where only the columns that hold a query are exchanged.  (MULTI: more tiles than that; 8
+// waves, whose query stays in registers beside the next tile.)  7B shape, one stream, 294
+// positions: 6.1 us per launch against 8.7 with 4 waves that walked three tiles each and
+// exchanged whole tiles; grouped queries, 32 streams, 310 positions: 6.7 against 9.0.
+// ---------------------------------------------------------------------------
+constexpr int kDecWaves = 16, kDecWavesMulti = 8;  // 4 and 2 per SIMD: 128 and 256 registers a wave
+
+template <int HD, bool F16, bool MULTI>
+__global__ __launch_bounds__(64 * (MULTI ? kDecWavesMulti : kDecWaves)) void attn_decode_kernel(AttnArgs a) {
+  constexpr int NC = HD / 16;  // k-tiles of a head
+  constexpr int NI = HD / 32;  // feature blocks of a head
+  extern __shared__ float dec_lds[];  // [waves][columns][HD + 4]: output, reference point, sum
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
+  const int j = lane & 31, g = lane >> 5;
+  const int b = blockIdx.y, group = a.n_q_heads / a.n_kv_heads, per_kv = (group + 31) >> 5;
+  const int hk = blockIdx.x / per_kv, c0 = (blockIdx.x - hk * per_kv) * 32;
+  const int nc = min(group - c0, 32);           // columns that hold a query
+  const int h0 = hk * group + c0, h = h0 + min(j, nc - 1);
+  const int pos = a.decode_pos, n_kt = (pos >> 5) + 1;
+
+  const size_t head_elems = (size_t)a.max_seq * HD;
+  const bf16_t* kbase = a.kv + (size_t)b * a.kv_stream_stride + (size_t)hk * head_elems + (size_t)lane * 8;
+  const bf16_t* vbase = kbase + (size_t)a.n_kv_heads * head_elems;
+  uint4 qf[NC], kf[NC], vf[NI * 2];
+  const bf16_t* qsrc = a.qbuf + ((size_t)(b >> 5) * a.n_q_heads + h) * (size_t)NC * 512 + (size_t)(((b & 31) + 32 * g) << 3);
+#pragma unroll
+  for (int c = 0; c < NC; ++c) qf[c] = *(const uint4*)(qsrc + (size_t)c * 512);
+  auto load_k = [&](int kt) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) kf[c] = *(const uint4*)(kbase + ((size_t)kt * NC + c) * 512);
+  };
+  auto load_v = [&](int kt) {
+#pragma unroll
+    for (int t = 0; t < NI * 2; ++t) vf[t] = *(const uint4*)(vbase + ((size_t)kt * NI * 2 + t) * 512);
+  };
+  load_k(min(w, n_kt - 1));
+  load_v(min(w, n_kt - 1));
+  __builtin_amdgcn_sched_barrier(0);
+
+  f32x16 o[NI];
+#pragma unroll
+  for (int ib = 0; ib < NI; ++ib)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) o[ib][i] = 0.f;
+  float m = -INFINITY, l = 0.f;
+  for (int kt = w; kt < n_kt; kt += nw) {
+    f32x16 s;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s[i] = 0.f;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) s = mfma32<F16>(kf[c], qf[c], s);
+    if (MULTI && kt + nw < n_kt) load_k(kt + nw);  // (flies during softmax and P.V)
+    // register 4*q4 + e of a lane is key 32*kt + 8*q4 + 4*g + e
+    float tmax = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int kp = 32 * kt + 8 * (i >> 2) + 4 * g + (i & 3);
+      s[i] = (kp <= pos) ? s[i] * a.scale_log2e : -INFINITY;
+      tmax = fmaxf(tmax, s[i]);
+    }
+    tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
+    const float m_new = fmaxf(m, tmax);  // (a tile holds at least one visible key)
+    const float alpha = (m_new == -INFINITY) ? 1.f : exp2f(m - m_new);
+    const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
+    m = m_new;
+    float psum = 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      s[i] = exp2f(s[i] - m_use);
+      psum += s[i];
+    }
+    l = l * alpha + psum;
+    uint4 pb[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      pb[t].x = pack_op2<F16>(s[8 * t + 0], s[8 * t + 1]);
+      pb[t].y = pack_op2<F16>(s[8 * t + 2], s[8 * t + 3]);
+      pb[t].z = pack_op2<F16>(s[8 * t + 4], s[8 * t + 5]);
+      pb[t].w = pack_op2<F16>(s[8 * t + 6], s[8 * t + 7]);
+    }
+#pragma unroll
+    for (int ib = 0; ib < NI; ++ib) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) o[ib][i] *= alpha;
+#pragma unroll
+      for (int t = 0; t < 2; ++t) o[ib] = mfma32<F16>(vf[ib * 2 + t], pb[t], o[ib]);
+    }
+    if (!MULTI) break;
+    if (kt + nw < n_kt) load_v(kt + nw);
+  }
+  l += __shfl_xor(l, 32);
+
+  constexpr int ROW = HD + 4;
+  if (j < nc) {
+    float* mine = dec_lds + ((size_t)w * nc + j) * ROW;
+#pragma unroll
+    for (int ib = 0; ib < NI; ++ib)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4)
+        *(float4*)(mine + 32 * ib + 8 * q4 + 4 * g) =
+            make_float4(o[ib][4 * q4], o[ib][4 * q4 + 1], o[ib][4 * q4 + 2], o[ib][4 * q4 + 3]);
+    if (g == 0) {
+      mine[HD] = m;
+      mine[HD + 1] = l;
+    }
+  }
+  __syncthreads();
+  // 4 features of one column per thread; the waves' parts in order (wave 0 has tile 0, whose
+  // first key every query sees, so M is finite)
+  const int n_w = min(nw, n_kt);
+  for (int e = tid; e < nc * (HD / 4); e += blockDim.x) {
+    const int col = e / (HD / 4), f = (e - col * (HD / 4)) * 4;
+    const float* src = dec_lds + (size_t)col * ROW;
+    const size_t step = (size_t)nc * ROW;
+    float M = src[HD];
+    for (int ww = 1; ww < n_w; ++ww) M = fmaxf(M, src[ww * step + HD]);
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    float L = 0.f;
+    for (int ww = 0; ww < n_w; ++ww) {
+      const float sc = exp2f(src[ww * step + HD] - M);
+      const float4 x = *(const float4*)(src + ww * step + f);
+      acc.x += sc * x.x; acc.y += sc * x.y; acc.z += sc * x.z; acc.w += sc * x.w;
+      L += sc * src[ww * step + HD + 1];
+    }
+    const float inv = 1.f / L;
+    *(uint2*)(a.out + frag_off(b, (h0 + col) * HD + f, a.kc_out)) =
+        make_uint2(pack_op2<F16>(acc.x * inv, acc.y * inv), pack_op2<F16>(acc.z * inv, acc.w * inv));
   }
 }
 
@@ -590,6 +716,20 @@ __global__ __launch_bounds__(256) void stats_reduce_kernel(const float* __restri
   }
 }
 
+static const size_t kDecLds = 144 * 1024;  // most that the waves of attn_decode_kernel exchange
+
+int attn_init() {
+  hipError_t e;
+#define VLAC_SET(HD_, F16_)                                                                             \
+  if ((e = hipFuncSetAttribute((const void*)attn_decode_kernel<HD_, F16_, false>,                        \
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kDecLds)) != hipSuccess) return (int)e; \
+  if ((e = hipFuncSetAttribute((const void*)attn_decode_kernel<HD_, F16_, true>,                         \
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kDecLds)) != hipSuccess) return (int)e;
+  VLAC_SET(128, true) VLAC_SET(128, false) VLAC_SET(64, true) VLAC_SET(64, false)
+#undef VLAC_SET
+  return 0;
+}
+
 bool attention_defers_stats(const vlac_ctx* c, int B, int L_v, int L_t) {
   // text rows of a stream lie in at most ceil(L_t / 32) + 1 tiles of 32 slots
   const int n_tt_max = (L_t + 31) / 32 + 1;
@@ -626,7 +766,7 @@ void launch_attention(vlac_ctx* c, int layer, int B, int rows_cap_per_stream, in
   a.attn_mean = out_attn_mean ? out_attn_mean + (size_t)layer * B * L_v : nullptr;
   a.attn_mean_stride = L_v;
   a.lv_pad = round_up(L_v > 0 ? L_v : 1, 32);
-  a.defer_stats = out_attn_mean && decode_pos < 0 && attention_defers_stats(c, B, L_v, L_t);
+  a.defer_stats = out_attn_mean && attention_defers_stats(c, B, L_v, L_t);
   if (a.defer_stats) {
     a.TT = kStatDeferTT;
     a.statp = c->statp + (size_t)layer * B * m.n_q_heads * kStatDeferTT * a.lv_pad;
@@ -635,6 +775,27 @@ void launch_attention(vlac_ctx* c, int layer, int B, int rows_cap_per_stream, in
     a.statp = c->statp;
   }
   a.stat_counters = c->stat_counters;
+  if (decode_pos >= 0) {
+    const int group = m.n_q_heads / m.n_kv_heads, nc = group < 32 ? group : 32;
+    const int n_kt = (decode_pos >> 5) + 1;
+    const size_t row = (size_t)nc * (m.head_dim + 4) * sizeof(float);  // LDS that a wave's part takes
+    const bool multi = n_kt > kDecWaves || n_kt * row > kDecLds;
+    int nw = multi ? kDecWavesMulti : n_kt;
+    while (nw * row > kDecLds) --nw;
+    const dim3 gridd(m.n_kv_heads * ((group + 31) / 32), B), block(64 * nw);
+#define VLAC_DEC(HD_, F16_)                                                                                  \
+  {                                                                                                         \
+    if (multi) hipLaunchKernelGGL((attn_decode_kernel<HD_, F16_, true>), gridd, block, nw * row, st, a);    \
+    else hipLaunchKernelGGL((attn_decode_kernel<HD_, F16_, false>), gridd, block, nw * row, st, a);         \
+  }
+    if (m.head_dim == 128) {
+      if (c->f16) VLAC_DEC(128, true) else VLAC_DEC(128, false)
+    } else {
+      if (c->f16) VLAC_DEC(64, true) else VLAC_DEC(64, false)
+    }
+#undef VLAC_DEC
+    return;
+  }
   // Sequences of 256 tokens or more of many streams (work for every CU several times over;
   // 32 streams x 304 tokens of the grouped-query model: 29.4 against 30.5 ms per full
   // prefill): streams with more
@@ -648,7 +809,7 @@ void launch_attention(vlac_ctx* c, int layer, int B, int rows_cap_per_stream, in
   // streams alone.
   const int groups = (rows_cap_per_stream + 127) / 128;
   a.rows4_from = 0;
-  if (decode_pos < 0 && rows_cap_per_stream >= 256 && (long long)groups * m.n_q_heads * B >= 512 &&
+  if (rows_cap_per_stream >= 256 && (long long)groups * m.n_q_heads * B >= 512 &&
       (!a.attn_mean || a.defer_stats)) {
     a.rows4_from = 65;
     dim3 grid4(m.n_q_heads, B, groups);
@@ -660,9 +821,7 @@ void launch_attention(vlac_ctx* c, int layer, int B, int rows_cap_per_stream, in
       else hipLaunchKernelGGL((attn_rows4_kernel<64, false>), grid4, dim3(256), 0, st, a);
     }
   }
-  const int group = m.n_q_heads / m.n_kv_heads;
-  a.dec_pack = decode_pos >= 0 && group > 1 && group <= 32;
-  dim3 grid((rows_cap_per_stream + 31) / 32, a.dec_pack ? m.n_kv_heads : m.n_q_heads, B);
+  dim3 grid((rows_cap_per_stream + 31) / 32, m.n_q_heads, B);
   if (m.head_dim == 128) {
     if (c->f16) hipLaunchKernelGGL((attn_rows_kernel<128, true>), grid, dim3(256), 0, st, a);
     else hipLaunchKernelGGL((attn_rows_kernel<128, false>), grid, dim3(256), 0, st, a);

@@ -347,6 +347,7 @@ void launch_embed_patches(vlac_ctx* c, const uint8_t* frame, int B, int H, int W
                           int stride, const int32_t* layer_count, float* embeds, int L, hipStream_t st);
 
 // attn.hip
+int attn_init();  // kernel attribute setup; returns hipError_t
 // Text tiles per stream that the deferred statistic reduction provides for (text rows
 // of a stream lie in at most ceil(L_t / 32) + 1 tiles: L_t <= 96).
 static const int kStatDeferTT = 4;
