@@ -62,7 +62,7 @@ void free_all(vlac_ctx* c) {
   }
   void* dev[] = {c->w_head, c->s_head, c->scale_tmp, c->wdeq, c->embed, c->g_final, c->rope_cos, c->rope_sin, c->h, c->hdec, c->xa, c->xf,
                  c->qbuf, c->partial, c->rpart, c->counters, c->rows, c->prev_slot, c->n_rows, c->slot_off, c->rank,
-                 c->m_layer, c->n_rows_bl, c->statp, c->stat_counters, c->logits, c->tokens,
+                 c->m_layer, c->n_rows_bl, c->statp, c->stat_counters, c->logits,
                  c->dec_rows, c->terms, c->flags, c->embed_list, c->embed_n, c->relevance, c->entropy, c->ratio_counters, c->errword, c->scratch_i,
                  c->zero_tile};
   for (void* p : dev) (void)hipFree(p);
@@ -208,7 +208,6 @@ int vlac_create(const vlac_model_cfg* cfg, vlac_ctx** out) {
   A_(statp, ctx->statp_floats);
   A_(stat_counters, mb);
   A_(logits, (size_t)mb * m.vocab);
-  A_(tokens, mb);
   A_(dec_rows, (size_t)ms * mb + ms + (size_t)ms * (mb + 1));
   A_(terms, (size_t)mb * 4096 * 3);
   A_(flags, (size_t)mb * 4096);
@@ -532,7 +531,7 @@ void run_layer(vlac_ctx* c, int layer, int B, int rows_cap, int rows_cap_per_str
   const int s_o = launch_gemm(c, EPI_RESID, W.wo, W.s_o, m.d_model / 32, c->kpad_q, c->xa, n_rows, n_host,
                               rows_cap, e, st);
   const SplitAdapt ad_o = gemm_resid_adapt(c, m.d_model / 32, c->kpad_q, rows_cap, n_rows, n_host);
-  if (rows_cap > 32 && s_o > 1)  // the few-rows kernel adds its splits up itself
+  if (s_o > 1)
     launch_resid_norm_rows(c->f16, resid_in, resid_stride, c->rpart, s_o, rows_cap, c->h, m.max_seq,
                            rows, nullptr, n_rows, n_host, rows_cap, W.g_ffn, m.rms_eps, m.d_model,
                            c->xa, kc_d, st, &ad_o);
@@ -543,7 +542,7 @@ void run_layer(vlac_ctx* c, int layer, int B, int rows_cap, int rows_cap_per_str
   e.resid_src = c->h; e.resid_seq_stride = m.max_seq;
   const int s_d = launch_gemm(c, EPI_RESID, W.wdown, W.s_down, m.d_model / 32, c->kpad_f, c->xf, n_rows, n_host,
                               rows_cap, e, st);
-  *pending = (rows_cap > 32 && s_d > 1) ? s_d : 0;
+  *pending = s_d > 1 ? s_d : 0;
   c->pending_adapt = gemm_resid_adapt(c, m.d_model / 32, c->kpad_f, rows_cap, n_rows, n_host);
 }
 
@@ -595,7 +594,7 @@ void run_layer_decode(vlac_ctx* c, int layer, int B, int pos, bf16_t* kv, Decode
   e.max_seq = m.max_seq;
   e.d_model = m.d_model;
   e.h_compact = 1; e.h_seq_stride = 1; e.resid_seq_stride = 1;
-  e.rpart = c->rpart; e.rpart_rows = B; e.defer_split = 1;
+  e.rpart = c->rpart; e.rpart_rows = B;
   e.xf = c->xf; e.kc_f = c->kpad_f / 16; e.d_ffn = m.d_ffn;
 
   NormIn n = decode_norm(c, B, r, W.g_attn, true);
@@ -616,7 +615,7 @@ void run_layer_decode(vlac_ctx* c, int layer, int B, int pos, bf16_t* kv, Decode
 // Final norm + output head + greedy token for B rows: (stream b, position pos) of the
 // residual stream, or, with `fused` given, the rows of a decode pass (norm fused).
 void run_head(vlac_ctx* c, int B, int pos, float* logits, size_t logits_stride, int32_t* out_token,
-              int out_stride, int32_t* token_copy, hipStream_t st, const NormIn* fused = nullptr) {
+              int out_stride, const NextEmbed& next, hipStream_t st, const NormIn* fused = nullptr) {
   const vlac_model_cfg& m = c->cfg;
   GemmEpi e;
   memset(&e, 0, sizeof(e));
@@ -635,7 +634,7 @@ void run_head(vlac_ctx* c, int B, int pos, float* logits, size_t logits_stride, 
                         m.d_model, c->xa, c->kpad_d / 16, st);
     launch_gemm(c, EPI_LOGITS, c->w_head, c->s_head, m.vocab / 32, c->kpad_d, c->xa, nullptr, B, B, e, st);
   }
-  launch_argmax(logits, logits_stride, B, m.vocab, out_token, out_stride, token_copy, st);
+  launch_argmax(logits, logits_stride, B, m.vocab, out_token, out_stride, next, st);
 }
 
 int weights_ready(const vlac_ctx* c) {
@@ -694,7 +693,7 @@ int vlac_sparse_prefill(vlac_ctx* ctx, const float* embeds, int B, int L_v, int 
                         ctx->n_rows + (nl - 1), rows_cap, ctx->g_final, m.rms_eps, m.d_model,
                         out_hidden, L, st);
   run_head(ctx, B, L - 1, out_logits ? out_logits : ctx->logits, (size_t)m.vocab, out_token, 1,
-           nullptr, st);
+           NextEmbed{nullptr, 0, nullptr, 0, 0}, st);
   VLAC_HIP(hipGetLastError());
   for (int b = 0; b < B; ++b) ctx->filled[b] = 1;
   return VLAC_OK;
@@ -715,17 +714,19 @@ int vlac_decode_action(vlac_ctx* ctx, int B, int L, int n_new, const int32_t* fi
   const bool fused = gemm_can_fuse_norm(B, L, ctx->kpad_d) && ctx->rpart_floats >= (size_t)8 * B * m.d_model;
   if (!fused) launch_decode_plan(ctx, B, L, n_new, st);
   for (int t = 0; t < n_new; ++t) {
-    const int32_t* tok = t == 0 ? first_token : ctx->tokens;
     float* logits = out_logits ? out_logits + (size_t)t * m.vocab : ctx->logits;
     const size_t lstride = out_logits ? (size_t)n_new * m.vocab : (size_t)m.vocab;
+    // (the residual rows of every later pass are written by the argmax of the pass before it)
+    const bool more = t + 1 < n_new;
     if (fused) {
       // rows (b, 0) of a [max_batch, 1, d] plane: the first residual row set
-      launch_embed_rows(ctx->embed, tok, B, m.d_model, m.vocab, ctx->hdec, 1, 0, st);
+      if (t == 0) launch_embed_rows(ctx->embed, first_token, B, m.d_model, m.vocab, ctx->hdec, 1, 0, st);
+      const NextEmbed next = {ctx->embed, m.d_model, more ? ctx->hdec : nullptr, 1, 0};
       DecodeResid r = {0, 0};
       for (int l = 0; l < m.n_layers; ++l)
         run_layer_decode(ctx, l, B, L + t, (bf16_t*)kv_cache, r, st);
       const NormIn n = decode_norm(ctx, B, r, ctx->g_final, false);
-      run_head(ctx, B, L + t, logits, lstride, out_tokens + t, n_new, ctx->tokens, st, &n);
+      run_head(ctx, B, L + t, logits, lstride, out_tokens + t, n_new, next, st, &n);
     } else {
       // More than 4 streams: the general layer pass over the rows (b, L + t).  With more than
       // 32 of them the prefill's GEMM and row kernels serve the pass, and those read the row
@@ -733,7 +734,8 @@ int vlac_decode_action(vlac_ctx* ctx, int B, int L, int n_new, const int32_t* fi
       // row lists.  Their projections with a residual may leave split-K partial rows
       // (`pending`), which the next layer's first row kernel adds up, and after the last
       // layer a row kernel without a norm.
-      launch_embed_rows(ctx->embed, tok, B, m.d_model, m.vocab, ctx->h, ms, L + t, st);
+      if (t == 0) launch_embed_rows(ctx->embed, first_token, B, m.d_model, m.vocab, ctx->h, ms, L, st);
+      const NextEmbed next = {ctx->embed, m.d_model, more ? ctx->h : nullptr, ms, L + t + 1};
       const int* drows = ctx->dec_rows + (size_t)t * m.max_batch;
       int pending = 0;
       for (int l = 0; l < m.n_layers; ++l)
@@ -743,7 +745,7 @@ int vlac_decode_action(vlac_ctx* ctx, int B, int L, int n_new, const int32_t* fi
         launch_resid_norm_rows(ctx->f16, ctx->h, ms, ctx->rpart, pending, B, ctx->h, ms, drows, nullptr,
                                nullptr, B, B, nullptr, m.rms_eps, m.d_model, ctx->xa, ctx->kpad_d / 16,
                                st, &ctx->pending_adapt);
-      run_head(ctx, B, L + t, logits, lstride, out_tokens + t, n_new, ctx->tokens, st);
+      run_head(ctx, B, L + t, logits, lstride, out_tokens + t, n_new, next, st);
     }
   }
   VLAC_HIP(hipGetLastError());

@@ -169,7 +169,6 @@ struct vlac_ctx {
   int stat_tt;      // text tiles per stream the statistic buffer provides for
   int* stat_counters;
   float* logits;    // [max_batch, vocab]
-  int* tokens;      // [max_batch] current token of the decode loop
   int* dec_rows;    // decode row lists
   uint32_t* terms;  // patch terms [max_batch, 4096, 3]
   uint8_t* flags;   // selection flags
@@ -228,8 +227,10 @@ void launch_resid_norm_rows(bool f16, const float* resid, int resid_seq_stride, 
 void launch_final_hidden(const float* src, int seq_stride, const int* rows, const int* n_rows,
                          int max_rows, const float* gain, float eps, int d, float* out, int L,
                          hipStream_t st);
+// where the embedding of a greedy token goes: row (b, h_pos) of h [B, h_seq, d] (h == nullptr: nowhere)
+struct NextEmbed { const bf16_t* embed; int d; float* h; int h_seq, h_pos; };
 void launch_argmax(const float* logits, size_t logits_stride, int B, int vocab, int32_t* out,
-                   int out_stride, int32_t* out2, hipStream_t st);
+                   int out_stride, const NextEmbed& next, hipStream_t st);
 void launch_embed_rows(const bf16_t* embed, const int32_t* tokens, int B, int d, int vocab, float* h,
                        int max_seq, int pos, hipStream_t st);
 // e4m3 storage: scales of the N source rows, then codes in fragment order (two k-tiles per
@@ -258,7 +259,6 @@ struct GemmEpi {
   const float* resid_src; int resid_seq_stride;
   float* h; int h_seq_stride; int h_compact; int d_model;
   float* rpart; int rpart_rows;  // split-K partial rows [split][rpart_rows][d_model]
-  int defer_split;  // few-rows kernel with S > 1: leave the partial rows in rpart
   // EPI_SWIGLU
   bf16_t* xf; int kc_f; int d_ffn;
   // EPI_LOGITS
@@ -330,8 +330,7 @@ __host__ __device__ inline TallPlan tall_plan(int tiles, int n_rows, int S_max, 
 SplitAdapt gemm_resid_adapt(vlac_ctx* c, int n_blocks, int kpad, int rows_cap, const int* n_rows, int n_rows_host);
 int gemm_init();  // one-time kernel attribute setup; returns hipError_t
 // returns the split-K factor used; for EPI_RESID a factor S > 1 means that the result is
-// NOT in the residual stream yet but in e.rpart as S partial rows (more than 32 rows:
-// always; at most 32 rows: if e.defer_split is set) for the consumer to add up
+// NOT in the residual stream yet but in e.rpart as S partial rows for the consumer to add up
 // (launch_resid_norm_rows, or NormIn::part of the next projection)
 int launch_gemm(vlac_ctx* c, int epi, const bf16_t* wp, const float* wscale, int n_blocks, int kpad,
                 const bf16_t* xp,

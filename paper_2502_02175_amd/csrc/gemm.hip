@@ -472,9 +472,10 @@ __global__ __launch_bounds__(256, XMODE == X_NORM8 ? 2 : 3) void gemm_few_kernel
   for (int i = 0; i < 16; ++i) acc[i] += red[0][i][lane] + red[1][i][lane] + red[2][i][lane];
   if constexpr (W8) scale_tile(a.wscale, nb, lane >> 5, acc);
 
-  if (EPI == EPI_RESID && a.S > 1 && a.e.defer_split) {
-    // the split's partial rows [split][row][feature] are left for the consumer (the
-    // fused norm of the next projection) to add up: nothing is handed over in here
+  if (EPI == EPI_RESID && a.S > 1) {
+    // the split's partial rows [split][row][feature] are left for the consumer (the fused
+    // norm of the next projection, or the residual + norm row kernel) to add up: nothing is
+    // handed over in here
     const int slot = lane & 31, g = lane >> 5;
     if (slot < n_rows) {
       float* dst = a.e.rpart + ((size_t)s * a.e.rpart_rows + slot) * a.e.d_model + nb * 32 + 4 * g;
