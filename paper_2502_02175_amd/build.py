@@ -26,7 +26,7 @@ def _run(cmd):
 # The sources that place waits for compiler-invisible copies by hand; libvlac_safe.so is the
 # same library with those sources compiled with -DVLAC_SAFE_WAITS (every such wait is for all
 # outstanding loads): a checking aid that a GPU test compares with libvlac.so bit for bit.
-HAND_WAITS = ["gemm_tall.hip", "attn.hip"]
+HAND_WAITS = ["gemm.hip", "gemm_tall.hip", "attn.hip"]
 LIB_SAFE = os.path.join(HERE, "libvlac_safe.so")
 
 

@@ -14,16 +14,11 @@
 //    holds one row and 4 x 4 consecutive features, which is what the fused
 //    epilogues want (rotary partners, gate/up pairs and packed 8-byte stores in
 //    one lane).
-//  * A workgroup is 4 waves = 4 x 32 output features over all rows of its row
-//    block (4 tiles of 32 rows, accumulators in registers; more rows = more row
-//    blocks, mapped to the same XCD so that they share the weight tiles in L2).  Weight tiles go
-//    global -> registers (each is used by exactly one wave, LDS would add
-//    nothing); the activation tiles, shared by the 4 waves, are staged through
-//    LDS, double buffered, 64 k per step.
-//  * Few rows mean few output tiles, so K is split over S workgroups per tile to
-//    fill 256 CUs; partial sums go to a workspace and the LAST workgroup to
-//    arrive (atomic counter, no waiting) adds them in fixed order and runs the
-//    epilogue: deterministic, no extra launch.
+//  * The kernel for one stream's prefill (gemm_rows_kernel): weight tiles go global ->
+//    registers (each is used by exactly one wave, LDS would add nothing), operand rows
+//    global -> LDS directly by two waves that do nothing else.  K is split over pairs of
+//    waves where the feature tiles are few, and over workgroups in the projections with a
+//    residual, whose partial rows the next row kernel adds up in fixed order.
 //  * Row counts live in device memory (they depend on the selection), the grid
 //    is sized for the worst case and surplus workgroups leave at once.
 //  * Workgroup ids are dealt round-robin to the 8 XCDs; row blocks of one weight
@@ -31,210 +26,278 @@
 #include <cstring>
 #include "gemm_epi.h"
 
-// Main loop, split-K hand-over and epilogue for a row block with exactly NA active
-// 32-row tiles (a template parameter, so that every loop is unrolled without guards
-// and the compiler can count the loads in flight exactly).
-template <int NA, int MT, int EPI, bool F16, bool W8>
-__device__ __forceinline__ void rows_body(const GemmArgs& a, uint4* lds, int* s_last, int tile,
-                                          int s, int mb, int n_rows, uint32_t pf0, uint32_t pf1) {
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int row0 = mb * MT * 32;
-  const int nb = tile * 4 + w;
-  const bool wave_on = nb < a.NB;
-  const int KC = 4 * a.KS;
-  const int q = a.KS / a.S, r = a.KS % a.S;
-  const int ks0 = s * q + min(s, r), n_ks = q + (s < r ? 1 : 0);
-  // (e4m3 weights: a 16-byte lane slot holds two k-tiles, a step is two slots per wave)
-  const uint4* wsrc = a.wp + ((size_t)(wave_on ? nb : a.NB - 1) * (W8 ? KC / 2 : KC) + (W8 ? 2 : 4) * ks0) * 64 + lane;
-  const uint4* xsrc = a.xp + ((size_t)(row0 >> 5) * KC + 4 * ks0) * 64 + tid;
+// Workgroup: 4 consumer waves and 2 producer waves.  The consumers are FB feature blocks x KP
+// parts of the K range (FB KP = 4); a consumer streams the weight tiles of its block and part
+// into registers, UK k-tiles ahead, and multiplies them by up to 8 row tiles whose operands it
+// reads from LDS.  The producers copy those operands global -> LDS directly into a ring of
+// ROWS_RING chunks, for nobody else's registers and nobody else's load queue: a wave's loads
+// return in issue order, so row operands (from L2) fetched by the consumers themselves would wait
+// behind weights from HBM, and storing them to LDS at every 64 k cost a barrier that all waves
+// reached together (with both operands and the LDS reads taken out, that kernel's 172 workgroups
+// still took 36 of the 49 us of the 7B gate/up projection at 109 rows: barriers, not memory).
+// Here one barrier per chunk remains, and the data it publishes is needed a chunk later.
+// What is left is the rate at which a CU fetches: a copy from L2 waits in one queue with the weights
+// from HBM (a probe that does nothing else: 27 us for the weights alone, 10 for the row operands
+// alone, 38 for both on 172 CUs, 34 on 256, whatever is in flight), so lanes of rows past the end
+// copy nothing and the tiles are cut to use most CUs.  7B shape, 109 rows, before and now: gate/up
+// 49.8 -> 41.7 us (4.3 TB/s of weights), QKV 41.2 -> 33.6, O 15 -> 14.4, FFN down 29 -> 26; four
+// layers with the head 742 -> 623 us, 192 rows 908 -> 804, 256 rows 995 -> 949.  Blocks of 8 row
+// tiles spill (256 rows: 1066); 32 weight tiles in flight: no faster.
+constexpr int ROWS_RING = 5;       // chunks of at most 32 KiB: all 160 KiB of a CU's LDS
+constexpr int rows_consumers(int FB) { return FB == 2 ? 4 : FB; }
+constexpr int rows_threads(int FB) { return 64 * (rows_consumers(FB) + 2); }
+constexpr int ROWS_UK = 16;        // weight tiles in flight per consumer (16 KiB)
 
+template <int NA, int FB>
+struct RowsShape {
+  static constexpr int NC = rows_consumers(FB), KP = NC / FB;
+  static constexpr int CT = (NA <= 4 ? 8 : 4) / KP;   // k-tiles per chunk and part
+  static constexpr int TILES = KP * CT * NA;          // operand tiles (1 KiB) per chunk
+  static constexpr int UK = ROWS_UK;                  // weight tiles in flight per consumer
+  static constexpr int XR = NA <= 4 ? 2 : 1;          // k-tiles of row operands in registers
+};
+
+// The K range of part `part` of split `s`: in 64-k steps (4 k-tiles), the longer ones first
+struct RowsRange { int k0, n; };
+__device__ inline RowsRange rows_range(int KS, int parts, int idx) {
+  const int q = KS / parts, r = KS - q * parts;
+  return {4 * (idx * q + min(idx, r)), 4 * (q + (idx < r ? 1 : 0))};
+}
+
+template <int N>
+__device__ inline void rows_wait() {
+#ifdef VLAC_SAFE_WAITS
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#else
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+#endif
+}
+// (waits for nothing by itself: a consumer's LDS reads of the chunk it leaves have been used by
+// then, a producer has waited for its copies)
+__device__ inline void rows_barrier() { asm volatile("s_barrier" ::: "memory"); }
+
+// A producer wave (half = 0, 1): with two K parts the operand tiles of part `half`, else those of
+// half the k-tiles of every chunk.  At the barrier that ends chunk c the chunks c + 1 and c + 2
+// have landed.
+template <int NA, int FB>
+__device__ __forceinline__ void rows_produce(const GemmArgs& a, uint4* lds, int half, int s, int rt0, int row_end) {
+  using Sh = RowsShape<NA, FB>;
+  constexpr int KP = Sh::KP, PER = Sh::TILES / 2;  // copies of a chunk per producer
+  static_assert((ROWS_RING - 3) * PER <= 63, "the counter holds 63");
+  const int KC = 4 * a.KS;
+  const uint32_t lane_off = (threadIdx.x & 63) * 16u;
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lds) + (uint32_t)half * (PER * 1024u);
+  const int n_max = __builtin_amdgcn_readfirstlane(rows_range(a.KS, a.S * KP, s * KP).n);
+  const int n_ch = (n_max + Sh::CT - 1) / Sh::CT, n_bar = n_max / Sh::CT;
+  RowsRange rg = rows_range(a.KS, a.S * KP, s * KP + (KP == 2 ? half : 0));
+  rg.k0 = __builtin_amdgcn_readfirstlane(rg.k0);  // (uniform, but divided with vector instructions)
+  rg.n = __builtin_amdgcn_readfirstlane(rg.n);
+  const int kt0 = KP == 2 ? 0 : half * (Sh::CT / 2);
+  const char* rows[NA];
+#pragma unroll
+  for (int m = 0; m < NA; ++m) rows[m] = (const char*)(a.xp + (size_t)min(rt0 + m, (row_end - 1) >> 5) * KC * 64);
+  // (lanes of rows past the end copy nothing: their columns of the product are dropped; row 0 of the
+  // last tile always exists, so every copy is issued and the count of copies in flight stays exact)
+  const bool row_on = ((row_end - 1) & ~31) + (int)(threadIdx.x & 31) < row_end;
+  auto copy = [&](uint32_t d, const char* src) {
+    asm volatile(
+        "s_mov_b32 m0, %0\n\t"
+        "s_nop 0\n\t"
+        "global_load_lds_dwordx4 %1, %2"
+        :
+        : "s"(d), "v"(lane_off), "s"(src)
+        : "memory", "m0");
+  };
+  auto issue = [&](int c, int slot) {
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      // (past the end of the part: a tile that nobody reads)
+      const int k = min(rg.k0 + min(c * Sh::CT + kt0 + u / NA, max(rg.n - 1, 0)), KC - 1);
+      const char* src = rows[u % NA] + (size_t)k * 1024;
+      const uint32_t d = lds0 + (uint32_t)(slot * Sh::TILES + u) * 1024u;
+      if (u % NA < NA - 2) copy(d, src);  // (only the last tile, or the last twice, can be ragged)
+      else if (rt0 + u % NA < (row_end - 1) >> 5 || row_on) copy(d, src);
+    }
+  };
+#pragma unroll
+  for (int i = 0; i < ROWS_RING - 1; ++i)
+    if (i < n_ch) issue(i, i);
+  if (ROWS_RING - 1 <= n_ch) rows_wait<(ROWS_RING - 3) * PER>();
+  else rows_wait<0>();
+  rows_barrier();
+  int slot = ROWS_RING - 1;
+  for (int c = 0; c < n_bar; ++c) {
+    if (c + ROWS_RING - 1 < n_ch) {
+      issue(c + ROWS_RING - 1, slot);
+      rows_wait<(ROWS_RING - 3) * PER>();
+    } else {
+      rows_wait<0>();
+    }
+    rows_barrier();
+    slot = slot + 1 == ROWS_RING ? 0 : slot + 1;
+  }
+}
+
+// The consumers' first UK weight tiles, asked for before the row count is known
+template <bool W8>
+struct RowsWeights {
+  static constexpr int N = W8 ? ROWS_UK / 2 : ROWS_UK;
+  uint4 t[N];
+};
+
+template <int NA, int FB, int EPI, bool F16, bool W8>
+__device__ __forceinline__ void rows_body(const GemmArgs& a, uint4* lds, RowsWeights<W8>& W, int tile, int s, int rt0,
+                                          int row_end) {
+  using Sh = RowsShape<NA, FB>;
+  constexpr int NC = Sh::NC, KP = Sh::KP, CT = Sh::CT, UK = Sh::UK, XR = Sh::XR, CH = Sh::TILES * 64;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int part = w / FB, nb = tile * FB + (w - part * FB), g = lane >> 5;
+  const bool wave_on = w < NC && nb < a.NB;
   f32x16 acc[NA];
 #pragma unroll
-  for (int mt = 0; mt < NA; ++mt)
+  for (int m = 0; m < NA; ++m)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[mt][i] = 0.f;
-  // Register stages as individually named variables (arrays of them end up in scratch
-  // memory): weight tiles (B0..B3) and activation tiles (A0..A3) of four steps each.
-  // Loads return in issue order, so a tile can only be consumed once everything issued
-  // before it has landed: the L2-resident activation tiles must be fetched as far ahead
-  // as the HBM-resident weight tiles, or they would wait behind them at every step.
-  uint4 B0_0, B0_1, B0_2, B0_3, B1_0, B1_1, B1_2, B1_3, B2_0, B2_1, B2_2, B2_3, B3_0, B3_1, B3_2, B3_3;
-  uint4 A0_0, A0_1, A0_2, A0_3, A1_0, A1_1, A1_2, A1_3, A2_0, A2_1, A2_2, A2_3, A3_0, A3_1, A3_2, A3_3;
-  A0_1 = A0_2 = A0_3 = A1_1 = A1_2 = A1_3 = make_uint4(0, 0, 0, 0);
-  A2_1 = A2_2 = A2_3 = A3_1 = A3_2 = A3_3 = make_uint4(0, 0, 0, 0);
+    for (int i = 0; i < 16; ++i) acc[m][i] = 0.f;
 
-  // step i of this workgroup covers k-tiles 4i .. 4i+3 of its K range
-#define VLAC_LOAD_B(i, P)                                   \
-  {                                                         \
-    const size_t k_ = (size_t)min((i), n_ks - 1) * (W8 ? 128 : 256); \
-    P##_0 = wsrc[k_];                                       \
-    P##_1 = wsrc[k_ + 64];                                  \
-    if constexpr (!W8) {                                    \
-      P##_2 = wsrc[k_ + 128];                               \
-      P##_3 = wsrc[k_ + 192];                               \
-    }                                                       \
-  }
-#define VLAC_LOAD_A(i, P)                                             \
-  {                                                                   \
-    const size_t k_ = (size_t)min((i), n_ks - 1) * 256;               \
-    P##_0 = xsrc[k_];                                                 \
-    if constexpr (NA > 1) P##_1 = xsrc[(size_t)KC * 64 + k_];         \
-    if constexpr (NA > 2) P##_2 = xsrc[(size_t)KC * 128 + k_];        \
-    if constexpr (NA > 3) P##_3 = xsrc[(size_t)KC * 192 + k_];        \
-  }
-#define VLAC_STORE_A(buf, P)                                                  \
-  {                                                                           \
-    lds[((buf) * MT + 0) * 256 + tid] = P##_0;                                \
-    if constexpr (NA > 1) lds[((buf) * MT + 1) * 256 + tid] = P##_1;          \
-    if constexpr (NA > 2) lds[((buf) * MT + 2) * 256 + tid] = P##_2;          \
-    if constexpr (NA > 3) lds[((buf) * MT + 3) * 256 + tid] = P##_3;          \
-  }
-#define VLAC_MMA(c, BW)                                                       \
-  _Pragma("unroll") for (int mt = 0; mt < NA; ++mt) acc[mt] =                 \
-      mfma32<F16>(BW, lds[(buf_ * MT + mt) * 256 + (c) * 64 + lane], acc[mt]);
-  // the weight tile of k-tile c of a step: a register of its own, or half of a slot of codes
-#define VLAC_MMA4(P)                                                                          \
-  if constexpr (W8) {                                                                         \
-    const uint4 w0_ = e4m3_slot_half(B##P##_0, 0), w1_ = e4m3_slot_half(B##P##_0, 1);         \
-    const uint4 w2_ = e4m3_slot_half(B##P##_1, 0), w3_ = e4m3_slot_half(B##P##_1, 1);         \
-    VLAC_MMA(0, w0_) VLAC_MMA(1, w1_) VLAC_MMA(2, w2_) VLAC_MMA(3, w3_)                       \
-  } else {                                                                                    \
-    VLAC_MMA(0, B##P##_0) VLAC_MMA(1, B##P##_1) VLAC_MMA(2, B##P##_2) VLAC_MMA(3, B##P##_3)   \
-  }
-  // Step i: stage slot P held step i (its activation tiles went to LDS during step i-1,
-  // its weight tiles are consumed now) and is refilled with step i+4; the activation
-  // tiles of step i+1 (slot PN) go to the other LDS buffer.  The phases are fenced
-  // against the instruction scheduler so that loads are issued in this order.
-#define VLAC_STEP(i, P, PN)                                                   \
-  {                                                                           \
-    const int buf_ = (i) & 1;                                                 \
-    __syncthreads();                                                          \
-    VLAC_LOAD_A((i) + 4, A##P)                                                \
-    __builtin_amdgcn_sched_barrier(0);                                        \
-    VLAC_MMA4(P)                                                              \
-    __builtin_amdgcn_sched_barrier(0);                                        \
-    VLAC_LOAD_B((i) + 4, B##P)                                                \
-    __builtin_amdgcn_sched_barrier(0);                                        \
-    VLAC_STORE_A(buf_ ^ 1, A##PN)                                             \
-  }
-
-  VLAC_LOAD_A(0, A0) VLAC_LOAD_B(0, B0)
-  VLAC_LOAD_A(1, A1) VLAC_LOAD_B(1, B1)
-  VLAC_LOAD_A(2, A2) VLAC_LOAD_B(2, B2)
-  VLAC_LOAD_A(3, A3) VLAC_LOAD_B(3, B3)
-  __builtin_amdgcn_sched_barrier(0);
-  asm volatile("" ::"v"(pf0), "v"(pf1));  // the touch loads end here, behind the real ones
-  VLAC_STORE_A(0, A0)
-  // Whole groups of 4 steps run in a loop without any branch inside (a conditional step
-  // would make the compiler assume the shortest path around the loop and wait for almost
-  // every load at the top of each iteration); the 0..3 remaining steps follow.
-  int i0 = 0;
-  for (; i0 + 4 <= n_ks; i0 += 4) {
-    VLAC_STEP(i0, 0, 1)
-    VLAC_STEP(i0 + 1, 1, 2)
-    VLAC_STEP(i0 + 2, 2, 3)
-    VLAC_STEP(i0 + 3, 3, 0)
-  }
-  if (i0 < n_ks) {
-    VLAC_STEP(i0, 0, 1)
-    if (i0 + 1 < n_ks) {
-      VLAC_STEP(i0 + 1, 1, 2)
-      if (i0 + 2 < n_ks) VLAC_STEP(i0 + 2, 2, 3)
+  int ids[NA];
+#pragma unroll
+  for (int m = 0; m < NA; ++m) ids[m] = 0;
+  if (w >= NC) {
+    rows_produce<NA, FB>(a, lds, w - Sh::NC, s, rt0, row_end);
+  } else {
+    const RowsRange rg = rows_range(a.KS, a.S * KP, s * KP + part);
+    const int n_max = rows_range(a.KS, a.S * KP, s * KP).n, n = rg.n;
+    const int n_min = KP == 1 ? n_max : rows_range(a.KS, a.S * KP, s * KP + KP - 1).n;
+    // (e4m3 weights: a 16-byte lane slot holds two k-tiles)
+    const int KC = 4 * a.KS;
+    const uint4* wsrc = a.wp + ((size_t)min(nb, a.NB - 1) * (W8 ? KC / 2 : KC) + (W8 ? rg.k0 / 2 : rg.k0)) * 64 + lane;
+    uint4 X[XR][NA];
+    int slot = 0;
+    const uint4 *cur = lds + (size_t)part * CT * NA * 64 + lane, *nxt = cur + CH;
+    auto next_chunk = [&]() {
+      rows_barrier();
+      slot = slot + 1 == ROWS_RING ? 0 : slot + 1;
+      cur = nxt;
+      nxt = slot + 1 == ROWS_RING ? nxt - (ROWS_RING - 1) * CH : nxt + CH;
+    };
+    // k-tile t of a run of UK: the products, and behind each the read of the operand XR k-tiles on
+    auto ktile = [&](int t, bool on) {
+      uint4 wt;
+      if constexpr (W8) wt = e4m3_slot_half(W.t[t >> 1], t & 1);
+      else wt = W.t[t];
+#pragma unroll
+      for (int m = 0; m < NA; ++m) {
+        if (on) acc[m] = mfma32<F16>(wt, X[t % XR][m], acc[m]);
+        const int c = t % CT + XR;
+        X[t % XR][m] = (c < CT ? cur + (c * NA + m) * 64 : nxt + ((c - CT) * NA + m) * 64)[0];
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    auto reload = [&](int t, int k) {  // W.t[t] <- k-tile k (and k + 1)
+      if constexpr (W8) {
+        if (t & 1) W.t[t >> 1] = ld_stream(wsrc + (size_t)(k >> 1) * 64);
+      } else {
+        W.t[t] = ld_stream(wsrc + (size_t)k * 64);
+      }
+    };
+    if (EPI != EPI_LOGITS && !(EPI == EPI_RESID && a.S > 1)) {
+      // (asked for here, used by the epilogue: one round trip less at the end)
+#pragma unroll
+      for (int m = 0; m < NA; ++m) ids[m] = a.e.rows[min((rt0 + m) * 32 + (lane & 31), row_end - 1)];
     }
-  }
-#undef VLAC_MMA4
-#undef VLAC_MMA
-#undef VLAC_STEP
-#undef VLAC_STORE_A
-#undef VLAC_LOAD_A
-#undef VLAC_LOAD_B
-
-  if constexpr (W8) {
-    if (wave_on) {
+    rows_barrier();
 #pragma unroll
-      for (int mt = 0; mt < NA; ++mt) scale_tile(a.wscale, nb, lane >> 5, acc[mt]);
-    }
-  }
-  if (EPI == EPI_RESID && a.S > 1) {
-    // Projection + residual with split K: every split writes its partial rows
-    // [split][row][feature] and is done; the row kernel that follows (residual add +
-    // RMSNorm) adds the splits up, so nothing is handed over inside this kernel.
-    if (!wave_on) return;
-    const int g = lane >> 5;
+    for (int x = 0; x < XR; ++x)
 #pragma unroll
-    for (int mt = 0; mt < NA; ++mt) {
-      const int slot = row0 + mt * 32 + (lane & 31);
-      if (slot < n_rows) {
-        float* dst = a.e.rpart + ((size_t)s * a.e.rpart_rows + slot) * a.e.d_model + nb * 32 + 4 * g;
+      for (int m = 0; m < NA; ++m) X[x][m] = cur[(x * NA + m) * 64];
+    // Runs without a branch inside (the compiler then counts the loads in flight exactly); the last
+    // full run and the rest step by 64 k and ask for no weights past the end.
+    int base = 0;
+    for (; base + 2 * UK <= n_min; base += UK) {
 #pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4)
-          *(float4*)(dst + 8 * q4) = make_float4(acc[mt][4 * q4], acc[mt][4 * q4 + 1],
-                                                 acc[mt][4 * q4 + 2], acc[mt][4 * q4 + 3]);
+      for (int t = 0; t < UK; ++t) {
+        ktile(t, true);
+        reload(t, base + t + UK);
+        if ((t + 1) % CT == 0) next_chunk();
       }
     }
-    return;
-  }
-  if (a.S > 1) {
-    // split-K: park the partial sums; the last workgroup of this (tile, row block) adds them up
-    const size_t per_wave = (size_t)MT * 16 * 64;
-    float* base = a.partial + ((size_t)(tile * a.MB + mb) * a.S) * 4 * per_wave;
-    float* mine = base + ((size_t)s * 4 + w) * per_wave + lane;
+    for (; base < n_max; base += UK) {
 #pragma unroll
-    for (int mt = 0; mt < NA; ++mt)
+      for (int u = 0; u < UK; u += 4) {
+        const int k = base + u;
+        if (k < n_max) {
+          const bool on = k < n;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) st_coherent(mine + (mt * 16 + i) * 64, acc[mt][i]);
-    stores_done();
-    __syncthreads();
-    if (tid == 0) {
-      int* cnt = a.counters + tile * a.MB + mb;
-      const int old = atomicAdd(cnt, 1);
-      *s_last = (old == a.S - 1);
-      if (old == a.S - 1) *cnt = 0;  // ready for the next launch
-    }
-    __syncthreads();
-    if (!*s_last) return;
+          for (int t = u; t < u + 4; ++t) {
+            if (on) ktile(t, true);
+            if ((t + 1) % CT == 0) next_chunk();
+          }
+          if (k + UK < n) {
 #pragma unroll
-    for (int mt = 0; mt < NA; ++mt)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[mt][i] = 0.f;
-    for (int ss = 0; ss < a.S; ++ss) {  // fixed order; a whole split's worth of loads in flight
-      const float* src = base + ((size_t)ss * 4 + w) * per_wave + lane;
-      float t[NA][16];
-#pragma unroll
-      for (int mt = 0; mt < NA; ++mt)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) t[mt][i] = ld_coherent(src + (mt * 16 + i) * 64);
-#pragma unroll
-      for (int mt = 0; mt < NA; ++mt)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[mt][i] += t[mt][i];
+            for (int t = u; t < u + 4; ++t) reload(t, k + (t - u) + UK);
+          }
+        }
+      }
     }
   }
 
-  if (!wave_on) return;
-  const int g = lane >> 5;
+  if constexpr (KP == 2) {
+    // The parts' sums meet in LDS: part 0 finishes the first NH row tiles, part 1 the others
+    // (sum = first part + second part).
+    constexpr int NH = (NA + 1) / 2;
+    __syncthreads();
+    static_assert(FB == 2, "the other part of a wave's block is two waves on");
+    float* mine = (float*)lds + (size_t)(w & 3) * (NH * 16 * 64) + lane;
+    const float* theirs = (const float*)lds + (size_t)((w & 3) ^ FB) * (NH * 16 * 64) + lane;
+    if (w < 4) {
 #pragma unroll
-  for (int mt = 0; mt < NA; ++mt) {
-    const int slot = row0 + mt * 32 + (lane & 31);
-    if (slot < n_rows) {
-      const int id = (EPI == EPI_LOGITS) ? 0 : a.e.rows[slot];
-      epilogue_tile<EPI, F16>(a.e, nb, slot, id, g, acc[mt]);
+      for (int m = 0; m < NA; ++m)
+        if ((m >= NH) != (part == 1)) {
+#pragma unroll
+          for (int i = 0; i < 16; ++i) mine[((m >= NH ? m - NH : m) * 16 + i) * 64] = acc[m][i];
+        }
+    }
+    __syncthreads();
+    if (w < 4) {
+#pragma unroll
+      for (int m = 0; m < NA; ++m)
+        if ((m >= NH) == (part == 1)) {
+#pragma unroll
+          for (int i = 0; i < 16; ++i) acc[m][i] += theirs[((m >= NH ? m - NH : m) * 16 + i) * 64];
+        }
+    }
+  }
+  if (!wave_on) return;
+#pragma unroll
+  for (int m = 0; m < NA; ++m) {
+    if (KP == 2 && (m >= (NA + 1) / 2) != (part == 1)) continue;
+    if constexpr (W8) scale_tile(a.wscale, nb, g, acc[m]);
+    const int row = (rt0 + m) * 32 + (lane & 31);
+    if (row >= row_end) continue;
+    if (EPI == EPI_RESID && a.S > 1) {
+      // Projection + residual with split K: every split writes its partial rows
+      // [split][row][feature] and is done; the row kernel that follows (residual add +
+      // RMSNorm) adds the splits up, so nothing is handed over between workgroups.
+      float* dst = a.e.rpart + ((size_t)s * a.e.rpart_rows + row) * a.e.d_model + nb * 32 + 4 * g;
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4)
+        *(float4*)(dst + 8 * q4) =
+            make_float4(acc[m][4 * q4], acc[m][4 * q4 + 1], acc[m][4 * q4 + 2], acc[m][4 * q4 + 3]);
+    } else {
+      epilogue_tile<EPI, F16>(a.e, nb, row, ids[m], g, acc[m]);
     }
   }
 }
 
-template <int MT, int EPI, bool F16, bool W8>
-__global__ __launch_bounds__(256) void gemm_rows_kernel(GemmArgs a) {
-  extern __shared__ uint4 lds[];  // [2][MT][256]: two stages of MT activation tiles x 4 k-tiles
-  __shared__ int s_last;
+template <int FB, int EPI, bool F16, bool W8>
+__global__ __launch_bounds__(rows_threads(FB)) void gemm_rows_kernel(GemmArgs a) {
+  extern __shared__ uint4 lds[];  // [ROWS_RING][part][k-tile][row tile][64]
   // workgroup id -> (row block, weight tile, split); id % 8 is the XCD.  With the row
   // count known on the host every row block has work, and the blocks of one weight tile
   // sit next to each other.  Otherwise the grid covers the largest possible row count,
   // and the row block is the slowest index: the workgroups of empty row blocks (which
   // only find that out from device memory) would else sit between the working ones in
-  // dispatch order and hold their places.  (Measured: that pays when one row block's
-  // workgroups fit on the chip at once, P <= 256; with more, the staggered start of the
-  // interleaved order is the better one.)
+  // dispatch order and hold their places.
   int mb, p;
   if (a.n_rows_val >= 0 || a.P > 256) {
     const int y = blockIdx.x >> 3;
@@ -247,30 +310,37 @@ __global__ __launch_bounds__(256) void gemm_rows_kernel(GemmArgs a) {
   }
   if (p >= a.P) return;
   const int tile = p / a.S, s = p - tile * a.S;
-  // The row count sits in device memory, and nothing can be loaded into registers before
-  // it is known (the loop is specialised by it).  The first row block, which always has
-  // work, touches the first 16 KiB of every wave's weight stream meanwhile (one dword per
-  // 128-byte line), so that the stream starts from L2 one round trip later.
-  uint32_t pf0 = 0, pf1 = 0;
-  if (mb == 0 && a.n_rows_val < 0) {
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, nb = min(tile * 4 + w, a.NB - 1);
-    const int q = a.KS / a.S, r = a.KS % a.S;
-    const int ks0 = s * q + min(s, r), n_ks = q + (s < r ? 1 : 0);
-    if (n_ks >= 4) {
-      const uint32_t* pw = (const uint32_t*)(a.wp + ((size_t)nb * 4 * a.KS + 4 * ks0) * (W8 ? 32 : 64)) + lane * 32;
-      pf0 = pw[0];
-      pf1 = pw[W8 ? 0 : 2048];
-    }
-  }
-  const int n_rows = a.n_rows_val >= 0 ? a.n_rows_val : *a.n_rows;
-  const int row0 = mb * MT * 32;
-  if (row0 >= n_rows || n_rows >= a.rows_hi) return;  // (rows_hi and more: the many-rows kernel's share)
-  static_assert(MT == 4, "row blocks are 4 tiles of 32 rows");
-  switch (min(MT, (n_rows - row0 + 31) >> 5)) {
-    case 1: rows_body<1, MT, EPI, F16, W8>(a, lds, &s_last, tile, s, mb, n_rows, pf0, pf1); break;
-    case 2: rows_body<2, MT, EPI, F16, W8>(a, lds, &s_last, tile, s, mb, n_rows, pf0, pf1); break;
-    case 3: rows_body<3, MT, EPI, F16, W8>(a, lds, &s_last, tile, s, mb, n_rows, pf0, pf1); break;
-    default: rows_body<4, MT, EPI, F16, W8>(a, lds, &s_last, tile, s, mb, n_rows, pf0, pf1); break;
+  // The first row block always has work: its consumers ask for their first weights before the
+  // row count (in device memory) is known.
+  constexpr int NC = rows_consumers(FB), KP = NC / FB;
+  RowsWeights<W8> W;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  auto first_weights = [&]() {
+    const RowsRange rg = rows_range(a.KS, a.S * KP, s * KP + w / FB);
+    const int KC = 4 * a.KS, nb = min(tile * FB + w % FB, a.NB - 1);
+    const uint4* src = a.wp + ((size_t)nb * (W8 ? KC / 2 : KC) + (W8 ? rg.k0 / 2 : rg.k0)) * 64 + (threadIdx.x & 63);
+    const int cnt = W8 ? rg.n / 2 : rg.n;  // (0: a part that K is too short for)
+#pragma unroll
+    for (int i = 0; i < RowsWeights<W8>::N; ++i)
+      if (i < cnt) W.t[i] = ld_stream(src + (size_t)i * 64);
+  };
+  if (mb == 0 && w < NC) first_weights();
+  const int n_rows = __builtin_amdgcn_readfirstlane(a.n_rows_val >= 0 ? a.n_rows_val : *a.n_rows);
+  // row tiles are dealt to as few blocks of at most 6 as hold them, in equal shares
+  const int n_rt = (n_rows + 31) >> 5, n_blk = (n_rt + 5) / 6;
+  if (mb >= n_blk || n_rows >= a.rows_hi) return;  // (rows_hi and more: the many-rows kernel's share)
+  if (mb != 0 && w < NC) first_weights();
+  const int rt0 = __builtin_amdgcn_readfirstlane(mb * n_rt / n_blk);
+  const int rt1 = __builtin_amdgcn_readfirstlane((mb + 1) * n_rt / n_blk), row_end = min(n_rows, 32 * rt1);
+  // (5 row tiles run as 6: a tile past the block's last is the last again, and dropped)
+  switch (rt1 - rt0) {
+#define VLAC_NA(N) rows_body<N, FB, EPI, F16, W8>(a, lds, W, tile, s, rt0, row_end); break;
+    case 1: VLAC_NA(1)
+    case 2: VLAC_NA(2)
+    case 3: VLAC_NA(3)
+    case 4: VLAC_NA(4)
+    default: VLAC_NA(6)
+#undef VLAC_NA
   }
 }
 
@@ -517,45 +587,48 @@ __global__ __launch_bounds__(256, XMODE == X_NORM8 ? 2 : 3) void gemm_few_kernel
   }
 }
 
-template <int MT, int EPI>
+static const int kRowsLds = ROWS_RING * 32 * 1024;
+
+template <int FB, int EPI>
 static hipError_t set_attr() {
-  hipError_t e = hipFuncSetAttribute((const void*)gemm_rows_kernel<MT, EPI, false, false>,
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, 2 * MT * 4096);
+  hipError_t e = hipFuncSetAttribute((const void*)gemm_rows_kernel<FB, EPI, false, false>,
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, kRowsLds);
   if (e != hipSuccess) return e;
-  e = hipFuncSetAttribute((const void*)gemm_rows_kernel<MT, EPI, true, false>,
-                          hipFuncAttributeMaxDynamicSharedMemorySize, 2 * MT * 4096);
+  e = hipFuncSetAttribute((const void*)gemm_rows_kernel<FB, EPI, true, false>,
+                          hipFuncAttributeMaxDynamicSharedMemorySize, kRowsLds);
   if (e != hipSuccess) return e;
-  return hipFuncSetAttribute((const void*)gemm_rows_kernel<MT, EPI, true, true>,
-                             hipFuncAttributeMaxDynamicSharedMemorySize, 2 * MT * 4096);
+  return hipFuncSetAttribute((const void*)gemm_rows_kernel<FB, EPI, true, true>,
+                             hipFuncAttributeMaxDynamicSharedMemorySize, kRowsLds);
 }
 
 int gemm_init() {
   hipError_t e;
-#define VLAC_SET(MT)                                                    \
-  if ((e = set_attr<MT, EPI_QKV>()) != hipSuccess) return (int)e;       \
-  if ((e = set_attr<MT, EPI_RESID>()) != hipSuccess) return (int)e;     \
-  if ((e = set_attr<MT, EPI_SWIGLU>()) != hipSuccess) return (int)e;    \
-  if ((e = set_attr<MT, EPI_LOGITS>()) != hipSuccess) return (int)e;
-  VLAC_SET(4)
+#define VLAC_SET(FB)                                                    \
+  if ((e = set_attr<FB, EPI_QKV>()) != hipSuccess) return (int)e;       \
+  if ((e = set_attr<FB, EPI_SWIGLU>()) != hipSuccess) return (int)e;
+  VLAC_SET(4) VLAC_SET(3) VLAC_SET(2)
+  if ((e = set_attr<4, EPI_RESID>()) != hipSuccess) return (int)e;
+  if ((e = set_attr<2, EPI_RESID>()) != hipSuccess) return (int)e;
+  if ((e = set_attr<4, EPI_LOGITS>()) != hipSuccess) return (int)e;
 #undef VLAC_SET
   return gemm_tall_init();
 }
 
-template <int MT, bool F16, bool W8>
-static void launch_mt(int epi, const GemmArgs& a, int grid, hipStream_t st) {
-  const size_t shm = (size_t)2 * MT * 4096;
+template <int FB, bool F16, bool W8>
+static void launch_rows(int epi, const GemmArgs& a, int grid, hipStream_t st) {
+  const dim3 g(grid), t(rows_threads(FB));
   switch (epi) {
     case EPI_QKV:
-      hipLaunchKernelGGL((gemm_rows_kernel<MT, EPI_QKV, F16, W8>), dim3(grid), dim3(256), shm, st, a);
+      hipLaunchKernelGGL((gemm_rows_kernel<FB, EPI_QKV, F16, W8>), g, t, kRowsLds, st, a);
       break;
-    case EPI_RESID:
-      hipLaunchKernelGGL((gemm_rows_kernel<MT, EPI_RESID, F16, W8>), dim3(grid), dim3(256), shm, st, a);
+    case EPI_RESID:  // (4 or 2 feature blocks)
+      hipLaunchKernelGGL((gemm_rows_kernel<FB == 4 ? 4 : 2, EPI_RESID, F16, W8>), g, t, kRowsLds, st, a);
       break;
     case EPI_SWIGLU:
-      hipLaunchKernelGGL((gemm_rows_kernel<MT, EPI_SWIGLU, F16, W8>), dim3(grid), dim3(256), shm, st, a);
+      hipLaunchKernelGGL((gemm_rows_kernel<FB, EPI_SWIGLU, F16, W8>), g, t, kRowsLds, st, a);
       break;
-    default:
-      hipLaunchKernelGGL((gemm_rows_kernel<MT, EPI_LOGITS, F16, W8>), dim3(grid), dim3(256), shm, st, a);
+    default:  // (always 4)
+      hipLaunchKernelGGL((gemm_rows_kernel<4, EPI_LOGITS, F16, W8>), g, t, kRowsLds, st, a);
       break;
   }
 }
@@ -615,27 +688,37 @@ static int tall_resid_smax(const vlac_ctx* c, int epi, int rows_cap, int d_model
   return fit >= 8 ? 8 : fit >= 3 ? (int)fit : 1;
 }
 
-// Split factor of the one-stream kernel (row blocks of 128 rows, MB of them in the grid).
-// Split K so that ONE row block (the sparse prefill usually fills one; a full recompute
-// runs several side by side) gives about one workgroup per CU.  The projections with
-// a residual round up (their splits cost next to nothing: the row kernel that follows
-// adds the partial rows); the others round DOWN: their split-K hand-over at the end of
-// the kernel costs more than leaving a third of the CUs without a workgroup (measured
-// at the 7B shape, 109 rows: gate/up with 172 tiles 52 us unsplit against 63 us in two
-// splits; QKV with 96 tiles 42 us in two splits against 52 us in three).
-static int rows_kernel_splits(const vlac_ctx* c, int epi, int n_blocks, int KS, int MB, int rpart_rows, int d_model) {
-  const int tiles = (n_blocks + 3) / 4;
-  int S = epi == EPI_RESID ? (256 + tiles - 1) / tiles : 256 / tiles;
+// Feature blocks per workgroup of the one-stream kernel (2 leave K to two pairs of waves).  What
+// a CU fetches is the limit (about 50 GB/s each with weights from HBM and row operands from L2 in
+// one queue), so taken is the width with the least rounds of 256 workgroups x bytes per workgroup:
+// its weight rows and, for up to 4 row tiles, all operand rows.  7B, 109 rows: gate/up (688 blocks)
+// 41.7 us with 3 against 46.8 with 4; QKV (384 blocks) 34 us with 2, K in two parts.
+// (The projections with a residual have split K besides: 4 blocks and 8 splits where K is long,
+// which fetches a third less per workgroup but doubles the partial rows; 2 blocks and half the
+// splits where it is not.)
+static int rows_kernel_fb(int epi, int n_blocks, int KS) {
+  if (epi == EPI_LOGITS) return 4;
+  if (epi == EPI_RESID) return KS >= 128 && n_blocks >= 128 ? 4 : 2;
+  int best = 4, least = 0x7fffffff;
+  for (int fb = 4; fb >= 2; --fb) {
+    const int cost = ((n_blocks + fb - 1) / fb + 255) / 256 * (32 * fb + 128);
+    if (cost < least) { least = cost; best = fb; }
+  }
+  return best;
+}
+
+// Split factor of the one-stream kernel: the projections with a residual, whose partial rows the
+// row kernel that follows adds up, split K so that ONE row block (the sparse prefill usually fills
+// one) gives about one workgroup per CU; a workgroup keeps at least 4 steps of 64 k.  The others
+// do not split over workgroups: a hand-over between them costs more than idle CUs.
+static int rows_kernel_splits(const vlac_ctx* c, int epi, int n_blocks, int KS, int rpart_rows, int d_model) {
+  if (epi != EPI_RESID) return 1;
+  const int fb = rows_kernel_fb(epi, n_blocks, KS), tiles = (n_blocks + fb - 1) / fb;
+  int S = (256 + tiles - 1) / tiles;
   if (S > KS / 4) S = KS / 4;
   if (S > 8) S = 8;
-  if (S < 1) S = 1;
-  if (epi == EPI_RESID) {
-    while (S > 1 && (size_t)S * rpart_rows * d_model > c->rpart_floats) --S;
-  } else {
-    while (S > 1 && (size_t)tiles * MB * S * 4 * 4 * 16 * 64 > c->partial_floats) --S;
-    if (tiles * MB > c->n_counters) S = 1;
-  }
-  return S;
+  while (S > 1 && (size_t)S * rpart_rows * d_model > c->rpart_floats) --S;
+  return S < 1 ? 1 : S;
 }
 
 // Where the many-rows kernel serves a capacity at which a sparse prefill usually leaves
@@ -668,7 +751,7 @@ SplitAdapt gemm_resid_adapt(vlac_ctx* c, int n_blocks, int kpad, int rows_cap, c
     ad.KS = kpad / 64;
     if (both) {
       ad.small_below = kSmallRows;
-      ad.S_small = rows_kernel_splits(c, EPI_RESID, n_blocks, kpad / 64, kSmallRows / 128, rows_cap, d_model);
+      ad.S_small = rows_kernel_splits(c, EPI_RESID, n_blocks, kpad / 64, rows_cap, d_model);
     }
   }
   return ad;
@@ -676,15 +759,21 @@ SplitAdapt gemm_resid_adapt(vlac_ctx* c, int n_blocks, int kpad, int rows_cap, c
 
 // the one-stream kernel for up to rows_cap rows; sets and returns a.S
 static int launch_rows_kernel(vlac_ctx* c, int epi, GemmArgs& a, int rows_cap, const GemmEpi& e, hipStream_t st) {
-  constexpr int MT = 4;
-  const int tiles = (a.NB + 3) / 4;
-  a.MB = (rows_cap + MT * 32 - 1) / (MT * 32);
-  a.S = rows_kernel_splits(c, epi, a.NB, a.KS, a.MB, e.rpart_rows, e.d_model);
+  const int fb = rows_kernel_fb(epi, a.NB, a.KS), tiles = (a.NB + fb - 1) / fb;
+  a.MB = ((rows_cap + 31) / 32 + 5) / 6;
+  a.S = rows_kernel_splits(c, epi, a.NB, a.KS, e.rpart_rows, e.d_model);
   a.P = tiles * a.S;
   const int grid = ((a.P + 7) / 8) * 8 * a.MB;
-  if (c->w8) launch_mt<MT, true, true>(epi, a, grid, st);
-  else if (c->f16) launch_mt<MT, true, false>(epi, a, grid, st);
-  else launch_mt<MT, false, false>(epi, a, grid, st);
+#define VLAC_ROWS(FB_)                                          \
+  {                                                             \
+    if (c->w8) launch_rows<FB_, true, true>(epi, a, grid, st);  \
+    else if (c->f16) launch_rows<FB_, true, false>(epi, a, grid, st); \
+    else launch_rows<FB_, false, false>(epi, a, grid, st);      \
+  }
+  if (fb == 4) VLAC_ROWS(4)
+  else if (fb == 3) VLAC_ROWS(3)
+  else VLAC_ROWS(2)
+#undef VLAC_ROWS
   return a.S;
 }
 
