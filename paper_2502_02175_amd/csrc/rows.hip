@@ -425,33 +425,58 @@ void launch_resid_norm_rows(bool f16, const float* resid, int resid_seq_stride, 
 #undef VLAC_RN
 }
 
-// Final RMSNorm of every row alive at the last layer, fp32 out [B, L, d].
+// Final RMSNorm of every row alive at the last layer, fp32 out [B, L, d].  One workgroup per row;
+// a thread keeps its share of the first 8192 values in registers, so that all loads of a row are
+// in flight together (one wave per row that read it twice, 256 values at a time: 12.5 us for 109
+// rows of 4096 values, now 5.5; 2712 rows 22 -> 16).
 __global__ __launch_bounds__(256) void final_hidden_kernel(
     const float* __restrict__ src, int seq_stride, const int* __restrict__ rows,
     const int* __restrict__ n_rows, const float* __restrict__ gain, float eps, int d,
     float* __restrict__ out, int L) {
-  const int slot = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  constexpr int NI = 8;
+  __shared__ float red[4];
+  const int slot = blockIdx.x, tid = threadIdx.x;
   if (slot >= *n_rows) return;
   const int id = rows[slot];
   const float* x = src + ((size_t)(id >> 16) * seq_stride + (id & 0xffff)) * d;
   float* y = out + ((size_t)(id >> 16) * L + (id & 0xffff)) * d;
+  float4 v[NI], g[NI];
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const int k = tid * 4 + i * 1024;
+    v[i] = g[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (k < d) {
+      v[i] = *(const float4*)(x + k);
+      g[i] = *(const float4*)(gain + k);
+    }
+  }
   float ss = 0.f;
-  for (int k = lane * 4; k < d; k += 256) {
-    const float4 v = *(const float4*)(x + k);
-    ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+#pragma unroll
+  for (int i = 0; i < NI; ++i) ss += v[i].x * v[i].x + v[i].y * v[i].y + v[i].z * v[i].z + v[i].w * v[i].w;
+  for (int k = tid * 4 + NI * 1024; k < d; k += 1024) {
+    const float4 q = *(const float4*)(x + k);
+    ss += q.x * q.x + q.y * q.y + q.z * q.z + q.w * q.w;
   }
   ss = wave_sum(ss);
-  const float r = rsqrtf(ss / (float)d + eps);
-  for (int k = lane * 4; k < d; k += 256) {
-    const float4 v = *(const float4*)(x + k), g = *(const float4*)(gain + k);
-    *(float4*)(y + k) = make_float4(v.x * r * g.x, v.y * r * g.y, v.z * r * g.z, v.w * r * g.w);
+  if ((tid & 63) == 0) red[tid >> 6] = ss;
+  __syncthreads();
+  const float r = rsqrtf((red[0] + red[1] + red[2] + red[3]) / (float)d + eps);
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const int k = tid * 4 + i * 1024;
+    if (k < d)
+      *(float4*)(y + k) = make_float4(v[i].x * r * g[i].x, v[i].y * r * g[i].y, v[i].z * r * g[i].z, v[i].w * r * g[i].w);
+  }
+  for (int k = tid * 4 + NI * 1024; k < d; k += 1024) {
+    const float4 q = *(const float4*)(x + k), h = *(const float4*)(gain + k);
+    *(float4*)(y + k) = make_float4(q.x * r * h.x, q.y * r * h.y, q.z * r * h.z, q.w * r * h.w);
   }
 }
 
 void launch_final_hidden(const float* src, int seq_stride, const int* rows, const int* n_rows,
                          int max_rows, const float* gain, float eps, int d, float* out, int L,
                          hipStream_t st) {
-  hipLaunchKernelGGL(final_hidden_kernel, dim3((max_rows + 3) / 4), dim3(256), 0, st, src,
+  hipLaunchKernelGGL(final_hidden_kernel, dim3(max_rows), dim3(256), 0, st, src,
                      seq_stride, rows, n_rows, gain, eps, d, out, L);
 }
 
