@@ -43,19 +43,25 @@
 
 namespace {
 
-#ifndef VLAC_TALL_RING
-#define VLAC_TALL_RING 5
-#endif
-constexpr int TALL_RING = VLAC_TALL_RING;  // LDS stages: 5 x 32 KiB is all the LDS of a CU
-// copies younger than the stage a step waits for: those of the TALL_RING - 2 stages behind it
-#if VLAC_TALL_RING == 5
-#define VLAC_TALL_WAIT() VLAC_VMCNT(24)
-#elif VLAC_TALL_RING == 4
-#define VLAC_TALL_WAIT() VLAC_VMCNT(16)
+// Per row-block size (RT row tiles per wave): a stage is 16 weight tiles and 4 RT activation tiles,
+// a quarter of which each wave copies; as many stages as a CU's 160 KiB of LDS hold.
+template <int RT>
+struct TallRing {
+  static constexpr int COPIES = 4 + RT;            // copies (1 KiB) per stage and wave
+  static constexpr int STAGE = 256 * COPIES;       // uint4 per stage: 32, 28 or 24 KiB
+  static constexpr int N = 160 / (4 * COPIES);     // stages: 5, 5 or 6
+  static constexpr int YOUNGER = COPIES * (N - 2); // copies behind the stage a step waits for
+  static_assert(YOUNGER <= 63, "the counter holds 63");
+};
+constexpr int kTallLds = 160 * 1024;
+template <int N>
+__device__ inline void tall_wait() {
+#ifdef VLAC_SAFE_WAITS
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #else
-#error "add the wait for this ring size"
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 #endif
-constexpr int TALL_STAGE = 2048;        // uint4 per stage: 32 tiles of 64
+}
 constexpr int kTallGrid = 256;          // one workgroup per CU (a workgroup takes all of a CU's LDS)
 
 // A work item: weight tile, K part, row block
@@ -63,12 +69,14 @@ struct TallItem { int tile, s, mb; };
 
 // RT: row tiles per wave (4: blocks of 256 rows, 3: of 192, 2: of 128); NA: how many of them hold rows.
 // Runs item `it`; `nx` is the item this workgroup runs next (chain: there is one, and the last
-// TALL_RING - 1 steps of this item copy its first stages instead of stages past the end).
-// prefilled: the copies of this item's first TALL_RING - 1 stages have been issued already (by
+// RING - 1 steps of this item copy its first stages instead of stages past the end).
+// prefilled: the copies of this item's first RING - 1 stages have been issued already (by
 // the item before) into the ring from `slot` on.  Returns the ring slot after the last stage.
 template <int RT, int NA, int EPI, bool F16>
 __device__ __forceinline__ int tall_body(const GemmArgs& a, uint4* lds, TallItem it, TallItem nx, bool chain,
                                           bool prefilled, int slot, int n_rows, int S) {
+  constexpr int RING = TallRing<RT>::N, STAGE = TallRing<RT>::STAGE, C = TallRing<RT>::COPIES;
+  constexpr int AHEAD = RING - 1;  // stages that the copies run ahead
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wi = w & 1, wj = w >> 1;  // feature half, row interleave
@@ -79,35 +87,33 @@ __device__ __forceinline__ int tall_body(const GemmArgs& a, uint4* lds, TallItem
   const int step0n = nx.s * sq + min(nx.s, sr), n_steps_n = sq + (nx.s < sr ? 1 : 0);
   const int row0 = it.mb * (64 * RT);
   const int nb0 = it.tile * 8;
-  // This wave copies, per stage, the weight tiles of feature blocks 2w, 2w + 1 and the
-  // activation tiles of row tiles 2w, 2w + 1 of the block (both k-tiles of each: 2 KiB that
-  // lie together in global memory and in LDS).  Row blocks of 128 rows have 4 row tiles:
-  // waves 2 and 3 copy tiles 4..7 all the same (clamped, unread).
+  // A stage in LDS: the 8 feature blocks, then the 2 RT row tiles, both k-tiles of each (2 KiB that
+  // lie together in global memory as well).  Wave w copies the C = 4 + RT KiB from w C on.
   // (scalar base addresses: a copy is then one scalar select, one scalar add and the load, with
   // the lane's 16-byte offset in one register for all of them; a wave has one instruction stream,
   // and what a copy costs to issue is taken from its MFMAs)
-  const char *src[4], *srcn[4];
-  uint32_t dst[4];
-  const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lds);
+  const char *src[C], *srcn[C];
+  const uint32_t dst0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lds) + (uint32_t)(w * C) * 1024u;
   const uint32_t lane_off = (uint32_t)lane * 16u;
 #pragma unroll
-  for (int p = 0; p < 2; ++p) {
-    const int fb = 2 * w + p;
-    src[p] = (const char*)(a.wp + ((size_t)min(nb0 + fb, a.NB - 1) * KC + 2 * step0) * 64);
-    srcn[p] = (const char*)(a.wp + ((size_t)min(nx.tile * 8 + fb, a.NB - 1) * KC + 2 * step0n) * 64);
-    dst[p] = lds0 + (uint32_t)(fb * 2) * 1024u;
-    src[2 + p] = (const char*)(a.xp + ((size_t)min((row0 >> 5) + fb, a.x_tiles - 1) * KC + 2 * step0) * 64);
-    srcn[2 + p] = (const char*)(a.xp + ((size_t)min(nx.mb * (2 * RT) + fb, a.x_tiles - 1) * KC + 2 * step0n) * 64);
-    dst[2 + p] = lds0 + 16384u + (uint32_t)(fb * 2) * 1024u;
+  for (int j = 0; j < C; ++j) {
+    const int c = w * C + j, row = c >> 1, half = c & 1;
+    auto base = [&](int tile, int mb, int step) {
+      const uint4* t = row < 8 ? a.wp + ((size_t)min(tile * 8 + row, a.NB - 1) * KC + 2 * step) * 64
+                               : a.xp + ((size_t)min(mb * (2 * RT) + row - 8, a.x_tiles - 1) * KC + 2 * step) * 64;
+      return (const char*)t + half * 1024;
+    };
+    src[j] = base(it.tile, it.mb, step0);
+    srcn[j] = base(nx.tile, nx.mb, step0n);
   }
-  // one eighth (j) of this wave's copies of stage i: k-tile j % 2 of operand tile row j / 2.
+  // copy j of this wave's C of stage i.
   // Stages past this item's last are the next item's first (chain), else its last again
   // (never read): the number of copies per step is the same at every step.
   auto copy_one = [&](int i, int slot_, int j) {
     const bool mine = i < n_steps || !chain;
     const size_t k = (size_t)(mine ? min(i, n_steps - 1) : min(i - n_steps, n_steps_n - 1)) * 2048;  // 2 k-tiles of 1 KiB
-    const char* sp = (mine ? src[j >> 1] : srcn[j >> 1]) + k + (j & 1) * 1024;
-    const uint32_t d = dst[j >> 1] + (uint32_t)slot_ * (TALL_STAGE * 16) + (uint32_t)(j & 1) * 1024u;
+    const char* sp = (mine ? src[j] : srcn[j]) + k;
+    const uint32_t d = dst0 + (uint32_t)slot_ * (STAGE * 16) + (uint32_t)j * 1024u;
     asm volatile(
         "s_mov_b32 m0, %0\n\t"
         "s_nop 0\n\t"
@@ -141,11 +147,11 @@ __device__ __forceinline__ int tall_body(const GemmArgs& a, uint4* lds, TallItem
       if (q == 4 + m) Xf[m] = s[1024 + (2 * m + wj) * 128];
   };
 
-  // Copies in flight: 8 per stage and wave.  When step i needs stage i + 1 (at its barrier)
-  // the stages i + 2 .. i + TALL_RING - 1 have been asked for behind it: "at most 8 (TALL_RING - 2)
+  // Copies in flight: C per stage and wave.  When step i needs stage i + 1 (at its barrier)
+  // the stages i + 2 .. i + RING - 1 have been asked for behind it: "at most C (RING - 2)
   // outstanding" means that this wave's part of stage i + 1 has landed, and the barrier makes
   // that all four parts.  The same barrier says that every wave has read all of stage i (its
-  // LDS reads are waited for before it), whose slot the copies of stage i + TALL_RING may then
+  // LDS reads are waited for before it), whose slot the copies of stage i + RING may then
   // overwrite; they are issued during step i + 1.  Stages are numbered on through a chain of
   // items, so all of this holds across the item boundary as well: the barrier of an item's
   // last step is the one that waits for the next item's stage 0.  (Other vector-memory
@@ -154,33 +160,34 @@ __device__ __forceinline__ int tall_body(const GemmArgs& a, uint4* lds, TallItem
   if (!prefilled) {
     int sl = slot;
 #pragma unroll
-    for (int i = 0; i < TALL_RING - 1; ++i) {
+    for (int i = 0; i < AHEAD; ++i) {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) copy_one(i, sl, j);
-      sl = sl + 1 == TALL_RING ? 0 : sl + 1;
+      for (int j = 0; j < C; ++j) copy_one(i, sl, j);
+      sl = sl + 1 == RING ? 0 : sl + 1;
     }
-    VLAC_TALL_WAIT();
+    tall_wait<TallRing<RT>::YOUNGER>();
     __syncthreads();
   }
   if constexpr (NA > 0) {
 #pragma unroll
-    for (int q = 0; q < 4 + NA; ++q) read_one(lds + slot * TALL_STAGE + lane, q, W0, X0);
+    for (int q = 0; q < 4 + NA; ++q) read_one(lds + slot * STAGE + lane, q, W0, X0);
   }
   for (int i = 0; i < n_steps; ++i) {
-    const int slot_next = slot + 1 == TALL_RING ? 0 : slot + 1, slot_copy = slot == 0 ? TALL_RING - 1 : slot - 1;
-    const uint4* cur = lds + slot * TALL_STAGE + lane;
-    const uint4* nxt = lds + slot_next * TALL_STAGE + lane;
-    // k-tile 0 of stage i (fragments W0, X0); meanwhile: read k-tile 1, copy stage i + TALL_RING - 1
+    const int slot_next = slot + 1 == RING ? 0 : slot + 1, slot_copy = slot == 0 ? RING - 1 : slot - 1;
+    const uint4* cur = lds + slot * STAGE + lane;
+    const uint4* nxt = lds + slot_next * STAGE + lane;
+    // k-tile 0 of stage i (fragments W0, X0); meanwhile: read k-tile 1, copy stage i + AHEAD
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int q = 0; q < 4 * NX; ++q) {
       if constexpr (NA > 0) acc[q / NX][q % NX] = mfma32<F16>(W0[q / NX], X0[q % NX], acc[q / NX][q % NX]);
       if constexpr (NA > 0) read_one(cur + 64, q, W1, X1);
-      if constexpr (NX >= 2) {  // one copy after each of the last 8 MFMAs
-        if (q >= 4 * NX - 8) copy_one(i + TALL_RING - 1, slot_copy, q - (4 * NX - 8));
-      } else {                  // 4 MFMAs (or none): two copies after each
-        copy_one(i + TALL_RING - 1, slot_copy, 2 * q);
-        copy_one(i + TALL_RING - 1, slot_copy, 2 * q + 1);
+      if constexpr (4 * NX >= C) {  // one copy after each of the last C MFMAs
+        if (q >= 4 * NX - C) copy_one(i + AHEAD, slot_copy, q - (4 * NX - C));
+      } else {                      // 4 MFMAs (or none): two copies after most
+#pragma unroll
+        for (int j = 0; j < C; ++j)
+          if (j * 4 * NX / C == q) copy_one(i + AHEAD, slot_copy, j);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -195,7 +202,7 @@ __device__ __forceinline__ int tall_body(const GemmArgs& a, uint4* lds, TallItem
     for (int q = 0; q < 4 * NX; ++q) {
       if constexpr (NA > 0) acc[q / NX][q % NX] = mfma32<F16>(W1[q / NX], X1[q % NX], acc[q / NX][q % NX]);
       if (q == 0) {
-        VLAC_TALL_WAIT();
+        tall_wait<TallRing<RT>::YOUNGER>();
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __syncthreads();
       } else if constexpr (NA > 0) {
@@ -305,7 +312,7 @@ __device__ __forceinline__ void tall_items(const GemmArgs& a, uint4* lds, const 
   int j = blockIdx.x >> 3;
   if (!exists(j)) return;
   // (chains need every part of K to have at least as many steps as the copies run ahead)
-  const bool can_chain = (2 * a.KS) / pl.S >= TALL_RING - 1;
+  const bool can_chain = (2 * a.KS) / pl.S >= TallRing<RT>::N - 1;
   TallItem it = item_of(j);
   bool prefilled = false;
   int slot = 0;
@@ -324,7 +331,7 @@ __device__ __forceinline__ void tall_items(const GemmArgs& a, uint4* lds, const 
 
 template <int EPI, bool F16>
 __global__ __launch_bounds__(256) void gemm_tall_kernel(GemmArgs a) {
-  extern __shared__ uint4 lds[];  // TALL_RING stages of 32 KiB
+  extern __shared__ uint4 lds[];  // TallRing<RT>::N stages
   const int n_rows = a.n_rows_val >= 0 ? a.n_rows_val : *a.n_rows;
   if (n_rows < a.rows_lo) return;  // the one-stream kernel's share
   const TallPlan pl = tall_plan((a.NB + 7) >> 3, n_rows, EPI == EPI_RESID ? a.S : 1, a.KS);
@@ -336,12 +343,12 @@ __global__ __launch_bounds__(256) void gemm_tall_kernel(GemmArgs a) {
 template <int EPI, bool F16>
 hipError_t set_lds() {
   return hipFuncSetAttribute((const void*)gemm_tall_kernel<EPI, F16>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             TALL_RING * TALL_STAGE * 16);
+                             kTallLds);
 }
 
 template <bool F16>
 void launch_tall_t(int epi, const GemmArgs& a, int grid, hipStream_t st) {
-  const size_t shm = (size_t)TALL_RING * TALL_STAGE * 16;
+  const size_t shm = kTallLds;
   switch (epi) {
     case EPI_QKV:
       hipLaunchKernelGGL((gemm_tall_kernel<EPI_QKV, F16>), dim3(grid), dim3(256), shm, st, a);
