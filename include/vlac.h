@@ -118,6 +118,9 @@ size_t vlac_kv_cache_bytes(const vlac_model_cfg* cfg);
  * projection may use (1 unless it adds to the residual stream; 1, 2, 3, 4, 6 or 8 parts are
  * considered, values above 8 count as 8; the library passes how many partial-row sets of the
  * call's row capacity its workspace holds: 8 up to 1024 rows, 3 beyond).
+ * (This is the cut into work items 256 features wide.  A projection that does not add to the
+ * residual stream is cut into items of 192 features x 192 or 320 rows instead, in calls with a
+ * capacity of up to 1536 rows, where those move less by the same estimate.)
  * Results: rows per work item (256, 192 or 128; a work item is 256 features wide), K parts,
  * work items (weight tiles x parts x row blocks).  Needs neither a context nor a GPU.
  * VLAC_E_NULL / VLAC_E_RANGE on null pointers or non-positive sizes. */

@@ -326,6 +326,31 @@ __host__ __device__ inline TallPlan tall_plan(int tiles, int n_rows, int S_max, 
 #undef VLAC_TALL_TRY
   return p;
 }
+// The projections without a residual epilogue (K unsplit) also know items of 192 features, 192 or
+// 320 rows tall (2 x (6 + 2 rt) KiB per 32-k step, rt = 3 or 5): taken where they move strictly less
+// by the same estimate than `pl`, the cut into items of 256 features.  That is where those leave
+// a round nearly empty: 7B gate/up, before and now, at 601 rows (430 items of 128 rows in two rounds
+// against 230 of 192 x 320 in one) 114 -> 102 us, at 288 rows (172 items against 230 of
+// 192 x 192) 74 -> 66 us; at thousands of rows the rounds are full and 256 x 256 moves least
+// per product (launch_gemm_tall offers them up to a capacity of 1536 rows).  Only NB (feature blocks of 32) and the row count decide: K cancels out.
+__host__ __device__ inline bool tall_plan_192(int NB, int n_rows, const TallPlan& pl, TallPlan* out) {
+  const int tiles = (NB + 5) / 6;
+  unsigned best = (((unsigned)pl.items() + 255u) >> 8) * 2u * (8u + 2u * (unsigned)pl.rt);
+  bool found = false;
+  for (int rt = 5; rt >= 3; rt -= 2) {
+    const unsigned rb = ((unsigned)n_rows + 64u * rt - 1u) / (64u * rt);
+    const unsigned cost = (((unsigned)tiles * rb + 255u) >> 8) * 2u * (6u + 2u * rt);
+    if (cost < best) {
+      best = cost;
+      found = true;
+      out->rt = rt;
+      out->tiles = tiles;
+      out->row_blocks = (int)rb;
+      out->S = 1;
+    }
+  }
+  return found;
+}
 // the same for the GEMM that launch_gemm(EPI_RESID, ...) with these arguments launches
 SplitAdapt gemm_resid_adapt(vlac_ctx* c, int n_blocks, int kpad, int rows_cap, const int* n_rows, int n_rows_host);
 int gemm_init();  // one-time kernel attribute setup; returns hipError_t

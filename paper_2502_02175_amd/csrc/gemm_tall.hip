@@ -43,11 +43,12 @@
 
 namespace {
 
-// Per row-block size (RT row tiles per wave): a stage is 16 weight tiles and 4 RT activation tiles,
-// a quarter of which each wave copies; as many stages as a CU's 160 KiB of LDS hold.
-template <int RT>
+// Per item shape (FW feature blocks and RT row tiles per wave): a stage is 4 FW weight tiles and
+// 4 RT activation tiles, a quarter of which each wave copies; as many stages as a CU's 160 KiB of
+// LDS hold.
+template <int FW, int RT>
 struct TallRing {
-  static constexpr int COPIES = 4 + RT;            // copies (1 KiB) per stage and wave
+  static constexpr int COPIES = FW + RT;           // copies (1 KiB) per stage and wave
   static constexpr int STAGE = 256 * COPIES;       // uint4 per stage: 32, 28 or 24 KiB
   static constexpr int N = 160 / (4 * COPIES);     // stages: 5, 5 or 6
   static constexpr int YOUNGER = COPIES * (N - 2); // copies behind the stage a step waits for
@@ -72,10 +73,10 @@ struct TallItem { int tile, s, mb; };
 // RING - 1 steps of this item copy its first stages instead of stages past the end).
 // prefilled: the copies of this item's first RING - 1 stages have been issued already (by
 // the item before) into the ring from `slot` on.  Returns the ring slot after the last stage.
-template <int RT, int NA, int EPI, bool F16>
+template <int FW, int RT, int NA, int EPI, bool F16>
 __device__ __forceinline__ int tall_body(const GemmArgs& a, uint4* lds, TallItem it, TallItem nx, bool chain,
                                           bool prefilled, int slot, int n_rows, int S) {
-  constexpr int RING = TallRing<RT>::N, STAGE = TallRing<RT>::STAGE, C = TallRing<RT>::COPIES;
+  constexpr int RING = TallRing<FW, RT>::N, STAGE = TallRing<FW, RT>::STAGE, C = TallRing<FW, RT>::COPIES;
   constexpr int AHEAD = RING - 1;  // stages that the copies run ahead
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -86,9 +87,9 @@ __device__ __forceinline__ int tall_body(const GemmArgs& a, uint4* lds, TallItem
   const int step0 = it.s * sq + min(it.s, sr), n_steps = sq + (it.s < sr ? 1 : 0);
   const int step0n = nx.s * sq + min(nx.s, sr), n_steps_n = sq + (nx.s < sr ? 1 : 0);
   const int row0 = it.mb * (64 * RT);
-  const int nb0 = it.tile * 8;
-  // A stage in LDS: the 8 feature blocks, then the 2 RT row tiles, both k-tiles of each (2 KiB that
-  // lie together in global memory as well).  Wave w copies the C = 4 + RT KiB from w C on.
+  const int nb0 = it.tile * (2 * FW);
+  // A stage in LDS: the 2 FW feature blocks, then the 2 RT row tiles, both k-tiles of each (2 KiB that
+  // lie together in global memory as well).  Wave w copies the C = FW + RT KiB from w C on.
   // (scalar base addresses: a copy is then one scalar select, one scalar add and the load, with
   // the lane's 16-byte offset in one register for all of them; a wave has one instruction stream,
   // and what a copy costs to issue is taken from its MFMAs)
@@ -99,8 +100,8 @@ __device__ __forceinline__ int tall_body(const GemmArgs& a, uint4* lds, TallItem
   for (int j = 0; j < C; ++j) {
     const int c = w * C + j, row = c >> 1, half = c & 1;
     auto base = [&](int tile, int mb, int step) {
-      const uint4* t = row < 8 ? a.wp + ((size_t)min(tile * 8 + row, a.NB - 1) * KC + 2 * step) * 64
-                               : a.xp + ((size_t)min(mb * (2 * RT) + row - 8, a.x_tiles - 1) * KC + 2 * step) * 64;
+      const uint4* t = row < 2 * FW ? a.wp + ((size_t)min(tile * (2 * FW) + row, a.NB - 1) * KC + 2 * step) * 64
+                               : a.xp + ((size_t)min(mb * (2 * RT) + row - 2 * FW, a.x_tiles - 1) * KC + 2 * step) * 64;
       return (const char*)t + half * 1024;
     };
     src[j] = base(it.tile, it.mb, step0);
@@ -124,27 +125,27 @@ __device__ __forceinline__ int tall_body(const GemmArgs& a, uint4* lds, TallItem
   };
 
   constexpr int NX = NA > 0 ? NA : 1;
-  f32x16 acc[4][NX];
+  f32x16 acc[FW][NX];
 #pragma unroll
-  for (int f = 0; f < 4; ++f)
+  for (int f = 0; f < FW; ++f)
 #pragma unroll
     for (int m = 0; m < NX; ++m)
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[f][m][i] = 0.f;
 
-  // Fragments of a k-tile: weight blocks 4 wi + f, row tiles 2 m + wj of the block (the two
+  // Fragments of a k-tile: weight blocks FW wi + f, row tiles 2 m + wj of the block (the two
   // row halves interleave, so that a ragged last block splits evenly).  A wave has one
   // instruction stream and nothing else runs on its SIMD, so whatever is not an MFMA is
   // issued BETWEEN the MFMAs of a k-tile, one piece after each: the LDS reads of the next
-  // k-tile's fragments (4 + NA of them) and the eight copies of a stage.
-  uint4 W0[4], X0[NX], W1[4], X1[NX];
-  auto read_one = [&](const uint4* s, int q, uint4(&Wf)[4], uint4(&Xf)[NX]) {
+  // k-tile's fragments (FW + NA of them) and the copies of a stage.
+  uint4 W0[FW], X0[NX], W1[FW], X1[NX];
+  auto read_one = [&](const uint4* s, int q, uint4(&Wf)[FW], uint4(&Xf)[NX]) {
 #pragma unroll
-    for (int f = 0; f < 4; ++f)
-      if (q == f) Wf[f] = s[(4 * wi + f) * 128];
+    for (int f = 0; f < FW; ++f)
+      if (q == f) Wf[f] = s[(FW * wi + f) * 128];
 #pragma unroll
     for (int m = 0; m < NA; ++m)
-      if (q == 4 + m) Xf[m] = s[1024 + (2 * m + wj) * 128];
+      if (q == FW + m) Xf[m] = s[FW * 256 + (2 * m + wj) * 128];
   };
 
   // Copies in flight: C per stage and wave.  When step i needs stage i + 1 (at its barrier)
@@ -165,12 +166,12 @@ __device__ __forceinline__ int tall_body(const GemmArgs& a, uint4* lds, TallItem
       for (int j = 0; j < C; ++j) copy_one(i, sl, j);
       sl = sl + 1 == RING ? 0 : sl + 1;
     }
-    tall_wait<TallRing<RT>::YOUNGER>();
+    tall_wait<TallRing<FW, RT>::YOUNGER>();
     __syncthreads();
   }
   if constexpr (NA > 0) {
 #pragma unroll
-    for (int q = 0; q < 4 + NA; ++q) read_one(lds + slot * STAGE + lane, q, W0, X0);
+    for (int q = 0; q < FW + NA; ++q) read_one(lds + slot * STAGE + lane, q, W0, X0);
   }
   for (int i = 0; i < n_steps; ++i) {
     const int slot_next = slot + 1 == RING ? 0 : slot + 1, slot_copy = slot == 0 ? RING - 1 : slot - 1;
@@ -179,30 +180,30 @@ __device__ __forceinline__ int tall_body(const GemmArgs& a, uint4* lds, TallItem
     // k-tile 0 of stage i (fragments W0, X0); meanwhile: read k-tile 1, copy stage i + AHEAD
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int q = 0; q < 4 * NX; ++q) {
+    for (int q = 0; q < FW * NX; ++q) {
       if constexpr (NA > 0) acc[q / NX][q % NX] = mfma32<F16>(W0[q / NX], X0[q % NX], acc[q / NX][q % NX]);
       if constexpr (NA > 0) read_one(cur + 64, q, W1, X1);
-      if constexpr (4 * NX >= C) {  // one copy after each of the last C MFMAs
-        if (q >= 4 * NX - C) copy_one(i + AHEAD, slot_copy, q - (4 * NX - C));
-      } else {                      // 4 MFMAs (or none): two copies after most
+      if constexpr (FW * NX >= C) {  // one copy after each of the last C MFMAs
+        if (q >= FW * NX - C) copy_one(i + AHEAD, slot_copy, q - (FW * NX - C));
+      } else {                      // fewer MFMAs than copies: some are followed by two
 #pragma unroll
         for (int j = 0; j < C; ++j)
-          if (j * 4 * NX / C == q) copy_one(i + AHEAD, slot_copy, j);
+          if (j * FW * NX / C == q) copy_one(i + AHEAD, slot_copy, j);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
     if constexpr (NA > 0) {
 #pragma unroll
-      for (int q = 4 * NX; q < 4 + NA; ++q) read_one(cur + 64, q, W1, X1);  // (NA = 1: 5 reads, 4 MFMAs)
+      for (int q = FW * NX; q < FW + NA; ++q) read_one(cur + 64, q, W1, X1);  // (NA = 1: 5 reads, 4 MFMAs)
     }
     // k-tile 1 (W1, X1): its first MFMA covers the barrier; then read k-tile 0 of stage i + 1
     // (after the last step: of a stage that is not this item's; the next item reads its own)
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int q = 0; q < 4 * NX; ++q) {
+    for (int q = 0; q < FW * NX; ++q) {
       if constexpr (NA > 0) acc[q / NX][q % NX] = mfma32<F16>(W1[q / NX], X1[q % NX], acc[q / NX][q % NX]);
       if (q == 0) {
-        tall_wait<TallRing<RT>::YOUNGER>();
+        tall_wait<TallRing<FW, RT>::YOUNGER>();
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __syncthreads();
       } else if constexpr (NA > 0) {
@@ -212,7 +213,7 @@ __device__ __forceinline__ int tall_body(const GemmArgs& a, uint4* lds, TallItem
     }
     if constexpr (NA > 0) {
 #pragma unroll
-      for (int q = 4 * NX - 1; q < 4 + NA; ++q) read_one(nxt, q, W0, X0);
+      for (int q = FW * NX - 1; q < FW + NA; ++q) read_one(nxt, q, W0, X0);
     }
     slot = slot_next;
   }
@@ -225,10 +226,10 @@ __device__ __forceinline__ int tall_body(const GemmArgs& a, uint4* lds, TallItem
     const int g = lane >> 5;
     if (a.wscale) {  // weights expanded from e4m3 codes: the scale of every output feature
 #pragma unroll
-      for (int f = 0; f < 4; ++f)
-        if (nb0 + 4 * wi + f < a.NB) {
+      for (int f = 0; f < FW; ++f)
+        if (nb0 + FW * wi + f < a.NB) {
 #pragma unroll
-          for (int m = 0; m < NA; ++m) scale_tile(a.wscale, nb0 + 4 * wi + f, g, acc[f][m]);
+          for (int m = 0; m < NA; ++m) scale_tile(a.wscale, nb0 + FW * wi + f, g, acc[f][m]);
         }
     }
     if (EPI == EPI_RESID && S > 1) {
@@ -239,9 +240,9 @@ __device__ __forceinline__ int tall_body(const GemmArgs& a, uint4* lds, TallItem
         const int slot_r = row0 + (2 * m + wj) * 32 + (lane & 31);
         if (slot_r < n_rows) {
 #pragma unroll
-          for (int f = 0; f < 4; ++f)
-            if (nb0 + 4 * wi + f < a.NB) {
-              float* dp = a.e.rpart + ((size_t)it.s * a.e.rpart_rows + slot_r) * a.e.d_model + (nb0 + 4 * wi + f) * 32 + 4 * g;
+          for (int f = 0; f < FW; ++f)
+            if (nb0 + FW * wi + f < a.NB) {
+              float* dp = a.e.rpart + ((size_t)it.s * a.e.rpart_rows + slot_r) * a.e.d_model + (nb0 + FW * wi + f) * 32 + 4 * g;
 #pragma unroll
               for (int q4 = 0; q4 < 4; ++q4)
                 *(float4*)(dp + 8 * q4) = make_float4(acc[f][m][4 * q4], acc[f][m][4 * q4 + 1],
@@ -256,8 +257,8 @@ __device__ __forceinline__ int tall_body(const GemmArgs& a, uint4* lds, TallItem
         if (slot_r < n_rows) {
           const int id = (EPI == EPI_LOGITS) ? 0 : a.e.rows[slot_r];
 #pragma unroll
-          for (int f = 0; f < 4; ++f)
-            if (nb0 + 4 * wi + f < a.NB) epilogue_tile<EPI, F16>(a.e, nb0 + 4 * wi + f, slot_r, id, g, acc[f][m]);
+          for (int f = 0; f < FW; ++f)
+            if (nb0 + FW * wi + f < a.NB) epilogue_tile<EPI, F16>(a.e, nb0 + FW * wi + f, slot_r, id, g, acc[f][m]);
         }
       }
     }
@@ -265,30 +266,22 @@ __device__ __forceinline__ int tall_body(const GemmArgs& a, uint4* lds, TallItem
   return slot;
 }
 
-template <int RT, int EPI, bool F16>
+template <int FW, int RT, int EPI, bool F16>
 __device__ __forceinline__ int tall_dispatch(const GemmArgs& a, uint4* lds, TallItem it, TallItem nx, bool chain,
                                               bool prefilled, int slot, int n_rows, int S) {
   // row tiles of this block, dealt to the two row halves alternately
   const int nt = min(2 * RT, (n_rows - it.mb * (64 * RT) + 31) >> 5);
   const int wj = __builtin_amdgcn_readfirstlane(threadIdx.x >> 7);
-  const int na = (nt - wj + 1) >> 1;  // wave-uniform
-#define VLAC_TALL_CASE(N) case N: return tall_body<RT, N, EPI, F16>(a, lds, it, nx, chain, prefilled, slot, n_rows, S);
-  switch (na) {
-    VLAC_TALL_CASE(0)
-    VLAC_TALL_CASE(1)
-    VLAC_TALL_CASE(2)
-    default:
-      if constexpr (RT == 2) return tall_body<RT, 2, EPI, F16>(a, lds, it, nx, chain, prefilled, slot, n_rows, S);
-      else if constexpr (RT == 3) return tall_body<RT, 3, EPI, F16>(a, lds, it, nx, chain, prefilled, slot, n_rows, S);
-      else {
-        if (na == 3) return tall_body<RT, 3, EPI, F16>(a, lds, it, nx, chain, prefilled, slot, n_rows, S);
-        return tall_body<RT, 4, EPI, F16>(a, lds, it, nx, chain, prefilled, slot, n_rows, S);
-      }
-  }
+  const int na = (nt - wj + 1) >> 1;  // wave-uniform, 0 .. RT
+#define VLAC_TALL_CASE(N)                                                                                      \
+  if constexpr (N < RT)                                                                                        \
+    if (na == N) return tall_body<FW, RT, N, EPI, F16>(a, lds, it, nx, chain, prefilled, slot, n_rows, S);
+  VLAC_TALL_CASE(0) VLAC_TALL_CASE(1) VLAC_TALL_CASE(2) VLAC_TALL_CASE(3) VLAC_TALL_CASE(4)
 #undef VLAC_TALL_CASE
+  return tall_body<FW, RT, RT, EPI, F16>(a, lds, it, nx, chain, prefilled, slot, n_rows, S);
 }
 
-template <int RT, int EPI, bool F16>
+template <int FW, int RT, int EPI, bool F16>
 __device__ __forceinline__ void tall_items(const GemmArgs& a, uint4* lds, const TallPlan& pl, int n_rows) {
   // Work items are (weight tile, K part, row block) triples, listed with the row blocks of one
   // weight tile and part next to each other, and the list is cut into eight equal runs, one
@@ -312,7 +305,7 @@ __device__ __forceinline__ void tall_items(const GemmArgs& a, uint4* lds, const 
   int j = blockIdx.x >> 3;
   if (!exists(j)) return;
   // (chains need every part of K to have at least as many steps as the copies run ahead)
-  const bool can_chain = (2 * a.KS) / pl.S >= TallRing<RT>::N - 1;
+  const bool can_chain = (2 * a.KS) / pl.S >= TallRing<FW, RT>::N - 1;
   TallItem it = item_of(j);
   bool prefilled = false;
   int slot = 0;
@@ -320,7 +313,7 @@ __device__ __forceinline__ void tall_items(const GemmArgs& a, uint4* lds, const 
     const int jn = j + stride;
     const bool chain = can_chain && exists(jn);
     const TallItem nx = chain ? item_of(jn) : it;
-    slot = tall_dispatch<RT, EPI, F16>(a, lds, it, nx, chain, prefilled, slot, n_rows, pl.S);
+    slot = tall_dispatch<FW, RT, EPI, F16>(a, lds, it, nx, chain, prefilled, slot, n_rows, pl.S);
     if (!exists(jn)) break;
     prefilled = chain;
     it = item_of(jn);
@@ -329,38 +322,50 @@ __device__ __forceinline__ void tall_items(const GemmArgs& a, uint4* lds, const 
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
-template <int EPI, bool F16>
+// NARROW: items of 192 features are in the choice (a kernel of its own: their code beside the other
+// shapes' cost a whole prefill of thousands of rows, where it is never taken, 0.3 to 0.5 %)
+template <int EPI, bool F16, bool NARROW>
 __global__ __launch_bounds__(256) void gemm_tall_kernel(GemmArgs a) {
-  extern __shared__ uint4 lds[];  // TallRing<RT>::N stages
+  extern __shared__ uint4 lds[];  // TallRing<FW, RT>::N stages
   const int n_rows = a.n_rows_val >= 0 ? a.n_rows_val : *a.n_rows;
   if (n_rows < a.rows_lo) return;  // the one-stream kernel's share
   const TallPlan pl = tall_plan((a.NB + 7) >> 3, n_rows, EPI == EPI_RESID ? a.S : 1, a.KS);
-  if (pl.rt == 4) tall_items<4, EPI, F16>(a, lds, pl, n_rows);
-  else if (pl.rt == 3) tall_items<3, EPI, F16>(a, lds, pl, n_rows);
-  else tall_items<2, EPI, F16>(a, lds, pl, n_rows);
+  if constexpr (NARROW) {
+    TallPlan p3;
+    if (tall_plan_192(a.NB, n_rows, pl, &p3)) {
+      if (p3.rt == 5) tall_items<3, 5, EPI, F16>(a, lds, p3, n_rows);
+      else tall_items<3, 3, EPI, F16>(a, lds, p3, n_rows);
+      return;
+    }
+  }
+  if (pl.rt == 4) tall_items<4, 4, EPI, F16>(a, lds, pl, n_rows);
+  else if (pl.rt == 3) tall_items<4, 3, EPI, F16>(a, lds, pl, n_rows);
+  else tall_items<4, 2, EPI, F16>(a, lds, pl, n_rows);
 }
 
-template <int EPI, bool F16>
+template <int EPI, bool F16, bool NARROW = false>
 hipError_t set_lds() {
-  return hipFuncSetAttribute((const void*)gemm_tall_kernel<EPI, F16>, hipFuncAttributeMaxDynamicSharedMemorySize,
+  return hipFuncSetAttribute((const void*)gemm_tall_kernel<EPI, F16, NARROW>, hipFuncAttributeMaxDynamicSharedMemorySize,
                              kTallLds);
 }
 
 template <bool F16>
-void launch_tall_t(int epi, const GemmArgs& a, int grid, hipStream_t st) {
+void launch_tall_t(int epi, const GemmArgs& a, int grid, bool narrow, hipStream_t st) {
   const size_t shm = kTallLds;
   switch (epi) {
     case EPI_QKV:
-      hipLaunchKernelGGL((gemm_tall_kernel<EPI_QKV, F16>), dim3(grid), dim3(256), shm, st, a);
+      if (narrow) hipLaunchKernelGGL((gemm_tall_kernel<EPI_QKV, F16, true>), dim3(grid), dim3(256), shm, st, a);
+      else hipLaunchKernelGGL((gemm_tall_kernel<EPI_QKV, F16, false>), dim3(grid), dim3(256), shm, st, a);
       break;
     case EPI_SWIGLU:
-      hipLaunchKernelGGL((gemm_tall_kernel<EPI_SWIGLU, F16>), dim3(grid), dim3(256), shm, st, a);
+      if (narrow) hipLaunchKernelGGL((gemm_tall_kernel<EPI_SWIGLU, F16, true>), dim3(grid), dim3(256), shm, st, a);
+      else hipLaunchKernelGGL((gemm_tall_kernel<EPI_SWIGLU, F16, false>), dim3(grid), dim3(256), shm, st, a);
       break;
     case EPI_RESID:
-      hipLaunchKernelGGL((gemm_tall_kernel<EPI_RESID, F16>), dim3(grid), dim3(256), shm, st, a);
+      hipLaunchKernelGGL((gemm_tall_kernel<EPI_RESID, F16, false>), dim3(grid), dim3(256), shm, st, a);
       break;
     default:
-      hipLaunchKernelGGL((gemm_tall_kernel<EPI_LOGITS, F16>), dim3(grid), dim3(256), shm, st, a);
+      hipLaunchKernelGGL((gemm_tall_kernel<EPI_LOGITS, F16, false>), dim3(grid), dim3(256), shm, st, a);
       break;
   }
 }
@@ -385,6 +390,10 @@ void launch_expand_e4m3(const uint4* codes, uint4* tiles, size_t n_slots, hipStr
 
 int gemm_tall_init() {
   hipError_t e;
+  if ((e = set_lds<EPI_QKV, true, true>()) != hipSuccess) return (int)e;
+  if ((e = set_lds<EPI_QKV, false, true>()) != hipSuccess) return (int)e;
+  if ((e = set_lds<EPI_SWIGLU, true, true>()) != hipSuccess) return (int)e;
+  if ((e = set_lds<EPI_SWIGLU, false, true>()) != hipSuccess) return (int)e;
   if ((e = set_lds<EPI_QKV, true>()) != hipSuccess) return (int)e;
   if ((e = set_lds<EPI_QKV, false>()) != hipSuccess) return (int)e;
   if ((e = set_lds<EPI_SWIGLU, true>()) != hipSuccess) return (int)e;
@@ -404,10 +413,18 @@ void launch_gemm_tall(bool f16, int epi, GemmArgs& a, int rows_cap, int S_max, h
   // the grid covers the most work items any row count up to rows_cap can give (the plan
   // changes its row blocks and K parts with the row count)
   const int tiles = (a.NB + 7) >> 3;
+  // (from kNarrowRows of capacity on two rounds of items and more are the rule, and a narrower item
+  // seldom saves one)
+  constexpr int kNarrowRows = 1536;
+  const bool narrow = (epi == EPI_QKV || epi == EPI_SWIGLU) && rows_cap <= kNarrowRows;
   int most = 0;
-  for (int n = 64; n < rows_cap + 64; n += 64)
-    most = std::max(most, tall_plan(tiles, std::min(n, rows_cap), a.S, a.KS).items());
+  for (int n = 64; n < rows_cap + 64; n += 64) {
+    const TallPlan pl = tall_plan(tiles, std::min(n, rows_cap), a.S, a.KS);
+    most = std::max(most, pl.items());
+    TallPlan p3;
+    if (narrow && tall_plan_192(a.NB, std::min(n, rows_cap), pl, &p3)) most = std::max(most, p3.items());
+  }
   const int grid = std::min(((most + 7) / 8) * 8, kTallGrid);
-  if (f16) launch_tall_t<true>(epi, a, grid, st);
-  else launch_tall_t<false>(epi, a, grid, st);
+  if (f16) launch_tall_t<true>(epi, a, grid, narrow, st);
+  else launch_tall_t<false>(epi, a, grid, narrow, st);
 }

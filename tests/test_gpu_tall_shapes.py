@@ -1,0 +1,60 @@
+"""The many-rows GEMM's work items of 192 features (192 and 320 rows tall) beside those of 256: row
+counts known to the host and not, ragged last blocks and last feature tiles, both operand types, and
+bit for bit against the build whose hand-placed waits are full ones."""
+import os
+
+import numpy as np
+import pytest
+
+import synth
+import paper_2502_02175_amd as V
+from oracle import vlac_oracle as O
+from helpers import GpuModel, oracle_model
+
+pytestmark = pytest.mark.gpu
+SAFE = os.path.join(os.path.dirname(V.lib_path()), "libvlac_safe.so")
+
+
+def passes(cfg, operand, emb, n_vis, keeps, std):
+    gm = GpuModel(cfg, seed=4, max_batch=1, max_seq=736, std=std, operand=operand)
+    try:
+        out = []
+        for L in (288, 320, 353, 519, 640, 704):
+            out.append(gm.prefill(emb[None, -L:], L - 8))
+        gm.prefill(emb[None], n_vis)
+        for i, k in enumerate(keeps):
+            out.append(gm.prefill(emb[None] + np.float32(0.125) * (i + 1), n_vis, [k]))
+        return out
+    finally:
+        gm.close()
+
+
+# (11008: gate/up of 688 feature blocks, 115 tiles of 192, the last of 4 blocks: 192 rows per item at
+# 288 .. 353 rows, 320 at 519 .. 640, items of 256 features at 704)
+@pytest.mark.parametrize("d,F,operand", [(320, 11008, "f16"), (256, 11008, "bf16")])
+def test_items_of_192_features(d, F, operand):
+    cfg = synth.ModelCfg(2, d, 4, 4, 64, F, 96)
+    std, tol = 1.0 / np.sqrt(d), 2e-2 if operand == "f16" else 8e-2
+    n_vis = 696
+    rng = np.random.default_rng(d)
+    emb = synth.round_bf16(rng.standard_normal((n_vis + 8, d))).astype(np.float32)
+    keeps = [rng.permutation(n_vis)[:n].tolist() for n in (60, 185, 300, 420)]
+    got = passes(cfg, operand, emb, n_vis, keeps, std)
+    try:
+        V.use_library(SAFE)
+        safe = passes(cfg, operand, emb, n_vis, keeps, std)
+    finally:
+        V.use_library(None)
+    for a, b in zip(got, safe):
+        for k in ("hidden", "logits", "attn_mean"):
+            assert np.array_equal(a[k], b[k], equal_nan=True)
+    om = oracle_model(cfg, seed=4, std=std)
+    for i, L in enumerate((288, 320, 353, 519, 640, 704)):
+        want = O.dense_forward(om, emb[-L:], L - 8, O.new_cache(cfg, 736))
+        assert np.abs(got[i]["hidden"][0] - want["hidden"]).max() <= tol, L
+    cache = O.new_cache(cfg, 736)
+    O.dense_forward(om, emb, n_vis, cache)
+    for i, k in enumerate(keeps):
+        want = O.sparse_forward(om, emb + np.float32(0.125) * (i + 1), n_vis, cache, [k] * 2)
+        alive = ~np.isnan(want["hidden"][:, 0])
+        assert np.abs(got[6 + i]["hidden"][0][alive] - want["hidden"][alive]).max() <= tol, len(k)
