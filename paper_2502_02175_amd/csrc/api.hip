@@ -429,7 +429,7 @@ int vlac_embed_patches(vlac_ctx* ctx, const uint8_t* frame_cur, int B, int H, in
   if ((reuse_order == nullptr) != (reuse_count == nullptr)) return VLAC_E_NULL;
   if (layer_count && !reuse_order) return VLAC_E_NULL;
   if (B < 1 || B > ctx->cfg.max_batch) return VLAC_E_RANGE;
-  // (8 patches of fp32 pixels are staged in 64 KiB of LDS: 3 patch^2 <= 2048)
+  // (the pixels of 32 patches are staged in LDS as bf16 operands: 127 KiB at 26 x 26)
   if (patch < 1 || patch > 26 || H < patch || W < patch || H % patch || W % patch) return VLAC_E_SHAPE;
   const long long L_v = (long long)(H / patch) * (W / patch);
   if (L_v > 4096 || L < L_v) return VLAC_E_SHAPE;
