@@ -332,13 +332,13 @@ __global__ __launch_bounds__(rows_threads(FB)) void gemm_rows_kernel(GemmArgs a)
   if (mb != 0 && w < NC) first_weights();
   const int rt0 = __builtin_amdgcn_readfirstlane(mb * n_rt / n_blk);
   const int rt1 = __builtin_amdgcn_readfirstlane((mb + 1) * n_rt / n_blk), row_end = min(n_rows, 32 * rt1);
-  // (5 row tiles run as 6: a tile past the block's last is the last again, and dropped)
   switch (rt1 - rt0) {
 #define VLAC_NA(N) rows_body<N, FB, EPI, F16, W8>(a, lds, W, tile, s, rt0, row_end); break;
     case 1: VLAC_NA(1)
     case 2: VLAC_NA(2)
     case 3: VLAC_NA(3)
     case 4: VLAC_NA(4)
+    case 5: VLAC_NA(5)
     default: VLAC_NA(6)
 #undef VLAC_NA
   }
