@@ -28,7 +28,7 @@
 
 // Workgroup: 4 consumer waves and 2 producer waves.  The consumers are FB feature blocks x KP
 // parts of the K range (FB KP = 4); a consumer streams the weight tiles of its block and part
-// into registers, UK k-tiles ahead, and multiplies them by up to 8 row tiles whose operands it
+// into registers, UK k-tiles ahead, and multiplies them by up to 6 row tiles whose operands it
 // reads from LDS.  The producers copy those operands global -> LDS directly into a ring of
 // ROWS_RING chunks, for nobody else's registers and nobody else's load queue: a wave's loads
 // return in issue order, so row operands (from L2) fetched by the consumers themselves would wait
@@ -41,19 +41,22 @@
 // alone, 38 for both on 172 CUs, 34 on 256, whatever is in flight), so lanes of rows past the end
 // copy nothing and the tiles are cut to use most CUs.  7B shape, 109 rows, before and now: gate/up
 // 49.8 -> 41.7 us (4.3 TB/s of weights), QKV 41.2 -> 33.6, O 15 -> 14.4, FFN down 29 -> 26; four
-// layers with the head 742 -> 623 us, 192 rows 908 -> 804, 256 rows 995 -> 949.  Blocks of 8 row
-// tiles spill (256 rows: 1066); 32 weight tiles in flight: no faster.
+// layers with the head 742 -> 628 us, 192 rows 908 -> 764.  32 weight tiles in flight: no faster.
+// A wave has 256 registers (6 waves on 4 SIMDs).  No instance spills: fewer weight tiles in flight
+// with 5 or 6 row tiles, the body of every row tile count kept apart from the others (see there),
+// and only as many weight tiles asked for ahead of the choice of the body as every body keeps.
+// (With 17 to 26 registers of every 16-bit instance spilled, 192 rows of 7B took 795 us per four
+// layers and the head, now 764; 109 rows 635, now 628.)
 constexpr int ROWS_RING = 5;       // chunks of at most 32 KiB: all 160 KiB of a CU's LDS
 constexpr int rows_consumers(int FB) { return FB == 2 ? 4 : FB; }
 constexpr int rows_threads(int FB) { return 64 * (rows_consumers(FB) + 2); }
-constexpr int ROWS_UK = 16;        // weight tiles in flight per consumer (16 KiB)
 
-template <int NA, int FB>
+template <int NA, int FB, bool W8>
 struct RowsShape {
   static constexpr int NC = rows_consumers(FB), KP = NC / FB;
   static constexpr int CT = (NA <= 4 ? 8 : 4) / KP;   // k-tiles per chunk and part
   static constexpr int TILES = KP * CT * NA;          // operand tiles (1 KiB) per chunk
-  static constexpr int UK = ROWS_UK;                  // weight tiles in flight per consumer
+  static constexpr int UK = NA <= 4 || W8 ? 16 : 12;  // weight tiles in flight per consumer (16 bits: 1 KiB each)
   static constexpr int XR = NA <= 4 ? 2 : 1;          // k-tiles of row operands in registers
 };
 
@@ -79,9 +82,9 @@ __device__ inline void rows_barrier() { asm volatile("s_barrier" ::: "memory"); 
 // A producer wave (half = 0, 1): with two K parts the operand tiles of part `half`, else those of
 // half the k-tiles of every chunk.  At the barrier that ends chunk c the chunks c + 1 and c + 2
 // have landed.
-template <int NA, int FB>
+template <int NA, int FB, bool W8>
 __device__ __forceinline__ void rows_produce(const GemmArgs& a, uint4* lds, int half, int s, int rt0, int row_end) {
-  using Sh = RowsShape<NA, FB>;
+  using Sh = RowsShape<NA, FB, W8>;
   constexpr int KP = Sh::KP, PER = Sh::TILES / 2;  // copies of a chunk per producer
   static_assert((ROWS_RING - 3) * PER <= 63, "the counter holds 63");
   const int KC = 4 * a.KS;
@@ -138,19 +141,24 @@ __device__ __forceinline__ void rows_produce(const GemmArgs& a, uint4* lds, int 
   }
 }
 
-// The consumers' first UK weight tiles, asked for before the row count is known
+// A consumer's weight tiles in flight; the first 8 of up to 16 are asked for before the row count is
+// known (e4m3 weights: two tiles to a 16-byte slot)
 template <bool W8>
 struct RowsWeights {
-  static constexpr int N = W8 ? ROWS_UK / 2 : ROWS_UK;
+  static constexpr int N = W8 ? 8 : 16, EARLY = N / 2;
   uint4 t[N];
 };
 
 template <int NA, int FB, int EPI, bool F16, bool W8>
 __device__ __forceinline__ void rows_body(const GemmArgs& a, uint4* lds, RowsWeights<W8>& W, int tile, int s, int rt0,
                                           int row_end) {
-  using Sh = RowsShape<NA, FB>;
+  using Sh = RowsShape<NA, FB, W8>;
   constexpr int NC = Sh::NC, KP = Sh::KP, CT = Sh::CT, UK = Sh::UK, XR = Sh::XR, CH = Sh::TILES * 64;
-  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // (Opaque copies of what addresses are made from: the bodies of all row tile counts are the
+  // branches of one switch, and the compiler would else compute the addresses of all of them ahead
+  // of it and spill.)
+  int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  asm volatile("" : "+v"(lane), "+s"(w), "+s"(tile), "+s"(s), "+s"(rt0));
   const int part = w / FB, nb = tile * FB + (w - part * FB), g = lane >> 5;
   const bool wave_on = w < NC && nb < a.NB;
   f32x16 acc[NA];
@@ -163,7 +171,7 @@ __device__ __forceinline__ void rows_body(const GemmArgs& a, uint4* lds, RowsWei
 #pragma unroll
   for (int m = 0; m < NA; ++m) ids[m] = 0;
   if (w >= NC) {
-    rows_produce<NA, FB>(a, lds, w - Sh::NC, s, rt0, row_end);
+    rows_produce<NA, FB, W8>(a, lds, w - Sh::NC, s, rt0, row_end);
   } else {
     const RowsRange rg = rows_range(a.KS, a.S * KP, s * KP + part);
     const int n_max = rows_range(a.KS, a.S * KP, s * KP).n, n = rg.n;
@@ -171,6 +179,9 @@ __device__ __forceinline__ void rows_body(const GemmArgs& a, uint4* lds, RowsWei
     // (e4m3 weights: a 16-byte lane slot holds two k-tiles)
     const int KC = 4 * a.KS;
     const uint4* wsrc = a.wp + ((size_t)min(nb, a.NB - 1) * (W8 ? KC / 2 : KC) + (W8 ? rg.k0 / 2 : rg.k0)) * 64 + lane;
+#pragma unroll
+    for (int i = RowsWeights<W8>::EARLY; i < (W8 ? UK / 2 : UK); ++i)
+      if (i < (W8 ? n / 2 : n)) W.t[i] = ld_stream(wsrc + (size_t)i * 64);
     uint4 X[XR][NA];
     int slot = 0;
     const uint4 *cur = lds + (size_t)part * CT * NA * 64 + lane, *nxt = cur + CH;
@@ -309,7 +320,7 @@ __global__ __launch_bounds__(rows_threads(FB)) void gemm_rows_kernel(GemmArgs a)
     p = blockIdx.x - mb * p8;
   }
   if (p >= a.P) return;
-  const int tile = p / a.S, s = p - tile * a.S;
+  const int tile = __builtin_amdgcn_readfirstlane(p / a.S), s = __builtin_amdgcn_readfirstlane(p - tile * a.S);
   // The first row block always has work: its consumers ask for their first weights before the
   // row count (in device memory) is known.
   constexpr int NC = rows_consumers(FB), KP = NC / FB;
@@ -321,7 +332,7 @@ __global__ __launch_bounds__(rows_threads(FB)) void gemm_rows_kernel(GemmArgs a)
     const uint4* src = a.wp + ((size_t)nb * (W8 ? KC / 2 : KC) + (W8 ? rg.k0 / 2 : rg.k0)) * 64 + (threadIdx.x & 63);
     const int cnt = W8 ? rg.n / 2 : rg.n;  // (0: a part that K is too short for)
 #pragma unroll
-    for (int i = 0; i < RowsWeights<W8>::N; ++i)
+    for (int i = 0; i < RowsWeights<W8>::EARLY; ++i)
       if (i < cnt) W.t[i] = ld_stream(src + (size_t)i * 64);
   };
   if (mb == 0 && w < NC) first_weights();

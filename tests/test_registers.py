@@ -1,0 +1,38 @@
+"""Registers of the built kernels, from the metadata that the compiler leaves in the library: the
+one-stream GEMM keeps everything of a wave in registers (a spill is traffic in its innermost loop
+that no result shows)."""
+import struct
+
+import paper_2502_02175_amd as V
+
+AMDGPU_METADATA, ELF_AMDGPU, SHT_NOTE = 32, 224, 7
+
+
+def kernels():
+    """-> {mangled name: its metadata} over all gfx code objects inside the library."""
+    import msgpack
+    data = open(V.lib_path(), "rb").read()
+    out, at = {}, data.find(b"\x7fELF", 4)
+    while at >= 0:
+        if struct.unpack_from("<H", data, at + 18)[0] == ELF_AMDGPU:
+            shoff, = struct.unpack_from("<Q", data, at + 40)
+            entsize, count = struct.unpack_from("<HH", data, at + 58)
+            for i in range(count):
+                kind, _, _, offset, size = struct.unpack_from("<IQQQQ", data, at + shoff + i * entsize + 4)
+                p, end = at + offset, at + offset + size
+                while kind == SHT_NOTE and p < end:
+                    name_len, desc_len, note = struct.unpack_from("<III", data, p)
+                    desc = p + 12 + (name_len + 3) // 4 * 4
+                    if note == AMDGPU_METADATA:
+                        for k in msgpack.unpackb(data[desc:desc + desc_len])["amdhsa.kernels"]:
+                            out[k[".name"]] = k
+                    p = desc + (desc_len + 3) // 4 * 4
+        at = data.find(b"\x7fELF", at + 4)
+    return out
+
+
+def test_the_one_stream_gemm_does_not_spill():
+    mine = {n: k for n, k in kernels().items() if "gemm_rows_kernel" in n}
+    assert len(mine) == 27  # feature blocks, epilogues, operand types
+    for n, k in mine.items():
+        assert k[".private_segment_fixed_size"] == 0 and k[".vgpr_spill_count"] == 0, n
