@@ -303,44 +303,52 @@ __device__ __forceinline__ void rows_body(const GemmArgs& a, uint4* lds, RowsWei
 template <int FB, int EPI, bool F16, bool W8>
 __global__ __launch_bounds__(rows_threads(FB)) void gemm_rows_kernel(GemmArgs a) {
   extern __shared__ uint4 lds[];  // [ROWS_RING][part][k-tile][row tile][64]
-  // workgroup id -> (row block, weight tile, split); id % 8 is the XCD.  With the row
-  // count known on the host every row block has work, and the blocks of one weight tile
-  // sit next to each other.  Otherwise the grid covers the largest possible row count,
-  // and the row block is the slowest index: the workgroups of empty row blocks (which
-  // only find that out from device memory) would else sit between the working ones in
-  // dispatch order and hold their places.
-  int mb, p;
-  if (a.n_rows_val >= 0 || a.P > 256) {
-    const int y = blockIdx.x >> 3;
-    mb = y % a.MB;
-    p = (y / a.MB) * 8 + (blockIdx.x & 7);
-  } else {
-    const int p8 = (a.P + 7) & ~7;
-    mb = blockIdx.x / p8;
-    p = blockIdx.x - mb * p8;
-  }
-  if (p >= a.P) return;
-  const int tile = __builtin_amdgcn_readfirstlane(p / a.S), s = __builtin_amdgcn_readfirstlane(p - tile * a.S);
-  // The first row block always has work: its consumers ask for their first weights before the
-  // row count (in device memory) is known.
+  // Workgroup id -> (row block, weight tile, split); id % 8 is the XCD, and the row blocks of one
+  // weight tile sit next to each other on it, so that they fetch it from HBM once.  The blocks are
+  // those that the row count gives, not those that the grid has room for: its surplus workgroups
+  // come last.  (With the blocks of an unknown count one behind the other the weights came from HBM
+  // once per block: 211 rows of 7B, 1037 us per four layers, then 935; 408 rows 1640 and 1422.)
+  // Where the count is in device memory the first weights are asked for as if there were one block,
+  // which is the rule, and once more if there are others.  (A loop, so that both go to the same
+  // registers: written one behind the other they are merged by copies, and a copy of a register
+  // waits for the load that fills it.)
   constexpr int NC = rows_consumers(FB), KP = NC / FB;
   RowsWeights<W8> W;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  auto first_weights = [&]() {
-    const RowsRange rg = rows_range(a.KS, a.S * KP, s * KP + w / FB);
-    const int KC = 4 * a.KS, nb = min(tile * FB + w % FB, a.NB - 1);
-    const uint4* src = a.wp + ((size_t)nb * (W8 ? KC / 2 : KC) + (W8 ? rg.k0 / 2 : rg.k0)) * 64 + (threadIdx.x & 63);
-    const int cnt = W8 ? rg.n / 2 : rg.n;  // (0: a part that K is too short for)
+  int n_rows = a.n_rows_val, n_rt = 0, n_blk = 1, mb = 0, tile, s;
+#pragma unroll 1
+  for (;;) {
+    int p = blockIdx.x;
+    if (n_rows >= 0) {
+      // row tiles are dealt to as few blocks of at most 6 as hold them, in equal shares
+      n_rt = (n_rows + 31) >> 5;
+      n_blk = (n_rt + 5) / 6;
+      if (n_blk == 0 || n_rows >= a.rows_hi) return;  // (rows_hi and more: the many-rows kernel's share)
+      if (n_blk > 1) {
+        const int y = blockIdx.x >> 3;
+        mb = y % n_blk;
+        p = (y / n_blk) * 8 + (blockIdx.x & 7);
+      } else if (a.n_rows_val < 0) {
+        if (p >= a.P) return;
+        break;  // (the weights asked for are the right ones)
+      }
+      if (p >= a.P) return;
+    }
+    tile = __builtin_amdgcn_readfirstlane(p / a.S);
+    s = __builtin_amdgcn_readfirstlane(p - tile * a.S);
+    if (p < a.P && w < NC) {
+      const RowsRange rg = rows_range(a.KS, a.S * KP, s * KP + w / FB);
+      const int nb = min(tile * FB + w % FB, a.NB - 1), kc = W8 ? 2 * a.KS : 4 * a.KS, k0 = W8 ? rg.k0 / 2 : rg.k0;
+      const uint4* src = a.wp + (size_t)nb * kc * 64 + (threadIdx.x & 63);
+      // (past the end of K the last tile is read again and not used)
 #pragma unroll
-    for (int i = 0; i < RowsWeights<W8>::EARLY; ++i)
-      if (i < cnt) W.t[i] = ld_stream(src + (size_t)i * 64);
-  };
-  if (mb == 0 && w < NC) first_weights();
-  const int n_rows = __builtin_amdgcn_readfirstlane(a.n_rows_val >= 0 ? a.n_rows_val : *a.n_rows);
-  // row tiles are dealt to as few blocks of at most 6 as hold them, in equal shares
-  const int n_rt = (n_rows + 31) >> 5, n_blk = (n_rt + 5) / 6;
-  if (mb >= n_blk || n_rows >= a.rows_hi) return;  // (rows_hi and more: the many-rows kernel's share)
-  if (mb != 0 && w < NC) first_weights();
+      for (int i = 0; i < RowsWeights<W8>::EARLY; ++i) W.t[i] = ld_stream(src + (size_t)min(k0 + i, kc - 1) * 64);
+    }
+    if (n_rows >= 0) break;
+    n_rows = __builtin_amdgcn_readfirstlane(*a.n_rows);
+  }
+  tile = __builtin_amdgcn_readfirstlane(tile);
+  s = __builtin_amdgcn_readfirstlane(s);
   const int rt0 = __builtin_amdgcn_readfirstlane(mb * n_rt / n_blk);
   const int rt1 = __builtin_amdgcn_readfirstlane((mb + 1) * n_rt / n_blk), row_end = min(n_rows, 32 * rt1);
   switch (rt1 - rt0) {
