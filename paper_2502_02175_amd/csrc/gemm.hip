@@ -28,7 +28,7 @@
 
 // Workgroup: 4 consumer waves and 2 producer waves.  The consumers are FB feature blocks x KP
 // parts of the K range (FB KP = 4); a consumer streams the weight tiles of its block and part
-// into registers, UK k-tiles ahead, and multiplies them by up to 6 row tiles whose operands it
+// into registers, UK k-tiles ahead, and multiplies them by up to 8 row tiles whose operands it
 // reads from LDS.  The producers copy those operands global -> LDS directly into a ring of
 // ROWS_RING chunks, for nobody else's registers and nobody else's load queue: a wave's loads
 // return in issue order, so row operands (from L2) fetched by the consumers themselves would wait
@@ -43,7 +43,7 @@
 // 49.8 -> 41.7 us (4.3 TB/s of weights), QKV 41.2 -> 33.6, O 15 -> 14.4, FFN down 29 -> 26; four
 // layers with the head 742 -> 628 us, 192 rows 908 -> 764.  32 weight tiles in flight: no faster.
 // A wave has 256 registers (6 waves on 4 SIMDs).  No instance spills: fewer weight tiles in flight
-// with 5 or 6 row tiles, the body of every row tile count kept apart from the others (see there),
+// with 5 row tiles and more, the body of every row tile count kept apart from the others (see there),
 // and only as many weight tiles asked for ahead of the choice of the body as every body keeps.
 // (With 17 to 26 registers of every 16-bit instance spilled, 192 rows of 7B took 795 us per four
 // layers and the head, now 764; 109 rows 635, now 628.)
@@ -56,7 +56,7 @@ struct RowsShape {
   static constexpr int NC = rows_consumers(FB), KP = NC / FB;
   static constexpr int CT = (NA <= 4 ? 8 : 4) / KP;   // k-tiles per chunk and part
   static constexpr int TILES = KP * CT * NA;          // operand tiles (1 KiB) per chunk
-  static constexpr int UK = NA <= 4 || W8 ? 16 : 12;  // weight tiles in flight per consumer (16 bits: 1 KiB each)
+  static constexpr int UK = NA <= 4 || W8 ? 16 : NA <= 6 ? 12 : 8;  // weight tiles in flight per consumer (16 bits: 1 KiB each)
   static constexpr int XR = NA <= 4 ? 2 : 1;          // k-tiles of row operands in registers
 };
 
@@ -320,9 +320,9 @@ __global__ __launch_bounds__(rows_threads(FB)) void gemm_rows_kernel(GemmArgs a)
   for (;;) {
     int p = blockIdx.x;
     if (n_rows >= 0) {
-      // row tiles are dealt to as few blocks of at most 6 as hold them, in equal shares
+      // row tiles are dealt in equal shares to as few blocks of at most 6, or of at most 8, as hold them
       n_rt = (n_rows + 31) >> 5;
-      n_blk = (n_rt + 5) / 6;
+      n_blk = (a.blk8 >> ((n_rt - 1) & 31)) & 1 ? (n_rt + 7) >> 3 : (n_rt + 5) / 6;
       if (n_blk == 0 || n_rows >= a.rows_hi) return;  // (rows_hi and more: the many-rows kernel's share)
       if (n_blk > 1) {
         const int y = blockIdx.x >> 3;
@@ -358,7 +358,9 @@ __global__ __launch_bounds__(rows_threads(FB)) void gemm_rows_kernel(GemmArgs a)
     case 3: VLAC_NA(3)
     case 4: VLAC_NA(4)
     case 5: VLAC_NA(5)
-    default: VLAC_NA(6)
+    case 6: VLAC_NA(6)
+    case 7: VLAC_NA(7)
+    default: VLAC_NA(8)
 #undef VLAC_NA
   }
 }
@@ -776,12 +778,30 @@ SplitAdapt gemm_resid_adapt(vlac_ctx* c, int n_blocks, int kpad, int rows_cap, c
   return ad;
 }
 
+// Row blocks of the one-stream kernel: bit n - 1 says that n row tiles (at most 32: 1023 rows) are cut
+// into blocks of up to 8 of them instead of 6, which saves a pass over the weights where it saves a
+// block (7, 8, 13 to 16, ... tiles).  A workgroup takes a CU's whole LDS, so what counts is rounds of
+// 256 workgroups x what a workgroup fetches per k (fb weight rows, a block's operand rows): blocks
+// of 6 where the launch is too small to fill the chip with fewer blocks, or where they leave the last
+// round fuller.  Four layers, blocks of at most 6, then this: 7B, 211 rows 935 and 799 us, 256 rows
+// 954 and 860; grouped queries, 256 rows 457 and 423; taken everywhere, 8 cost 240 instead of 207 us at 211 rows of
+// the tiny shape (22 workgroups) and 742 instead of 671 at 600 rows of grouped queries with 8-bit weights.
+static uint32_t rows_blocks_of_8(int P, int fb, int rows_cap) {
+  uint32_t mask = 0;
+  for (int rt = 1; rt <= 32 && rt <= (rows_cap + 31) / 32; ++rt) {
+    auto cost = [&](int n) { return (P * n + 255) / 256 * (fb + (rt + n - 1) / n); };
+    if (cost((rt + 7) / 8) < cost((rt + 5) / 6)) mask |= 1u << (rt - 1);
+  }
+  return mask;
+}
+
 // the one-stream kernel for up to rows_cap rows; sets and returns a.S
 static int launch_rows_kernel(vlac_ctx* c, int epi, GemmArgs& a, int rows_cap, const GemmEpi& e, hipStream_t st) {
   const int fb = rows_kernel_fb(epi, a.NB, a.KS), tiles = (a.NB + fb - 1) / fb;
   a.MB = ((rows_cap + 31) / 32 + 5) / 6;
   a.S = rows_kernel_splits(c, epi, a.NB, a.KS, e.rpart_rows, e.d_model);
   a.P = tiles * a.S;
+  a.blk8 = rows_blocks_of_8(a.P, fb, rows_cap);
   const int grid = ((a.P + 7) / 8) * 8 * a.MB;
 #define VLAC_ROWS(FB_)                                          \
   {                                                             \

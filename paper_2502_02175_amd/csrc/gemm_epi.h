@@ -14,6 +14,7 @@ struct GemmArgs {
   int n_rows_val;     // >= 0: the row count is known on the host, n_rows is not read
   int rows_lo, rows_hi;  // the launch has work only if rows_lo <= row count < rows_hi (two kernels share a GEMM)
   int S, MB, P;       // split-K factor, row blocks, weight tiles * S
+  uint32_t blk8;      // one-stream GEMM: bit n - 1 = n row tiles (<= 32) are cut into blocks of up to 8 (else 6)
   int x_tiles;        // many-rows GEMM: 32-row tiles the activation buffer holds (copies are clamped to it)
   float* partial;
   int* counters;

@@ -72,21 +72,22 @@ def test_full_waits_change_no_bit(name, cfg, B, n_vis, n_txt, reuse_counts):
 # The one-stream GEMM (up to a capacity of 511 rows; 8-bit weights: up to 1023).  Its ring holds 5 chunks of
 # 8 k-tiles (4 with more than 4 row tiles; half of that per part where two pairs of waves share K).
 ONE_STREAM = [
-    # d, F, head dim, layers, operand: feature blocks per workgroup (QKV, gate/up, residual) and k-tiles of K
-    (64, 272, 64, 2, "f16"),       # 2, 2, 2; 4 k-tiles: one chunk, and a part of K that has none
-    (128, 272, 64, 2, "f16w8"),    # 2, 2, 2; 8 and 20 k-tiles: fewer chunks than the ring holds
-    (320, 8240, 64, 2, "f16"),     # 2, 3, 2; 20 and 516 k-tiles: as many chunks as the ring, and far more
-    (320, 8240, 64, 2, "f16w8"),
-    (576, 12320, 64, 2, "bf16"),   # 2, 4, 2; 36 k-tiles
-    (1344, 1008, 64, 2, "f16"),    # 2, 2, 2; 84 k-tiles in parts of 44 and 40
-    (4096, 8256, 128, 1, "f16"),   # 2, 4, 4: the residual projection over 4 feature blocks
-    (4096, 8256, 128, 1, "f16w8"),
+    # d, F, query heads, head dim, layers, operand: feature blocks per workgroup (QKV, gate/up, residual) and k-tiles of K
+    (64, 272, 4, 64, 2, "f16"),       # 2, 2, 2; 4 k-tiles: one chunk, and a part of K that has none
+    (128, 272, 4, 64, 2, "f16w8"),    # 2, 2, 2; 8 and 20 k-tiles: fewer chunks than the ring holds
+    (320, 8240, 4, 64, 2, "f16"),     # 2, 3, 2; 20 and 516 k-tiles: as many chunks as the ring, and far more
+    (320, 8240, 4, 64, 2, "f16w8"),
+    (576, 12320, 4, 64, 2, "bf16"),   # 2, 4, 2; 36 k-tiles
+    (1344, 1008, 4, 64, 2, "f16"),    # 2, 2, 2; 84 k-tiles in parts of 44 and 40
+    (4096, 8256, 64, 128, 1, "f16"),   # 2, 4, 4: the residual projections over 4 feature blocks; enough workgroups
+                                       # everywhere for 7 and 8 row tiles in one block
+    (4096, 8256, 64, 128, 1, "f16w8"),
 ]
 
 
-def run_one_stream(d, F, hd, layers, operand, known, unknown):
+def run_one_stream(d, F, hq, hd, layers, operand, known, unknown):
     """Full prefills of `known` rows (a count the host has), sparse ones that leave `unknown` rows."""
-    cfg = synth.ModelCfg(layers, d, 4, 2, hd, F, 96)
+    cfg = synth.ModelCfg(layers, d, hq, 2, hd, F, 96)
     top = max(known + unknown)
     L = max(unknown) + 40
     rng = np.random.default_rng(d + F)
@@ -103,8 +104,8 @@ def run_one_stream(d, F, hd, layers, operand, known, unknown):
         gm.close()
 
 
-@pytest.mark.parametrize("d,F,hd,layers,operand", ONE_STREAM)
-def test_full_waits_change_no_bit_of_the_one_stream_gemm(d, F, hd, layers, operand):
+@pytest.mark.parametrize("d,F,hq,hd,layers,operand", ONE_STREAM)
+def test_full_waits_change_no_bit_of_the_one_stream_gemm(d, F, hq, hd, layers, operand):
     """1 to 8 row tiles in one block where the launch allows, 2 blocks and more of equal and unequal
     size, full and ragged last tiles."""
     known = [33, 64, 95, 129, 161, 193, 225, 256]
@@ -114,9 +115,9 @@ def test_full_waits_change_no_bit_of_the_one_stream_gemm(d, F, hd, layers, opera
         unknown += [600]
     try:
         V.use_library(None)
-        ref, kv_ref = run_one_stream(d, F, hd, layers, operand, known, unknown)
+        ref, kv_ref = run_one_stream(d, F, hq, hd, layers, operand, known, unknown)
         V.use_library(SAFE)
-        got, kv_got = run_one_stream(d, F, hd, layers, operand, known, unknown)
+        got, kv_got = run_one_stream(d, F, hq, hd, layers, operand, known, unknown)
     finally:
         V.use_library(None)
     assert np.isfinite(ref[0]["logits"]).all()
