@@ -23,6 +23,7 @@
 //    is sized for the worst case and surplus workgroups leave at once.
 //  * Workgroup ids are dealt round-robin to the 8 XCDs; row blocks of one weight
 //    tile are mapped to the same XCD so that they share its L2.
+#include <algorithm>
 #include <cstring>
 #include "gemm_epi.h"
 
@@ -728,18 +729,28 @@ static int rows_kernel_fb(int epi, int n_blocks, int KS) {
   return best;
 }
 
+// Row blocks of the one-stream kernel at most (see rows_blocks_of_8)
+static int rows_blocks_max(int rows) { return ((rows + 31) / 32 + 5) / 6; }
+
 // Split factor of the one-stream kernel: the projections with a residual, whose partial rows the
-// row kernel that follows adds up, split K so that ONE row block (the sparse prefill usually fills
-// one) gives about one workgroup per CU; a workgroup keeps at least 4 steps of 64 k.  The others
-// do not split over workgroups: a hand-over between them costs more than idle CUs.
-static int rows_kernel_splits(const vlac_ctx* c, int epi, int n_blocks, int KS, int rpart_rows, int d_model) {
+// row kernel that follows adds up, split K.  Taken is the split with the least rounds of 256
+// workgroups x (a workgroup's steps of 64 k, and 4 for its start and end); a workgroup keeps at
+// least 4 steps.  The blocks that multiply the workgroups are known with the row count; where only
+// its bound is known every count of blocks up to that weighs the same.  (With the split that gives
+// one block a workgroup per CU, two blocks took two rounds: grouped queries with 8-bit weights, 28
+// layers, 384 rows 3607 us, now 3226; at most 288 rows, 262 recomputed, 3230 and 2825.)
+// The others do not split over workgroups: a hand-over between them costs more than idle CUs.
+static int rows_kernel_splits(const vlac_ctx* c, int epi, int n_blocks, int KS, int rpart_rows, int d_model, int rows_cap,
+                              bool known) {
   if (epi != EPI_RESID) return 1;
-  const int fb = rows_kernel_fb(epi, n_blocks, KS), tiles = (n_blocks + fb - 1) / fb;
-  int S = (256 + tiles - 1) / tiles;
-  if (S > KS / 4) S = KS / 4;
-  if (S > 8) S = 8;
-  while (S > 1 && (size_t)S * rpart_rows * d_model > c->rpart_floats) --S;
-  return S < 1 ? 1 : S;
+  const int fb = rows_kernel_fb(epi, n_blocks, KS), tiles = (n_blocks + fb - 1) / fb, most = rows_blocks_max(rows_cap);
+  int best = 1, least = 0x7fffffff;
+  for (int S = 1; S <= 8 && S <= std::max(KS / 4, 1) && (size_t)S * rpart_rows * d_model <= c->rpart_floats; ++S) {
+    int cost = 0;
+    for (int n = known ? most : 1; n <= most; ++n) cost += (tiles * S * n + 255) / 256 * ((KS + S - 1) / S + 4);
+    if (cost < least) { least = cost; best = S; }
+  }
+  return best;
 }
 
 // Where the many-rows kernel serves a capacity at which a sparse prefill usually leaves
@@ -772,7 +783,7 @@ SplitAdapt gemm_resid_adapt(vlac_ctx* c, int n_blocks, int kpad, int rows_cap, c
     ad.KS = kpad / 64;
     if (both) {
       ad.small_below = kSmallRows;
-      ad.S_small = rows_kernel_splits(c, EPI_RESID, n_blocks, kpad / 64, rows_cap, d_model);
+      ad.S_small = rows_kernel_splits(c, EPI_RESID, n_blocks, kpad / 64, rows_cap, d_model, kSmallRows - 1, false);
     }
   }
   return ad;
@@ -798,8 +809,8 @@ static uint32_t rows_blocks_of_8(int P, int fb, int rows_cap) {
 // the one-stream kernel for up to rows_cap rows; sets and returns a.S
 static int launch_rows_kernel(vlac_ctx* c, int epi, GemmArgs& a, int rows_cap, const GemmEpi& e, hipStream_t st) {
   const int fb = rows_kernel_fb(epi, a.NB, a.KS), tiles = (a.NB + fb - 1) / fb;
-  a.MB = ((rows_cap + 31) / 32 + 5) / 6;
-  a.S = rows_kernel_splits(c, epi, a.NB, a.KS, e.rpart_rows, e.d_model);
+  a.MB = rows_blocks_max(rows_cap);
+  a.S = rows_kernel_splits(c, epi, a.NB, a.KS, e.rpart_rows, e.d_model, rows_cap, a.n_rows_val >= 0);
   a.P = tiles * a.S;
   a.blk8 = rows_blocks_of_8(a.P, fb, rows_cap);
   const int grid = ((a.P + 7) / 8) * 8 * a.MB;
