@@ -110,6 +110,35 @@ def test_embed_at_the_edges_of_its_tiles(B, H, W, patch, skew):
         gm.close()
 
 
+@pytest.mark.parametrize("B,H,W,patch", [
+    (1, 14 * 3, 14 * 4, 14),       # 588 values: the last tile of 16 is padded
+    (18, 14 * 30, 14 * 31, 14),    # the wide form
+    (1, 13 * 3, 13 * 4, 13),
+])
+def test_large_and_infinite_weights(B, H, W, patch):
+    """What is finite stays finite (weights near the top of the type, whose sums are not), and an
+    infinite weight in the last row of w_proj gives infinities of the pixel's sign, not NaN."""
+    cfg = synth.CONFIGS["tiny"]
+    gm = GpuModel(cfg, seed=0, max_batch=B, max_seq=32)
+    try:
+        rng = np.random.default_rng(patch)
+        frames = rng.integers(0, 256, size=(B, H, W, 3), dtype=np.uint8)
+        w = synth.round_bf16(synth.projection_matrix(cfg.d_model, patch, 9))
+        w[:, 1] = np.ldexp(w[:, 1], 125)                       # embeddings of up to about 1e38
+        w[-1, 2] = np.inf
+        w[0, 3] = -np.inf
+        got = run_embed(gm, frames, patch, w)
+        for b in (0, B - 1):
+            want = O.embed_patches(frames[b], patch, w)
+            big = 2.0 ** 125
+            assert np.abs(want[:, 1]).max() < 3e38 and np.abs(got[b][:, 1] / big - want[:, 1] / big).max() <= 1e-5
+            np.testing.assert_array_equal(got[b][:, 2:4], want[:, 2:4])
+            rest = [0] + list(range(4, cfg.d_model))
+            assert np.abs(got[b][:, rest] - want[:, rest]).max() <= 1e-5
+    finally:
+        gm.close()
+
+
 def test_embed_feeds_the_sparse_prefill():
     """Two steps at the tiny configuration: frame -> Alg. 1 -> embeddings of the recomputed
     patches only -> sparse prefill, all on the GPU, against the oracle's chain."""
