@@ -253,7 +253,7 @@ int embed_init() {
 
 // Workgroups of 512 features and 64 patches from the size on at which they fill the chip once
 // (256 of them; the number of live patches is known on the device only, so all are counted), and
-// patches of up to 15 x 15 pixels, two groups of which fit the LDS of a CU.  Both sides, per call: at
+// patches of up to 14 x 14 pixels, two groups of which fit the LDS of a CU (15 x 15: 86 KiB each).  Both sides, per call: at
 // 128 such workgroups (4 x 256 patches, d_model 4096) 29 us against 22 with KS = 4, at 256 (2 x
 // 1024) 33 against 38, at 1024 (8 x 1024) 85 against 117.
 static const long long kEmbWide = 256;

@@ -75,7 +75,10 @@ def test_embed_matches_oracle(H, W, patch):
     (1, 14, 14 * 33, 14, 1),        # buffers that allow no wide loads and stores
     (4, 256, 256, 4, 0),            # 256 groups of 64 patches: the wide form
     (4, 256, 256, 4, 1),
-    (7, 3 * 40, 3 * 50, 3, 0),      # odd patches, the wide form with a ragged last group
+    (8, 3 * 40, 3 * 50, 3, 0),      # odd patches, the wide form with a ragged last group, 2 k-tiles
+    (18, 14 * 30, 14 * 31, 14, 0),  # the wide form at its largest patch: 37 k-tiles, the last one padded,
+    (18, 14 * 30, 14 * 31, 14, 1),  # 15 groups per stream, the last of 34 patches or less
+    (7, 15 * 30, 15 * 40, 15, 0),   # larger patches: never the wide form
 ])
 def test_embed_at_the_edges_of_its_tiles(B, H, W, patch, skew):
     """Every product is exact, so what is left is the rounding of an fp32 sum of 3 patch^2 terms
