@@ -8,6 +8,8 @@
 //   final_hidden              final RMSNorm to fp32 (output)
 //   argmax_rows, embed_rows   greedy token, token embedding lookup (decode)
 //   pack_weights              weights -> fragment order (once per model)
+#include <algorithm>
+
 #include "common.h"
 
 // ---------------------------------------------------------------------------
@@ -425,8 +427,9 @@ void launch_resid_norm_rows(bool f16, const float* resid, int resid_seq_stride, 
 #undef VLAC_RN
 }
 
-// Final RMSNorm of every row alive at the last layer, fp32 out [B, L, d].  One workgroup per row;
-// a thread keeps its share of the first 8192 values in registers, so that all loads of a row are
+// Final RMSNorm of every row alive at the last layer, fp32 out [B, L, d].  A workgroup per row, or,
+// of more rows than kFinalGrid, per row of every kFinalGrid-th (a launch has room for 2^32 threads, a
+// call may have more rows than 2^24); a thread keeps its share of the first 8192 values in registers, so that all loads of a row are
 // in flight together (one wave per row that read it twice, 256 values at a time: 12.5 us for 109
 // rows of 4096 values, now 5.5; 2712 rows 22 -> 16).
 __global__ __launch_bounds__(256) void final_hidden_kernel(
@@ -435,48 +438,52 @@ __global__ __launch_bounds__(256) void final_hidden_kernel(
     float* __restrict__ out, int L) {
   constexpr int NI = 8;
   __shared__ float red[4];
-  const int slot = blockIdx.x, tid = threadIdx.x;
-  if (slot >= *n_rows) return;
-  const int id = rows[slot];
-  const float* x = src + ((size_t)(id >> 16) * seq_stride + (id & 0xffff)) * d;
-  float* y = out + ((size_t)(id >> 16) * L + (id & 0xffff)) * d;
-  float4 v[NI], g[NI];
+  const int tid = threadIdx.x, n = *n_rows;
+  for (int slot = blockIdx.x; slot < n; slot += gridDim.x) {
+    const int id = rows[slot];
+    const float* x = src + ((size_t)(id >> 16) * seq_stride + (id & 0xffff)) * d;
+    float* y = out + ((size_t)(id >> 16) * L + (id & 0xffff)) * d;
+    float4 v[NI], g[NI];
 #pragma unroll
-  for (int i = 0; i < NI; ++i) {
-    const int k = tid * 4 + i * 1024;
-    v[i] = g[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (k < d) {
-      v[i] = *(const float4*)(x + k);
-      g[i] = *(const float4*)(gain + k);
+    for (int i = 0; i < NI; ++i) {
+      const int k = tid * 4 + i * 1024;
+      v[i] = g[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (k < d) {
+        v[i] = *(const float4*)(x + k);
+        g[i] = *(const float4*)(gain + k);
+      }
     }
-  }
-  float ss = 0.f;
+    float ss = 0.f;
 #pragma unroll
-  for (int i = 0; i < NI; ++i) ss += v[i].x * v[i].x + v[i].y * v[i].y + v[i].z * v[i].z + v[i].w * v[i].w;
-  for (int k = tid * 4 + NI * 1024; k < d; k += 1024) {
-    const float4 q = *(const float4*)(x + k);
-    ss += q.x * q.x + q.y * q.y + q.z * q.z + q.w * q.w;
-  }
-  ss = wave_sum(ss);
-  if ((tid & 63) == 0) red[tid >> 6] = ss;
-  __syncthreads();
-  const float r = rsqrtf((red[0] + red[1] + red[2] + red[3]) / (float)d + eps);
+    for (int i = 0; i < NI; ++i) ss += v[i].x * v[i].x + v[i].y * v[i].y + v[i].z * v[i].z + v[i].w * v[i].w;
+    for (int k = tid * 4 + NI * 1024; k < d; k += 1024) {
+      const float4 q = *(const float4*)(x + k);
+      ss += q.x * q.x + q.y * q.y + q.z * q.z + q.w * q.w;
+    }
+    ss = wave_sum(ss);
+    if ((tid & 63) == 0) red[tid >> 6] = ss;
+    __syncthreads();
+    const float r = rsqrtf((red[0] + red[1] + red[2] + red[3]) / (float)d + eps);
 #pragma unroll
-  for (int i = 0; i < NI; ++i) {
-    const int k = tid * 4 + i * 1024;
-    if (k < d)
-      *(float4*)(y + k) = make_float4(v[i].x * r * g[i].x, v[i].y * r * g[i].y, v[i].z * r * g[i].z, v[i].w * r * g[i].w);
-  }
-  for (int k = tid * 4 + NI * 1024; k < d; k += 1024) {
-    const float4 q = *(const float4*)(x + k), h = *(const float4*)(gain + k);
-    *(float4*)(y + k) = make_float4(q.x * r * h.x, q.y * r * h.y, q.z * r * h.z, q.w * r * h.w);
+    for (int i = 0; i < NI; ++i) {
+      const int k = tid * 4 + i * 1024;
+      if (k < d)
+        *(float4*)(y + k) = make_float4(v[i].x * r * g[i].x, v[i].y * r * g[i].y, v[i].z * r * g[i].z, v[i].w * r * g[i].w);
+    }
+    for (int k = tid * 4 + NI * 1024; k < d; k += 1024) {
+      const float4 q = *(const float4*)(x + k), h = *(const float4*)(gain + k);
+      *(float4*)(y + k) = make_float4(q.x * r * h.x, q.y * r * h.y, q.z * r * h.z, q.w * r * h.w);
+    }
+    __syncthreads();  // (red is free again)
   }
 }
+
+static const int kFinalGrid = 4096;
 
 void launch_final_hidden(const float* src, int seq_stride, const int* rows, const int* n_rows,
                          int max_rows, const float* gain, float eps, int d, float* out, int L,
                          hipStream_t st) {
-  hipLaunchKernelGGL(final_hidden_kernel, dim3(max_rows), dim3(256), 0, st, src,
+  hipLaunchKernelGGL(final_hidden_kernel, dim3(std::min(max_rows, kFinalGrid)), dim3(256), 0, st, src,
                      seq_stride, rows, n_rows, gain, eps, d, out, L);
 }
 

@@ -198,6 +198,21 @@ def test_many_long_streams_head_dim_64():
         gm.close()
 
 
+def test_hidden_states_of_more_rows_than_the_final_norm_has_workgroups():
+    """4800 rows over 4096 workgroups: some take two rows."""
+    cfg = synth.ModelCfg(1, 64, 4, 4, 64, 96, 64)
+    B, n_vis, n_txt = 16, 280, 20
+    om = oracle_model(cfg, seed=3, std=0.1)
+    gm = GpuModel(cfg, seed=3, max_batch=B, max_seq=320, std=0.1)
+    try:
+        emb = synth.round_bf16(np.random.default_rng(5).standard_normal((B, n_vis + n_txt, cfg.d_model)))
+        got = gm.prefill(emb, n_vis)
+        for b in range(B):
+            check(got, O.dense_forward(om, emb[b], n_vis, O.new_cache(cfg, 320)), b)
+    finally:
+        gm.close()
+
+
 def test_mid_size_split_k_with_layer_varying_reuse():
     """d = 1024: the projection GEMMs split K over workgroups and hand partial rows to the
     next row kernel; with reuse counts that grow over depth the row lists of consecutive
