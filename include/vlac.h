@@ -119,13 +119,20 @@ size_t vlac_kv_cache_bytes(const vlac_model_cfg* cfg);
  * considered, values above 8 count as 8; the library passes how many partial-row sets of the
  * call's row capacity its workspace holds: 8 up to 1024 rows, 3 beyond).
  * (This is the cut into work items 256 features wide.  A projection that does not add to the
- * residual stream is cut into items of 192 features x 192 or 320 rows instead, in calls with a
- * capacity of up to 1536 rows, where those move less by the same estimate.)
+ * residual stream may be cut into items of 192 features instead: vlac_plan_unsplit_gemm.)
  * Results: rows per work item (256, 192 or 128; a work item is 256 features wide), K parts,
  * work items (weight tiles x parts x row blocks).  Needs neither a context nor a GPU.
  * VLAC_E_NULL / VLAC_E_RANGE on null pointers or non-positive sizes. */
 int vlac_plan_many_rows_gemm(int out_features, int k, int rows, int max_splits,
                              int* block_rows, int* k_splits, int* work_items);
+
+/* The same for a projection that does not add to the residual stream (QKV, gate/up), K
+ * unsplit: in calls with a capacity (streams x tokens) of up to 1536 rows such a projection is
+ * cut into work items of 192 features x 320 or 192 rows where those move less by the same
+ * estimate (2 x (6 + 2 rt) KiB per 32-k step, rt = rows / 64) than the items of 256 features
+ * above; otherwise into these.  Results: features and rows per work item, work items. */
+int vlac_plan_unsplit_gemm(int out_features, int rows, int capacity,
+                           int* item_features, int* item_rows, int* work_items);
 
 /* Zero-fills stream b's part of the cache and marks it "never filled": the next
  * prefill of that stream must be a full one.  Must be called once per stream

@@ -68,6 +68,8 @@ def lib():
         L.vlac_status_string.argtypes = [i32]
         L.vlac_plan_many_rows_gemm.restype = C.c_int
         L.vlac_plan_many_rows_gemm.argtypes = [C.c_int] * 4 + [C.POINTER(C.c_int)] * 3
+        L.vlac_plan_unsplit_gemm.restype = C.c_int
+        L.vlac_plan_unsplit_gemm.argtypes = [C.c_int] * 3 + [C.POINTER(C.c_int)] * 3
         L.vlac_kv_cache_bytes.restype = C.c_size_t
         L.vlac_kv_cache_bytes.argtypes = [C.POINTER(ModelCfg)]
         L.vlac_create.argtypes = [C.POINTER(ModelCfg), C.POINTER(vp)]
@@ -150,6 +152,15 @@ def vlac_plan_many_rows_gemm(out_features, k, rows, max_splits=1):
     if st != 0:
         raise VlacError(st, "vlac_plan_many_rows_gemm")
     return tf.value, ks.value, wi.value
+
+
+def vlac_plan_unsplit_gemm(out_features, rows, capacity):
+    """-> (features and rows per work item, work items); no GPU needed."""
+    nf, nr, wi = C.c_int(), C.c_int(), C.c_int()
+    st = lib().vlac_plan_unsplit_gemm(out_features, rows, capacity, C.byref(nf), C.byref(nr), C.byref(wi))
+    if st != 0:
+        raise VlacError(st, "vlac_plan_unsplit_gemm")
+    return nf.value, nr.value, wi.value
 
 
 def vlac_kv_cache_bytes(cfg):

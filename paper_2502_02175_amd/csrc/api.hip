@@ -104,6 +104,20 @@ int vlac_plan_many_rows_gemm(int out_features, int k, int rows, int max_splits,
   return VLAC_OK;
 }
 
+int vlac_plan_unsplit_gemm(int out_features, int rows, int capacity, int* item_features, int* item_rows,
+                           int* work_items) {
+  if (!item_features || !item_rows || !work_items) return VLAC_E_NULL;
+  if (out_features < 1 || rows < 1 || capacity < rows) return VLAC_E_RANGE;
+  const int blocks = (out_features + 31) / 32;
+  TallPlan pl = tall_plan((blocks + 7) / 8, rows, 1, 1), p3;
+  const bool narrow = capacity <= kNarrowRows && tall_plan_192(blocks, rows, pl, &p3);
+  if (narrow) pl = p3;
+  *item_features = narrow ? 192 : 256;
+  *item_rows = 64 * pl.rt;
+  *work_items = pl.items();
+  return VLAC_OK;
+}
+
 size_t vlac_kv_cache_bytes(const vlac_model_cfg* cfg) {
   if (!cfg || check_cfg(cfg) != VLAC_OK) return 0;
   return kv_elems_per_stream(*cfg) * cfg->max_batch * sizeof(bf16_t);

@@ -332,7 +332,10 @@ __host__ __device__ inline TallPlan tall_plan(int tiles, int n_rows, int S_max, 
 // a round nearly empty: 7B gate/up, before and now, at 601 rows (430 items of 128 rows in two rounds
 // against 230 of 192 x 320 in one) 114 -> 102 us, at 288 rows (172 items against 230 of
 // 192 x 192) 74 -> 66 us; at thousands of rows the rounds are full and 256 x 256 moves least
-// per product (launch_gemm_tall offers them up to a capacity of 1536 rows).  Only NB (feature blocks of 32) and the row count decide: K cancels out.
+// per product (they are offered up to a capacity of kNarrowRows).  Only NB (feature blocks of 32)
+// and the row count decide: K cancels out.
+// (From kNarrowRows on two rounds of items and more are the rule, and a narrower item seldom saves one.)
+static const int kNarrowRows = 1536;
 __host__ __device__ inline bool tall_plan_192(int NB, int n_rows, const TallPlan& pl, TallPlan* out) {
   const int tiles = (NB + 5) / 6;
   unsigned best = (((unsigned)pl.items() + 255u) >> 8) * 2u * (8u + 2u * (unsigned)pl.rt);

@@ -413,9 +413,6 @@ void launch_gemm_tall(bool f16, int epi, GemmArgs& a, int rows_cap, int S_max, h
   // the grid covers the most work items any row count up to rows_cap can give (the plan
   // changes its row blocks and K parts with the row count)
   const int tiles = (a.NB + 7) >> 3;
-  // (from kNarrowRows of capacity on two rounds of items and more are the rule, and a narrower item
-  // seldom saves one)
-  constexpr int kNarrowRows = 1536;
   const bool narrow = (epi == EPI_QKV || epi == EPI_SWIGLU) && rows_cap <= kNarrowRows;
   int most = 0;
   for (int n = 64; n < rows_cap + 64; n += 64) {

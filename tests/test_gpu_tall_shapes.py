@@ -12,6 +12,7 @@ from oracle import vlac_oracle as O
 from helpers import GpuModel, oracle_model
 
 pytestmark = pytest.mark.gpu
+KNOWN = (288, 320, 353, 404, 519, 640, 704)   # row counts of full prefills
 SAFE = os.path.join(os.path.dirname(V.lib_path()), "libvlac_safe.so")
 
 
@@ -19,7 +20,7 @@ def passes(cfg, operand, emb, n_vis, keeps, std):
     gm = GpuModel(cfg, seed=4, max_batch=1, max_seq=736, std=std, operand=operand)
     try:
         out = []
-        for L in (288, 320, 353, 519, 640, 704):
+        for L in KNOWN:
             out.append(gm.prefill(emb[None, -L:], L - 8))
         gm.prefill(emb[None], n_vis)
         for i, k in enumerate(keeps):
@@ -29,8 +30,10 @@ def passes(cfg, operand, emb, n_vis, keeps, std):
         gm.close()
 
 
-# (11008: gate/up of 688 feature blocks, 115 tiles of 192, the last of 4 blocks: 192 rows per item at
-# 288 .. 353 rows, 320 at 519 .. 640, items of 256 features at 704)
+# (11008: gate/up of 688 feature blocks, 115 tiles of 192 features, the last of 4 blocks)
+ITEMS = {288: (192, 192), 320: (192, 192), 353: (192, 192), 404: (256, 256), 519: (192, 320), 640: (192, 320), 704: (192, 192)}
+
+
 @pytest.mark.parametrize("d,F,operand", [(320, 11008, "f16"), (256, 11008, "bf16")])
 def test_items_of_192_features(d, F, operand):
     cfg = synth.ModelCfg(2, d, 4, 4, 64, F, 96)
@@ -38,6 +41,8 @@ def test_items_of_192_features(d, F, operand):
     n_vis = 696
     rng = np.random.default_rng(d)
     emb = synth.round_bf16(rng.standard_normal((n_vis + 8, d))).astype(np.float32)
+    for L in KNOWN:  # which items the gate/up projection of each count runs
+        assert V.vlac_plan_unsplit_gemm(2 * F, L, L)[:2] == ITEMS[L], L
     keeps = [rng.permutation(n_vis)[:n].tolist() for n in (60, 185, 300, 420)]
     got = passes(cfg, operand, emb, n_vis, keeps, std)
     try:
@@ -49,7 +54,7 @@ def test_items_of_192_features(d, F, operand):
         for k in ("hidden", "logits", "attn_mean"):
             assert np.array_equal(a[k], b[k], equal_nan=True)
     om = oracle_model(cfg, seed=4, std=std)
-    for i, L in enumerate((288, 320, 353, 519, 640, 704)):
+    for i, L in enumerate(KNOWN):
         want = O.dense_forward(om, emb[-L:], L - 8, O.new_cache(cfg, 736))
         assert np.abs(got[i]["hidden"][0] - want["hidden"]).max() <= tol, L
     cache = O.new_cache(cfg, 736)
@@ -57,4 +62,4 @@ def test_items_of_192_features(d, F, operand):
     for i, k in enumerate(keeps):
         want = O.sparse_forward(om, emb + np.float32(0.125) * (i + 1), n_vis, cache, [k] * 2)
         alive = ~np.isnan(want["hidden"][:, 0])
-        assert np.abs(got[6 + i]["hidden"][0][alive] - want["hidden"][alive]).max() <= tol, len(k)
+        assert np.abs(got[len(KNOWN) + i]["hidden"][0][alive] - want["hidden"][alive]).max() <= tol, len(k)

@@ -72,9 +72,46 @@ def test_invariants_over_row_counts(n, k, smax):
         assert cost(block, s) == min(cost(b, S) for b in (128, 192, 256) for S in (1, 2, 3, 4, 6, 8) if S <= (smax if k >= 1536 else 1))
 
 
+def test_items_of_192_features():
+    """A projection without a residual in a call of up to 1536 rows: items of 192 features x 320 or 192
+    rows (16 or 12 KiB x 2 per step) where rounds x KiB are strictly less than with 256 features."""
+    plan = V.vlac_plan_unsplit_gemm
+    # 7B gate/up (86 tiles of 256, 115 of 192).  288 rows: 172 items of 256 or 192 rows, one round x 28;
+    # 230 of 192 x 192, one round x 24
+    assert plan(22016, 288, 288) == (192, 192, 230)
+    # 404 rows: 172 items of 256 rows, one round x 32; 230 of 320 rows, one round x 32: no less
+    assert plan(22016, 404, 404) == (256, 256, 172)
+    # 519 and 601 rows: 430 items of 128 rows take two rounds x 24, 230 of 192 x 320 one x 32
+    assert plan(22016, 519, 601) == (192, 320, 230)
+    # 704 rows: 344 items of 192 rows, two rounds x 28; 460 of 192 x 192, two rounds x 24
+    assert plan(22016, 704, 704) == (192, 192, 460)
+    # 7B QKV (48 tiles, 64): one round of 96 items of 192 rows at 288 rows as well, but 144 of 128 rows
+    # move 24 each, and 128 of 192 x 192 no less
+    assert plan(12288, 288, 288) == (256, 128, 144)
+    # 700 rows: 288 items of 128 rows take two rounds, 192 of 192 rows one x 28; 256 of 192 x 192 one x 24
+    assert plan(12288, 700, 700) == (192, 192, 256)
+    # from a capacity of 1537 rows on only the items of 256 features
+    assert plan(12288, 700, 1536) == (192, 192, 256) and plan(12288, 700, 1537) == (256, 192, 192)
+
+
+@pytest.mark.parametrize("n", [768, 1536, 2048, 12288, 17920, 22016])
+def test_unsplit_plan_is_the_least_estimate(n):
+    for rows in range(1, 1537, 7):
+        feats, item_rows, items = V.vlac_plan_unsplit_gemm(n, rows, 1536)
+        cost = lambda f, r: -(-(-(-n // f) * -(-rows // r)) // 256) * 2 * (f // 32 + r // 32)
+        wide = min(cost(256, r) for r in (256, 192, 128))
+        assert items == -(-n // feats) * -(-rows // item_rows)
+        assert cost(feats, item_rows) == min([wide] + [cost(192, r) for r in (320, 192)])
+        assert (feats == 192) == (min(cost(192, r) for r in (320, 192)) < wide)
+        assert feats == 192 or (item_rows, items) == PLAN(n, 4096, rows, 1)[::2]
+
+
 def test_bad_arguments():
     lib = V.lib()
     out = C.c_int()
     assert lib.vlac_plan_many_rows_gemm(4096, 4096, 100, 1, None, C.byref(out), C.byref(out)) == -1
     for bad in ((0, 4096, 100, 1), (4096, 0, 100, 1), (4096, 4096, 0, 1), (4096, 4096, 100, 0)):
         assert lib.vlac_plan_many_rows_gemm(*bad, C.byref(out), C.byref(out), C.byref(out)) == -3
+    assert lib.vlac_plan_unsplit_gemm(4096, 100, 100, None, C.byref(out), C.byref(out)) == -1
+    for bad in ((0, 100, 100), (4096, 0, 100), (4096, 100, 99)):
+        assert lib.vlac_plan_unsplit_gemm(*bad, C.byref(out), C.byref(out), C.byref(out)) == -3
