@@ -155,7 +155,8 @@ int vlac_create(const vlac_model_cfg* cfg, vlac_ctx** out) {
   hipError_t e = hipGetDevice(&ctx->device);
   const int nl = m.n_layers, mb = m.max_batch, ms = m.max_seq, mr = ctx->max_rows;
   const int kpad_x = ctx->kpad_d > ctx->kpad_q ? ctx->kpad_d : ctx->kpad_q;
-  ctx->partial_floats = (size_t)64 << 20;  // 256 MiB of split-K workspace
+  // split-K workspace of the few-rows GEMM: it splits fewer than 256 weight blocks, in up to 8 parts of 1024 sums
+  ctx->partial_floats = (size_t)256 * 8 * 1024;
   // partial rows of the projection + residual GEMMs: up to 8 splits of up to 1024 rows
   ctx->rpart_floats = (size_t)8 * (mr < 1024 ? mr : 1024) * m.d_model;
   // (more rows: 3 splits of all rows)
