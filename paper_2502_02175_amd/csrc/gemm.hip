@@ -119,7 +119,7 @@ __device__ __forceinline__ void rows_produce(const GemmArgs& a, uint4* lds, int 
       const int k = min(rg.k0 + min(c * Sh::CT + kt0 + u / NA, max(rg.n - 1, 0)), KC - 1);
       const char* src = rows[u % NA] + (size_t)k * 1024;
       const uint32_t d = lds0 + (uint32_t)(slot * Sh::TILES + u) * 1024u;
-      if (u % NA < NA - 2) copy(d, src);  // (only the last tile, or the last twice, can be ragged)
+      if (u % NA < NA - 2) copy(d, src);  // (only the last tile can be ragged)
       else if (rt0 + u % NA < (row_end - 1) >> 5 || row_on) copy(d, src);
     }
   };

@@ -13,13 +13,14 @@
 //  * Operands are in fragment order (common.h): a tile is 1 KiB that a wave copies global ->
 //    LDS as it lies (global_load_lds_dwordx4: lane l's 16 bytes land at base + 16 l) and
 //    reads back with one 16-byte LDS read per lane, conflict-free.
-//  * A stage is 32 k: 16 weight tiles + 16 activation tiles = 32 KiB; a ring of 5 stages
-//    (all 160 KiB of a CU's LDS), copies run 4 stages ahead.  Every wave copies 8 tiles per
-//    stage, whatever the row count (tiles past the end are clamped to a valid one and never
-//    read), so that the number of copies in flight is the same for every wave at every step:
+//  * A stage is 32 k: at 256 x 256, 16 weight tiles + 16 activation tiles = 32 KiB; a ring of 5
+//    stages (all 160 KiB of a CU's LDS), copies run 4 stages ahead (lower items: stages of 28 and 24
+//    KiB, 5 and 6 of them, see TallRing).  Every wave copies a quarter of a stage, 8, 7 or 6 tiles,
+//    whatever the row count (tiles past the end are clamped to a valid one and never read), so
+//    that the number of copies in flight is the same for every wave at every step:
 //    the copies are inline assembly that the compiler does not see (it treats its own
 //    LDS-direct loads as aliasing every LDS read and drains the load queue at each), and
-//    their waits are placed by hand (VLAC_VMCNT; a build with -DVLAC_SAFE_WAITS waits for
+//    their waits are placed by hand (tall_wait; a build with -DVLAC_SAFE_WAITS waits for
 //    everything instead and must give the same bits).
 //  * One barrier per stage, placed behind the first MFMA of its second k-tile: the fragments
 //    of a k-tile are read while the MFMAs of the one before run, across the barrier as well.
