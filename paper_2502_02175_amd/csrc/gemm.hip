@@ -683,20 +683,18 @@ bool gemm_can_fuse_norm(int n_rows_host, int decode_pos, int kpad) {
 
 // From this many rows on (the capacity of the launch: streams x tokens; the actual row count
 // is known on the device only) the GEMMs go to the kernel built for matrix-core bound
-// work.  Measured at the 7B shape, 32 layers, by ACTUAL row count: the one-stream kernel
-// wins below about 250 rows (218 rows: 7.1 against 7.8 ms per prefill), the many-rows
-// kernel above (327 rows: 10.3 against 9.2 ms, 576 rows: 13.8 against 10.2 ms); a
-// capacity of 512 rows (two 7B streams, one stream with two camera views) mostly means
-// more than 250 recomputed rows.  (Weights stored as e4m3 codes: the many-rows kernel has
+// work.  By ACTUAL row count the one-stream kernel wins up to about 260 rows where two of
+// them share a launch (below) and up to 352 where it is alone (kTallKnownRows); a capacity of
+// 512 rows (two 7B streams, one stream with two camera views) mostly means more.  (Weights stored as e4m3 codes: the many-rows kernel has
 // no variant for them; up to 1023 rows stay with the one-stream kernel, from 1024 rows on
 // the matrix is expanded to fp16 before every launch, 3 bytes of traffic per weight
 // against the 2 rows flops per weight that such a launch spends on it.)
 static const int kTallRows = 512;
-// (A launch whose row count is known on the host, a full recompute, goes by that count: from
-// kTallKnownRows rows on the many-rows kernel reads the weights once where the one-stream kernel
-// fetches them per block of 128 rows: 288 rows of one 7B stream, 32 layers: 8.1 against 9.3 ms;
-// 256 rows, two blocks: 7.65 against 7.25 ms, the one-stream kernel keeps them.)
-static const int kTallKnownRows = 257;
+// (A launch whose row count is known on the host, a full recompute, goes by that count.  One-stream
+// against many-rows kernel, four layers and the head, 7B: 256 rows 866 and 1037 us, 288 rows 969
+// and 987, 352 rows 1132 and 1145, 384 rows 1116 and 1103 (another card); grouped queries: 288 rows 445
+// and 544, 352 rows 523 and 595.)
+static const int kTallKnownRows = 353;
 static bool use_tall(const vlac_ctx* c, int rows_cap, int n_rows_host = -1) {
   if (c->w8) return rows_cap >= 1024 && c->wdeq;
   return rows_cap >= kTallRows || (n_rows_host >= kTallKnownRows && rows_cap > 32);
@@ -755,10 +753,11 @@ static int rows_kernel_splits(const vlac_ctx* c, int epi, int n_blocks, int KS, 
 
 // Where the many-rows kernel serves a capacity at which a sparse prefill usually leaves
 // fewer than kSmallRows rows (the count is known on the device only), BOTH kernels are
-// launched for a GEMM and each leaves at once if the count is the other's.  Measured at
-// the 7B shape, two streams of 288 tokens: 116 rows 5.6 against 7.9 ms per 32-layer
-// prefill, 218 rows 7.3 against 7.8 ms, and 0.4 ms more where the many-rows kernel works
-// (128 idle launches of 3 us); at 70 % static about 0.38 of the capacity is recomputed,
+// launched for a GEMM and each leaves at once if the count is the other's.  Measured with
+// two streams of 288 tokens, four layers and the head, one-stream against many-rows kernel, the
+// idle launches included: 7B, about 142 rows 742 and 964 us, 218 rows 879 and 1036, 269 rows 1119 and
+// 1102, 320 rows 1180 and 1154 (grouped queries 429 and 575 at 218 rows, 544 and 589 at 320); and
+// 3 us per GEMM more for the idle launch where the many-rows kernel works; at 70 % static about 0.38 of the capacity is recomputed,
 // so from a capacity of 768 rows on the second launch would mostly be the idle one; and
 // where the reuse lists are too short to leave fewer than kSmallRows rows (top-k 100 of two
 // camera views), only the many-rows kernel is launched.
