@@ -27,8 +27,8 @@
 #include <cstring>
 #include "gemm_epi.h"
 
-// Workgroup: 4 consumer waves and 2 producer waves.  The consumers are FB feature blocks x KP
-// parts of the K range (FB KP = 4); a consumer streams the weight tiles of its block and part
+// Workgroup: up to 6 consumer waves and 2 producer waves.  The consumers are fb feature blocks, or 2 of
+// them x 2 parts of the K range (KP); a consumer streams the weight tiles of its block and part
 // into registers, UK k-tiles ahead, and multiplies them by up to 8 row tiles whose operands it
 // reads from LDS.  The producers copy those operands global -> LDS directly into a ring of
 // ROWS_RING chunks, for nobody else's registers and nobody else's load queue: a wave's loads
@@ -43,18 +43,29 @@
 // copy nothing and the tiles are cut to use most CUs.  7B shape, 109 rows, before and now: gate/up
 // 49.8 -> 41.7 us (4.3 TB/s of weights), QKV 41.2 -> 33.6, O 15 -> 14.4, FFN down 29 -> 26; four
 // layers with the head 742 -> 628 us, 192 rows 908 -> 764.  32 weight tiles in flight: no faster.
-// A wave has 256 registers (6 waves on 4 SIMDs).  No instance spills: fewer weight tiles in flight
+// fb and the row blocks follow from the row count, in the kernel where only the device knows it
+// (rows_cut): with two row blocks of 288 rows QKV runs 256 workgroups of 3 feature blocks in one round
+// instead of 384 of 2 in two, gate/up 230 of 6 instead of 460 of 3.  Four layers of 7B and the head,
+// fb by the launch alone and by the row count: 211 rows 824 -> 794 us, 259 rows 1020 -> 907, 288 rows 999 ->
+// 877, 437 rows 1514 -> 1326.  (K of QKV or gate/up split over workgroups instead, the last wave to
+// arrive adding up: 3 us per hand-over, 288 rows -58 us where this gives -120, 109 rows +10.)
+// The arguments are read together at the start: the argument buffer lies in host memory, and an argument
+// that is first read later is a round trip there (decode, 32 streams of grouped queries 1545 -> 1522 us,
+// the tiny shape's step 284 -> 280, for the few-rows kernel and this one).
+// A wave has 256 registers (up to 8 waves on 4 SIMDs).  No instance spills: fewer weight tiles in flight
 // with 5 row tiles and more, the body of every row tile count kept apart from the others (see there),
 // and only as many weight tiles asked for ahead of the choice of the body as every body keeps.
 // (With 17 to 26 registers of every 16-bit instance spilled, 192 rows of 7B took 795 us per four
 // layers and the head, now 764; 109 rows 635, now 628.)
 constexpr int ROWS_RING = 5;       // chunks of at most 32 KiB: all 160 KiB of a CU's LDS
-constexpr int rows_consumers(int FB) { return FB == 2 ? 4 : FB; }
-constexpr int rows_threads(int FB) { return 64 * (rows_consumers(FB) + 2); }
+constexpr int ROWS_FB_MIN = 2, ROWS_FB_MAX = 6;  // feature blocks per workgroup: 2 (K in two parts) or 3 to 6
+constexpr int ROWS_PAIR_NA = 6;  // most row tiles per wave with 2 feature blocks where the launch has both forms
+// The forms of the kernel: every row count with 2 feature blocks, none, or some (the count decides)
+enum { ROWS_PAIRS = 2, ROWS_SINGLE = 3, ROWS_MIXED = 4 };
+constexpr int rows_threads(int form) { return 64 * ((form == ROWS_PAIRS ? 4 : ROWS_FB_MAX) + 2); }  // (at most)
 
-template <int NA, int FB, bool W8>
+template <int NA, int KP, bool W8>
 struct RowsShape {
-  static constexpr int NC = rows_consumers(FB), KP = NC / FB;
   static constexpr int CT = (NA <= 4 ? 8 : 4) / KP;   // k-tiles per chunk and part
   static constexpr int TILES = KP * CT * NA;          // operand tiles (1 KiB) per chunk
   static constexpr int UK = NA <= 4 || W8 ? 16 : NA <= 6 ? 12 : 8;  // weight tiles in flight per consumer (16 bits: 1 KiB each)
@@ -83,10 +94,10 @@ __device__ inline void rows_barrier() { asm volatile("s_barrier" ::: "memory"); 
 // A producer wave (half = 0, 1): with two K parts the operand tiles of part `half`, else those of
 // half the k-tiles of every chunk.  At the barrier that ends chunk c the chunks c + 1 and c + 2
 // have landed.
-template <int NA, int FB, bool W8>
+template <int NA, int KP, bool W8>
 __device__ __forceinline__ void rows_produce(const GemmArgs& a, uint4* lds, int half, int s, int rt0, int row_end) {
-  using Sh = RowsShape<NA, FB, W8>;
-  constexpr int KP = Sh::KP, PER = Sh::TILES / 2;  // copies of a chunk per producer
+  using Sh = RowsShape<NA, KP, W8>;
+  constexpr int PER = Sh::TILES / 2;  // copies of a chunk per producer
   static_assert((ROWS_RING - 3) * PER <= 63, "the counter holds 63");
   const int KC = 4 * a.KS;
   const uint32_t lane_off = (threadIdx.x & 63) * 16u;
@@ -150,18 +161,19 @@ struct RowsWeights {
   uint4 t[N];
 };
 
-template <int NA, int FB, int EPI, bool F16, bool W8>
-__device__ __forceinline__ void rows_body(const GemmArgs& a, uint4* lds, RowsWeights<W8>& W, int tile, int s, int rt0,
-                                          int row_end) {
-  using Sh = RowsShape<NA, FB, W8>;
-  constexpr int NC = Sh::NC, KP = Sh::KP, CT = Sh::CT, UK = Sh::UK, XR = Sh::XR, CH = Sh::TILES * 64;
+template <int NA, int KP, int FORM, int EPI, bool F16, bool W8>
+__device__ __forceinline__ void rows_body(const GemmArgs& a, uint4* lds, RowsWeights<W8>& W, int fb, int tile, int s,
+                                          int rt0, int row_end) {
+  using Sh = RowsShape<NA, KP, W8>;
+  constexpr bool IDS_EARLY = KP == 2 || NA <= 6;
+  constexpr int CT = Sh::CT, UK = Sh::UK, XR = Sh::XR, CH = Sh::TILES * 64;
   // (Opaque copies of what addresses are made from: the bodies of all row tile counts are the
   // branches of one switch, and the compiler would else compute the addresses of all of them ahead
   // of it and spill.)
   int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   asm volatile("" : "+v"(lane), "+s"(w), "+s"(tile), "+s"(s), "+s"(rt0));
-  const int part = w / FB, nb = tile * FB + (w - part * FB), g = lane >> 5;
-  const bool wave_on = w < NC && nb < a.NB;
+  const int part = KP == 2 ? w >> 1 : 0, nb = KP == 2 ? tile * 2 + (w & 1) : tile * fb + w, g = lane >> 5;
+  const bool wave_on = w < fb * KP && nb < a.NB;
   f32x16 acc[NA];
 #pragma unroll
   for (int m = 0; m < NA; ++m)
@@ -171,10 +183,12 @@ __device__ __forceinline__ void rows_body(const GemmArgs& a, uint4* lds, RowsWei
   int ids[NA];
 #pragma unroll
   for (int m = 0; m < NA; ++m) ids[m] = 0;
-  if (w >= NC) {
-    rows_produce<NA, FB, W8>(a, lds, w - Sh::NC, s, rt0, row_end);
+  if (const int p0 = FORM == ROWS_PAIRS ? 4 : a.waves - 2; w >= p0) {
+    rows_produce<NA, KP, W8>(a, lds, w - p0, s, rt0, row_end);
   } else {
-    const RowsRange rg = rows_range(a.KS, a.S * KP, s * KP + part);
+    RowsRange rg = rows_range(a.KS, a.S * KP, s * KP + part);
+    // (opaque: simplified by KP = 1 the last steps keep more weight tiles alive, and spill)
+    if constexpr (KP == 1) asm volatile("" : "+s"(rg.n));
     const int n_max = rows_range(a.KS, a.S * KP, s * KP).n, n = rg.n;
     const int n_min = KP == 1 ? n_max : rows_range(a.KS, a.S * KP, s * KP + KP - 1).n;
     // (e4m3 weights: a 16-byte lane slot holds two k-tiles)
@@ -212,8 +226,8 @@ __device__ __forceinline__ void rows_body(const GemmArgs& a, uint4* lds, RowsWei
         W.t[t] = ld_stream(wsrc + (size_t)k * 64);
       }
     };
-    if (EPI != EPI_LOGITS && !(EPI == EPI_RESID && a.S > 1)) {
-      // (asked for here, used by the epilogue: one round trip less at the end)
+    if (IDS_EARLY && EPI != EPI_LOGITS && !(EPI == EPI_RESID && a.S > 1)) {
+      // (asked for here, used by the epilogue: one round trip less at the end, where registers are left)
 #pragma unroll
       for (int m = 0; m < NA; ++m) ids[m] = a.e.rows[min((rt0 + m) * 32 + (lane & 31), row_end - 1)];
     }
@@ -258,9 +272,8 @@ __device__ __forceinline__ void rows_body(const GemmArgs& a, uint4* lds, RowsWei
     // (sum = first part + second part).
     constexpr int NH = (NA + 1) / 2;
     __syncthreads();
-    static_assert(FB == 2, "the other part of a wave's block is two waves on");
     float* mine = (float*)lds + (size_t)(w & 3) * (NH * 16 * 64) + lane;
-    const float* theirs = (const float*)lds + (size_t)((w & 3) ^ FB) * (NH * 16 * 64) + lane;
+    const float* theirs = (const float*)lds + (size_t)((w & 3) ^ 2) * (NH * 16 * 64) + lane;
     if (w < 4) {
 #pragma unroll
       for (int m = 0; m < NA; ++m)
@@ -280,6 +293,10 @@ __device__ __forceinline__ void rows_body(const GemmArgs& a, uint4* lds, RowsWei
     }
   }
   if (!wave_on) return;
+  if (!IDS_EARLY && EPI != EPI_LOGITS && !(EPI == EPI_RESID && a.S > 1)) {
+#pragma unroll
+    for (int m = 0; m < NA; ++m) ids[m] = a.e.rows[min((rt0 + m) * 32 + (lane & 31), row_end - 1)];
+  }
 #pragma unroll
   for (int m = 0; m < NA; ++m) {
     if (KP == 2 && (m >= (NA + 1) / 2) != (part == 1)) continue;
@@ -301,69 +318,106 @@ __device__ __forceinline__ void rows_body(const GemmArgs& a, uint4* lds, RowsWei
   }
 }
 
-template <int FB, int EPI, bool F16, bool W8>
-__global__ __launch_bounds__(rows_threads(FB)) void gemm_rows_kernel(GemmArgs a) {
+// How a row count (in tiles of 32, at most 32 of them) is cut: feature blocks per workgroup and row
+// blocks, 4 bits each in GemmArgs::cut, worked out by the host (rows_cut).
+struct RowsCut { int fb, blocks; };
+__host__ __device__ inline RowsCut rows_cut_of(uint64_t cut0, uint64_t cut1, int n_rt) {
+  const int i = (n_rt - 1) & 31;
+  const int code = (int)((i < 16 ? cut0 : cut1) >> (4 * (i & 15))) & 15;
+  return {ROWS_FB_MIN + (code >> 1), code & 1 ? (n_rt + 7) >> 3 : (n_rt + 5) / 6};
+}
+__host__ __device__ inline int rows_tiles(int NB, int fb) {  // (divisions by constants)
+  return fb == 2 ? (NB + 1) / 2 : fb == 3 ? (NB + 2) / 3 : fb == 4 ? (NB + 3) / 4 : fb == 5 ? (NB + 4) / 5 : (NB + 5) / 6;
+}
+
+template <int FORM, int EPI, bool F16, bool W8>
+__global__ __launch_bounds__(rows_threads(FORM)) void gemm_rows_kernel(GemmArgs a) {
   extern __shared__ uint4 lds[];  // [ROWS_RING][part][k-tile][row tile][64]
   // Workgroup id -> (row block, weight tile, split); id % 8 is the XCD, and the row blocks of one
   // weight tile sit next to each other on it, so that they fetch it from HBM once.  The blocks are
   // those that the row count gives, not those that the grid has room for: its surplus workgroups
   // come last.  (With the blocks of an unknown count one behind the other the weights came from HBM
   // once per block: 211 rows of 7B, 1037 us per four layers, then 935; 408 rows 1640 and 1422.)
-  // Where the count is in device memory the first weights are asked for as if there were one block,
-  // which is the rule, and once more if there are others.  (A loop, so that both go to the same
-  // registers: written one behind the other they are merged by copies, and a copy of a register
-  // waits for the load that fills it.)
-  constexpr int NC = rows_consumers(FB), KP = NC / FB;
+  // Where the count is in device memory the first weights are asked for as if there were one block
+  // and the feature blocks per workgroup of few rows, which is the rule, and once more if it is not so.
+  // (A loop, so that both go to the same registers: written one behind the other they are merged by
+  // copies, and a copy of a register waits for the load that fills it.)
+  uint64_t cut0 = a.cut[0], cut1 = a.cut[1];
+  asm volatile("" : "+s"(cut0), "+s"(cut1));  // (read here; else the one that is needed is read when the count is known)
+  asm volatile("" ::"s"(a.xp), "s"(a.e.rows), "s"(a.waves));
   RowsWeights<W8> W;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  int n_rows = a.n_rows_val, n_rt = 0, n_blk = 1, mb = 0, tile, s;
+  constexpr int FB = FORM == ROWS_PAIRS ? 2 : EPI == EPI_RESID || EPI == EPI_LOGITS ? 4 : 0;  // (one for all counts)
+  int n_rows = a.n_rows_val, n_rt = 0, n_blk = 1, mb = 0, fb = FB ? FB : a.fb_first, tile, s;
 #pragma unroll 1
   for (;;) {
     int p = blockIdx.x;
     if (n_rows >= 0) {
       // row tiles are dealt in equal shares to as few blocks of at most 6, or of at most 8, as hold them
       n_rt = (n_rows + 31) >> 5;
-      n_blk = (a.blk8 >> ((n_rt - 1) & 31)) & 1 ? (n_rt + 7) >> 3 : (n_rt + 5) / 6;
-      if (n_blk == 0 || n_rows >= a.rows_hi) return;  // (rows_hi and more: the many-rows kernel's share)
+      if (n_rt == 0 || n_rows >= a.rows_hi) return;  // (rows_hi and more: the many-rows kernel's share)
+      const RowsCut cut = rows_cut_of(cut0, cut1, n_rt);
+      const bool asked = a.n_rows_val < 0 && cut.blocks == 1 && (FB || cut.fb == fb);
+      n_blk = cut.blocks;
+      if (!FB) fb = cut.fb;
       if (n_blk > 1) {
         const int y = blockIdx.x >> 3;
         mb = y % n_blk;
         p = (y / n_blk) * 8 + (blockIdx.x & 7);
-      } else if (a.n_rows_val < 0) {
-        if (p >= a.P) return;
-        break;  // (the weights asked for are the right ones)
       }
-      if (p >= a.P) return;
+      if (p >= rows_tiles(a.NB, fb) * a.S) return;
+      if (asked) break;  // (the weights asked for are the right ones)
     }
     tile = __builtin_amdgcn_readfirstlane(p / a.S);
     s = __builtin_amdgcn_readfirstlane(p - tile * a.S);
-    if (p < a.P && w < NC) {
-      const RowsRange rg = rows_range(a.KS, a.S * KP, s * KP + w / FB);
-      const int nb = min(tile * FB + w % FB, a.NB - 1), kc = W8 ? 2 * a.KS : 4 * a.KS, k0 = W8 ? rg.k0 / 2 : rg.k0;
+    const int KP = fb == 2 ? 2 : 1;
+    if (w < fb * KP && tile * fb < a.NB) {
+      const RowsRange rg = rows_range(a.KS, a.S * KP, s * KP + (fb == 2 ? w >> 1 : 0));
+      const int nb = min(tile * fb + (fb == 2 ? w & 1 : w), a.NB - 1), kc = W8 ? 2 * a.KS : 4 * a.KS, k0 = W8 ? rg.k0 / 2 : rg.k0;
       const uint4* src = a.wp + (size_t)nb * kc * 64 + (threadIdx.x & 63);
       // (past the end of K the last tile is read again and not used)
 #pragma unroll
       for (int i = 0; i < RowsWeights<W8>::EARLY; ++i) W.t[i] = ld_stream(src + (size_t)min(k0 + i, kc - 1) * 64);
     }
     if (n_rows >= 0) break;
-    n_rows = __builtin_amdgcn_readfirstlane(*a.n_rows);
+    // (a scalar load, written by the kernels before this one: a vector load would wait for the weights)
+    n_rows = *(const __attribute__((address_space(4))) int*)a.n_rows;
   }
+  if (!FB) fb = __builtin_amdgcn_readfirstlane(fb);
+  if (FORM != ROWS_PAIRS && w >= (fb == 2 ? 4 : fb) && w < a.waves - 2) return;  // no feature block for this wave
   tile = __builtin_amdgcn_readfirstlane(tile);
   s = __builtin_amdgcn_readfirstlane(s);
   const int rt0 = __builtin_amdgcn_readfirstlane(mb * n_rt / n_blk);
   const int rt1 = __builtin_amdgcn_readfirstlane((mb + 1) * n_rt / n_blk), row_end = min(n_rows, 32 * rt1);
-  switch (rt1 - rt0) {
-#define VLAC_NA(N) rows_body<N, FB, EPI, F16, W8>(a, lds, W, tile, s, rt0, row_end); break;
-    case 1: VLAC_NA(1)
-    case 2: VLAC_NA(2)
-    case 3: VLAC_NA(3)
-    case 4: VLAC_NA(4)
-    case 5: VLAC_NA(5)
-    case 6: VLAC_NA(6)
-    case 7: VLAC_NA(7)
-    default: VLAC_NA(8)
-#undef VLAC_NA
+#define VLAC_NA(N, KP) rows_body<N, KP, FORM, EPI, F16, W8>(a, lds, W, fb, tile, s, rt0, row_end)
+  if (FORM == ROWS_PAIRS || (FORM == ROWS_MIXED && fb == 2)) {
+    switch (rt1 - rt0) {
+      case 1: VLAC_NA(1, 2); break;
+      case 2: VLAC_NA(2, 2); break;
+      case 3: VLAC_NA(3, 2); break;
+      case 4: VLAC_NA(4, 2); break;
+      case 5: VLAC_NA(5, 2); break;
+      case 6: VLAC_NA(6, 2); break;
+      case 7:
+        if constexpr (FORM == ROWS_PAIRS) VLAC_NA(7, 2);
+        break;
+      default:
+        static_assert(ROWS_PAIR_NA == 6, "the cases above");
+        if constexpr (FORM == ROWS_PAIRS) VLAC_NA(8, 2);
+    }
+  } else if constexpr (FORM != ROWS_PAIRS) {
+    switch (rt1 - rt0) {
+      case 1: VLAC_NA(1, 1); break;
+      case 2: VLAC_NA(2, 1); break;
+      case 3: VLAC_NA(3, 1); break;
+      case 4: VLAC_NA(4, 1); break;
+      case 5: VLAC_NA(5, 1); break;
+      case 6: VLAC_NA(6, 1); break;
+      case 7: VLAC_NA(7, 1); break;
+      default: VLAC_NA(8, 1);
+    }
   }
+#undef VLAC_NA
 }
 
 // ---------------------------------------------------------------------------
@@ -392,6 +446,7 @@ __global__ __launch_bounds__(256, XMODE == X_NORM8 ? 2 : 3) void gemm_few_kernel
   extern __shared__ uint4 xlds[];  // operand slices [k/8 - lo8][row]
   constexpr int U = 8;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  read_epilogue_args<EPI>(a);
   const int nb = blockIdx.x / a.S, s = blockIdx.x - nb * a.S;
   const int n_rows = min(a.n_rows_val >= 0 ? a.n_rows_val : *a.n_rows, 32);
   if (n_rows <= 0) return;
@@ -611,47 +666,41 @@ __global__ __launch_bounds__(256, XMODE == X_NORM8 ? 2 : 3) void gemm_few_kernel
 
 static const int kRowsLds = ROWS_RING * 32 * 1024;
 
-template <int FB, int EPI>
+template <int FORM, int EPI>
 static hipError_t set_attr() {
-  hipError_t e = hipFuncSetAttribute((const void*)gemm_rows_kernel<FB, EPI, false, false>,
+  hipError_t e = hipFuncSetAttribute((const void*)gemm_rows_kernel<FORM, EPI, false, false>,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, kRowsLds);
   if (e != hipSuccess) return e;
-  e = hipFuncSetAttribute((const void*)gemm_rows_kernel<FB, EPI, true, false>,
+  e = hipFuncSetAttribute((const void*)gemm_rows_kernel<FORM, EPI, true, false>,
                           hipFuncAttributeMaxDynamicSharedMemorySize, kRowsLds);
   if (e != hipSuccess) return e;
-  return hipFuncSetAttribute((const void*)gemm_rows_kernel<FB, EPI, true, true>,
+  return hipFuncSetAttribute((const void*)gemm_rows_kernel<FORM, EPI, true, true>,
                              hipFuncAttributeMaxDynamicSharedMemorySize, kRowsLds);
 }
 
 int gemm_init() {
   hipError_t e;
-#define VLAC_SET(FB)                                                    \
-  if ((e = set_attr<FB, EPI_QKV>()) != hipSuccess) return (int)e;       \
-  if ((e = set_attr<FB, EPI_SWIGLU>()) != hipSuccess) return (int)e;
-  VLAC_SET(4) VLAC_SET(3) VLAC_SET(2)
-  if ((e = set_attr<4, EPI_RESID>()) != hipSuccess) return (int)e;
-  if ((e = set_attr<2, EPI_RESID>()) != hipSuccess) return (int)e;
-  if ((e = set_attr<4, EPI_LOGITS>()) != hipSuccess) return (int)e;
+#define VLAC_SET(FORM)                                                    \
+  if ((e = set_attr<FORM, EPI_QKV>()) != hipSuccess) return (int)e;       \
+  if ((e = set_attr<FORM, EPI_SWIGLU>()) != hipSuccess) return (int)e;
+  VLAC_SET(ROWS_PAIRS) VLAC_SET(ROWS_SINGLE) VLAC_SET(ROWS_MIXED)
+  if ((e = set_attr<ROWS_PAIRS, EPI_RESID>()) != hipSuccess) return (int)e;
+  if ((e = set_attr<ROWS_SINGLE, EPI_RESID>()) != hipSuccess) return (int)e;
+  if ((e = set_attr<ROWS_SINGLE, EPI_LOGITS>()) != hipSuccess) return (int)e;
 #undef VLAC_SET
   return gemm_tall_init();
 }
 
-template <int FB, bool F16, bool W8>
+template <int FORM, bool F16, bool W8>
 static void launch_rows(int epi, const GemmArgs& a, int grid, hipStream_t st) {
-  const dim3 g(grid), t(rows_threads(FB));
+  constexpr int ONE = FORM == ROWS_PAIRS ? ROWS_PAIRS : ROWS_SINGLE;  // (projections with a residual: one fb for all)
+  const dim3 g(grid), t(64 * a.waves);
   switch (epi) {
-    case EPI_QKV:
-      hipLaunchKernelGGL((gemm_rows_kernel<FB, EPI_QKV, F16, W8>), g, t, kRowsLds, st, a);
-      break;
-    case EPI_RESID:  // (4 or 2 feature blocks)
-      hipLaunchKernelGGL((gemm_rows_kernel<FB == 4 ? 4 : 2, EPI_RESID, F16, W8>), g, t, kRowsLds, st, a);
-      break;
-    case EPI_SWIGLU:
-      hipLaunchKernelGGL((gemm_rows_kernel<FB, EPI_SWIGLU, F16, W8>), g, t, kRowsLds, st, a);
-      break;
-    default:  // (always 4)
-      hipLaunchKernelGGL((gemm_rows_kernel<4, EPI_LOGITS, F16, W8>), g, t, kRowsLds, st, a);
-      break;
+    case EPI_QKV: hipLaunchKernelGGL((gemm_rows_kernel<FORM, EPI_QKV, F16, W8>), g, t, kRowsLds, st, a); break;
+    case EPI_RESID: hipLaunchKernelGGL((gemm_rows_kernel<ONE, EPI_RESID, F16, W8>), g, t, kRowsLds, st, a); break;
+    case EPI_SWIGLU: hipLaunchKernelGGL((gemm_rows_kernel<FORM, EPI_SWIGLU, F16, W8>), g, t, kRowsLds, st, a); break;
+    default:  // (always 4 feature blocks)
+      hipLaunchKernelGGL((gemm_rows_kernel<ROWS_SINGLE, EPI_LOGITS, F16, W8>), g, t, kRowsLds, st, a); break;
   }
 }
 
@@ -681,23 +730,17 @@ bool gemm_can_fuse_norm(int n_rows_host, int decode_pos, int kpad) {
          (size_t)(kpad / 8) * n_rows_host * 16 <= kStageBytes;
 }
 
-// From this many rows on (the capacity of the launch: streams x tokens; the actual row count
-// is known on the device only) the GEMMs go to the kernel built for matrix-core bound
-// work.  By ACTUAL row count the one-stream kernel wins up to about 260 rows where two of
-// them share a launch (below) and up to 352 where it is alone (kTallKnownRows); a capacity of
-// 512 rows (two 7B streams, one stream with two camera views) mostly means more.  (Weights stored as e4m3 codes: the many-rows kernel has
+// From this many rows on (the capacity of the launch: streams x tokens; the actual row count of a
+// sparse prefill is known on the device only) the GEMMs go to the kernel built for matrix-core bound
+// work.  Full recomputes, four layers and the head, many-rows against one-stream kernel: 7B, 352 rows
+// 1069 and 941 us, 448 rows 1211 and 1154, 500 rows 1376 and 1323; grouped queries, 380 rows 589
+// and 472, 500 rows 636 and 578.  (Weights stored as e4m3 codes: the many-rows kernel has
 // no variant for them; up to 1023 rows stay with the one-stream kernel, from 1024 rows on
 // the matrix is expanded to fp16 before every launch, 3 bytes of traffic per weight
 // against the 2 rows flops per weight that such a launch spends on it.)
 static const int kTallRows = 512;
-// (A launch whose row count is known on the host, a full recompute, goes by that count.  One-stream
-// against many-rows kernel, four layers and the head, 7B: 256 rows 866 and 1037 us, 288 rows 969
-// and 987, 352 rows 1132 and 1145, 384 rows 1116 and 1103 (another card); grouped queries: 288 rows 445
-// and 544, 352 rows 523 and 595.)
-static const int kTallKnownRows = 353;
-static bool use_tall(const vlac_ctx* c, int rows_cap, int n_rows_host = -1) {
-  if (c->w8) return rows_cap >= 1024 && c->wdeq;
-  return rows_cap >= kTallRows || (n_rows_host >= kTallKnownRows && rows_cap > 32);
+static bool use_tall(const vlac_ctx* c, int rows_cap) {
+  return c->w8 ? rows_cap >= 1024 && c->wdeq : rows_cap >= kTallRows;
 }
 
 // Most splits the many-rows GEMM with a residual epilogue may use (they need S partial rows
@@ -708,26 +751,12 @@ static int tall_resid_smax(const vlac_ctx* c, int epi, int rows_cap, int d_model
   return fit >= 8 ? 8 : fit >= 3 ? (int)fit : 1;
 }
 
-// Feature blocks per workgroup of the one-stream kernel (2 leave K to two pairs of waves).  What
-// a CU fetches is the limit (about 50 GB/s each with weights from HBM and row operands from L2 in
-// one queue), so taken is the width with the least rounds of 256 workgroups x bytes per workgroup:
-// its weight rows and, for up to 4 row tiles, all operand rows.  7B, 109 rows: gate/up (688 blocks)
-// 41.7 us with 3 against 46.8 with 4; QKV (384 blocks) 34 us with 2, K in two parts.
-// (The projections with a residual have split K besides: 4 blocks and 8 splits where K is long,
-// which fetches a third less per workgroup but doubles the partial rows; 2 blocks and half the
-// splits where it is not.)
-static int rows_kernel_fb(int epi, int n_blocks, int KS) {
-  if (epi == EPI_LOGITS) return 4;
-  if (epi == EPI_RESID) return KS >= 128 && n_blocks >= 128 ? 4 : 2;
-  int best = 4, least = 0x7fffffff;
-  for (int fb = 4; fb >= 2; --fb) {
-    const int cost = ((n_blocks + fb - 1) / fb + 255) / 256 * (32 * fb + 128);
-    if (cost < least) { least = cost; best = fb; }
-  }
-  return best;
-}
+// Feature blocks per workgroup of the projections with a residual, which split K besides (2 leave K
+// to two pairs of waves): 4 blocks and 8 splits where K is long, which fetches a third less per
+// workgroup but doubles the partial rows; 2 blocks and half the splits where it is not.
+static int rows_resid_fb(int n_blocks, int KS) { return KS >= 128 && n_blocks >= 128 ? 4 : 2; }
 
-// Row blocks of the one-stream kernel at most (see rows_blocks_of_8)
+// Row blocks of the one-stream kernel at most (see rows_cut)
 static int rows_blocks_max(int rows) { return ((rows + 31) / 32 + 5) / 6; }
 
 // Split factor of the one-stream kernel: the projections with a residual, whose partial rows the
@@ -741,7 +770,7 @@ static int rows_blocks_max(int rows) { return ((rows + 31) / 32 + 5) / 6; }
 static int rows_kernel_splits(const vlac_ctx* c, int epi, int n_blocks, int KS, int rpart_rows, int d_model, int rows_cap,
                               bool known) {
   if (epi != EPI_RESID) return 1;
-  const int fb = rows_kernel_fb(epi, n_blocks, KS), tiles = (n_blocks + fb - 1) / fb, most = rows_blocks_max(rows_cap);
+  const int tiles = rows_tiles(n_blocks, rows_resid_fb(n_blocks, KS)), most = rows_blocks_max(rows_cap);
   int best = 1, least = 0x7fffffff;
   for (int S = 1; S <= 8 && S <= std::max(KS / 4, 1) && (size_t)S * rpart_rows * d_model <= c->rpart_floats; ++S) {
     int cost = 0;
@@ -751,27 +780,25 @@ static int rows_kernel_splits(const vlac_ctx* c, int epi, int n_blocks, int KS, 
   return best;
 }
 
-// Where the many-rows kernel serves a capacity at which a sparse prefill usually leaves
-// fewer than kSmallRows rows (the count is known on the device only), BOTH kernels are
-// launched for a GEMM and each leaves at once if the count is the other's.  Measured with
-// two streams of 288 tokens, four layers and the head, one-stream against many-rows kernel, the
-// idle launches included: 7B, about 142 rows 742 and 964 us, 218 rows 879 and 1036, 269 rows 1119 and
-// 1102, 320 rows 1180 and 1154 (grouped queries 429 and 575 at 218 rows, 544 and 589 at 320); and
-// 3 us per GEMM more for the idle launch where the many-rows kernel works; at 70 % static about 0.38 of the capacity is recomputed,
-// so from a capacity of 768 rows on the second launch would mostly be the idle one; and
-// where the reuse lists are too short to leave fewer than kSmallRows rows (top-k 100 of two
-// camera views), only the many-rows kernel is launched.
-static const int kSmallRows = 257;
+// Where the many-rows kernel serves a capacity at which a sparse prefill usually leaves few rows
+// (the count is known on the device only), BOTH kernels are launched for a GEMM: up to
+// kSmallRows - 1 rows the one-stream kernel works, from there on the other, and the idle one leaves at
+// once, which costs 3 us per GEMM.  So both are launched only where the reuse lists are long enough to
+// leave fewer than kFewRows rows (top-k 100 of two camera views is not), and up to a capacity
+// of 767 rows: at 70 % static about 0.38 of it is recomputed, more than that and the second launch would
+// mostly be the idle one.  Two streams of 288 tokens, four layers and the head, one-stream against
+// many-rows kernel: 7B, about 142 rows 742 and 964 us, 218 rows 879 and 1036; for more see kTallRows.
+static const int kSmallRows = 449, kFewRows = 257;
 // (Rows longer than 8192 elements: the row kernel that adds the partial rows up there takes a
 // fixed split factor, so the choice between two kernels with different factors is not offered.)
 static bool use_both(const vlac_ctx* c, int rows_cap, int n_rows_host) {
-  return use_tall(c, rows_cap, n_rows_host) && !c->w8 && n_rows_host < 0 && rows_cap < 768 && c->rows_floor < kSmallRows &&
+  return use_tall(c, rows_cap) && !c->w8 && n_rows_host < 0 && rows_cap < 768 && c->rows_floor < kFewRows &&
          c->cfg.d_model <= 8192;
 }
 
 SplitAdapt gemm_resid_adapt(vlac_ctx* c, int n_blocks, int kpad, int rows_cap, const int* n_rows, int n_rows_host) {
   SplitAdapt ad = {nullptr, -1, 0, 0, 0, 0, 0};
-  if (!use_tall(c, rows_cap, n_rows_host)) return ad;
+  if (!use_tall(c, rows_cap)) return ad;
   const int d_model = n_blocks * 32;
   const bool both = use_both(c, rows_cap, n_rows_host);
   ad.S_tall = tall_resid_smax(c, EPI_RESID, rows_cap, d_model);
@@ -788,40 +815,64 @@ SplitAdapt gemm_resid_adapt(vlac_ctx* c, int n_blocks, int kpad, int rows_cap, c
   return ad;
 }
 
-// Row blocks of the one-stream kernel: bit n - 1 says that n row tiles (at most 32: 1023 rows) are cut
-// into blocks of up to 8 of them instead of 6, which saves a pass over the weights where it saves a
-// block (7, 8, 13 to 16, ... tiles).  A workgroup takes a CU's whole LDS, so what counts is rounds of
-// 256 workgroups x what a workgroup fetches per k (fb weight rows, a block's operand rows): blocks
-// of 6 where the launch is too small to fill the chip with fewer blocks, or where they leave the last
-// round fuller.  Four layers, blocks of at most 6, then this: 7B, 211 rows 935 and 799 us, 256 rows
-// 954 and 860; grouped queries, 256 rows 457 and 423; taken everywhere, 8 cost 240 instead of 207 us at 211 rows of
-// the tiny shape (22 workgroups) and 742 instead of 671 at 600 rows of grouped queries with 8-bit weights.
-static uint32_t rows_blocks_of_8(int P, int fb, int rows_cap) {
-  uint32_t mask = 0;
-  for (int rt = 1; rt <= 32 && rt <= (rows_cap + 31) / 32; ++rt) {
-    auto cost = [&](int n) { return (P * n + 255) / 256 * (fb + (rt + n - 1) / n); };
-    if (cost((rt + 7) / 8) < cost((rt + 5) / 6)) mask |= 1u << (rt - 1);
+// With fewer workgroups than this even two feature blocks each leave the chip half empty: then 2 it is, whatever the
+// row count (grouped queries, QKV of 64 blocks, 211 and 288 rows: 3 and 4 blocks 14 and 19 us per four layers slower)
+static const int kRowsPairTiles = 128;
+
+// How the one-stream kernel cuts `rt` row tiles (at most 32: 1023 rows) and NB feature blocks: blocks of
+// at most 6 or 8 row tiles, 2 to 6 feature blocks per workgroup (the projections with a residual: as
+// given, with their S splits).  A workgroup takes a CU's whole LDS, so what counts is rounds of 256
+// workgroups x what a workgroup fetches per k (its weight rows, a block's operand rows; a CU fetches
+// about 50 GB/s with weights from HBM and row operands from L2 in one queue).
+// (2 feature blocks take K in two parts and half as many k-tiles per barrier: 7 row tiles of 7B QKV
+// are faster with 3 in two blocks, 6 with 2)
+static RowsCut rows_cut(int epi, int NB, int KS, int S, int rt, bool pairs_only, int* code) {
+  RowsCut best = {0, 0};
+  int least = 0x7fffffff;
+  const int fix = epi == EPI_LOGITS ? 4 : epi == EPI_RESID ? rows_resid_fb(NB, KS) : pairs_only ? 2 : 0;
+  for (int fb = ROWS_FB_MIN; fb <= ROWS_FB_MAX; ++fb) {
+    if (fix && fb != fix) continue;
+    for (int eight = 0; eight < 2; ++eight) {
+      const int n = eight ? (rt + 7) / 8 : (rt + 5) / 6, na = (rt + n - 1) / n;
+      if (!fix && fb == 2 && na > ROWS_PAIR_NA) continue;
+      const int cost = (rows_tiles(NB, fb) * S * n + 255) / 256 * (fb + na) + n - 1;
+      if (cost < least) {
+        least = cost;
+        best = {fb, n};
+        *code = (fb - ROWS_FB_MIN) << 1 | eight;
+      }
+    }
   }
-  return mask;
+  return best;
 }
 
 // the one-stream kernel for up to rows_cap rows; sets and returns a.S
 static int launch_rows_kernel(vlac_ctx* c, int epi, GemmArgs& a, int rows_cap, const GemmEpi& e, hipStream_t st) {
-  const int fb = rows_kernel_fb(epi, a.NB, a.KS), tiles = (a.NB + fb - 1) / fb;
-  a.MB = rows_blocks_max(rows_cap);
   a.S = rows_kernel_splits(c, epi, a.NB, a.KS, e.rpart_rows, e.d_model, rows_cap, a.n_rows_val >= 0);
-  a.P = tiles * a.S;
-  a.blk8 = rows_blocks_of_8(a.P, fb, rows_cap);
-  const int grid = ((a.P + 7) / 8) * 8 * a.MB;
-#define VLAC_ROWS(FB_)                                          \
-  {                                                             \
-    if (c->w8) launch_rows<FB_, true, true>(epi, a, grid, st);  \
-    else if (c->f16) launch_rows<FB_, true, false>(epi, a, grid, st); \
-    else launch_rows<FB_, false, false>(epi, a, grid, st);      \
+  // (few feature blocks: a workgroup each, whatever the row count, and the two parts of K halve the chain)
+  const bool pairs_only = rows_tiles(a.NB, 2) < kRowsPairTiles;
+  const int rt_cap = std::min((rows_cap + 31) / 32, 32), rt_known = a.n_rows_val >= 0 ? (a.n_rows_val + 31) / 32 : 0;
+  a.cut[0] = a.cut[1] = 0;
+  int grid = 0, fb_most = 0, fb_least = ROWS_FB_MAX;
+  for (int rt = rt_known ? rt_known : 1; rt <= (rt_known ? rt_known : rt_cap); ++rt) {
+    int code = 0;
+    const RowsCut cut = rows_cut(epi, a.NB, a.KS, a.S, rt, pairs_only, &code);
+    a.cut[(rt - 1) >> 4] |= (uint64_t)code << (4 * ((rt - 1) & 15));
+    if (rt <= 4) a.fb_first = cut.fb;  // (what few rows usually get)
+    fb_most = std::max(fb_most, cut.fb);
+    fb_least = std::min(fb_least, cut.fb);
+    grid = std::max(grid, (rows_tiles(a.NB, cut.fb) * a.S + 7) / 8 * 8 * cut.blocks);
   }
-  if (fb == 4) VLAC_ROWS(4)
-  else if (fb == 3) VLAC_ROWS(3)
-  else VLAC_ROWS(2)
+  a.waves = 2 + (fb_least == 2 ? std::max(fb_most, 4) : fb_most);
+#define VLAC_ROWS(FORM_)                                                                  \
+  {                                                                                       \
+    if (c->w8) launch_rows<FORM_, true, true>(epi, a, grid, st);                   \
+    else if (c->f16) launch_rows<FORM_, true, false>(epi, a, grid, st);            \
+    else launch_rows<FORM_, false, false>(epi, a, grid, st);                       \
+  }
+  if (fb_most == 2) VLAC_ROWS(ROWS_PAIRS)
+  else if (fb_least > 2) VLAC_ROWS(ROWS_SINGLE)
+  else VLAC_ROWS(ROWS_MIXED)
 #undef VLAC_ROWS
   return a.S;
 }
@@ -858,27 +909,26 @@ int launch_gemm(vlac_ctx* c, int epi, const bf16_t* wp, const float* wscale, int
     if (S > 8) S = 8;
     if (S < 1 || n_blocks > c->n_counters || (size_t)n_blocks * 8 * 1024 > c->partial_floats) S = 1;
     a.S = S;
-    a.MB = 1;
-    a.P = n_blocks * S;
+    const int grid = n_blocks * S;
     if (norm) {  // only offered when gemm_can_fuse_norm() holds
       // LDS for the normalised rows: this workgroup's share of K, [k/8][row] 16-byte slices
       const int per = ((KC + S - 1) / S + (c->w8 ? 1 : 0)) & ~(c->w8 ? 1 : 0);  // as in the kernel
       const size_t shm = (size_t)(2 * per) * n_rows_host * 16;
       if (norm->d <= 4096) {
-        if (c->w8) launch_few<true, X_NORM4, true>(epi, a, a.P, shm, st);
-        else if (c->f16) launch_few<true, X_NORM4, false>(epi, a, a.P, shm, st);
-        else launch_few<false, X_NORM4, false>(epi, a, a.P, shm, st);
+        if (c->w8) launch_few<true, X_NORM4, true>(epi, a, grid, shm, st);
+        else if (c->f16) launch_few<true, X_NORM4, false>(epi, a, grid, shm, st);
+        else launch_few<false, X_NORM4, false>(epi, a, grid, shm, st);
       } else {
-        if (c->w8) launch_few<true, X_NORM8, true>(epi, a, a.P, shm, st);
-        else if (c->f16) launch_few<true, X_NORM8, false>(epi, a, a.P, shm, st);
-        else launch_few<false, X_NORM8, false>(epi, a, a.P, shm, st);
+        if (c->w8) launch_few<true, X_NORM8, true>(epi, a, grid, shm, st);
+        else if (c->f16) launch_few<true, X_NORM8, false>(epi, a, grid, shm, st);
+        else launch_few<false, X_NORM8, false>(epi, a, grid, shm, st);
       }
     } else {
-      if (c->w8) launch_few<true, X_GLOBAL, true>(epi, a, a.P, 0, st);
-      else if (c->f16) launch_few<true, X_GLOBAL, false>(epi, a, a.P, 0, st);
-      else launch_few<false, X_GLOBAL, false>(epi, a, a.P, 0, st);
+      if (c->w8) launch_few<true, X_GLOBAL, true>(epi, a, grid, 0, st);
+      else if (c->f16) launch_few<true, X_GLOBAL, false>(epi, a, grid, 0, st);
+      else launch_few<false, X_GLOBAL, false>(epi, a, grid, 0, st);
     }
-  } else if (use_tall(c, rows_cap, n_rows_host)) {
+  } else if (use_tall(c, rows_cap)) {
     int S_small = 0;
     if (use_both(c, rows_cap, n_rows_host)) {
       GemmArgs r = a;

@@ -1,25 +1,32 @@
 // Shared by the GEMM kernels: launch arguments and the fused epilogues.
 #pragma once
+#include <stddef.h>
+
 #include "common.h"
 
 struct GemmArgs {
+  // what a workgroup needs before it can ask for anything, in one line of the argument buffer
   const uint4* wp;    // weights, fragment order, 64 uint4 per tile (e4m3 codes: per two tiles)
-  const float* wscale;  // e4m3 weights: scale per output feature (packed row order), else null
   const uint4* xp;    // activations, fragment order
-  const uint4* zero_tile;  // 1 KiB of zeros
-  NormIn norm;        // fused RMSNorm of the input rows (few-rows kernel only)
+  const int* n_rows;  // device: rows in use
+  uint64_t cut[2];    // one-stream GEMM: how n row tiles (n <= 32) are cut, 4 bits at n - 1 (rows_cut_of)
+  int n_rows_val;     // >= 0: the row count is known on the host, n_rows is not read
   int NB;             // weight row blocks (32 output features each)
   int KS;             // K steps (64 k = 4 tiles each)
-  const int* n_rows;  // device: rows in use
-  int n_rows_val;     // >= 0: the row count is known on the host, n_rows is not read
-  int rows_lo, rows_hi;  // the launch has work only if rows_lo <= row count < rows_hi (two kernels share a GEMM)
-  int S, MB, P;       // split-K factor, row blocks, weight tiles * S
-  uint32_t blk8;      // one-stream GEMM: bit n - 1 = n row tiles (<= 32) are cut into blocks of up to 8 (else 6)
+  int S;              // split-K factor
+  int rows_hi;        // the launch has work only if rows_lo <= row count < rows_hi (two kernels share a GEMM)
+  int fb_first;       // one-stream GEMM: the feature blocks per workgroup that it assumes until the row count is known
+  int waves;          // one-stream GEMM: waves of a workgroup
+  int rows_lo;
   int x_tiles;        // many-rows GEMM: 32-row tiles the activation buffer holds (copies are clamped to it)
+  const float* wscale;  // e4m3 weights: scale per output feature (packed row order), else null
+  const uint4* zero_tile;  // 1 KiB of zeros
   float* partial;
   int* counters;
-  GemmEpi e;
+  GemmEpi e;          // (what EPI_QKV reads starts a line)
+  NormIn norm;        // fused RMSNorm of the input rows (few-rows kernel only)
 };
+static_assert(offsetof(GemmArgs, waves) == 64 && offsetof(GemmArgs, e) + offsetof(GemmEpi, rope_cos) == 128, "lines of 64 bytes");
 
 // e4m3 weights: a lane's 8 codes of one k-tile (two dwords) -> its 8 fp16 operand values.
 // The hardware conversion decodes OCP e4m3 (verified code by code); every e4m3 value is an
@@ -46,6 +53,21 @@ __device__ inline void scale_tile(const float* wscale, int nb, int g, f32x16& ac
     const float4 s = *(const float4*)(wscale + nb * 32 + 8 * q4 + 4 * g);
     acc[4 * q4] *= s.x; acc[4 * q4 + 1] *= s.y; acc[4 * q4 + 2] *= s.z; acc[4 * q4 + 3] *= s.w;
   }
+}
+
+// Reads the arguments that the epilogue needs together with the first ones: the argument buffer lies in
+// host memory, and every read that waits for something else first is a round trip there of its own.
+template <int EPI>
+__device__ __forceinline__ void read_epilogue_args(const GemmArgs& a) {
+  if constexpr (EPI == EPI_QKV)
+    asm volatile("" ::"s"(a.e.rows), "s"(a.e.rope_cos), "s"(a.e.rope_sin), "s"(a.e.qbuf), "s"(a.e.kv), "s"(a.e.kv_stream_stride),
+                 "s"(a.e.kv_layer_off), "s"(a.e.n_q_heads), "s"(a.e.max_seq));
+  else if constexpr (EPI == EPI_RESID)
+    asm volatile("" ::"s"(a.e.rows), "s"(a.e.d_model), "s"(a.e.rpart), "s"(a.e.rpart_rows));
+  else if constexpr (EPI == EPI_SWIGLU)
+    asm volatile("" ::"s"(a.e.rows), "s"(a.e.xf), "s"(a.e.kc_f));
+  else
+    asm volatile("" ::"s"(a.e.logits), "s"(a.e.logits_stride));
 }
 
 __device__ inline float silu_f(float x) { return x / (1.f + __expf(-x)); }

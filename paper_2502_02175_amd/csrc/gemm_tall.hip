@@ -408,8 +408,6 @@ int gemm_tall_init() {
 
 void launch_gemm_tall(bool f16, int epi, GemmArgs& a, int rows_cap, int S_max, hipStream_t st) {
   a.S = (epi == EPI_RESID && S_max > 1) ? S_max : 1;
-  a.MB = (rows_cap + 127) / 128;
-  a.P = 0;
   a.x_tiles = (rows_cap + 31) / 32;
   // the grid covers the most work items any row count up to rows_cap can give (the plan
   // changes its row blocks and K parts with the row count)
