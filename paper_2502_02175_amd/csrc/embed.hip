@@ -12,6 +12,8 @@
 // it did with fp32 multiply-adds, and nothing is larger on the way than at the end: finite
 // results stay finite.  The patches to do are compacted into a list first, so that the work is
 // proportional to their number.
+#include <type_traits>
+
 #include "common.h"
 
 // list[b][0 .. n_live[b]) = the patches of stream b that are NOT among the first m reuse
@@ -54,6 +56,8 @@ __global__ __launch_bounds__(256) void embed_mark_kernel(const int32_t* __restri
   if (tid == 0) n_live[b] = base;
 }
 
+typedef uint32_t u32x4_u __attribute__((ext_vector_type(4), aligned(1)));
+
 // Workgroup (x: 512 / KS output features, y: group of 32 RT live patches, z: stream).  The pixels
 // of the group go to LDS as bf16 operands in fragment order ([k/16][lane] of 16 bytes, lane =
 // patch + 32 (k/8 % 2)).  KS = 1: a wave multiplies them by 128 features of its own; KS = 4: the
@@ -68,6 +72,10 @@ __global__ __launch_bounds__(256) void embed_mark_kernel(const int32_t* __restri
 // patches per workgroup that this replaces: 166 patches of one stream 12 us (42 before),
 // 4800 patches of 8 streams 66 us (537 before; 192 with KS = 4 and two row tiles, which stages
 // the same pixels 32 times).
+// The pixels come by 16-byte loads at any address and the weights by a scalar address per k-tile: d_model 4096,
+// 8 x 1024 patches 70 -> 67 us of 14 x 14 pixels, front end 115 -> 112; 16 x 16 179 -> 168; 16 x 1024 of 13 x 13
+// (2-byte loads at even rows, single bytes at the odd ones before) 198 -> 165.  The phases of a workgroup add up:
+// staging 13 us, products 28, output 15 of the 67 at 8 x 1024.
 // (EMB_D k-tiles of weights in flight per wave: with 2 row tiles only 2, so that a
 // second workgroup fits the CU: 85 -> 72 us per call at 8 x 1024 patches)
 template <int RT, int KS, bool VEC>
@@ -79,7 +87,8 @@ __global__ __launch_bounds__(256, 2) void embed_patches_kernel(const uint8_t* __
   extern __shared__ uint4 px[];  // [RT][k-tiles][64]; KS = 4: then, per row tile, the waves' sums
   constexpr int PB = 32 * RT, EMB_D = RT == 2 ? 2 : 4;
   const int gw = W / patch, dp = 3 * patch * patch, prow = 3 * patch, n_kt = (dp + 15) >> 4;
-  const int b = blockIdx.z, g0 = blockIdx.y * PB, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int b = blockIdx.z, g0 = blockIdx.y * PB, tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nl = n_live[b];
   if (g0 >= nl) return;
   const int* mine = list + (size_t)b * 4096 + g0;
@@ -91,43 +100,93 @@ __global__ __launch_bounds__(256, 2) void embed_patches_kernel(const uint8_t* __
   // this wave's k-tiles [kt0, kt1); past the last weight row it is read again (see the pixels)
   const int kt0 = KS == 1 ? 0 : w * n_kt / 4, kt1 = KS == 1 ? n_kt : (w + 1) * n_kt / 4;
   uint2 wb[EMB_D][8];
+  // (a scalar address per k-tile and the lane's offsets of its 8 rows, the last k-tile's beside the
+  // others': the loop multiplies nothing)
+  uint32_t off[8], off_last[8];
+  const uint32_t off_max = 2u * ((uint32_t)(dp - 1 - (n_kt - 1) * 16) * (uint32_t)d + (uint32_t)fl);
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {
+    off[u] = u == 0 ? 2u * ((uint32_t)(8 * g) * (uint32_t)d + (uint32_t)fl) : off[u - 1] + 2u * (uint32_t)d;
+    off_last[u] = min(off[u], off_max);
+  }
   auto load_w = [&](int kt, uint2(&x)[8]) {
+    const char* base = (const char*)(w_proj + (size_t)kt * 16 * d);
+    const bool last = kt == n_kt - 1;
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const bf16_t* src = w_proj + (size_t)min(kt * 16 + 8 * g + u, dp - 1) * d + fl;
+      const bf16_t* src = (const bf16_t*)(base + (last ? off_last[u] : off[u]));
       if constexpr (VEC) x[u] = *(const uint2*)src;
       else x[u] = make_uint2(src[0] | ((uint32_t)src[1] << 16), src[2] | ((uint32_t)src[3] << 16));
     }
   };
+  auto first_weights = [&]() {
 #pragma unroll
-  for (int s = 0; s < EMB_D; ++s) load_w(min(kt0 + s, n_kt - 1), wb[s]);
+    for (int s = 0; s < EMB_D; ++s) load_w(min(kt0 + s, n_kt - 1), wb[s]);
+  };
 
-  // pixels: a thread takes pixel row y of one patch, two pixels at a time where the row lies on
-  // an even address and starts at an even k; unused patches of the group stay undefined (an
+  // pixels: every thread has one patch of the group; unused patches of the group stay undefined (an
   // operand row only reaches its own result row)
   uint16_t* px16 = (uint16_t*)px;
   auto odd = [](uint32_t v) { return fmaf(1.f / 128.f, (float)v, -255.f / 256.f); };  // (2 v - 255) / 256, exact
-  for (int e = tid; e < PB * patch; e += 256) {
-    const int p = e % PB, y = e / PB;
-    if (p >= cnt) continue;
-    const int i = mine[p], r = i / gw, c = i - r * gw;
-    const uint8_t* src = frame + (((size_t)b * H + (size_t)r * patch + y) * W + (size_t)c * patch) * 3;
+  {
+    constexpr int STEP = 256 / PB;
+    const int p = tid % PB, q0 = tid / PB;
+    const int i = mine[min(p, cnt - 1)], r = i / gw, c = i - r * gw;
+    const size_t pitch = (size_t)W * 3;
+    const uint8_t* src = frame + ((size_t)b * H + (size_t)r * patch) * pitch + (size_t)c * prow;
     uint16_t* dst = px16 + (size_t)(p >> 5) * n_kt * 512 + (p & 31) * 8;
-    auto at = [&](int k) { return dst + (k >> 4) * 512 + ((k >> 3) & 1) * 256 + (k & 7); };
-    const int k0 = y * prow;
-    int x = 0;
-    if (((((uintptr_t)src) | (uintptr_t)k0) & 1) == 0) {
-      for (; x + 14 <= prow; x += 14) {
-        uint16_t v[7];
+    auto at = [&](int k) { return dst + ((k >> 3) << 8) + (k & 7); };
+    // 16 bytes at a time, at whatever address (the last ones of a pixel row end with it and overlap those
+    // before), several loads in flight; PAIRS: two pixels per store (even patches: every row starts at an
+    // even k).  The first weights are asked for behind the first pixels, which are used first.
+    auto stage = [&](auto pairs) {
+      constexpr int U = RT == 1 ? 6 : 4;  // (14 x 14 pixels: all of a thread's loads at once, or in three groups)
+      const int n_ch = (prow + 15) >> 4, n_q = patch * n_ch, inv = (65536 + n_ch - 1) / n_ch;  // (n_q <= 130)
+      u32x4_u v[U];
+      int k[U];
+      auto load = [&](int q) {
 #pragma unroll
-        for (int u = 0; u < 7; ++u) v[u] = *(const uint16_t*)(src + x + 2 * u);
+        for (int u = 0; u < U; ++u) {
+          const int t = min(q + u * STEP, n_q - 1), y = (t * inv) >> 16, x = min((t - y * n_ch) * 16, prow - 16);
+          k[u] = y * prow + x;
+          v[u] = *(const u32x4_u*)(src + y * pitch + x);
+        }
+      };
+      auto store = [&](int q) {
 #pragma unroll
-        for (int u = 0; u < 7; ++u)
-          *(uint32_t*)at(k0 + x + 2 * u) = __builtin_amdgcn_perm(__float_as_uint(odd((uint32_t)v[u] >> 8)),
-                                                                 __float_as_uint(odd((uint32_t)v[u] & 255u)), 0x07060302u);
+        for (int u = 0; u < U; ++u)
+          if (p < cnt && q + u * STEP < n_q) {
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+              const uint32_t two = v[u][t >> 1] >> (16 * (t & 1));
+              const uint32_t lo = __float_as_uint(odd(two & 255u)), hi = __float_as_uint(odd((two >> 8) & 255u));
+              if constexpr (decltype(pairs)::value) {
+                *(uint32_t*)at(k[u] + 2 * t) = __builtin_amdgcn_perm(hi, lo, 0x07060302u);
+              } else {
+                *at(k[u] + 2 * t) = (uint16_t)(lo >> 16);
+                *at(k[u] + 2 * t + 1) = (uint16_t)(hi >> 16);
+              }
+            }
+          }
+      };
+      load(q0);
+      __builtin_amdgcn_sched_barrier(0);
+      first_weights();
+      __builtin_amdgcn_sched_barrier(0);
+      store(q0);
+      for (int q = q0 + U * STEP; q < n_q; q += U * STEP) {
+        load(q);
+        store(q);
       }
+    };
+    if (prow >= 16) {
+      if (patch & 1) stage(std::false_type{});
+      else stage(std::true_type{});
+    } else {
+      first_weights();
+      for (int y = q0; y < patch && p < cnt; y += STEP)
+        for (int x = 0; x < prow; ++x) *at(y * prow + x) = (uint16_t)(__float_as_uint(odd(src[y * pitch + x])) >> 16);
     }
-    for (; x < prow; ++x) *at(k0 + x) = (uint16_t)(__float_as_uint(odd(src[x])) >> 16);
   }
   if (const int n_pad = n_kt * 16 - dp; n_pad > 0) {
     // k past the last pixel: the last weight row is read again there, and the last pixel's value x is
@@ -170,7 +229,9 @@ __global__ __launch_bounds__(256, 2) void embed_patches_kernel(const uint8_t* __
       }
       op[t] = make_uint4(v[0], v[1], v[2], v[3]);
     }
+    __builtin_amdgcn_sched_barrier(0);
     load_w(min(kt + EMB_D, n_kt - 1), x);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int m = 0; m < RT; ++m) {
       const uint4 q = px[((size_t)m * n_kt + kt) * 64 + lane];
