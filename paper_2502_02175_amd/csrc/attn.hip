@@ -57,8 +57,10 @@ __global__ __launch_bounds__(256) void attn_rows_kernel(AttnArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int j = lane & 31, g = lane >> 5;
   const int b = blockIdx.z;
-  const int off_b = a.slot_off[b];
-  const int n_b = a.slot_off[b + 1] - off_b;
+  read_args(a.rows, a.qbuf, a.out, a.kc_out, a.kv, a.kv_stream_stride, a.n_q_heads, a.n_kv_heads, a.max_seq, a.L_v, a.L_t,
+            a.scale_log2e, a.attn_mean, a.statp, a.TT, a.lv_pad, a.defer_stats, a.rows4_from);
+  const int off_b = ld_scalar(a.slot_off + b);
+  const int n_b = ld_scalar(a.slot_off + b + 1) - off_b;
   const int s0 = blockIdx.x * 32;
   if (s0 >= n_b) return;
   if (a.rows4_from > 0 && n_b >= a.rows4_from) return;
@@ -66,7 +68,7 @@ __global__ __launch_bounds__(256) void attn_rows_kernel(AttnArgs a) {
   const bool valid = s0 + j < n_b;
   const int sg = off_b + (valid ? s0 + j : n_b - 1);  // this lane's query slot
   const int pos = valid ? (a.rows[sg] & 0xffff) : 0;
-  const int pos_last = a.rows[off_b + min(s0 + 31, n_b - 1)] & 0xffff;
+  const int pos_last = ld_scalar(a.rows + off_b + min(s0 + 31, n_b - 1)) & 0xffff;
   const int n_kt = (pos_last >> 5) + 1;
 
   const size_t head_elems = (size_t)a.max_seq * HD;
@@ -274,6 +276,7 @@ __global__ __launch_bounds__(64 * (MULTI ? kDecWavesMulti : kDecWaves)) void att
   constexpr int NC = HD / 16;  // k-tiles of a head
   constexpr int NI = HD / 32;  // feature blocks of a head
   extern __shared__ float dec_lds[];  // [waves][columns][HD + 4]: output, reference point, sum
+  read_args(a.decode_pos, a.qbuf, a.out, a.kc_out, a.kv, a.kv_stream_stride, a.n_q_heads, a.n_kv_heads, a.max_seq, a.scale_log2e);
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
   const int j = lane & 31, g = lane >> 5;
   const int b = blockIdx.y, group = a.n_q_heads / a.n_kv_heads, per_kv = (group + 31) >> 5;
@@ -431,8 +434,10 @@ __global__ __launch_bounds__(256, 3) void attn_rows4_kernel(AttnArgs a) {
   const int j = lane & 31, g = lane >> 5;
   // grid (heads, streams, query blocks): the query block is the slowest index, see below
   const int b = blockIdx.y, h = blockIdx.x;
-  const int off_b = a.slot_off[b];
-  const int n_b = a.slot_off[b + 1] - off_b;
+  read_args(a.rows, a.qbuf, a.out, a.kc_out, a.kv, a.kv_stream_stride, a.n_q_heads, a.n_kv_heads, a.max_seq, a.L_v, a.L_t,
+            a.scale_log2e, a.attn_mean, a.statp, a.TT, a.lv_pad, a.rows4_from);
+  const int off_b = ld_scalar(a.slot_off + b);
+  const int n_b = ld_scalar(a.slot_off + b + 1) - off_b;
   // the stream's query tiles are dealt to its workgroups in equal shares of at most 4 (33
   // tiles: 9 workgroups of 3 or 4, not 8 of 4 and one with a single busy wave)
   const int n_qt = (n_b + 31) >> 5, n_wg = (n_qt + 3) >> 2;
@@ -453,7 +458,7 @@ __global__ __launch_bounds__(256, 3) void attn_rows4_kernel(AttnArgs a) {
   const int n_kt = (pos_last >> 5) + 1;  // 0 for a wave without queries
   const int pos_first = __builtin_amdgcn_readfirstlane(pos);  // lane 0: the wave's first query
   // rows ascend by position: the workgroup needs the key tiles of its last query
-  const int pos_wg = a.rows[off_b + min(qt_end * 32 - 1, n_b - 1)] & 0xffff;
+  const int pos_wg = ld_scalar(a.rows + off_b + min(qt_end * 32 - 1, n_b - 1)) & 0xffff;
   const int n_kt_wg = (pos_wg >> 5) + 1;
 
   const size_t head_elems = (size_t)a.max_seq * HD;
@@ -700,8 +705,9 @@ __global__ __launch_bounds__(256) void stats_reduce_kernel(const float* __restri
                                                            float* __restrict__ attn_mean) {
   __shared__ float sums[4][64];
   const int layer = blockIdx.x, b = blockIdx.y, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  read_args(statp, slot_off, slot_stride, B, n_q_heads, TT, lv_pad, L_v, L_t, attn_mean);
   const int* so = slot_off + (size_t)layer * slot_stride;
-  const int n_b = so[b + 1] - so[b];
+  const int n_b = ld_scalar(so + b + 1) - ld_scalar(so + b);
   const int x_first = (n_b - L_t) >> 5;
   const int n_tt = ((n_b - 1) >> 5) - x_first + 1;
   const int n_part = n_q_heads * n_tt, per = (n_part + 3) >> 2, p_end = min(n_part, (w + 1) * per);

@@ -344,7 +344,7 @@ __global__ __launch_bounds__(rows_threads(FORM)) void gemm_rows_kernel(GemmArgs 
   // copies, and a copy of a register waits for the load that fills it.)
   uint64_t cut0 = a.cut[0], cut1 = a.cut[1];
   asm volatile("" : "+s"(cut0), "+s"(cut1));  // (read here; else the one that is needed is read when the count is known)
-  asm volatile("" ::"s"(a.xp), "s"(a.e.rows), "s"(a.waves));
+  read_args(a.xp, a.e.rows, a.waves);
   RowsWeights<W8> W;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   constexpr int FB = FORM == ROWS_PAIRS ? 2 : EPI == EPI_RESID || EPI == EPI_LOGITS ? 4 : 0;  // (one for all counts)
@@ -381,7 +381,7 @@ __global__ __launch_bounds__(rows_threads(FORM)) void gemm_rows_kernel(GemmArgs 
     }
     if (n_rows >= 0) break;
     // (a scalar load, written by the kernels before this one: a vector load would wait for the weights)
-    n_rows = *(const __attribute__((address_space(4))) int*)a.n_rows;
+    n_rows = ld_scalar(a.n_rows);
   }
   if (!FB) fb = __builtin_amdgcn_readfirstlane(fb);
   if (FORM != ROWS_PAIRS && w >= (fb == 2 ? 4 : fb) && w < a.waves - 2) return;  // no feature block for this wave

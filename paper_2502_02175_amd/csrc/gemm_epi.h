@@ -55,19 +55,15 @@ __device__ inline void scale_tile(const float* wscale, int nb, int g, f32x16& ac
   }
 }
 
-// Reads the arguments that the epilogue needs together with the first ones: the argument buffer lies in
-// host memory, and every read that waits for something else first is a round trip there of its own.
+// The arguments that the epilogue needs, read with the first ones
 template <int EPI>
 __device__ __forceinline__ void read_epilogue_args(const GemmArgs& a) {
   if constexpr (EPI == EPI_QKV)
-    asm volatile("" ::"s"(a.e.rows), "s"(a.e.rope_cos), "s"(a.e.rope_sin), "s"(a.e.qbuf), "s"(a.e.kv), "s"(a.e.kv_stream_stride),
-                 "s"(a.e.kv_layer_off), "s"(a.e.n_q_heads), "s"(a.e.max_seq));
-  else if constexpr (EPI == EPI_RESID)
-    asm volatile("" ::"s"(a.e.rows), "s"(a.e.d_model), "s"(a.e.rpart), "s"(a.e.rpart_rows));
-  else if constexpr (EPI == EPI_SWIGLU)
-    asm volatile("" ::"s"(a.e.rows), "s"(a.e.xf), "s"(a.e.kc_f));
-  else
-    asm volatile("" ::"s"(a.e.logits), "s"(a.e.logits_stride));
+    read_args(a.e.rows, a.e.rope_cos, a.e.rope_sin, a.e.qbuf, a.e.kv, a.e.kv_stream_stride, a.e.kv_layer_off,
+              a.e.n_q_heads, a.e.max_seq);
+  else if constexpr (EPI == EPI_RESID) read_args(a.e.rows, a.e.d_model, a.e.rpart, a.e.rpart_rows);
+  else if constexpr (EPI == EPI_SWIGLU) read_args(a.e.rows, a.e.xf, a.e.kc_f);
+  else read_args(a.e.logits, a.e.logits_stride);
 }
 
 __device__ inline float silu_f(float x) { return x / (1.f + __expf(-x)); }

@@ -24,6 +24,7 @@ __global__ __launch_bounds__(256) void plan_counts_kernel(
     int* __restrict__ rank, int* __restrict__ m_layer, int* __restrict__ n_rows_bl, int B,
     int* __restrict__ errword) {
   __shared__ int red[4];
+  read_args(L_t, n_layers, reuse_order, reuse_count, stride, layer_count, m_layer, n_rows_bl, B, errword);
   const int b = blockIdx.x, tid = threadIdx.x;
   int* rk = rank + (size_t)b * max_seq;
   for (int v = tid; v < L_v; v += 256) rk[v] = 0x7fffffff;
@@ -78,6 +79,7 @@ __global__ __launch_bounds__(256) void plan_rows_kernel(
     int* __restrict__ slot_off, int* __restrict__ prev_slot) {
   __shared__ int wsum[4], wsum_p[4];
   __shared__ int base_s, base_p;
+  read_args(L_v, L_t, n_layers, max_seq, max_rows, max_batch, rank, m_layer, n_rows_bl, B, rows, n_rows, slot_off, prev_slot);
   const int l = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int L = L_v + L_t;
   if (l == n_layers) {
@@ -93,8 +95,8 @@ __global__ __launch_bounds__(256) void plan_rows_kernel(
   }
   int off = 0, off_p = 0;  // first slot of this stream at this layer / at the layer before
   for (int k = 0; k < b; ++k) {
-    off += n_rows_bl[(size_t)l * B + k];
-    if (l > 0) off_p += n_rows_bl[(size_t)(l - 1) * B + k];
+    off += ld_scalar(n_rows_bl + (size_t)l * B + k);
+    if (l > 0) off_p += ld_scalar(n_rows_bl + (size_t)(l - 1) * B + k);
   }
   if (tid == 0) {
     slot_off[(size_t)l * (max_batch + 1) + b] = off;
@@ -182,9 +184,10 @@ __global__ __launch_bounds__(256) void rmsnorm_rows_kernel(
     const float* __restrict__ src, int seq_stride, const int* __restrict__ rows,
     const int* __restrict__ n_rows, int n_rows_host, int decode_pos,
     const float* __restrict__ gain, float eps, int d, bf16_t* __restrict__ xp, int KC) {
-  const int slot = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (slot >= (n_rows_host >= 0 ? n_rows_host : *n_rows)) return;
-  const int id = decode_pos >= 0 ? ((slot << 16) | decode_pos) : rows[slot];
+  read_args(src, seq_stride, rows, decode_pos, gain, eps, d, xp, KC);
+  const int slot = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (slot >= (n_rows_host >= 0 ? n_rows_host : ld_scalar(n_rows))) return;
+  const int id = decode_pos >= 0 ? ((slot << 16) | decode_pos) : ld_scalar(rows + slot);
   const float* x = src + ((size_t)(id >> 16) * seq_stride + (id & 0xffff)) * d;
   float ss = 0.f;
   for (int k = lane * 4; k < d; k += 256) {
@@ -213,9 +216,10 @@ __global__ __launch_bounds__(256) void rmsnorm_rows_reg_kernel(
     const float* __restrict__ src, int seq_stride, const int* __restrict__ rows,
     const int* __restrict__ n_rows, int n_rows_host, int decode_pos,
     const float* __restrict__ gain, float eps, int d, bf16_t* __restrict__ xp, int KC) {
-  const int slot = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (slot >= (n_rows_host >= 0 ? n_rows_host : *n_rows)) return;
-  const int id = decode_pos >= 0 ? ((slot << 16) | decode_pos) : rows[slot];
+  read_args(src, seq_stride, rows, decode_pos, gain, eps, d, xp, KC);
+  const int slot = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (slot >= (n_rows_host >= 0 ? n_rows_host : ld_scalar(n_rows))) return;
+  const int id = decode_pos >= 0 ? ((slot << 16) | decode_pos) : ld_scalar(rows + slot);
   const float* x = src + ((size_t)(id >> 16) * seq_stride + (id & 0xffff)) * d;
   const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
   float4 a[NI], b[NI], ga[NI], gb[NI];
@@ -282,17 +286,23 @@ __global__ __launch_bounds__(256) void resid_norm_rows_kernel(
     const int* __restrict__ part_slot, const int* __restrict__ n_rows, int n_rows_host,
     const float* __restrict__ gain, float eps, int d, bf16_t* __restrict__ xp, int KC, SplitAdapt adapt) {
   __shared__ float red[4];
+  read_args(resid, resid_seq_stride, part, S, part_rows, h, h_seq_stride, rows, part_slot, n_rows, n_rows_host, gain, eps, d,
+            xp, KC, adapt.n_rows, adapt.n_rows_host, adapt.n_blocks, adapt.KS, adapt.S_tall, adapt.small_below, adapt.S_small);
+  // (asked for together; the lists have room for every slot of the grid, and past the end of
+  // a list nothing is done with what they hold there)
   const int slot = blockIdx.x, tid = threadIdx.x;
-  if (slot >= (n_rows_host >= 0 ? n_rows_host : *n_rows)) return;
-  const int id = rows[slot];
+  const int n = n_rows_host >= 0 ? n_rows_host : ld_scalar(n_rows), id = ld_scalar(rows + slot);
   // the partial rows are indexed by the slot the row had when the GEMM ran
-  const int pslot = part_slot ? part_slot[slot] : slot;
+  const int pslot = part_slot ? ld_scalar(part_slot + slot) : slot;
+  // the GEMM's row count, where that is what its split factor followed from
+  const int n_g = adapt.n_blocks > 0 && adapt.n_rows_host < 0 ? ld_scalar(adapt.n_rows) : adapt.n_rows_host;
+  read_args(n, id, pslot, n_g);
+  if (slot >= n) return;
   const float* r = resid + ((size_t)(id >> 16) * resid_seq_stride + (id & 0xffff)) * d;
   float* y = h + ((size_t)(id >> 16) * h_seq_stride + (id & 0xffff)) * d;
   if (adapt.n_blocks > 0) {
     // the GEMM chose its split factor from its row count; unsplit, it added to the
     // residual stream itself and left no partial rows
-    const int n_g = adapt.n_rows_host >= 0 ? adapt.n_rows_host : *adapt.n_rows;
     S = n_g < adapt.small_below ? adapt.S_small : tall_plan((adapt.n_blocks + 7) >> 3, n_g, adapt.S_tall, adapt.KS).S;
     if (S == 1) {
       S = 0;
@@ -438,9 +448,10 @@ __global__ __launch_bounds__(256) void final_hidden_kernel(
     float* __restrict__ out, int L) {
   constexpr int NI = 8;
   __shared__ float red[4];
-  const int tid = threadIdx.x, n = *n_rows;
+  read_args(src, seq_stride, rows, gain, eps, d, out, L);
+  const int tid = threadIdx.x, n = ld_scalar(n_rows);
   for (int slot = blockIdx.x; slot < n; slot += gridDim.x) {
-    const int id = rows[slot];
+    const int id = ld_scalar(rows + slot);
     const float* x = src + ((size_t)(id >> 16) * seq_stride + (id & 0xffff)) * d;
     float* y = out + ((size_t)(id >> 16) * L + (id & 0xffff)) * d;
     float4 v[NI], g[NI];
@@ -511,6 +522,7 @@ __global__ __launch_bounds__(1024) void argmax_kernel(const float* __restrict__ 
                                                       int h_seq, int h_pos) {
   __shared__ float bv[16];
   __shared__ int bi[16];
+  read_args(logits, logits_stride, vocab, out, out_stride, embed, d, h, h_seq, h_pos);
   const int b = blockIdx.x, tid = threadIdx.x;
   const float* x = logits + (size_t)b * logits_stride;
   float best = -INFINITY;
