@@ -45,16 +45,18 @@ struct AttnArgs {
   int rows4_from;       // > 0: streams with at least this many rows are left to attn_rows4_kernel
 };
 
-// (one wave per SIMD: held to 256 registers for two, it spills and takes 14.9 us instead of 12.8 at 109
-// rows of one 7B stream, 45 instead of 42 at 519)
+// Two workgroups per CU: the next tile's K lands in the registers of this one's, and the waves merge one
+// feature block each instead of one wave all of them, so that a wave keeps within 256 registers without
+// spills (364 before, one workgroup per CU: 288 workgroups of 9 query tiles x 32 heads took two rounds).
+// 7B, one stream: 288 rows 19.1 -> 14.6 us, 519 of 601 rows 34.4 -> 26.0, bf16 42.2 -> 28.5, 109 rows 12.6 -> 11.
 template <int HD, bool F16>
-__global__ __launch_bounds__(256) void attn_rows_kernel(AttnArgs a) {
+__global__ __launch_bounds__(256, 2) void attn_rows_kernel(AttnArgs a) {
   constexpr int NC = HD / 16;  // k-tiles of a head
   constexpr int NI = HD / 32;  // feature blocks of a head
-  __shared__ float cmb[3][2 + NI * 16][64];  // waves 1..3 park (max, sum, output) here
+  __shared__ float cmb[4][2 + (HD == 128 ? 3 : 2) * 16][64];  // the waves park (max, sum, the blocks they do not finish) here
   __shared__ float fin[2][64];               // merged max and 1/sum per lane
   __shared__ int s_last;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int j = lane & 31, g = lane >> 5;
   const int b = blockIdx.z;
   read_args(a.rows, a.qbuf, a.out, a.kc_out, a.kv, a.kv_stream_stride, a.n_q_heads, a.n_kv_heads, a.max_seq, a.L_v, a.L_t,
@@ -101,15 +103,17 @@ __global__ __launch_bounds__(256) void attn_rows_kernel(AttnArgs a) {
     for (int i = 0; i < 16; ++i) o[ib][i] = 0.f;
   float m = -INFINITY, l = 0.f;
 
-  uint4 kf[NC], kn[NC];
+  uint4 kf[NC];
   if (w < n_kt) load_k(w, kf);
   for (int kt = w; kt < n_kt; kt += 4) {
     f32x16 s;
     scores(kf, s);
-    uint4 vf[NI * 2];  // this tile's V, and the next tile's K, fly during the softmax arithmetic
+    __builtin_amdgcn_sched_barrier(0);
+    uint4 vf[NI * 2];  // this tile's V, and the next tile's K in the registers of this one's, fly during the softmax
 #pragma unroll
     for (int t = 0; t < NI * 2; ++t) vf[t] = *(const uint4*)(vbase + ((size_t)kt * NI * 2 + t) * 512);
-    if (kt + 4 < n_kt) load_k(kt + 4, kn);
+    if (kt + 4 < n_kt) load_k(kt + 4, kf);
+    __builtin_amdgcn_sched_barrier(0);
     // register 4*q4 + e of a lane is key 32*kt + 8*q4 + 4*g + e
     float tmax = -INFINITY;
 #pragma unroll
@@ -147,47 +151,59 @@ __global__ __launch_bounds__(256) void attn_rows_kernel(AttnArgs a) {
 #pragma unroll
       for (int t = 0; t < 2; ++t) o[ib] = mfma32<F16>(vf[ib * 2 + t], pb[t], o[ib]);
     }
-#pragma unroll
-    for (int c = 0; c < NC; ++c) kf[c] = kn[c];
   }
   l += __shfl_xor(l, 32);
 
-  // merge the 4 waves (wave 0 owns tile 0, so its max is finite: key 0 is visible to every query)
-  if (w > 0) {
-    cmb[w - 1][0][lane] = m;
-    cmb[w - 1][1][lane] = l;
+  // Merge the 4 waves, wave ib the feature block ib of all of them, in the order of the waves (wave 0
+  // owns tile 0, so its max is finite: key 0 is visible to every query)
+  f32x16 own;
+  cmb[w][0][lane] = m;
+  cmb[w][1][lane] = l;
 #pragma unroll
-    for (int ib = 0; ib < NI; ++ib)
+  for (int ib = 0; ib < NI; ++ib) {
+    if (ib == w) own = o[ib];
+    else {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) cmb[w - 1][2 + ib * 16 + i][lane] = o[ib][i];
+      for (int i = 0; i < 16; ++i) cmb[w][2 + (w < ib ? ib - 1 : ib) * 16 + i][lane] = o[ib][i];
+    }
   }
   __syncthreads();
-  if (w == 0) {
+  if (w < NI) {
+    f32x16 acc;
+    m = cmb[0][0][lane];
+    l = cmb[0][1][lane];
+#pragma unroll 1
+    for (int ww = 0; ww < 4; ++ww) {
+      f32x16 t = own;
+      if (ww != w) {
 #pragma unroll
-    for (int ww = 0; ww < 3; ++ww) {
+        for (int i = 0; i < 16; ++i) t[i] = cmb[ww][2 + (ww < w ? w - 1 : w) * 16 + i][lane];
+      }
+      if (ww == 0) {
+        acc = t;
+        continue;
+      }
       const float m_w = cmb[ww][0][lane], l_w = cmb[ww][1][lane];
       const float m_new = fmaxf(m, m_w);
       const float a0 = exp2f(m - m_new), a1 = exp2f(m_w - m_new);
       m = m_new;
       l = l * a0 + l_w * a1;
 #pragma unroll
-      for (int ib = 0; ib < NI; ++ib)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) o[ib][i] = o[ib][i] * a0 + cmb[ww][2 + ib * 16 + i][lane] * a1;
+      for (int i = 0; i < 16; ++i) acc[i] = acc[i] * a0 + t[i] * a1;
     }
     const float inv = 1.f / l;
-    fin[0][lane] = m;
-    fin[1][lane] = (valid && pos >= a.L_v) ? inv : 0.f;  // (the statistic counts text rows only)
+    if (w == 0) {
+      fin[0][lane] = m;
+      fin[1][lane] = (valid && pos >= a.L_v) ? inv : 0.f;  // (the statistic counts text rows only)
+    }
     if (valid) {
 #pragma unroll
-      for (int ib = 0; ib < NI; ++ib)
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          const int f = h * HD + 32 * ib + 8 * q4 + 4 * g;
-          *(uint2*)(a.out + frag_off(sg, f, a.kc_out)) =
-              make_uint2(pack_op2<F16>(o[ib][4 * q4] * inv, o[ib][4 * q4 + 1] * inv),
-                         pack_op2<F16>(o[ib][4 * q4 + 2] * inv, o[ib][4 * q4 + 3] * inv));
-        }
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const int f = h * HD + 32 * w + 8 * q4 + 4 * g;
+        *(uint2*)(a.out + frag_off(sg, f, a.kc_out)) =
+            make_uint2(pack_op2<F16>(acc[4 * q4] * inv, acc[4 * q4 + 1] * inv),
+                       pack_op2<F16>(acc[4 * q4 + 2] * inv, acc[4 * q4 + 3] * inv));
+      }
     }
   }
 
@@ -836,7 +852,10 @@ void launch_attention(vlac_ctx* c, int layer, int B, int rows_cap_per_stream, in
       else hipLaunchKernelGGL((attn_rows4_kernel<64, false>), grid4, dim3(256), 0, st, a);
     }
   }
-  dim3 grid((rows_cap_per_stream + 31) / 32, m.n_q_heads, B);
+  // (beside the other kernel only streams of up to rows4_from - 1 rows are left to this one: two query tiles;
+  // with a workgroup for every tile of every stream the idle launch takes 6.6 us at 8 x 1057 tokens, so 5.0)
+  const int rows_most = a.rows4_from > 0 ? a.rows4_from - 1 : rows_cap_per_stream;
+  dim3 grid((rows_most + 31) / 32, m.n_q_heads, B);
   if (m.head_dim == 128) {
     if (c->f16) hipLaunchKernelGGL((attn_rows_kernel<128, true>), grid, dim3(256), 0, st, a);
     else hipLaunchKernelGGL((attn_rows_kernel<128, false>), grid, dim3(256), 0, st, a);
