@@ -31,12 +31,16 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-__device__ inline bf16_t f2bf(float x) {  // fp32 -> bf16, round to nearest even
-  uint32_t u = __float_as_uint(x);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (bf16_t)((u >> 16) | 0x40);  // NaN stays NaN
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (bf16_t)(u >> 16);
+// fp32 -> bf16, round to nearest even, by the chip's own conversion of two values (the same bits as the
+// integer arithmetic it replaces for all 2^32 inputs, NaN and subnormals among them, in a seventh of
+// the instructions).  Calls with bf16 operands: 601 tokens of 7B 1345 -> 1304 us, 32 streams of grouped queries
+// 2959 -> 2834, 109 rows of 7B 652 -> 628, decode of 16 grouped-query streams 970 -> 933.
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef float f32x2v __attribute__((ext_vector_type(2)));
+__device__ inline uint32_t f2bf2(float lo, float hi) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2v){lo, hi}, bf16x2_t));
 }
+__device__ inline bf16_t f2bf(float x) { return __builtin_bit_cast(bf16_t, (__bf16)x); }
 __device__ inline uint16_t f2h(float x) {  // fp32 -> fp16, round to nearest even, saturating
   const _Float16 h = (_Float16)fminf(fmaxf(x, -65504.f), 65504.f);
   return __builtin_bit_cast(uint16_t, h);
@@ -48,7 +52,8 @@ __device__ inline uint16_t f2op(float x) {
 }
 template <bool F16>
 __device__ inline uint32_t pack_op2(float lo, float hi) {
-  return (uint32_t)f2op<F16>(lo) | ((uint32_t)f2op<F16>(hi) << 16);
+  if constexpr (F16) return (uint32_t)f2h(lo) | ((uint32_t)f2h(hi) << 16);
+  else return f2bf2(lo, hi);
 }
 // Hand-over of partial results between workgroups (split-K sums, attention
 // statistics).  The 8 XCDs have one L2 each, and an agent-scope fence
