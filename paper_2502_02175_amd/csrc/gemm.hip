@@ -44,10 +44,11 @@
 // 49.8 -> 41.7 us (4.3 TB/s of weights), QKV 41.2 -> 33.6, O 15 -> 14.4, FFN down 29 -> 26; four
 // layers with the head 742 -> 628 us, 192 rows 908 -> 764.  32 weight tiles in flight: no faster.
 // fb and the row blocks follow from the row count, in the kernel where only the device knows it
-// (rows_cut): with two row blocks of 288 rows QKV runs 256 workgroups of 3 feature blocks in one round
-// instead of 384 of 2 in two, gate/up 230 of 6 instead of 460 of 3.  Four layers of 7B and the head,
-// fb by the launch alone and by the row count: 211 rows 824 -> 794 us, 259 rows 1020 -> 907, 288 rows 999 ->
-// 877, 437 rows 1514 -> 1326.  (K of QKV or gate/up split over workgroups instead, the last wave to
+// (rows_cut): with two row blocks of 288 rows gate/up runs 230 workgroups of 6 feature blocks in one round
+// instead of 460 of 3 in two, and QKV, where the host knows the count, 256 of 3 instead of 384 of 2.
+// Four layers of 7B and the head, before and now: 288 rows known to
+// the host 1005 -> 874 us, 448 rows (many-rows kernel before) 1313 -> 1190; counted by the device 259 rows 1065 -> 1010,
+// 437 rows 1544 -> 1425.  (K of QKV or gate/up split over workgroups instead, the last wave to
 // arrive adding up: 3 us per hand-over, 288 rows -58 us where this gives -120, 109 rows +10.)
 // The arguments are read together at the start: the argument buffer lies in host memory, and an argument
 // that is first read later is a round trip there (decode, 32 streams of grouped queries 1545 -> 1522 us,
@@ -59,10 +60,11 @@
 // layers and the head, now 764; 109 rows 635, now 628.)
 constexpr int ROWS_RING = 5;       // chunks of at most 32 KiB: all 160 KiB of a CU's LDS
 constexpr int ROWS_FB_MIN = 2, ROWS_FB_MAX = 6;  // feature blocks per workgroup: 2 (K in two parts) or 3 to 6
-constexpr int ROWS_PAIR_NA = 6;  // most row tiles per wave with 2 feature blocks where the launch has both forms
-// The forms of the kernel: every row count with 2 feature blocks, none, or some (the count decides)
-enum { ROWS_PAIRS = 2, ROWS_SINGLE = 3, ROWS_MIXED = 4 };
-constexpr int rows_threads(int form) { return 64 * ((form == ROWS_PAIRS ? 4 : ROWS_FB_MAX) + 2); }  // (at most)
+constexpr int ROWS_PAIR_NA = 6;  // most row tiles per wave with 2 feature blocks where others are in the choice
+// The forms of the kernel: 2 feature blocks per workgroup, up to 4, up to 6
+enum { ROWS_PAIRS = 2, ROWS_FOUR = 4, ROWS_SIX = 6 };
+constexpr int rows_consumers(int form) { return form == ROWS_SIX ? 6 : 4; }
+constexpr int rows_threads(int form) { return 64 * (rows_consumers(form) + 2); }
 
 template <int NA, int KP, bool W8>
 struct RowsShape {
@@ -183,8 +185,8 @@ __device__ __forceinline__ void rows_body(const GemmArgs& a, uint4* lds, RowsWei
   int ids[NA];
 #pragma unroll
   for (int m = 0; m < NA; ++m) ids[m] = 0;
-  if (const int p0 = FORM == ROWS_PAIRS ? 4 : a.waves - 2; w >= p0) {
-    rows_produce<NA, KP, W8>(a, lds, w - p0, s, rt0, row_end);
+  if (w >= rows_consumers(FORM)) {
+    rows_produce<NA, KP, W8>(a, lds, w - rows_consumers(FORM), s, rt0, row_end);
   } else {
     RowsRange rg = rows_range(a.KS, a.S * KP, s * KP + part);
     // (opaque: simplified by KP = 1 the last steps keep more weight tiles alive, and spill)
@@ -344,7 +346,7 @@ __global__ __launch_bounds__(rows_threads(FORM)) void gemm_rows_kernel(GemmArgs 
   // copies, and a copy of a register waits for the load that fills it.)
   uint64_t cut0 = a.cut[0], cut1 = a.cut[1];
   asm volatile("" : "+s"(cut0), "+s"(cut1));  // (read here; else the one that is needed is read when the count is known)
-  read_args(a.xp, a.e.rows, a.waves);
+  read_args(a.xp, a.e.rows);
   RowsWeights<W8> W;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   constexpr int FB = FORM == ROWS_PAIRS ? 2 : EPI == EPI_RESID || EPI == EPI_LOGITS ? 4 : 0;  // (one for all counts)
@@ -370,10 +372,10 @@ __global__ __launch_bounds__(rows_threads(FORM)) void gemm_rows_kernel(GemmArgs 
     }
     tile = __builtin_amdgcn_readfirstlane(p / a.S);
     s = __builtin_amdgcn_readfirstlane(p - tile * a.S);
-    const int KP = fb == 2 ? 2 : 1;
+    constexpr int KP = FORM == ROWS_PAIRS ? 2 : 1;
     if (w < fb * KP && tile * fb < a.NB) {
-      const RowsRange rg = rows_range(a.KS, a.S * KP, s * KP + (fb == 2 ? w >> 1 : 0));
-      const int nb = min(tile * fb + (fb == 2 ? w & 1 : w), a.NB - 1), kc = W8 ? 2 * a.KS : 4 * a.KS, k0 = W8 ? rg.k0 / 2 : rg.k0;
+      const RowsRange rg = rows_range(a.KS, a.S * KP, s * KP + (KP == 2 ? w >> 1 : 0));
+      const int nb = min(tile * fb + (KP == 2 ? w & 1 : w), a.NB - 1), kc = W8 ? 2 * a.KS : 4 * a.KS, k0 = W8 ? rg.k0 / 2 : rg.k0;
       const uint4* src = a.wp + (size_t)nb * kc * 64 + (threadIdx.x & 63);
       // (past the end of K the last tile is read again and not used)
 #pragma unroll
@@ -384,38 +386,22 @@ __global__ __launch_bounds__(rows_threads(FORM)) void gemm_rows_kernel(GemmArgs 
     n_rows = ld_scalar(a.n_rows);
   }
   if (!FB) fb = __builtin_amdgcn_readfirstlane(fb);
-  if (FORM != ROWS_PAIRS && w >= (fb == 2 ? 4 : fb) && w < a.waves - 2) return;  // no feature block for this wave
+  if (FORM != ROWS_PAIRS && w >= fb && w < rows_consumers(FORM)) return;  // no feature block for this wave
   tile = __builtin_amdgcn_readfirstlane(tile);
   s = __builtin_amdgcn_readfirstlane(s);
   const int rt0 = __builtin_amdgcn_readfirstlane(mb * n_rt / n_blk);
   const int rt1 = __builtin_amdgcn_readfirstlane((mb + 1) * n_rt / n_blk), row_end = min(n_rows, 32 * rt1);
-#define VLAC_NA(N, KP) rows_body<N, KP, FORM, EPI, F16, W8>(a, lds, W, fb, tile, s, rt0, row_end)
-  if (FORM == ROWS_PAIRS || (FORM == ROWS_MIXED && fb == 2)) {
-    switch (rt1 - rt0) {
-      case 1: VLAC_NA(1, 2); break;
-      case 2: VLAC_NA(2, 2); break;
-      case 3: VLAC_NA(3, 2); break;
-      case 4: VLAC_NA(4, 2); break;
-      case 5: VLAC_NA(5, 2); break;
-      case 6: VLAC_NA(6, 2); break;
-      case 7:
-        if constexpr (FORM == ROWS_PAIRS) VLAC_NA(7, 2);
-        break;
-      default:
-        static_assert(ROWS_PAIR_NA == 6, "the cases above");
-        if constexpr (FORM == ROWS_PAIRS) VLAC_NA(8, 2);
-    }
-  } else if constexpr (FORM != ROWS_PAIRS) {
-    switch (rt1 - rt0) {
-      case 1: VLAC_NA(1, 1); break;
-      case 2: VLAC_NA(2, 1); break;
-      case 3: VLAC_NA(3, 1); break;
-      case 4: VLAC_NA(4, 1); break;
-      case 5: VLAC_NA(5, 1); break;
-      case 6: VLAC_NA(6, 1); break;
-      case 7: VLAC_NA(7, 1); break;
-      default: VLAC_NA(8, 1);
-    }
+#define VLAC_NA(N) rows_body<N, KP, FORM, EPI, F16, W8>(a, lds, W, fb, tile, s, rt0, row_end)
+  constexpr int KP = FORM == ROWS_PAIRS ? 2 : 1;
+  switch (rt1 - rt0) {
+    case 1: VLAC_NA(1); break;
+    case 2: VLAC_NA(2); break;
+    case 3: VLAC_NA(3); break;
+    case 4: VLAC_NA(4); break;
+    case 5: VLAC_NA(5); break;
+    case 6: VLAC_NA(6); break;
+    case 7: VLAC_NA(7); break;
+    default: VLAC_NA(8);
   }
 #undef VLAC_NA
 }
@@ -683,24 +669,24 @@ int gemm_init() {
 #define VLAC_SET(FORM)                                                    \
   if ((e = set_attr<FORM, EPI_QKV>()) != hipSuccess) return (int)e;       \
   if ((e = set_attr<FORM, EPI_SWIGLU>()) != hipSuccess) return (int)e;
-  VLAC_SET(ROWS_PAIRS) VLAC_SET(ROWS_SINGLE) VLAC_SET(ROWS_MIXED)
+  VLAC_SET(ROWS_PAIRS) VLAC_SET(ROWS_FOUR) VLAC_SET(ROWS_SIX)
   if ((e = set_attr<ROWS_PAIRS, EPI_RESID>()) != hipSuccess) return (int)e;
-  if ((e = set_attr<ROWS_SINGLE, EPI_RESID>()) != hipSuccess) return (int)e;
-  if ((e = set_attr<ROWS_SINGLE, EPI_LOGITS>()) != hipSuccess) return (int)e;
+  if ((e = set_attr<ROWS_FOUR, EPI_RESID>()) != hipSuccess) return (int)e;
+  if ((e = set_attr<ROWS_FOUR, EPI_LOGITS>()) != hipSuccess) return (int)e;
 #undef VLAC_SET
   return gemm_tall_init();
 }
 
 template <int FORM, bool F16, bool W8>
 static void launch_rows(int epi, const GemmArgs& a, int grid, hipStream_t st) {
-  constexpr int ONE = FORM == ROWS_PAIRS ? ROWS_PAIRS : ROWS_SINGLE;  // (projections with a residual: one fb for all)
-  const dim3 g(grid), t(64 * a.waves);
+  constexpr int ONE = FORM == ROWS_PAIRS ? ROWS_PAIRS : ROWS_FOUR;  // (projections with a residual: 2 or 4)
+  const dim3 g(grid), t(rows_threads(FORM));
   switch (epi) {
     case EPI_QKV: hipLaunchKernelGGL((gemm_rows_kernel<FORM, EPI_QKV, F16, W8>), g, t, kRowsLds, st, a); break;
-    case EPI_RESID: hipLaunchKernelGGL((gemm_rows_kernel<ONE, EPI_RESID, F16, W8>), g, t, kRowsLds, st, a); break;
+    case EPI_RESID: hipLaunchKernelGGL((gemm_rows_kernel<ONE, EPI_RESID, F16, W8>), g, dim3(rows_threads(ONE)), kRowsLds, st, a); break;
     case EPI_SWIGLU: hipLaunchKernelGGL((gemm_rows_kernel<FORM, EPI_SWIGLU, F16, W8>), g, t, kRowsLds, st, a); break;
     default:  // (always 4 feature blocks)
-      hipLaunchKernelGGL((gemm_rows_kernel<ROWS_SINGLE, EPI_LOGITS, F16, W8>), g, t, kRowsLds, st, a); break;
+      hipLaunchKernelGGL((gemm_rows_kernel<ROWS_FOUR, EPI_LOGITS, F16, W8>), g, dim3(rows_threads(ROWS_FOUR)), kRowsLds, st, a); break;
   }
 }
 
@@ -826,15 +812,15 @@ static const int kRowsPairTiles = 128;
 // about 50 GB/s with weights from HBM and row operands from L2 in one queue).
 // (2 feature blocks take K in two parts and half as many k-tiles per barrier: 7 row tiles of 7B QKV
 // are faster with 3 in two blocks, 6 with 2)
-static RowsCut rows_cut(int epi, int NB, int KS, int S, int rt, bool pairs_only, int* code) {
+static RowsCut rows_cut(int epi, int NB, int KS, int S, int rt, int k_parts, int* code) {
   RowsCut best = {0, 0};
   int least = 0x7fffffff;
-  const int fix = epi == EPI_LOGITS ? 4 : epi == EPI_RESID ? rows_resid_fb(NB, KS) : pairs_only ? 2 : 0;
+  const int fix = epi == EPI_LOGITS ? 4 : epi == EPI_RESID ? rows_resid_fb(NB, KS) : k_parts == 2 ? 2 : 0;
   for (int fb = ROWS_FB_MIN; fb <= ROWS_FB_MAX; ++fb) {
     if (fix && fb != fix) continue;
     for (int eight = 0; eight < 2; ++eight) {
       const int n = eight ? (rt + 7) / 8 : (rt + 5) / 6, na = (rt + n - 1) / n;
-      if (!fix && fb == 2 && na > ROWS_PAIR_NA) continue;
+      if (!fix && fb == 2 && (k_parts == 1 || na > ROWS_PAIR_NA)) continue;
       const int cost = (rows_tiles(NB, fb) * S * n + 255) / 256 * (fb + na) + n - 1;
       if (cost < least) {
         least = cost;
@@ -849,21 +835,21 @@ static RowsCut rows_cut(int epi, int NB, int KS, int S, int rt, bool pairs_only,
 // the one-stream kernel for up to rows_cap rows; sets and returns a.S
 static int launch_rows_kernel(vlac_ctx* c, int epi, GemmArgs& a, int rows_cap, const GemmEpi& e, hipStream_t st) {
   a.S = rows_kernel_splits(c, epi, a.NB, a.KS, e.rpart_rows, e.d_model, rows_cap, a.n_rows_val >= 0);
-  // (few feature blocks: a workgroup each, whatever the row count, and the two parts of K halve the chain)
-  const bool pairs_only = rows_tiles(a.NB, 2) < kRowsPairTiles;
   const int rt_cap = std::min((rows_cap + 31) / 32, 32), rt_known = a.n_rows_val >= 0 ? (a.n_rows_val + 31) / 32 : 0;
+  // K in two parts or not: where the device counts the rows, one or the other for every count, as few
+  // rows have it, so that a row's result does not depend on how many others are recomputed
+  int code = 0, k_parts = 0;
+  if (rows_tiles(a.NB, 2) < kRowsPairTiles) k_parts = 2;
+  else if (!rt_known) k_parts = rows_cut(epi, a.NB, a.KS, a.S, std::min(rt_cap, 4), 0, &code).fb == 2 ? 2 : 1;
   a.cut[0] = a.cut[1] = 0;
-  int grid = 0, fb_most = 0, fb_least = ROWS_FB_MAX;
+  int grid = 0, fb_most = 0;
   for (int rt = rt_known ? rt_known : 1; rt <= (rt_known ? rt_known : rt_cap); ++rt) {
-    int code = 0;
-    const RowsCut cut = rows_cut(epi, a.NB, a.KS, a.S, rt, pairs_only, &code);
+    const RowsCut cut = rows_cut(epi, a.NB, a.KS, a.S, rt, k_parts, &code);
     a.cut[(rt - 1) >> 4] |= (uint64_t)code << (4 * ((rt - 1) & 15));
     if (rt <= 4) a.fb_first = cut.fb;  // (what few rows usually get)
     fb_most = std::max(fb_most, cut.fb);
-    fb_least = std::min(fb_least, cut.fb);
     grid = std::max(grid, (rows_tiles(a.NB, cut.fb) * a.S + 7) / 8 * 8 * cut.blocks);
   }
-  a.waves = 2 + (fb_least == 2 ? std::max(fb_most, 4) : fb_most);
 #define VLAC_ROWS(FORM_)                                                                  \
   {                                                                                       \
     if (c->w8) launch_rows<FORM_, true, true>(epi, a, grid, st);                   \
@@ -871,8 +857,8 @@ static int launch_rows_kernel(vlac_ctx* c, int epi, GemmArgs& a, int rows_cap, c
     else launch_rows<FORM_, false, false>(epi, a, grid, st);                       \
   }
   if (fb_most == 2) VLAC_ROWS(ROWS_PAIRS)
-  else if (fb_least > 2) VLAC_ROWS(ROWS_SINGLE)
-  else VLAC_ROWS(ROWS_MIXED)
+  else if (fb_most <= 4) VLAC_ROWS(ROWS_FOUR)
+  else VLAC_ROWS(ROWS_SIX)
 #undef VLAC_ROWS
   return a.S;
 }

@@ -1,7 +1,5 @@
 // Shared by the GEMM kernels: launch arguments and the fused epilogues.
 #pragma once
-#include <stddef.h>
-
 #include "common.h"
 
 struct GemmArgs {
@@ -16,18 +14,15 @@ struct GemmArgs {
   int S;              // split-K factor
   int rows_hi;        // the launch has work only if rows_lo <= row count < rows_hi (two kernels share a GEMM)
   int fb_first;       // one-stream GEMM: the feature blocks per workgroup that it assumes until the row count is known
-  int waves;          // one-stream GEMM: waves of a workgroup
   int rows_lo;
   int x_tiles;        // many-rows GEMM: 32-row tiles the activation buffer holds (copies are clamped to it)
   const float* wscale;  // e4m3 weights: scale per output feature (packed row order), else null
   const uint4* zero_tile;  // 1 KiB of zeros
   float* partial;
   int* counters;
-  GemmEpi e;          // (what EPI_QKV reads starts a line)
+  GemmEpi e;
   NormIn norm;        // fused RMSNorm of the input rows (few-rows kernel only)
 };
-static_assert(offsetof(GemmArgs, waves) == 64 && offsetof(GemmArgs, e) + offsetof(GemmEpi, rope_cos) == 128, "lines of 64 bytes");
-
 // e4m3 weights: a lane's 8 codes of one k-tile (two dwords) -> its 8 fp16 operand values.
 // The hardware conversion decodes OCP e4m3 (verified code by code); every e4m3 value is an
 // fp16 value, so the second conversion is exact.
