@@ -62,7 +62,7 @@ void free_all(vlac_ctx* c) {
   }
   void* dev[] = {c->w_head, c->s_head, c->scale_tmp, c->wdeq, c->embed, c->g_final, c->rope_cos, c->rope_sin, c->h, c->hdec, c->xa, c->xf,
                  c->qbuf, c->partial, c->rpart, c->counters, c->rows, c->prev_slot, c->n_rows, c->slot_off, c->rank,
-                 c->m_layer, c->n_rows_bl, c->statp, c->stat_counters, c->logits,
+                 c->m_layer, c->n_rows_bl, c->statp, c->stat_counters, c->logits, c->head_best,
                  c->dec_rows, c->terms, c->flags, c->embed_list, c->embed_n, c->relevance, c->entropy, c->ratio_counters, c->errword, c->scratch_i,
                  c->zero_tile};
   for (void* p : dev) (void)hipFree(p);
@@ -223,6 +223,7 @@ int vlac_create(const vlac_model_cfg* cfg, vlac_ctx** out) {
   A_(statp, ctx->statp_floats);
   A_(stat_counters, mb);
   A_(logits, (size_t)mb * m.vocab);
+  A_(head_best, (size_t)mb * (m.vocab / 32));
   A_(dec_rows, (size_t)ms * mb + ms + (size_t)ms * (mb + 1));
   A_(terms, (size_t)mb * 4096 * 3);
   A_(flags, (size_t)mb * 4096);
@@ -635,7 +636,7 @@ void run_head(vlac_ctx* c, int B, int pos, float* logits, size_t logits_stride, 
   GemmEpi e;
   memset(&e, 0, sizeof(e));
   e.decode_pos = pos;
-  e.logits = logits; e.vocab = m.vocab; e.logits_stride = logits_stride;
+  e.logits = logits; e.vocab = m.vocab; e.logits_stride = logits_stride; e.best = c->head_best;
   if (fused) {
     launch_gemm(c, EPI_LOGITS, c->w_head, c->s_head, m.vocab / 32, c->kpad_d, c->xa, nullptr, B, B, e, st, fused);
   } else if (gemm_can_fuse_norm(B, pos, c->kpad_d)) {
@@ -649,7 +650,7 @@ void run_head(vlac_ctx* c, int B, int pos, float* logits, size_t logits_stride, 
                         m.d_model, c->xa, c->kpad_d / 16, st);
     launch_gemm(c, EPI_LOGITS, c->w_head, c->s_head, m.vocab / 32, c->kpad_d, c->xa, nullptr, B, B, e, st);
   }
-  launch_argmax(logits, logits_stride, B, m.vocab, out_token, out_stride, next, st);
+  launch_argmax(c->head_best, B, m.vocab, out_token, out_stride, next, st);
 }
 
 int weights_ready(const vlac_ctx* c) {

@@ -190,6 +190,7 @@ struct vlac_ctx {
   int stat_tt;      // text tiles per stream the statistic buffer provides for
   int* stat_counters;
   float* logits;    // [max_batch, vocab]
+  float2* head_best;  // [max_batch, vocab / 32] greatest logit of every feature block, and its token
   int* dec_rows;    // decode row lists
   uint32_t* terms;  // patch terms [max_batch, 4096, 3]
   uint8_t* flags;   // selection flags
@@ -250,8 +251,8 @@ void launch_final_hidden(const float* src, int seq_stride, const int* rows, cons
                          hipStream_t st);
 // where the embedding of a greedy token goes: row (b, h_pos) of h [B, h_seq, d] (h == nullptr: nowhere)
 struct NextEmbed { const bf16_t* embed; int d; float* h; int h_seq, h_pos; };
-void launch_argmax(const float* logits, size_t logits_stride, int B, int vocab, int32_t* out,
-                   int out_stride, const NextEmbed& next, hipStream_t st);
+void launch_argmax(const float2* best, int B, int vocab, int32_t* out, int out_stride, const NextEmbed& next,
+                   hipStream_t st);
 void launch_embed_rows(const bf16_t* embed, const int32_t* tokens, int B, int d, int vocab, float* h,
                        int max_seq, int pos, hipStream_t st);
 // e4m3 storage: scales of the N source rows, then codes in fragment order (two k-tiles per
@@ -284,6 +285,7 @@ struct GemmEpi {
   bf16_t* xf; int kc_f; int d_ffn;
   // EPI_LOGITS
   float* logits; int vocab; size_t logits_stride;  // elements between rows
+  float2* best;  // [row][vocab / 32]: the greatest logit of a feature block and its token (as bits)
 };
 // RMSNorm fused into the few-rows GEMM: x = src row (+ split-K partial rows, in split
 // order), operand = x * rsqrt(mean(x^2) + eps) * gain

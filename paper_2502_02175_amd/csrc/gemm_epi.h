@@ -58,7 +58,7 @@ __device__ __forceinline__ void read_epilogue_args(const GemmArgs& a) {
               a.e.n_q_heads, a.e.max_seq);
   else if constexpr (EPI == EPI_RESID) read_args(a.e.rows, a.e.d_model, a.e.rpart, a.e.rpart_rows);
   else if constexpr (EPI == EPI_SWIGLU) read_args(a.e.rows, a.e.xf, a.e.kc_f);
-  else read_args(a.e.logits, a.e.logits_stride);
+  else read_args(a.e.logits, a.e.logits_stride, a.e.best, a.e.vocab);
 }
 
 __device__ inline float silu_f(float x) { return x / (1.f + __expf(-x)); }
@@ -139,6 +139,18 @@ __device__ inline void epilogue_tile(const GemmEpi& e, int nb, int slot, int id,
           make_uint2(pack_op2<F16>(o[0], o[1]), pack_op2<F16>(o[2], o[3]));
     }
   } else {  // EPI_LOGITS: slot is the stream
+    // (with the logits the greatest of the block's 32 and its token, ties -> lower id, a NaN never: what is
+    // left for the argmax are vocab / 32 pairs)
+    float v = -INFINITY;
+    int token = 0x7fffffff;
+    auto take = [&](float x, int t) {
+      if (x > v || (x == v && t < token)) { v = x; token = t; }
+    };
+#pragma unroll
+    for (int i = 0; i < 16; ++i) take(acc[i], nb * 32 + 8 * (i >> 2) + 4 * g + (i & 3));
+    const float v2 = __shfl_xor(v, 32);
+    take(v2, __shfl_xor(token, 32));
+    if (g == 0) e.best[(size_t)slot * (e.vocab >> 5) + nb] = make_float2(v, __int_as_float(token));
     float* out = e.logits + (size_t)slot * e.logits_stride + nb * 32 + 4 * g;
 #pragma unroll
     for (int q4 = 0; q4 < 4; ++q4)
