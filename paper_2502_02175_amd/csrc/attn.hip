@@ -45,6 +45,20 @@ struct AttnArgs {
   int rows4_from;       // > 0: streams with at least this many rows are left to attn_rows4_kernel
 };
 
+// Two probabilities -> one operand dword.  They lie in [0, 256], so the fp16 conversion
+// (round to nearest even, as everywhere) needs no saturation.
+template <bool F16>
+__device__ inline uint32_t pack_p2(float lo, float hi) {
+  if constexpr (F16) {
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+    const f32x2 v = {lo, hi};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, f16x2));
+  } else {
+    return pack_op2<false>(lo, hi);
+  }
+}
+
 // Two workgroups per CU: the next tile's K lands in the registers of this one's, and the waves merge one
 // feature block each instead of one wave all of them, so that a wave keeps within 256 registers without
 // spills (364 before, one workgroup per CU: 288 workgroups of 9 query tiles x 32 heads took two rounds).
@@ -139,10 +153,10 @@ __global__ __launch_bounds__(256, 2) void attn_rows_kernel(AttnArgs a) {
     uint4 pb[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      pb[t].x = pack_op2<F16>(pr[8 * t + 0], pr[8 * t + 1]);
-      pb[t].y = pack_op2<F16>(pr[8 * t + 2], pr[8 * t + 3]);
-      pb[t].z = pack_op2<F16>(pr[8 * t + 4], pr[8 * t + 5]);
-      pb[t].w = pack_op2<F16>(pr[8 * t + 6], pr[8 * t + 7]);
+      pb[t].x = pack_p2<F16>(pr[8 * t + 0], pr[8 * t + 1]);
+      pb[t].y = pack_p2<F16>(pr[8 * t + 2], pr[8 * t + 3]);
+      pb[t].z = pack_p2<F16>(pr[8 * t + 4], pr[8 * t + 5]);
+      pb[t].w = pack_p2<F16>(pr[8 * t + 6], pr[8 * t + 7]);
     }
 #pragma unroll
     for (int ib = 0; ib < NI; ++ib) {
@@ -356,10 +370,10 @@ __global__ __launch_bounds__(64 * (MULTI ? kDecWavesMulti : kDecWaves)) void att
     uint4 pb[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      pb[t].x = pack_op2<F16>(s[8 * t + 0], s[8 * t + 1]);
-      pb[t].y = pack_op2<F16>(s[8 * t + 2], s[8 * t + 3]);
-      pb[t].z = pack_op2<F16>(s[8 * t + 4], s[8 * t + 5]);
-      pb[t].w = pack_op2<F16>(s[8 * t + 6], s[8 * t + 7]);
+      pb[t].x = pack_p2<F16>(s[8 * t + 0], s[8 * t + 1]);
+      pb[t].y = pack_p2<F16>(s[8 * t + 2], s[8 * t + 3]);
+      pb[t].z = pack_p2<F16>(s[8 * t + 4], s[8 * t + 5]);
+      pb[t].w = pack_p2<F16>(s[8 * t + 6], s[8 * t + 7]);
     }
 #pragma unroll
     for (int ib = 0; ib < NI; ++ib) {
@@ -408,20 +422,6 @@ __global__ __launch_bounds__(64 * (MULTI ? kDecWavesMulti : kDecWaves)) void att
     const float inv = 1.f / L;
     *(uint2*)(a.out + frag_off(b, (h0 + col) * HD + f, a.kc_out)) =
         make_uint2(pack_op2<F16>(acc.x * inv, acc.y * inv), pack_op2<F16>(acc.z * inv, acc.w * inv));
-  }
-}
-
-// Two probabilities -> one operand dword.  They lie in [0, 256], so the fp16 conversion
-// (round to nearest even, as everywhere) needs no saturation.
-template <bool F16>
-__device__ inline uint32_t pack_p2(float lo, float hi) {
-  if constexpr (F16) {
-    typedef float f32x2 __attribute__((ext_vector_type(2)));
-    typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-    const f32x2 v = {lo, hi};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, f16x2));
-  } else {
-    return pack_op2<false>(lo, hi);
   }
 }
 

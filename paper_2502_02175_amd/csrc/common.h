@@ -45,6 +45,13 @@ __device__ inline uint16_t f2h(float x) {  // fp32 -> fp16, round to nearest eve
   const _Float16 h = (_Float16)fminf(fmaxf(x, -65504.f), 65504.f);
   return __builtin_bit_cast(uint16_t, h);
 }
+// Two results of arithmetic at once (median and packed conversion: 3 instructions instead of 7; the same
+// bits as f2h of each for all inputs but signalling NaNs, which no arithmetic returns)
+typedef _Float16 f16x2v __attribute__((ext_vector_type(2)));
+__device__ inline uint32_t f2h2(float lo, float hi) {
+  const f32x2v v = {__builtin_amdgcn_fmed3f(lo, -65504.f, 65504.f), __builtin_amdgcn_fmed3f(hi, -65504.f, 65504.f)};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, f16x2v));
+}
 template <bool F16>
 __device__ inline uint16_t f2op(float x) {
   if constexpr (F16) return f2h(x);
@@ -52,7 +59,7 @@ __device__ inline uint16_t f2op(float x) {
 }
 template <bool F16>
 __device__ inline uint32_t pack_op2(float lo, float hi) {
-  if constexpr (F16) return (uint32_t)f2h(lo) | ((uint32_t)f2h(hi) << 16);
+  if constexpr (F16) return f2h2(lo, hi);
   else return f2bf2(lo, hi);
 }
 // Hand-over of partial results between workgroups (split-K sums, attention

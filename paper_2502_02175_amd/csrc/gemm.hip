@@ -46,10 +46,10 @@
 // fb and the row blocks follow from the row count, in the kernel where only the device knows it
 // (rows_cut): with two row blocks of 288 rows gate/up runs 230 workgroups of 6 feature blocks in one round
 // instead of 460 of 3 in two, and QKV, where the host knows the count, 256 of 3 instead of 384 of 2.
-// Four layers of 7B and the head, before and now: 288 rows known to
-// the host 1005 -> 874 us, 448 rows (many-rows kernel before) 1313 -> 1190; counted by the device 259 rows 1065 -> 1010,
-// 437 rows 1544 -> 1425.  (K of QKV or gate/up split over workgroups instead, the last wave to
-// arrive adding up: 3 us per hand-over, 288 rows -58 us where this gives -120, 109 rows +10.)
+// Four layers of 7B and the head, before and now (later steps of the other kernels included): 288 rows known
+// to the host 1005 -> 857 us, 448 rows (the many-rows kernel before) 1313 -> 1182; counted by the device
+// 259 rows 1065 -> 1000, 437 rows 1544 -> 1412.  (K of QKV or gate/up split over workgroups instead, the last
+// wave to arrive adding up: 3 us per hand-over, 288 rows -58 us where this gave -120, 109 rows +10.)
 // The arguments are read together at the start: the argument buffer lies in host memory, and an argument
 // that is first read later is a round trip there (decode, 32 streams of grouped queries 1545 -> 1522 us,
 // the tiny shape's step 284 -> 280, for the few-rows kernel and this one).
