@@ -205,8 +205,8 @@ int vlac_select_static(vlac_ctx* ctx, const uint8_t* frame_prev, const uint8_t* 
  * context's workspace: code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc.  Same arguments, same results bit for bit, but no context: n_layers (of
  * attn_mean, 1..512; ignored when attn_mean is NULL) is passed directly, and the scratch of
- * the three kernels (patch terms, scores, flags: 17 bytes per patch) lives in a fixed array
- * of VLAC_NOALLOC_MAX_PATCHES patches (1.1 MB) that the library's code object places in the
+ * the three kernels (patch terms, similarities, scores, flags: 25 bytes per patch) lives in a fixed array
+ * of VLAC_NOALLOC_MAX_PATCHES patches (1.6 MB) that the library's code object places in the
  * memory of every GPU it is loaded on, until the process ends.  The call makes no
  * allocation of any kind; B * L_v beyond the limit returns VLAC_E_RANGE (as do the argument
  * errors of vlac_select_static, with the same statuses), and nothing is queued then.

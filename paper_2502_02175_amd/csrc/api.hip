@@ -63,7 +63,7 @@ void free_all(vlac_ctx* c) {
   void* dev[] = {c->w_head, c->s_head, c->scale_tmp, c->wdeq, c->embed, c->g_final, c->rope_cos, c->rope_sin, c->h, c->hdec, c->xa, c->xf,
                  c->qbuf, c->partial, c->rpart, c->counters, c->rows, c->prev_slot, c->n_rows, c->slot_off, c->rank,
                  c->m_layer, c->n_rows_bl, c->statp, c->stat_counters, c->logits, c->head_best,
-                 c->dec_rows, c->terms, c->flags, c->embed_list, c->embed_n, c->relevance, c->entropy, c->ratio_counters, c->errword, c->scratch_i,
+                 c->dec_rows, c->terms, c->similar, c->flags, c->embed_list, c->embed_n, c->relevance, c->entropy, c->ratio_counters, c->errword, c->scratch_i,
                  c->zero_tile};
   for (void* p : dev) (void)hipFree(p);
   for (int i = 0; i < c->prof_cap; ++i) {
@@ -226,6 +226,7 @@ int vlac_create(const vlac_model_cfg* cfg, vlac_ctx** out) {
   A_(head_best, (size_t)mb * (m.vocab / 32));
   A_(dec_rows, (size_t)ms * mb + ms + (size_t)ms * (mb + 1));
   A_(terms, (size_t)mb * 4096 * 3);
+  A_(similar, (size_t)mb * 4096);
   A_(flags, (size_t)mb * 4096);
   A_(embed_list, (size_t)mb * 4096);
   A_(embed_n, mb);
@@ -479,9 +480,9 @@ int vlac_select_static(vlac_ctx* ctx, const uint8_t* frame_prev, const uint8_t* 
     n_rel = nr < 0 ? 0 : (nr > (double)L_v ? (int)L_v : (int)nr);
   }
   hipStream_t st = (hipStream_t)stream;
-  launch_patch_terms(frame_prev, frame_cur, B, H, W, patch, ctx->terms, attn_mean, ctx->cfg.n_layers, layer_mask,
-                     ctx->relevance, st);
-  launch_select(ctx->terms, B, (int)L_v, tau_num, tau_den, top_k, n_rel, ctx->flags, ctx->relevance, out_idx, out_order,
+  launch_patch_terms(frame_prev, frame_cur, B, H, W, patch, tau_num, tau_den, ctx->terms, ctx->similar, attn_mean,
+                     ctx->cfg.n_layers, layer_mask, ctx->relevance, st);
+  launch_select(ctx->terms, ctx->similar, B, (int)L_v, top_k, n_rel, ctx->flags, ctx->relevance, out_idx, out_order,
                 out_count, out_relevance, stride, st);
   VLAC_HIP(hipGetLastError());
   return VLAC_OK;

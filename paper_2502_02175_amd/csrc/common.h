@@ -214,6 +214,7 @@ struct vlac_ctx {
   // per-launch timing of one GEMM class (vlac_profile_select)
   int prof_kind, prof_n, prof_cap;
   hipEvent_t *prof_start, *prof_stop, *prof_mark;
+  double* similar;  // [max_batch, 4096] Sim^2 of every patch, -1 where it is below the threshold
 };
 
 #define VLAC_HIP(call)                         \
@@ -229,10 +230,10 @@ struct vlac_ctx {
 
 // select.hip
 // terms of every patch, and its score: attn_mean averaged over the layers of the mask (0 without attn_mean)
-void launch_patch_terms(const uint8_t* prev, const uint8_t* cur, int B, int H, int W, int patch, uint32_t* terms,
-                        const float* attn_mean, int n_layers, const uint8_t* layer_mask_host, float* score,
+void launch_patch_terms(const uint8_t* prev, const uint8_t* cur, int B, int H, int W, int patch, int tau_num, int tau_den,
+                        uint32_t* terms, double* similar, const float* attn_mean, int n_layers, const uint8_t* layer_mask_host, float* score,
                         hipStream_t st);
-void launch_select(const uint32_t* terms, int B, int L_v, int tau_num, int tau_den, int top_k, int n_rel,
+void launch_select(const uint32_t* terms, const double* similar, int B, int L_v, int top_k, int n_rel,
                    uint8_t* flags, const float* score, int32_t* out_idx, int32_t* out_order,
                    int32_t* out_count, float* out_relevance, int stride, hipStream_t st);
 int select_scratch_init();  // resolves the fixed scratch of vlac_select_static_noalloc on the current device; hipError_t

@@ -46,17 +46,26 @@ __device__ inline void relevance_scores(const float* __restrict__ attn_mean, int
   score[(size_t)b * L_v + j] = s;
 }
 
+struct Frac { uint64_t num, den; };  // Sim^2 as an exact fraction
+
+__device__ inline Frac sim_fraction(uint32_t dot, uint32_t na, uint32_t nb) {
+  // two all-zero patches are identical, exactly one all-zero patch is dissimilar
+  if (na == 0 && nb == 0) return {1, 1};
+  if (na == 0 || nb == 0) return {0, 1};
+  return {(uint64_t)dot * dot, (uint64_t)na * nb};
+}
+
 // ---------------------------------------------------------------------------
 // Eq. (sim) terms.  One workgroup per (patch row, stream); behind them in the grid the workgroups
 // that compute the scores, 256 patches each, beside the pixels instead of once per workgroup of
-// the ranking kernel (64 times per stream at 1024 patches: 59 us of ranking for 8 such streams,
-// 18 us now).
+// the ranking kernel (64 times per stream at 1024 patches: 59 us of ranking for 8 such streams then,
+// 18 without).
 // ---------------------------------------------------------------------------
 template <int VEC>
 __global__ __launch_bounds__(256) void patch_terms_kernel(const uint8_t* __restrict__ prev,
                                                           const uint8_t* __restrict__ cur, int H,
-                                                          int W, int patch,
-                                                          uint32_t* __restrict__ terms,
+                                                          int W, int patch, uint64_t tn2, uint64_t td2,
+                                                          uint32_t* __restrict__ terms, double* __restrict__ similar,
                                                           const float* __restrict__ attn_mean, int n_layers,
                                                           LayerMask layer_mask, float* __restrict__ score) {
   extern __shared__ uint32_t acc[];  // [gw][3]
@@ -127,23 +136,32 @@ __global__ __launch_bounds__(256) void patch_terms_kernel(const uint8_t* __restr
   const int Lv = gw * gh;
   for (int i = tid; i < gw * 3; i += 256)
     terms[((size_t)b * Lv + (size_t)pr * gw) * 3 + i] = acc[i];
+  // Sim^2 of every patch once, here, and not in every workgroup of the ranking kernel (64 times per stream at
+  // 1024 patches: ranking of 8 such streams 17.6 us, 14.7 now; this kernel 10.7, 10.9); -1: below the threshold
+  for (int j = tid; j < gw; j += 256) {
+    const Frac f = sim_fraction(acc[j * 3], acc[j * 3 + 1], acc[j * 3 + 2]);
+    const bool pass = (u128)f.num * td2 >= (u128)tn2 * f.den;
+    similar[(size_t)b * Lv + (size_t)pr * gw + j] = pass ? (double)f.num / (double)f.den : -1.0;
+  }
 }
 
-void launch_patch_terms(const uint8_t* prev, const uint8_t* cur, int B, int H, int W, int patch,
-                        uint32_t* terms, const float* attn_mean, int n_layers, const uint8_t* layer_mask_host,
+void launch_patch_terms(const uint8_t* prev, const uint8_t* cur, int B, int H, int W, int patch, int tau_num,
+                        int tau_den, uint32_t* terms, double* similar, const float* attn_mean, int n_layers, const uint8_t* layer_mask_host,
                         float* score, hipStream_t st) {
   const int gw = W / patch, gh = H / patch;
   LayerMask lm;
   for (int i = 0; i < 16; ++i) lm.w[i] = 0;
   for (int l = 0; l < n_layers && l < 512; ++l)
     if (!layer_mask_host || layer_mask_host[l]) lm.w[l >> 5] |= 1u << (l & 31);
+  const uint64_t tn2 = (uint64_t)tau_num * (uint64_t)tau_num;
+  const uint64_t td2 = (uint64_t)tau_den * (uint64_t)tau_den;
   const size_t shm = (size_t)gw * 3 * sizeof(uint32_t);
   const bool vec = ((size_t)patch * W * 3) % 16 == 0 && ((size_t)H * W * 3) % 16 == 0 &&
                    ((uintptr_t)prev % 16 == 0) && ((uintptr_t)cur % 16 == 0);
   dim3 grid(gh + (gw * gh + 255) / 256, B);
 #define VLAC_TERMS(VEC_)                                                                                        \
-  hipLaunchKernelGGL(patch_terms_kernel<VEC_>, grid, dim3(256), shm, st, prev, cur, H, W, patch, terms, attn_mean, \
-                     n_layers, lm, score)
+  hipLaunchKernelGGL(patch_terms_kernel<VEC_>, grid, dim3(256), shm, st, prev, cur, H, W, patch, tn2, td2, terms, \
+                     similar, attn_mean, n_layers, lm, score)
   if (vec) VLAC_TERMS(16);
   else VLAC_TERMS(1);
 #undef VLAC_TERMS
@@ -152,36 +170,24 @@ void launch_patch_terms(const uint8_t* prev, const uint8_t* cur, int B, int H, i
 // ---------------------------------------------------------------------------
 // Threshold, Top-k, relevance filter.
 // ---------------------------------------------------------------------------
-struct Frac { uint64_t num, den; };  // Sim^2 as an exact fraction
-
-__device__ inline Frac sim_fraction(uint32_t dot, uint32_t na, uint32_t nb) {
-  // two all-zero patches are identical, exactly one all-zero patch is dissimilar
-  if (na == 0 && nb == 0) return {1, 1};
-  if (na == 0 || nb == 0) return {0, 1};
-  return {(uint64_t)dot * dot, (uint64_t)na * nb};
-}
-
 // grid (ceil(L_v / 16), B).  flags[b, i] = 1 iff patch i is in P_final.
 // A workgroup ranks 256 / SEL_LPT patches, SEL_LPT lanes to a patch: every lane counts, over
 // its share of the other patches, those that come before its patch (by similarity for Top-k,
 // by score for the relevance quantile), and the counts are added up across the lanes
 // (integers: the result does not depend on how the patches are dealt).  Every workgroup
-// first builds the stream's similarities and scores in LDS, so many lanes per patch pay
+// first copies the stream's similarities and scores to LDS, so many lanes per patch pay
 // while the launch is small (16 lanes: 8 us instead of 46 us at one stream of 256 patches)
 // and one lane per patch is right once the streams alone fill the chip.
 template <int SEL_LPT>
 __global__ __launch_bounds__(256) void select_rank_kernel(
-    const uint32_t* __restrict__ terms, int L_v, uint64_t tn2, uint64_t td2, int top_k,
+    const uint32_t* __restrict__ terms, const double* __restrict__ similar, int L_v, int top_k,
     const float* __restrict__ relevance, int n_rel, uint8_t* __restrict__ flags) {
   __shared__ double approx[SEL_MAX_LV];
   __shared__ float score[SEL_MAX_LV];
-  __shared__ uint8_t pass[SEL_MAX_LV];
   const int b = blockIdx.y, tid = threadIdx.x;
   const uint32_t* t = terms + (size_t)b * L_v * 3;
   for (int j = tid; j < L_v; j += 256) {
-    const Frac f = sim_fraction(t[j * 3], t[j * 3 + 1], t[j * 3 + 2]);
-    pass[j] = (u128)f.num * td2 >= (u128)tn2 * f.den;
-    approx[j] = (double)f.num / (double)f.den;
+    approx[j] = similar[(size_t)b * L_v + j];
     score[j] = relevance[(size_t)b * L_v + j];
   }
   __syncthreads();
@@ -190,15 +196,16 @@ __global__ __launch_bounds__(256) void select_rank_kernel(
   const int i = blockIdx.x * SEL_PPW + tid / SEL_LPT;
   const bool live = i < L_v;           // (a patch's 16 lanes lie in one wave and leave together)
   const int ii = live ? i : 0;
-  const bool passed = pass[ii] && top_k > 0;
+  const bool passed = approx[ii] >= 0 && top_k > 0;
   int rank = 0, rr = 0;
   if (passed) {
     // rank among the passers: higher similarity first, ties -> lower index
     const double ai = approx[ii];
     const Frac fi = sim_fraction(t[ii * 3], t[ii * 3 + 1], t[ii * 3 + 2]);
     for (int j = sub; j < L_v; j += SEL_LPT) {
-      if (!pass[j] || j == ii) continue;
-      const double dlt = approx[j] - ai;
+      const double aj = approx[j];
+      if (aj < 0 || j == ii) continue;
+      const double dlt = aj - ai;
       bool beats;
       if (dlt > 1e-12) beats = true;
       else if (dlt < -1e-12) beats = false;
@@ -271,16 +278,14 @@ __global__ __launch_bounds__(256) void select_order_kernel(
   if (ord < stride) out_order[(size_t)b * stride + ord] = i;
 }
 
-void launch_select(const uint32_t* terms, int B, int L_v, int tau_num, int tau_den, int top_k, int n_rel,
+void launch_select(const uint32_t* terms, const double* similar, int B, int L_v, int top_k, int n_rel,
                    uint8_t* flags, const float* score, int32_t* out_idx, int32_t* out_order,
                    int32_t* out_count, float* out_relevance, int stride, hipStream_t st) {
-  const uint64_t tn2 = (uint64_t)tau_num * (uint64_t)tau_num;
-  const uint64_t td2 = (uint64_t)tau_den * (uint64_t)tau_den;
   const long long patches = (long long)B * L_v;
 #define VLAC_RANK(LPT_)                                                                            \
   {                                                                                                \
     const dim3 grid((L_v * LPT_ + 255) / 256, B);                                                   \
-    hipLaunchKernelGGL(select_rank_kernel<LPT_>, grid, dim3(256), 0, st, terms, L_v, tn2, td2, top_k, score, n_rel, \
+    hipLaunchKernelGGL(select_rank_kernel<LPT_>, grid, dim3(256), 0, st, terms, similar, L_v, top_k, score, n_rel, \
                        flags);                                                                      \
     hipLaunchKernelGGL(select_order_kernel<LPT_>, grid, dim3(256), 0, st, flags, score, L_v, out_idx, out_order, \
                        out_count, out_relevance, stride);                                           \
@@ -399,17 +404,18 @@ void launch_layer_ratio(const float* attn_mean, int n_layers, int B, int L_v, fl
 
 // ---------------------------------------------------------------------------
 // Alg. 1 for callers that cannot allocate: the same three kernels, with their scratch (the
-// patch terms, the score of every patch and the selection flags, which vlac_select_static
+// patch terms, the similarity and score of every patch and the selection flags, which vlac_select_static
 // keeps in its context) in a fixed array in device memory.  Every GPU holds its own copy of
 // the array at its own address; host code only ever uses the address that
 // hipGetSymbolAddress returns for the current device, never the array's name.  Nothing in
-// the array has to start at zero: patch_terms_kernel writes all terms and scores of the call's
+// the array has to start at zero: patch_terms_kernel writes all terms, similarities and scores of the call's
 // patches, select_rank_kernel all their flags, before anything reads them.
 // ---------------------------------------------------------------------------
 namespace {
 
 constexpr size_t kNoAllocPatches = VLAC_NOALLOC_MAX_PATCHES;
-constexpr size_t kTermsOff = 0;                                   // uint32 [patches][3]
+constexpr size_t kSimilarOff = 0;                                 // double [patches]
+constexpr size_t kTermsOff = kSimilarOff + kNoAllocPatches * 8;   // uint32 [patches][3]
 constexpr size_t kScoreOff = kTermsOff + kNoAllocPatches * 12;    // float  [patches]
 constexpr size_t kFlagsOff = kScoreOff + kNoAllocPatches * 4;     // uint8  [patches]
 constexpr size_t kScratchBytes = kFlagsOff + kNoAllocPatches;
@@ -475,13 +481,14 @@ extern "C" int vlac_select_static_noalloc(const uint8_t* frame_prev, const uint8
     (void)hipGetLastError();
     return VLAC_E_HIP;
   }
+  double* similar = (double*)(ws + kSimilarOff);
   uint32_t* terms = (uint32_t*)(ws + kTermsOff);
   float* score = (float*)(ws + kScoreOff);
   uint8_t* flags = (uint8_t*)(ws + kFlagsOff);
   hipStream_t st = (hipStream_t)stream;
-  launch_patch_terms(frame_prev, frame_cur, B, H, W, patch, terms, attn_mean, attn_mean ? n_layers : 0, layer_mask,
-                     score, st);
-  launch_select(terms, B, (int)L_v, tau_num, tau_den, top_k, n_rel, flags, score, out_idx, out_order, out_count,
+  launch_patch_terms(frame_prev, frame_cur, B, H, W, patch, tau_num, tau_den, terms, similar, attn_mean,
+                     attn_mean ? n_layers : 0, layer_mask, score, st);
+  launch_select(terms, similar, B, (int)L_v, top_k, n_rel, flags, score, out_idx, out_order, out_count,
                 out_relevance, stride, st);
   return hipGetLastError() == hipSuccess ? VLAC_OK : VLAC_E_HIP;
 }
