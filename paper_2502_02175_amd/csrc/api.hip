@@ -62,8 +62,8 @@ void free_all(vlac_ctx* c) {
   }
   void* dev[] = {c->w_head, c->s_head, c->scale_tmp, c->wdeq, c->embed, c->g_final, c->rope_cos, c->rope_sin, c->h, c->hdec, c->xa, c->xf,
                  c->qbuf, c->partial, c->rpart, c->counters, c->rows, c->prev_slot, c->n_rows, c->slot_off, c->rank,
-                 c->m_layer, c->n_rows_bl, c->statp, c->stat_counters, c->logits, c->head_best,
-                 c->dec_rows, c->terms, c->similar, c->flags, c->embed_list, c->embed_n, c->relevance, c->entropy, c->ratio_counters, c->errword, c->scratch_i,
+                 c->m_layer, c->n_rows_bl, c->statp, c->stat_counters, c->logits,
+                 c->dec_rows, c->similar, c->flags, c->embed_list, c->embed_n, c->relevance, c->entropy, c->ratio_counters, c->errword, c->scratch_i,
                  c->zero_tile};
   for (void* p : dev) (void)hipFree(p);
   for (int i = 0; i < c->prof_cap; ++i) {
@@ -222,11 +222,13 @@ int vlac_create(const vlac_model_cfg* cfg, vlac_ctx** out) {
   }
   A_(statp, ctx->statp_floats);
   A_(stat_counters, mb);
-  A_(logits, (size_t)mb * m.vocab);
-  A_(head_best, (size_t)mb * (m.vocab / 32));
+  // (one allocation each, as vlac_create is all allocations: the logits and the head's pairs, the similarities
+  // and the terms of the patches)
+  A_(logits, (size_t)mb * m.vocab + 2 * (size_t)mb * (m.vocab / 32));
+  ctx->head_best = ctx->logits ? (float2*)(ctx->logits + (size_t)mb * m.vocab) : nullptr;
   A_(dec_rows, (size_t)ms * mb + ms + (size_t)ms * (mb + 1));
-  A_(terms, (size_t)mb * 4096 * 3);
-  A_(similar, (size_t)mb * 4096);
+  A_(similar, (size_t)mb * 4096 + (size_t)mb * 4096 * 3 / 2);
+  ctx->terms = ctx->similar ? (uint32_t*)(ctx->similar + (size_t)mb * 4096) : nullptr;
   A_(flags, (size_t)mb * 4096);
   A_(embed_list, (size_t)mb * 4096);
   A_(embed_n, mb);
