@@ -201,9 +201,11 @@ __global__ __launch_bounds__(256, 2) void attn_rows_kernel(AttnArgs a) {
       const float m_new = fmaxf(m, m_w);
       const float a0 = exp2f(m - m_new), a1 = exp2f(m_w - m_new);
       m = m_new;
-      l = l * a0 + l_w * a1;
+      l = fmaf(l, a0, l_w * a1);
+      // (which of the two products is rounded is written out: left to the compiler it changed with the
+      // code around it, and with it the last bits of every result)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) acc[i] = acc[i] * a0 + t[i] * a1;
+      for (int i = 0; i < 16; ++i) acc[i] = fmaf(acc[i], a0, t[i] * a1);
     }
     const float inv = 1.f / l;
     if (w == 0) {
