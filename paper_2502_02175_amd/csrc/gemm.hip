@@ -27,7 +27,7 @@
 #include <cstring>
 #include "gemm_epi.h"
 
-// Workgroup: up to 6 consumer waves and 2 producer waves.  The consumers are fb feature blocks, or 2 of
+// Workgroup: up to 6 consumer waves and 2 producer waves.  The consumers are fb feature blocks, or 2 or 3 of
 // them x 2 parts of the K range (KP); a consumer streams the weight tiles of its block and part
 // into registers, UK k-tiles ahead, and multiplies them by up to 8 row tiles whose operands it
 // reads from LDS.  The producers copy those operands global -> LDS directly into a ring of
@@ -45,10 +45,10 @@
 // layers with the head 742 -> 628 us, 192 rows 908 -> 764.  32 weight tiles in flight: no faster.
 // fb and the row blocks follow from the row count, in the kernel where only the device knows it
 // (rows_cut): with two row blocks of 288 rows gate/up runs 230 workgroups of 6 feature blocks in one round
-// instead of 460 of 3 in two, and QKV, where the host knows the count, 256 of 3 instead of 384 of 2.
+// instead of 460 of 3 in two, and QKV 256 of 3 instead of 384 of 2, both with K in two parts.
 // Four layers of 7B and the head, before and now (later steps of the other kernels included): 288 rows known
-// to the host 1005 -> 857 us, 448 rows (the many-rows kernel before) 1313 -> 1182; counted by the device
-// 259 rows 1065 -> 1000, 437 rows 1544 -> 1412.  (K of QKV or gate/up split over workgroups instead, the last
+// to the host 1008 -> 865 us, 440 rows (the many-rows kernel before) 1314 -> 1176; counted by the device
+// 262 rows 1064 -> 936 (1008 with 2 blocks for QKV), 478 rows 1537 -> 1310 (1419).  (K of QKV or gate/up split over workgroups instead, the last
 // wave to arrive adding up: 3 us per hand-over, 288 rows -58 us where this gave -120, 109 rows +10.)
 // The arguments are read together at the start: the argument buffer lies in host memory, and an argument
 // that is first read later is a round trip there (decode, 32 streams of grouped queries 1545 -> 1522 us,
@@ -61,9 +61,11 @@
 constexpr int ROWS_RING = 5;       // chunks of at most 32 KiB: all 160 KiB of a CU's LDS
 constexpr int ROWS_FB_MIN = 2, ROWS_FB_MAX = 6;  // feature blocks per workgroup: 2 (K in two parts) or 3 to 6
 constexpr int ROWS_PAIR_NA = 6;  // most row tiles per wave with 2 feature blocks where others are in the choice
-// The forms of the kernel: 2 feature blocks per workgroup, up to 4, up to 6
-enum { ROWS_PAIRS = 2, ROWS_FOUR = 4, ROWS_SIX = 6 };
-constexpr int rows_consumers(int form) { return form == ROWS_SIX ? 6 : 4; }
+// The forms of the kernel.  K in two parts: 2 feature blocks per workgroup (projections with a residual), 2 or 3
+// (QKV, gate/up); K whole: up to 4, up to 6
+enum { ROWS_PAIRS = 2, ROWS_THREES = 3, ROWS_FOUR = 4, ROWS_SIX = 6 };
+constexpr int rows_parts(int form) { return form <= ROWS_THREES ? 2 : 1; }
+constexpr int rows_consumers(int form) { return form == ROWS_SIX || form == ROWS_THREES ? 6 : 4; }
 constexpr int rows_threads(int form) { return 64 * (rows_consumers(form) + 2); }
 
 template <int NA, int KP, bool W8>
@@ -174,7 +176,7 @@ __device__ __forceinline__ void rows_body(const GemmArgs& a, uint4* lds, RowsWei
   // of it and spill.)
   int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   asm volatile("" : "+v"(lane), "+s"(w), "+s"(tile), "+s"(s), "+s"(rt0));
-  const int part = KP == 2 ? w >> 1 : 0, nb = KP == 2 ? tile * 2 + (w & 1) : tile * fb + w, g = lane >> 5;
+  const int part = KP == 2 && w >= fb ? 1 : 0, nb = tile * fb + w - part * fb, g = lane >> 5;
   const bool wave_on = w < fb * KP && nb < a.NB;
   f32x16 acc[NA];
 #pragma unroll
@@ -274,9 +276,9 @@ __device__ __forceinline__ void rows_body(const GemmArgs& a, uint4* lds, RowsWei
     // (sum = first part + second part).
     constexpr int NH = (NA + 1) / 2;
     __syncthreads();
-    float* mine = (float*)lds + (size_t)(w & 3) * (NH * 16 * 64) + lane;
-    const float* theirs = (const float*)lds + (size_t)((w & 3) ^ 2) * (NH * 16 * 64) + lane;
-    if (w < 4) {
+    float* mine = (float*)lds + (size_t)w * (NH * 16 * 64) + lane;
+    const float* theirs = (const float*)lds + (size_t)(part ? w - fb : w + fb) * (NH * 16 * 64) + lane;
+    if (w < 2 * fb) {
 #pragma unroll
       for (int m = 0; m < NA; ++m)
         if ((m >= NH) != (part == 1)) {
@@ -285,7 +287,7 @@ __device__ __forceinline__ void rows_body(const GemmArgs& a, uint4* lds, RowsWei
         }
     }
     __syncthreads();
-    if (w < 4) {
+    if (w < 2 * fb) {
 #pragma unroll
       for (int m = 0; m < NA; ++m)
         if ((m >= NH) == (part == 1)) {
@@ -349,6 +351,7 @@ __global__ __launch_bounds__(rows_threads(FORM)) void gemm_rows_kernel(GemmArgs 
   read_args(a.xp, a.e.rows);
   RowsWeights<W8> W;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  constexpr int KP = rows_parts(FORM);
   constexpr int FB = FORM == ROWS_PAIRS ? 2 : EPI == EPI_RESID || EPI == EPI_LOGITS ? 4 : 0;  // (one for all counts)
   int n_rows = a.n_rows_val, n_rt = 0, n_blk = 1, mb = 0, fb = FB ? FB : a.fb_first, tile, s;
 #pragma unroll 1
@@ -372,10 +375,10 @@ __global__ __launch_bounds__(rows_threads(FORM)) void gemm_rows_kernel(GemmArgs 
     }
     tile = __builtin_amdgcn_readfirstlane(p / a.S);
     s = __builtin_amdgcn_readfirstlane(p - tile * a.S);
-    constexpr int KP = FORM == ROWS_PAIRS ? 2 : 1;
     if (w < fb * KP && tile * fb < a.NB) {
-      const RowsRange rg = rows_range(a.KS, a.S * KP, s * KP + (KP == 2 ? w >> 1 : 0));
-      const int nb = min(tile * fb + (KP == 2 ? w & 1 : w), a.NB - 1), kc = W8 ? 2 * a.KS : 4 * a.KS, k0 = W8 ? rg.k0 / 2 : rg.k0;
+      const int part = KP == 2 && w >= fb ? 1 : 0;
+      const RowsRange rg = rows_range(a.KS, a.S * KP, s * KP + part);
+      const int nb = min(tile * fb + w - part * fb, a.NB - 1), kc = W8 ? 2 * a.KS : 4 * a.KS, k0 = W8 ? rg.k0 / 2 : rg.k0;
       const uint4* src = a.wp + (size_t)nb * kc * 64 + (threadIdx.x & 63);
       // (past the end of K the last tile is read again and not used)
 #pragma unroll
@@ -386,13 +389,12 @@ __global__ __launch_bounds__(rows_threads(FORM)) void gemm_rows_kernel(GemmArgs 
     n_rows = ld_scalar(a.n_rows);
   }
   if (!FB) fb = __builtin_amdgcn_readfirstlane(fb);
-  if (FORM != ROWS_PAIRS && w >= fb && w < rows_consumers(FORM)) return;  // no feature block for this wave
+  if (FORM != ROWS_PAIRS && w >= fb * KP && w < rows_consumers(FORM)) return;  // no feature block for this wave
   tile = __builtin_amdgcn_readfirstlane(tile);
   s = __builtin_amdgcn_readfirstlane(s);
   const int rt0 = __builtin_amdgcn_readfirstlane(mb * n_rt / n_blk);
   const int rt1 = __builtin_amdgcn_readfirstlane((mb + 1) * n_rt / n_blk), row_end = min(n_rows, 32 * rt1);
 #define VLAC_NA(N) rows_body<N, KP, FORM, EPI, F16, W8>(a, lds, W, fb, tile, s, rt0, row_end)
-  constexpr int KP = FORM == ROWS_PAIRS ? 2 : 1;
   switch (rt1 - rt0) {
     case 1: VLAC_NA(1); break;
     case 2: VLAC_NA(2); break;
@@ -669,7 +671,7 @@ int gemm_init() {
 #define VLAC_SET(FORM)                                                    \
   if ((e = set_attr<FORM, EPI_QKV>()) != hipSuccess) return (int)e;       \
   if ((e = set_attr<FORM, EPI_SWIGLU>()) != hipSuccess) return (int)e;
-  VLAC_SET(ROWS_PAIRS) VLAC_SET(ROWS_FOUR) VLAC_SET(ROWS_SIX)
+  VLAC_SET(ROWS_THREES) VLAC_SET(ROWS_FOUR) VLAC_SET(ROWS_SIX)
   if ((e = set_attr<ROWS_PAIRS, EPI_RESID>()) != hipSuccess) return (int)e;
   if ((e = set_attr<ROWS_FOUR, EPI_RESID>()) != hipSuccess) return (int)e;
   if ((e = set_attr<ROWS_FOUR, EPI_LOGITS>()) != hipSuccess) return (int)e;
@@ -677,16 +679,19 @@ int gemm_init() {
   return gemm_tall_init();
 }
 
+template <int FORM, int EPI, bool F16, bool W8>
+static void launch_rows_one(const GemmArgs& a, int grid, hipStream_t st) {
+  hipLaunchKernelGGL((gemm_rows_kernel<FORM, EPI, F16, W8>), dim3(grid), dim3(rows_threads(FORM)), kRowsLds, st, a);
+}
+// (QKV and gate/up have no form of pairs, the projections with a residual 2 or 4 feature blocks, the head 4)
 template <int FORM, bool F16, bool W8>
 static void launch_rows(int epi, const GemmArgs& a, int grid, hipStream_t st) {
-  constexpr int ONE = FORM == ROWS_PAIRS ? ROWS_PAIRS : ROWS_FOUR;  // (projections with a residual: 2 or 4)
-  const dim3 g(grid), t(rows_threads(FORM));
+  constexpr int MANY = FORM == ROWS_PAIRS ? ROWS_THREES : FORM, RESID = FORM == ROWS_PAIRS ? ROWS_PAIRS : ROWS_FOUR;
   switch (epi) {
-    case EPI_QKV: hipLaunchKernelGGL((gemm_rows_kernel<FORM, EPI_QKV, F16, W8>), g, t, kRowsLds, st, a); break;
-    case EPI_RESID: hipLaunchKernelGGL((gemm_rows_kernel<ONE, EPI_RESID, F16, W8>), g, dim3(rows_threads(ONE)), kRowsLds, st, a); break;
-    case EPI_SWIGLU: hipLaunchKernelGGL((gemm_rows_kernel<FORM, EPI_SWIGLU, F16, W8>), g, t, kRowsLds, st, a); break;
-    default:  // (always 4 feature blocks)
-      hipLaunchKernelGGL((gemm_rows_kernel<ROWS_FOUR, EPI_LOGITS, F16, W8>), g, dim3(rows_threads(ROWS_FOUR)), kRowsLds, st, a); break;
+    case EPI_QKV: launch_rows_one<MANY, EPI_QKV, F16, W8>(a, grid, st); break;
+    case EPI_RESID: launch_rows_one<RESID, EPI_RESID, F16, W8>(a, grid, st); break;
+    case EPI_SWIGLU: launch_rows_one<MANY, EPI_SWIGLU, F16, W8>(a, grid, st); break;
+    default: launch_rows_one<ROWS_FOUR, EPI_LOGITS, F16, W8>(a, grid, st); break;
   }
 }
 
@@ -806,46 +811,48 @@ SplitAdapt gemm_resid_adapt(vlac_ctx* c, int n_blocks, int kpad, int rows_cap, c
 static const int kRowsPairTiles = 128;
 
 // How the one-stream kernel cuts `rt` row tiles (at most 32: 1023 rows) and NB feature blocks: blocks of
-// at most 6 or 8 row tiles, 2 to 6 feature blocks per workgroup (the projections with a residual: as
-// given, with their S splits).  A workgroup takes a CU's whole LDS, so what counts is rounds of 256
-// workgroups x what a workgroup fetches per k (its weight rows, a block's operand rows; a CU fetches
-// about 50 GB/s with weights from HBM and row operands from L2 in one queue).
-// (2 feature blocks take K in two parts and half as many k-tiles per barrier: 7 row tiles of 7B QKV
-// are faster with 3 in two blocks, 6 with 2)
-static RowsCut rows_cut(int epi, int NB, int KS, int S, int rt, int k_parts, int* code) {
-  RowsCut best = {0, 0};
-  int least = 0x7fffffff;
-  const int fix = epi == EPI_LOGITS ? 4 : epi == EPI_RESID ? rows_resid_fb(NB, KS) : k_parts == 2 ? 2 : 0;
-  for (int fb = ROWS_FB_MIN; fb <= ROWS_FB_MAX; ++fb) {
-    if (fix && fb != fix) continue;
+// at most 6 or 8 row tiles, feature blocks per workgroup 2 or 3 with K in two parts and 3 to 6 with K whole (the
+// projections with a residual: as given, with their S splits).  A workgroup takes a CU's whole LDS, so
+// what counts is rounds of 256 workgroups x what a workgroup fetches per k (its weight rows, a block's
+// operand rows; a CU fetches about 50 GB/s with weights from HBM and row operands from L2 in one queue).
+// (7 row tiles of 7B QKV are faster with 3 feature blocks in two row blocks than with 2 in one, 6 with 2)
+struct RowsChoice { RowsCut cut; int code, cost; };
+static RowsChoice rows_cut(int epi, int NB, int KS, int S, int rt, int k_parts) {
+  RowsChoice best = {{0, 0}, 0, 0x7fffffff};
+  const bool pairs_only = rows_tiles(NB, 2) < kRowsPairTiles;
+  const int fix = epi == EPI_LOGITS ? 4 : epi == EPI_RESID ? rows_resid_fb(NB, KS) : 0;
+  const int lo = fix ? fix : k_parts == 2 ? 2 : 3, hi = fix ? fix : k_parts == 1 ? ROWS_FB_MAX : pairs_only ? 2 : 3;
+  for (int fb = lo; fb <= hi; ++fb) {
     for (int eight = 0; eight < 2; ++eight) {
       const int n = eight ? (rt + 7) / 8 : (rt + 5) / 6, na = (rt + n - 1) / n;
-      if (!fix && fb == 2 && (k_parts == 1 || na > ROWS_PAIR_NA)) continue;
+      if (fb == 2 && hi > 2 && na > ROWS_PAIR_NA) continue;
       const int cost = (rows_tiles(NB, fb) * S * n + 255) / 256 * (fb + na) + n - 1;
-      if (cost < least) {
-        least = cost;
-        best = {fb, n};
-        *code = (fb - ROWS_FB_MIN) << 1 | eight;
-      }
+      if (cost < best.cost) best = {{fb, n}, (fb - ROWS_FB_MIN) << 1 | eight, cost};
     }
   }
   return best;
+}
+
+// K in two parts where two feature blocks per workgroup fit one round of the chip.  It is so for every row count
+// that the device decides, so that a row's result does not depend on how many others are recomputed; where the host
+// knows the count K may stay whole if that is cheaper (8-bit weights, 600 rows of 7B: QKV in one round instead of two).
+static int rows_k_parts(int epi, int NB, int KS, int rt_known) {
+  if (NB > 512) return 1;
+  if (!rt_known || rows_tiles(NB, 2) < kRowsPairTiles) return 2;
+  return rows_cut(epi, NB, KS, 1, rt_known, 1).cost < rows_cut(epi, NB, KS, 1, rt_known, 2).cost ? 1 : 2;
 }
 
 // the one-stream kernel for up to rows_cap rows; sets and returns a.S
 static int launch_rows_kernel(vlac_ctx* c, int epi, GemmArgs& a, int rows_cap, const GemmEpi& e, hipStream_t st) {
   a.S = rows_kernel_splits(c, epi, a.NB, a.KS, e.rpart_rows, e.d_model, rows_cap, a.n_rows_val >= 0);
   const int rt_cap = std::min((rows_cap + 31) / 32, 32), rt_known = a.n_rows_val >= 0 ? (a.n_rows_val + 31) / 32 : 0;
-  // K in two parts or not: where the device counts the rows, one or the other for every count, as few
-  // rows have it, so that a row's result does not depend on how many others are recomputed
-  int code = 0, k_parts = 0;
-  if (rows_tiles(a.NB, 2) < kRowsPairTiles) k_parts = 2;
-  else if (!rt_known) k_parts = rows_cut(epi, a.NB, a.KS, a.S, std::min(rt_cap, 4), 0, &code).fb == 2 ? 2 : 1;
+  const int k_parts = rows_k_parts(epi, a.NB, a.KS, rt_known);
   a.cut[0] = a.cut[1] = 0;
   int grid = 0, fb_most = 0;
   for (int rt = rt_known ? rt_known : 1; rt <= (rt_known ? rt_known : rt_cap); ++rt) {
-    const RowsCut cut = rows_cut(epi, a.NB, a.KS, a.S, rt, k_parts, &code);
-    a.cut[(rt - 1) >> 4] |= (uint64_t)code << (4 * ((rt - 1) & 15));
+    const RowsChoice ch = rows_cut(epi, a.NB, a.KS, a.S, rt, k_parts);
+    const RowsCut cut = ch.cut;
+    a.cut[(rt - 1) >> 4] |= (uint64_t)ch.code << (4 * ((rt - 1) & 15));
     if (rt <= 4) a.fb_first = cut.fb;  // (what few rows usually get)
     fb_most = std::max(fb_most, cut.fb);
     grid = std::max(grid, (rows_tiles(a.NB, cut.fb) * a.S + 7) / 8 * 8 * cut.blocks);
@@ -856,7 +863,9 @@ static int launch_rows_kernel(vlac_ctx* c, int epi, GemmArgs& a, int rows_cap, c
     else if (c->f16) launch_rows<FORM_, true, false>(epi, a, grid, st);            \
     else launch_rows<FORM_, false, false>(epi, a, grid, st);                       \
   }
-  if (fb_most == 2) VLAC_ROWS(ROWS_PAIRS)
+  if (epi == EPI_LOGITS || (epi == EPI_RESID && fb_most == 4)) VLAC_ROWS(ROWS_FOUR)
+  else if (epi == EPI_RESID) VLAC_ROWS(ROWS_PAIRS)
+  else if (k_parts == 2) VLAC_ROWS(ROWS_THREES)
   else if (fb_most <= 4) VLAC_ROWS(ROWS_FOUR)
   else VLAC_ROWS(ROWS_SIX)
 #undef VLAC_ROWS

@@ -48,3 +48,28 @@ def test_feature_blocks_by_row_count(d, F, hq, operand):
                 assert np.abs(got["hidden"][b][alive] - want["hidden"][alive]).max() <= TOL[operand], (reused, b)
     finally:
         gm.close()
+
+
+@pytest.mark.parametrize("operand", ["f16", "bf16", "f16w8"])
+def test_rows_do_not_depend_on_who_counts_them(operand):
+    """K and V of the first layer come from the embeddings through QKV alone (264 feature blocks, K in two
+    parts), so a full recompute (rows counted by the host) and a pass with reuse lists of which no
+    entry is used (the same rows, counted on the device) must leave the same cache bit for bit."""
+    import torch
+    d, F, hq, n_txt = 320, 272, 128, 8
+    cfg = synth.ModelCfg(1, d, hq, 2, 64, F, 96)
+    gm = GpuModel(cfg, seed=6, max_batch=1, max_seq=512, std=1.0 / np.sqrt(d), operand=operand)
+    rng = np.random.default_rng(7)
+    try:
+        emb = synth.round_bf16(rng.standard_normal((504, d)))
+        # (from 449 rows on a known count of this shape takes K whole, which is the cheaper cut there)
+        for L in (64, 192, 193, 224, 257, 288, 289, 352, 384, 385, 448):
+            one = emb[None, -L:]
+            gm.prefill(one, L - n_txt)
+            known = gm.kv.clone()
+            gm.prefill(one + np.float32(0.25), L - n_txt)
+            assert not torch.equal(gm.kv, known), L
+            gm.prefill(one, L - n_txt, [list(range(L // 2))], [[0]])
+            assert torch.equal(gm.kv, known), L
+    finally:
+        gm.close()
