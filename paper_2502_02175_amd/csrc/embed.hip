@@ -63,6 +63,7 @@ typedef uint32_t u32x4_u __attribute__((ext_vector_type(4), aligned(1)));
 // patch + 32 (k/8 % 2)).  KS = 1: a wave multiplies them by 128 features of its own; KS = 4: the
 // waves share 128 features, take a quarter of the k-tiles each, and their sums meet in LDS, which
 // gives a small call four times the workgroups and a quarter of the chain.
+// TWO: few patches of an even width in a frame at an even address, see the staging.
 // A wave's operand tile t (of 4) covers the features 4 j + t, j = lane % 32: a lane then reads
 // 4 neighbouring features of a weight row with one 8-byte load (w_proj is [k][feature], so the 8
 // values of k that an operand wants are 8 loads, 8 rows of it, and two byte permutations per
@@ -78,7 +79,7 @@ typedef uint32_t u32x4_u __attribute__((ext_vector_type(4), aligned(1)));
 // staging 13 us, products 28, output 15 of the 67 at 8 x 1024.
 // (EMB_D k-tiles of weights in flight per wave: with 2 row tiles only 2, so that a
 // second workgroup fits the CU: 85 -> 72 us per call at 8 x 1024 patches)
-template <int RT, int KS, bool VEC>
+template <int RT, int KS, bool VEC, bool TWO>
 __global__ __launch_bounds__(256, 2) void embed_patches_kernel(const uint8_t* __restrict__ frame, int H, int W,
                                                             int patch, const bf16_t* __restrict__ w_proj,
                                                             int d, const int* __restrict__ list,
@@ -140,7 +141,7 @@ __global__ __launch_bounds__(256, 2) void embed_patches_kernel(const uint8_t* __
     // before), several loads in flight; PAIRS: two pixels per store (even patches: every row starts at an
     // even k).  The first weights are asked for behind the first pixels, which are used first.
     auto stage = [&](auto pairs) {
-      constexpr int U = RT == 1 ? 6 : 4;  // (14 x 14 pixels: all of a thread's loads at once, or in three groups)
+      constexpr int U = RT == 1 ? 6 : 4;  // (loads in flight: 14 x 14 pixels in three groups, 13 x 13 of few patches at once)
       const int n_ch = (prow + 15) >> 4, n_q = patch * n_ch, inv = (65536 + n_ch - 1) / n_ch;  // (n_q <= 130)
       u32x4_u v[U];
       int k[U];
@@ -179,9 +180,10 @@ __global__ __launch_bounds__(256, 2) void embed_patches_kernel(const uint8_t* __
         store(q);
       }
     };
-    if (RT == 1 && (patch & 1) == 0 && ((uintptr_t)frame & 1) == 0) {
-      // (few patches, rows on even addresses: two-byte loads, seven in flight, behind the first weights.  With
-      // the 16-byte loads below 166 patches of one stream took 10.9 us, so 9.9; 12 streams of 90 patches 23.2 and 21.4)
+    if constexpr (TWO) {
+      // (few patches of rows on even addresses: two-byte loads, seven in flight, behind the first weights, in an
+      // instance of their own.  166 patches of one stream 10.0 -> 9.6 us, 12 streams of 90 patches 20.4 -> 19.7
+      // against one instance with both ways in it, whose 224 registers are 172 here; with the 16-byte loads 10.9 and 23.2)
       first_weights();
       for (int y = q0; y < patch && p < cnt; y += STEP) {
         const uint8_t* row = src + y * pitch;
@@ -323,10 +325,11 @@ static size_t embed_lds(int RT, int KS, int dp) {
 
 int embed_init() {
   hipError_t e;
-#define VLAC_EMB_SET(RT_, KS_, VEC_)                                                                     \
-  if ((e = hipFuncSetAttribute((const void*)embed_patches_kernel<RT_, KS_, VEC_>,                         \
+#define VLAC_EMB_SET(RT_, KS_, VEC_, TWO_)                                                               \
+  if ((e = hipFuncSetAttribute((const void*)embed_patches_kernel<RT_, KS_, VEC_, TWO_>,                   \
                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)) != hipSuccess) return (int)e;
-  VLAC_EMB_SET(1, 4, true) VLAC_EMB_SET(1, 4, false) VLAC_EMB_SET(2, 1, true) VLAC_EMB_SET(2, 1, false)
+  VLAC_EMB_SET(1, 4, true, true) VLAC_EMB_SET(1, 4, false, true) VLAC_EMB_SET(1, 4, true, false)
+  VLAC_EMB_SET(1, 4, false, false) VLAC_EMB_SET(2, 1, true, false) VLAC_EMB_SET(2, 1, false, false)
 #undef VLAC_EMB_SET
   return 0;
 }
@@ -347,14 +350,16 @@ void launch_embed_patches(vlac_ctx* c, const uint8_t* frame, int B, int H, int W
   const bool wide = (long long)((d + 511) / 512) * ((L_v + 63) / 64) * B >= kEmbWide && embed_lds(2, 1, dp) <= 80 * 1024;
   // (8-byte weight loads and 16-byte stores where the caller's buffers allow them)
   const bool vec = (uintptr_t)w_proj % 8 == 0 && (uintptr_t)embeds % 16 == 0;
-#define VLAC_EMB(RT_, KS_, VEC_)                                                                           \
-  hipLaunchKernelGGL((embed_patches_kernel<RT_, KS_, VEC_>),                                               \
+#define VLAC_EMB(RT_, KS_, VEC_, TWO_)                                                                     \
+  hipLaunchKernelGGL((embed_patches_kernel<RT_, KS_, VEC_, TWO_>),                                         \
                      dim3((d + 512 / KS_ - 1) / (512 / KS_), (L_v + 32 * RT_ - 1) / (32 * RT_), B), dim3(256), \
                      embed_lds(RT_, KS_, dp), st, frame, H, W, patch, w_proj, d, c->embed_list, c->embed_n, embeds, L)
   if (wide) {
-    if (vec) VLAC_EMB(2, 1, true); else VLAC_EMB(2, 1, false);
+    if (vec) VLAC_EMB(2, 1, true, false); else VLAC_EMB(2, 1, false, false);
+  } else if ((patch & 1) == 0 && ((uintptr_t)frame & 1) == 0) {
+    if (vec) VLAC_EMB(1, 4, true, true); else VLAC_EMB(1, 4, false, true);
   } else {
-    if (vec) VLAC_EMB(1, 4, true); else VLAC_EMB(1, 4, false);
+    if (vec) VLAC_EMB(1, 4, true, false); else VLAC_EMB(1, 4, false, false);
   }
 #undef VLAC_EMB
 }

@@ -36,3 +36,11 @@ def test_the_one_stream_gemm_does_not_spill():
     assert len(mine) == 27  # feature blocks, epilogues, operand types
     for n, k in mine.items():
         assert k[".private_segment_fixed_size"] == 0 and k[".vgpr_spill_count"] == 0, n
+
+
+def test_the_embedding_of_few_patches_keeps_one_way_of_staging():
+    """With the two-byte and the 16-byte staging in one instance it takes 224 registers and 0.5 us more of 10."""
+    mine = {n: k for n, k in kernels().items() if "embed_patches_kernelILi1E" in n}
+    two = [k[".vgpr_count"] for n, k in mine.items() if "ELb1EEv" in n]
+    assert len(mine) == 4 and len(two) == 2
+    assert max(two) <= 192 and all(k[".vgpr_spill_count"] == 0 for k in mine.values())
