@@ -27,6 +27,7 @@ def _run(cmd):
 # same library with those sources compiled with -DVLAC_SAFE_WAITS (every such wait is for all
 # outstanding loads): a checking aid that a GPU test compares with libvlac.so bit for bit.
 HAND_WAITS = ["gemm.hip", "gemm_tall.hip", "attn.hip"]
+CHECKS = ["convert_check.hip"]  # kernels that only tests call: linked into libvlac_safe.so
 LIB_SAFE = os.path.join(HERE, "libvlac_safe.so")
 
 
@@ -35,12 +36,13 @@ def build(verbose=False):
     os.makedirs(OBJ, exist_ok=True)
     jobs = [(s, os.path.join(OBJ, s.replace(".hip", ".o")), []) for s in SOURCES]
     jobs += [(s, os.path.join(OBJ, s.replace(".hip", ".safe.o")), ["-DVLAC_SAFE_WAITS"]) for s in HAND_WAITS]
+    checks = [(s, os.path.join(OBJ, s.replace(".hip", ".o")), []) for s in CHECKS]
     with ThreadPoolExecutor(max_workers=8) as ex:
-        list(ex.map(lambda j: _run([hipcc, *FLAGS, *j[2], "-c", os.path.join(SRC, j[0]), "-o", j[1]]), jobs))
+        list(ex.map(lambda j: _run([hipcc, *FLAGS, *j[2], "-c", os.path.join(SRC, j[0]), "-o", j[1]]), jobs + checks))
     objs = [j[1] for j in jobs if not j[2]]
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs])
     safe = [o.replace(".o", ".safe.o") if os.path.basename(o).replace(".o", ".hip") in HAND_WAITS else o for o in objs]
-    _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB_SAFE, *safe])
+    _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB_SAFE, *safe, *(j[1] for j in checks)])
     if verbose:
         print("built", LIB, "and", LIB_SAFE)
     return LIB

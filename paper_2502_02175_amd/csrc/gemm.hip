@@ -725,7 +725,9 @@ bool gemm_can_fuse_norm(int n_rows_host, int decode_pos, int kpad) {
 // sparse prefill is known on the device only) the GEMMs go to the kernel built for matrix-core bound
 // work.  Full recomputes, four layers and the head, many-rows against one-stream kernel: 7B, 352 rows
 // 1069 and 941 us, 448 rows 1211 and 1154, 500 rows 1376 and 1323; grouped queries, 380 rows 589
-// and 472, 500 rows 636 and 578.  (Weights stored as e4m3 codes: the many-rows kernel has
+// and 472, 500 rows 636 and 578.  Decode passes of many streams, four layers, two tokens of 7B: 353 streams 3404 and 2960,
+// 400 streams 3708 and 3427, 500 streams 4260 and 4077; three tokens of grouped queries: 353 streams
+// 1918 and 1492, 500 streams 2157 and 1933.  (Weights stored as e4m3 codes: the many-rows kernel has
 // no variant for them; up to 1023 rows stay with the one-stream kernel, from 1024 rows on
 // the matrix is expanded to fp16 before every launch, 3 bytes of traffic per weight
 // against the 2 rows flops per weight that such a launch spends on it.)
@@ -758,10 +760,10 @@ static int rows_blocks_max(int rows) { return ((rows + 31) / 32 + 5) / 6; }
 // one block a workgroup per CU, two blocks took two rounds: grouped queries with 8-bit weights, 28
 // layers, 384 rows 3607 us, now 3226; at most 288 rows, 262 recomputed, 3230 and 2825.)
 // The others do not split over workgroups: a hand-over between them costs more than idle CUs.
-static int rows_kernel_splits(const vlac_ctx* c, int epi, int n_blocks, int KS, int rpart_rows, int d_model, int rows_cap,
+static int rows_kernel_splits(const vlac_ctx* c, int epi, int n_blocks, int KS, int rpart_rows, int d_model, int rows_most,
                               bool known) {
   if (epi != EPI_RESID) return 1;
-  const int tiles = rows_tiles(n_blocks, rows_resid_fb(n_blocks, KS)), most = rows_blocks_max(rows_cap);
+  const int tiles = rows_tiles(n_blocks, rows_resid_fb(n_blocks, KS)), most = rows_blocks_max(rows_most);
   int best = 1, least = 0x7fffffff;
   for (int S = 1; S <= 8 && S <= std::max(KS / 4, 1) && (size_t)S * rpart_rows * d_model <= c->rpart_floats; ++S) {
     int cost = 0;
@@ -774,11 +776,19 @@ static int rows_kernel_splits(const vlac_ctx* c, int epi, int n_blocks, int KS, 
 // Where the many-rows kernel serves a capacity at which a sparse prefill usually leaves few rows
 // (the count is known on the device only), BOTH kernels are launched for a GEMM: up to
 // kSmallRows - 1 rows the one-stream kernel works, from there on the other, and the idle one leaves at
-// once, which costs 3 us per GEMM.  So both are launched only where the reuse lists are long enough to
+// once, which costs 3 us per GEMM (456 rows, 7B: 1346 us for four layers and the head without the idle one, 1357
+// with it).  So both are launched only where the reuse lists are long enough to
 // leave fewer than kFewRows rows (top-k 100 of two camera views is not), and up to a capacity
 // of 767 rows: at 70 % static about 0.38 of it is recomputed, more than that and the second launch would
-// mostly be the idle one.  Two streams of 288 tokens, four layers and the head, one-stream against
-// many-rows kernel: 7B, about 142 rows 742 and 964 us, 218 rows 879 and 1036; for more see kTallRows.
+// mostly be the idle one.  Two streams of 288 tokens with long lists used in part (rows counted on the
+// device), four layers and the head, one-stream against many-rows kernel, us:
+//   rows        258          320          384          448
+//   7B f16      945 1110     991 1142    1085 1199    1180 1337
+//   7B bf16                  (296 rows: 958 1129)    1061 1175    1149 1311
+//   grouped q.  437  610     454  616     494  626     516  656
+// (7B, about 142 rows 742 and 964, 218 rows 879 and 1036; one stream of 720 tokens, 270 rows 1005 and 1164, 420 rows
+// 1216 and 1387.)  The K splits of the one-stream kernel are those of up to kFewRows - 1 rows, which is what
+// such a call usually has (chosen over all counts up to kSmallRows - 1, grouped queries took 479 us at 258 rows, 543 at 384).
 static const int kSmallRows = 449, kFewRows = 257;
 // (Rows longer than 8192 elements: the row kernel that adds the partial rows up there takes a
 // fixed split factor, so the choice between two kernels with different factors is not offered.)
@@ -800,7 +810,7 @@ SplitAdapt gemm_resid_adapt(vlac_ctx* c, int n_blocks, int kpad, int rows_cap, c
     ad.KS = kpad / 64;
     if (both) {
       ad.small_below = kSmallRows;
-      ad.S_small = rows_kernel_splits(c, EPI_RESID, n_blocks, kpad / 64, rows_cap, d_model, kSmallRows - 1, false);
+      ad.S_small = rows_kernel_splits(c, EPI_RESID, n_blocks, kpad / 64, rows_cap, d_model, kFewRows - 1, false);
     }
   }
   return ad;
@@ -842,9 +852,9 @@ static int rows_k_parts(int epi, int NB, int KS, int rt_known) {
   return rows_cut(epi, NB, KS, 1, rt_known, 1).cost < rows_cut(epi, NB, KS, 1, rt_known, 2).cost ? 1 : 2;
 }
 
-// the one-stream kernel for up to rows_cap rows; sets and returns a.S
-static int launch_rows_kernel(vlac_ctx* c, int epi, GemmArgs& a, int rows_cap, const GemmEpi& e, hipStream_t st) {
-  a.S = rows_kernel_splits(c, epi, a.NB, a.KS, e.rpart_rows, e.d_model, rows_cap, a.n_rows_val >= 0);
+// the one-stream kernel for up to rows_cap rows, K split as for up to rows_split of them; sets and returns a.S
+static int launch_rows_kernel(vlac_ctx* c, int epi, GemmArgs& a, int rows_cap, int rows_split, const GemmEpi& e, hipStream_t st) {
+  a.S = rows_kernel_splits(c, epi, a.NB, a.KS, e.rpart_rows, e.d_model, rows_split, a.n_rows_val >= 0);
   const int rt_cap = std::min((rows_cap + 31) / 32, 32), rt_known = a.n_rows_val >= 0 ? (a.n_rows_val + 31) / 32 : 0;
   const int k_parts = rows_k_parts(epi, a.NB, a.KS, rt_known);
   a.cut[0] = a.cut[1] = 0;
@@ -928,7 +938,7 @@ int launch_gemm(vlac_ctx* c, int epi, const bf16_t* wp, const float* wscale, int
     if (use_both(c, rows_cap, n_rows_host)) {
       GemmArgs r = a;
       r.rows_hi = kSmallRows;
-      S_small = launch_rows_kernel(c, epi, r, kSmallRows - 1, e, st);
+      S_small = launch_rows_kernel(c, epi, r, kSmallRows - 1, kFewRows - 1, e, st);
       a.rows_lo = kSmallRows;
     }
     if (c->w8) {
@@ -939,7 +949,7 @@ int launch_gemm(vlac_ctx* c, int epi, const bf16_t* wp, const float* wscale, int
     launch_gemm_tall(c->f16, epi, a, rows_cap, tall_resid_smax(c, epi, rows_cap, e.d_model), st);
     if (S_small > a.S) a.S = S_small;  // (the caller learns the most splits either kernel may leave)
   } else {
-    launch_rows_kernel(c, epi, a, rows_cap, e, st);
+    launch_rows_kernel(c, epi, a, rows_cap, rows_cap, e, st);
   }
   if (timed) {
     (void)hipEventRecord(c->prof_stop[c->prof_n], st);

@@ -160,7 +160,7 @@ __device__ inline void epilogue_tile(const GemmEpi& e, int nb, int slot, int id,
 }
 
 // gemm_tall.hip: the many-rows kernel with both operands through LDS (its plan: common.h).
-// The caller has filled every field of `a` except S, MB, P and x_tiles; S_max: most K splits
+// The caller has filled every field of `a` except S and x_tiles; S_max: most K splits
 // (1 unless the projection adds to the residual stream).
 void launch_gemm_tall(bool f16, int epi, GemmArgs& a, int rows_cap, int S_max, hipStream_t st);
 int gemm_tall_init();  // kernel attribute setup; returns hipError_t

@@ -90,7 +90,7 @@ def test_7b_full_depth_properties():
     equality is bit for bit, whatever is reused, as long as the same GEMM kernel serves: the
     reference is the prefill with an EMPTY reuse list, whose row count the kernels read from
     device memory like any sparse prefill's); the full recompute proper, whose row count the
-    host knows, runs the many-rows GEMM at this size and agrees to rounding; reused cache rows
+    host knows, may split the K of the projections with a residual otherwise and agrees to rounding; reused cache rows
     are untouched; 6 decoded tokens are reproducible."""
     import torch
     prev, cur, redrawn, e_prev, e_cur = inputs(seed=1)
@@ -222,9 +222,9 @@ def test_hires_batched_streams_with_few_and_many_rows():
 @pytest.mark.parametrize("static_frac", [0.8, 0.2])
 def test_two_streams_share_a_pass_with_few_or_many_rows(static_frac):
     """Two 7B-shaped streams of 288 tokens (a capacity of 576 rows, 2 layers): for a GEMM of
-    such a pass both the one-stream and the many-rows kernel are launched, and the row count
-    on the device says which of them works (80% static: 180 rows, the one-stream kernel and
-    its 8 split-K partial rows; 20% static: 470 rows, the many-rows kernel and its plan)."""
+    such a pass with long reuse lists both the one-stream and the many-rows kernel are launched, and
+    the row count on the device says which of them works (80% static: 180 rows, the one-stream kernel
+    and its split-K partial rows); with short ones only the many-rows kernel is (20% static: 470 rows)."""
     _check_streams(CFG.with_layers(2), B=2, n_vis=256, n_txt=32, static_frac=static_frac, seed=21, n_new=1)
 
 

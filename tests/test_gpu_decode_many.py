@@ -1,6 +1,7 @@
 """Decode passes (Sec. 3.1, KV-cache decode of the later action tokens) with more streams
 than the few-rows GEMM kernel serves: from 33 streams on a decode pass runs through the
-prefill's GEMM and row kernels, which take their rows from a row list.  Every stream's logits
+prefill's GEMM and row kernels, which take their rows from a row list (up to 511 streams the one-stream GEMM,
+from 512 on the many-rows one).  Every stream's logits
 of every decoded token against the oracle."""
 import numpy as np
 import pytest
@@ -21,6 +22,10 @@ def margin(x):
 @pytest.mark.parametrize("name,cfg,B", [
     ("tiny, 33 streams", synth.CONFIGS["tiny"], 33),
     ("grouped queries, 40 streams", synth.ModelCfg(3, 256, 8, 2, 128, 352, 320, rope_base=1.0e6), 40),
+    ("353 streams", synth.ModelCfg(2, 128, 4, 2, 64, 352, 160), 353),   # 12 row tiles, one row in the last
+    ("QKV in three blocks, 449 streams", synth.ModelCfg(2, 128, 128, 2, 64, 352, 160), 449),
+    ("511 streams", synth.ModelCfg(2, 128, 4, 2, 64, 352, 160), 511),
+    ("512 streams", synth.ModelCfg(2, 128, 4, 2, 64, 352, 160), 512),
 ])
 def test_decode_with_more_than_32_streams(name, cfg, B):
     n_vis, n_txt, n_new = 48, 11, 3

@@ -1,7 +1,7 @@
 """The one-stream GEMM where the row count decides how many feature blocks a workgroup takes: two and
-three row blocks with counts that the host knows and counts that it does not, launches that hold both
-forms (K in two parts or not), and two streams whose row count lies on either side of the limit
-between it and the many-rows GEMM.  Against the oracle; the tolerance is that of the operand roundings."""
+three row blocks with counts that the host knows and counts that it does not, K in two parts and whole, and
+two streams whose row count lies on either side of the limit between it and the many-rows GEMM, with lists so
+short that only the latter is launched and with lists so long that both are.  Against the oracle; the tolerance is that of the operand roundings."""
 import numpy as np
 import pytest
 
@@ -16,7 +16,7 @@ TOL = {"f16": 2e-2, "f16w8": 2e-2, "bf16": 8e-2}
 @pytest.mark.parametrize("d,F,hq,operand", [
     (320, 8240, 4, "f16"),     # gate/up: 515 blocks, 3 per workgroup, 5 with two row blocks
     (320, 8240, 4, "bf16"),
-    (320, 272, 128, "f16"),    # QKV: 264 blocks, 2 per workgroup up to 6 row tiles, 3 with two row blocks
+    (320, 272, 128, "f16"),    # QKV: 264 blocks, K in two parts, 2 per workgroup up to 6 row tiles, 3 with two row blocks
     (320, 272, 128, "f16w8"),
 ])
 def test_feature_blocks_by_row_count(d, F, hq, operand):
@@ -38,14 +38,28 @@ def test_feature_blocks_by_row_count(d, F, hq, operand):
         for b in range(2):
             O.dense_forward(om, two[b], n_vis, caches[b])
         gm.prefill(two, n_vis)
-        for reused in ((208, 208), (150, 169), (128, 0), (64, 63), (60, 5)):  # 160, 257, 448, 449, 511 rows
-            keep = [rng.permutation(n_vis)[:k].tolist() for k in reused]
+
+        def check(lists, counts):
+            nonlocal two
             two = synth.round_bf16(two + 0.1 * rng.standard_normal(two.shape))
-            got = gm.prefill(two, n_vis, [k + [] for k in keep])
+            got = gm.prefill(two, n_vis, lists, counts)
             for b in range(2):
-                want = O.sparse_forward(om, two[b], n_vis, caches[b], [keep[b]] * 2)
+                want = O.sparse_forward(om, two[b], n_vis, caches[b], [lists[b][:m] for m in counts[b]])
                 alive = ~np.isnan(want["hidden"][:, 0])
-                assert np.abs(got["hidden"][b][alive] - want["hidden"][alive]).max() <= TOL[operand], (reused, b)
+                assert np.abs(got["hidden"][b][alive] - want["hidden"][alive]).max() <= TOL[operand], (counts, b)
+                assert np.abs(got["attn_mean"][:, b] - want["attn_mean"]).max() <= TOL[operand], (counts, b)
+
+        # lists as long as they are used: 257 rows and more are certain, and only the many-rows GEMM is launched
+        for reused in ((150, 150), (128, 0), (64, 63), (60, 5)):  # 276, 448, 449, 511 rows
+            assert 2 * (288 - max(reused)) >= 257
+            check([rng.permutation(n_vis)[:max(k, 1)].tolist() for k in reused], [[k, k] for k in reused])
+        # long lists, used in part: both are launched, and the count says which works (up to 448 rows the one-stream
+        # GEMM); its partial rows are added up in its own format, also where the next layer's count is the other's
+        assert 2 * (288 - 208) < 257
+        lists = [rng.permutation(n_vis)[:208].tolist() for _ in range(2)]
+        for first, last in ((160, 160), (256, 256), (257, 257), (288, 288), (384, 384), (385, 385), (447, 447), (448, 448),
+                            (449, 449), (450, 450), (512, 512), (449, 448), (450, 257), (512, 160)):
+            check(lists, [[(576 - n + b) // 2 for n in (first, last)] for b in range(2)])
     finally:
         gm.close()
 
@@ -71,5 +85,29 @@ def test_rows_do_not_depend_on_who_counts_them(operand):
             assert not torch.equal(gm.kv, known), L
             gm.prefill(one, L - n_txt, [list(range(L // 2))], [[0]])
             assert torch.equal(gm.kv, known), L
+    finally:
+        gm.close()
+
+
+def test_rows_do_not_depend_on_how_many_streams_share_a_call():
+    """A stream of 256 tokens alone (a capacity of 256 rows: the one-stream GEMM) and beside another one (512
+    rows: both GEMMs are launched, the one-stream one works): K of the projections with a residual is split as
+    for few rows in either case, so every row must come out the same, bit for bit."""
+    d, n_vis, n_txt = 1536, 240, 16
+    cfg = synth.ModelCfg(2, d, 12, 2, 128, 8960, 96)
+    gm = GpuModel(cfg, seed=6, max_batch=2, max_seq=256, std=1.28 / np.sqrt(d), gen_device="cuda:0")
+    rng = np.random.default_rng(9)
+    try:
+        first = synth.round_bf16(rng.standard_normal((2, n_vis + n_txt, d)))
+        then = synth.round_bf16(first + 0.2 * rng.standard_normal(first.shape))
+        lists = [rng.permutation(n_vis)[:200].tolist() for _ in range(2)]
+        for n in (200, 198, 130):  # 56 to 126 rows a stream (the list's whole length in none but the first)
+            out = []
+            for B in (1, 2):
+                gm.prefill(first, n_vis)
+                out.append(gm.prefill(then[:B], n_vis, lists[:B], [[n, n]] * B))
+            for k in ("hidden", "logits", "attn_mean"):
+                a, b = (o[k][:, :1] if k == "attn_mean" else o[k][:1] for o in out)
+                assert np.array_equal(a, b, equal_nan=True), (n, k)
     finally:
         gm.close()

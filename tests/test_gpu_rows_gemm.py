@@ -1,5 +1,5 @@
 """The one-stream GEMM kernel at the edges of its tiles: row counts around multiples of 32 and of
-its blocks of 6 or 8 row tiles, 2, 3 and 4 feature blocks per workgroup with a ragged last one, K ranges
+its blocks of 6 or 8 row tiles, 2 to 6 feature blocks per workgroup with a ragged last one, K in two parts or whole, K ranges
 shorter and longer than what a wave has in flight and of unequal parts, 16-bit and 8-bit weights.
 Against the oracle; the tolerance is that of the operand roundings."""
 import numpy as np
@@ -17,13 +17,13 @@ TOL = {"f16": 2e-2, "f16w8": 2e-2, "bf16": 8e-2}
     (64, 272, 4, "f16"),       # one step of K: the second part has none
     (64, 272, 4, "f16w8"),
     (128, 272, 4, "f16"),      # 2 blocks per workgroup everywhere, K of 2 to 5 steps
-    (320, 8240, 4, "f16"),     # gate/up: 515 blocks, 3 per workgroup (172: 7 and 8 row tiles in one block); FFN down: 129 steps
+    (320, 8240, 4, "f16"),     # gate/up: 515 blocks, 3 per workgroup (172), 5 with two row blocks; FFN down: 129 steps
     (576, 12320, 4, "f16"),    # gate/up: 770 blocks, 4 per workgroup (193); 36 k-tiles
     (576, 8240, 4, "bf16"),
     (1344, 1008, 4, "f16"),    # K of 21 steps in two parts of 11 and 10
     (320, 8240, 4, "f16w8"),
     (1344, 1008, 4, "f16w8"),
-    (320, 272, 128, "f16"),    # QKV: 264 blocks, 2 per workgroup (132: 7 and 8 row tiles in one block)
+    (320, 272, 128, "f16"),    # QKV: 264 blocks, K in two parts, 2 per workgroup (132), 3 from 7 row tiles on (88, two row blocks)
     (320, 272, 128, "f16w8"),
     (1536, 2048, 4, "bf16"),   # FFN down: 24 x 5 workgroups, 13 to 16 row tiles in two blocks
 ])

@@ -12,7 +12,7 @@ from oracle import vlac_oracle as O
 from helpers import GpuModel, oracle_model
 
 pytestmark = pytest.mark.gpu
-KNOWN = (288, 320, 353, 404, 519, 640, 704)   # row counts of full prefills (up to 352: the one-stream kernel, same oracle)
+KNOWN = (288, 320, 353, 404, 519, 640, 704)   # row counts of full prefills (of one stream's 736: below 512 rows the one-stream kernel, same oracle)
 SAFE = os.path.join(os.path.dirname(V.lib_path()), "libvlac_safe.so")
 
 
