@@ -186,7 +186,8 @@ __global__ __launch_bounds__(256, 2) void attn_rows_kernel(AttnArgs a) {
     f32x16 acc;
     m = cmb[0][0][lane];
     l = cmb[0][1][lane];
-#pragma unroll 1
+    // (as a loop it moved the 16 sums of every turn: 80 rows of the tiny shape 155.4 -> 154.2 us)
+#pragma unroll
     for (int ww = 0; ww < 4; ++ww) {
       f32x16 t = own;
       if (ww != w) {
