@@ -61,8 +61,8 @@
 constexpr int ROWS_RING = 5;       // chunks of at most 32 KiB: all 160 KiB of a CU's LDS
 constexpr int ROWS_FB_MIN = 2, ROWS_FB_MAX = 6;  // feature blocks per workgroup: 2 (K in two parts) or 3 to 6
 constexpr int ROWS_PAIR_NA = 6;  // most row tiles per wave with 2 feature blocks where others are in the choice
-// The forms of the kernel.  K in two parts: 2 feature blocks per workgroup (projections with a residual), 2 or 3
-// (QKV, gate/up); K whole: up to 4, up to 6
+// The forms of the kernel.  K in two parts: 2 feature blocks per workgroup, 2 or 3 (QKV only); K whole: up to 4 (not
+// QKV), up to 6.  (Where 2 are enough the form of 2 or 3 costs 0.4 us more of 5 at the tiny shape.)
 enum { ROWS_PAIRS = 2, ROWS_THREES = 3, ROWS_FOUR = 4, ROWS_SIX = 6 };
 constexpr int rows_parts(int form) { return form <= ROWS_THREES ? 2 : 1; }
 constexpr int rows_consumers(int form) { return form == ROWS_SIX || form == ROWS_THREES ? 6 : 4; }
@@ -176,7 +176,8 @@ __device__ __forceinline__ void rows_body(const GemmArgs& a, uint4* lds, RowsWei
   // of it and spill.)
   int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   asm volatile("" : "+v"(lane), "+s"(w), "+s"(tile), "+s"(s), "+s"(rt0));
-  const int part = KP == 2 && w >= fb ? 1 : 0, nb = tile * fb + w - part * fb, g = lane >> 5;
+  const int part = FORM == ROWS_PAIRS ? w >> 1 : KP == 2 && w >= fb ? 1 : 0;
+  const int nb = FORM == ROWS_PAIRS ? tile * 2 + (w & 1) : tile * fb + w - part * fb, g = lane >> 5;
   const bool wave_on = w < fb * KP && nb < a.NB;
   f32x16 acc[NA];
 #pragma unroll
@@ -276,8 +277,9 @@ __device__ __forceinline__ void rows_body(const GemmArgs& a, uint4* lds, RowsWei
     // (sum = first part + second part).
     constexpr int NH = (NA + 1) / 2;
     __syncthreads();
-    float* mine = (float*)lds + (size_t)w * (NH * 16 * 64) + lane;
-    const float* theirs = (const float*)lds + (size_t)(part ? w - fb : w + fb) * (NH * 16 * 64) + lane;
+    const int at = FORM == ROWS_PAIRS ? w & 3 : w, from = FORM == ROWS_PAIRS ? at ^ 2 : part ? w - fb : w + fb;
+    float* mine = (float*)lds + (size_t)at * (NH * 16 * 64) + lane;
+    const float* theirs = (const float*)lds + (size_t)from * (NH * 16 * 64) + lane;
     if (w < 2 * fb) {
 #pragma unroll
       for (int m = 0; m < NA; ++m)
@@ -376,9 +378,9 @@ __global__ __launch_bounds__(rows_threads(FORM)) void gemm_rows_kernel(GemmArgs 
     tile = __builtin_amdgcn_readfirstlane(p / a.S);
     s = __builtin_amdgcn_readfirstlane(p - tile * a.S);
     if (w < fb * KP && tile * fb < a.NB) {
-      const int part = KP == 2 && w >= fb ? 1 : 0;
+      const int part = FORM == ROWS_PAIRS ? w >> 1 : KP == 2 && w >= fb ? 1 : 0;
       const RowsRange rg = rows_range(a.KS, a.S * KP, s * KP + part);
-      const int nb = min(tile * fb + w - part * fb, a.NB - 1), kc = W8 ? 2 * a.KS : 4 * a.KS, k0 = W8 ? rg.k0 / 2 : rg.k0;
+      const int nb = min(FORM == ROWS_PAIRS ? tile * 2 + (w & 1) : tile * fb + w - part * fb, a.NB - 1), kc = W8 ? 2 * a.KS : 4 * a.KS, k0 = W8 ? rg.k0 / 2 : rg.k0;
       const uint4* src = a.wp + (size_t)nb * kc * 64 + (threadIdx.x & 63);
       // (past the end of K the last tile is read again and not used)
 #pragma unroll
@@ -669,9 +671,9 @@ static hipError_t set_attr() {
 int gemm_init() {
   hipError_t e;
 #define VLAC_SET(FORM)                                                    \
-  if ((e = set_attr<FORM, EPI_QKV>()) != hipSuccess) return (int)e;       \
+  if ((e = set_attr<FORM == ROWS_FOUR ? ROWS_THREES : FORM, EPI_QKV>()) != hipSuccess) return (int)e; \
   if ((e = set_attr<FORM, EPI_SWIGLU>()) != hipSuccess) return (int)e;
-  VLAC_SET(ROWS_THREES) VLAC_SET(ROWS_FOUR) VLAC_SET(ROWS_SIX)
+  VLAC_SET(ROWS_PAIRS) VLAC_SET(ROWS_FOUR) VLAC_SET(ROWS_SIX)
   if ((e = set_attr<ROWS_PAIRS, EPI_RESID>()) != hipSuccess) return (int)e;
   if ((e = set_attr<ROWS_FOUR, EPI_RESID>()) != hipSuccess) return (int)e;
   if ((e = set_attr<ROWS_FOUR, EPI_LOGITS>()) != hipSuccess) return (int)e;
@@ -683,14 +685,15 @@ template <int FORM, int EPI, bool F16, bool W8>
 static void launch_rows_one(const GemmArgs& a, int grid, hipStream_t st) {
   hipLaunchKernelGGL((gemm_rows_kernel<FORM, EPI, F16, W8>), dim3(grid), dim3(rows_threads(FORM)), kRowsLds, st, a);
 }
-// (QKV and gate/up have no form of pairs, the projections with a residual 2 or 4 feature blocks, the head 4)
+// (which forms a projection has: see above; the projections with a residual take 2 or 4 feature blocks, the head 4)
 template <int FORM, bool F16, bool W8>
 static void launch_rows(int epi, const GemmArgs& a, int grid, hipStream_t st) {
-  constexpr int MANY = FORM == ROWS_PAIRS ? ROWS_THREES : FORM, RESID = FORM == ROWS_PAIRS ? ROWS_PAIRS : ROWS_FOUR;
+  constexpr int QKV = FORM == ROWS_FOUR ? ROWS_SIX : FORM, GATE_UP = FORM == ROWS_THREES ? ROWS_PAIRS : FORM,
+                RESID = FORM == ROWS_PAIRS ? ROWS_PAIRS : ROWS_FOUR;
   switch (epi) {
-    case EPI_QKV: launch_rows_one<MANY, EPI_QKV, F16, W8>(a, grid, st); break;
+    case EPI_QKV: launch_rows_one<QKV, EPI_QKV, F16, W8>(a, grid, st); break;
     case EPI_RESID: launch_rows_one<RESID, EPI_RESID, F16, W8>(a, grid, st); break;
-    case EPI_SWIGLU: launch_rows_one<MANY, EPI_SWIGLU, F16, W8>(a, grid, st); break;
+    case EPI_SWIGLU: launch_rows_one<GATE_UP, EPI_SWIGLU, F16, W8>(a, grid, st); break;
     default: launch_rows_one<ROWS_FOUR, EPI_LOGITS, F16, W8>(a, grid, st); break;
   }
 }
@@ -821,7 +824,7 @@ SplitAdapt gemm_resid_adapt(vlac_ctx* c, int n_blocks, int kpad, int rows_cap, c
 static const int kRowsPairTiles = 128;
 
 // How the one-stream kernel cuts `rt` row tiles (at most 32: 1023 rows) and NB feature blocks: blocks of
-// at most 6 or 8 row tiles, feature blocks per workgroup 2 or 3 with K in two parts and 3 to 6 with K whole (the
+// at most 6 or 8 row tiles, feature blocks per workgroup 2 (QKV: or 3) with K in two parts and 3 to 6 with K whole (the
 // projections with a residual: as given, with their S splits).  A workgroup takes a CU's whole LDS, so
 // what counts is rounds of 256 workgroups x what a workgroup fetches per k (its weight rows, a block's
 // operand rows; a CU fetches about 50 GB/s with weights from HBM and row operands from L2 in one queue).
@@ -829,7 +832,7 @@ static const int kRowsPairTiles = 128;
 struct RowsChoice { RowsCut cut; int code, cost; };
 static RowsChoice rows_cut(int epi, int NB, int KS, int S, int rt, int k_parts) {
   RowsChoice best = {{0, 0}, 0, 0x7fffffff};
-  const bool pairs_only = rows_tiles(NB, 2) < kRowsPairTiles;
+  const bool pairs_only = epi != EPI_QKV || rows_tiles(NB, 2) < kRowsPairTiles;
   const int fix = epi == EPI_LOGITS ? 4 : epi == EPI_RESID ? rows_resid_fb(NB, KS) : 0;
   const int lo = fix ? fix : k_parts == 2 ? 2 : 3, hi = fix ? fix : k_parts == 1 ? ROWS_FB_MAX : pairs_only ? 2 : 3;
   for (int fb = lo; fb <= hi; ++fb) {
@@ -873,9 +876,8 @@ static int launch_rows_kernel(vlac_ctx* c, int epi, GemmArgs& a, int rows_cap, i
     else if (c->f16) launch_rows<FORM_, true, false>(epi, a, grid, st);            \
     else launch_rows<FORM_, false, false>(epi, a, grid, st);                       \
   }
-  if (epi == EPI_LOGITS || (epi == EPI_RESID && fb_most == 4)) VLAC_ROWS(ROWS_FOUR)
-  else if (epi == EPI_RESID) VLAC_ROWS(ROWS_PAIRS)
-  else if (k_parts == 2) VLAC_ROWS(ROWS_THREES)
+  if (fb_most == 2) VLAC_ROWS(ROWS_PAIRS)
+  else if (epi == EPI_QKV && k_parts == 2) VLAC_ROWS(ROWS_THREES)
   else if (fb_most <= 4) VLAC_ROWS(ROWS_FOUR)
   else VLAC_ROWS(ROWS_SIX)
 #undef VLAC_ROWS

@@ -16,6 +16,7 @@ TOL = {"f16": 2e-2, "f16w8": 2e-2, "bf16": 8e-2}
 @pytest.mark.parametrize("d,F,hq,operand", [
     (320, 8240, 4, "f16"),     # gate/up: 515 blocks, 3 per workgroup, 5 with two row blocks
     (320, 8240, 4, "bf16"),
+    (320, 4400, 4, "f16"),     # gate/up: 275 blocks, pairs with K in two parts or more blocks with K whole
     (320, 272, 128, "f16"),    # QKV: 264 blocks, K in two parts, 2 per workgroup up to 6 row tiles, 3 with two row blocks
     (320, 272, 128, "f16w8"),
 ])
