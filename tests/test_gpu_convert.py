@@ -11,7 +11,6 @@ import pytest
 
 import paper_2502_02175_amd as V
 
-pytestmark = pytest.mark.gpu
 SAFE = os.path.join(os.path.dirname(V.lib_path()), "libvlac_safe.so")
 
 
@@ -40,6 +39,7 @@ def f16_bits(u):
     return np.where(mag > 0x7f800000, 0xfbff, out).astype(np.uint16)
 
 
+@pytest.mark.gpu
 def test_conversions_bit_for_bit():
     import torch
     lows = [0x0000, 0x0001, 0x0fff, 0x1000, 0x1001, 0x1fff, 0x2000, 0x2fff, 0x3000, 0x3001, 0x5000, 0x7000, 0x7fff, 0x8000, 0x8001,

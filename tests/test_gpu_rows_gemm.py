@@ -25,6 +25,7 @@ TOL = {"f16": 2e-2, "f16w8": 2e-2, "bf16": 8e-2}
     (1344, 1008, 4, "f16w8"),
     (320, 272, 128, "f16"),    # QKV: 264 blocks, K in two parts, 2 per workgroup (132), 3 from 7 row tiles on (88, two row blocks)
     (320, 272, 128, "f16w8"),
+    (128, 272, 256, "f16"),    # QKV: 520 blocks, K whole, 3 to 6 per workgroup
     (1536, 2048, 4, "bf16"),   # FFN down: 24 x 5 workgroups, 13 to 16 row tiles in two blocks
 ])
 def test_rows_gemm_at_the_edges(d, F, hq, operand):

@@ -70,7 +70,7 @@ def test_full_waits_change_no_bit(name, cfg, B, n_vis, n_txt, reuse_counts):
 
 
 # The one-stream GEMM (up to a capacity of 511 rows; 8-bit weights: up to 1023).  Its ring holds 5 chunks of
-# 8 k-tiles (4 with more than 4 row tiles; half of that per part where two pairs of waves share K).
+# 8 k-tiles (4 with more than 4 row tiles; half of that per part where two sets of waves share K).
 ONE_STREAM = [
     # d, F, query heads, head dim, layers, operand: feature blocks per workgroup (QKV, gate/up, residual) and k-tiles of K
     (64, 272, 4, 64, 2, "f16"),       # 2, 2, 2; 4 k-tiles: one chunk, and a part of K that has none
@@ -79,7 +79,10 @@ ONE_STREAM = [
     (320, 8240, 4, 64, 2, "f16w8"),
     (576, 12320, 4, 64, 2, "bf16"),   # 2, 4, 2; 36 k-tiles
     (1344, 1008, 4, 64, 2, "f16"),    # 2, 2, 2; 84 k-tiles in parts of 44 and 40
-    (4096, 8256, 64, 128, 1, "f16"),   # 2, 4, 4: the residual projections over 4 feature blocks; enough workgroups
+    (320, 272, 128, 64, 2, "bf16"),   # 2 or 3 by the row count, 2, 2; 20 k-tiles in parts of 12 and 8
+    (320, 272, 128, 64, 2, "f16w8"),
+    (128, 272, 256, 64, 1, "f16"),    # 3 to 6 by the row count, 2, 2; 8 and 1024 k-tiles
+    (4096, 8256, 64, 128, 1, "f16"),   # 2 or 3, 4, 4: the residual projections over 4 feature blocks; enough workgroups
                                        # everywhere for 7 and 8 row tiles in one block
     (4096, 8256, 64, 128, 1, "f16w8"),
 ]
