@@ -61,21 +61,54 @@ __device__ __forceinline__ void read_epilogue_args(const GemmArgs& a) {
   else read_args(a.e.logits, a.e.logits_stride, a.e.best, a.e.vocab);
 }
 
-__device__ inline float silu_f(float x) { return x / (1.f + __expf(-x)); }
+// x / (1 + e^-x) by the chip's reciprocal (1 ulp): the exponential before it is the larger error, and the result is
+// rounded to 16 bits.  (An IEEE division is ten instructions more, 1280 of the 3600 that a wave of the
+// many-rows kernel spent on a work item of 256 x 256 after its last product.)
+__device__ inline float silu_f(float x) { return x * __builtin_amdgcn_rcpf(1.f + __expf(-x)); }
+
+// What an epilogue reads from memory for one tile: rotary factors of a query or key block, residual rows of a
+// projection.  It is asked for apart from what is done with it: behind the stores of another tile the compiler
+// keeps a load where it is (they might overlap), and every tile would be a round trip of its own.
+template <int EPI>
+struct EpiIn {};
+template <>
+struct EpiIn<EPI_QKV> { float4 c[2], s[2]; };
+template <>
+struct EpiIn<EPI_RESID> { float4 r[4]; };
+
+template <int EPI>
+__device__ __forceinline__ void epilogue_load(const GemmEpi& e, int nb, int id, int g, EpiIn<EPI>& in) {
+  if constexpr (EPI == EPI_QKV) {
+    const int half = e.head_dim >> 1, bph = e.head_dim >> 5;  // (2 or 4 blocks per head)
+    if (nb < (e.n_q_heads + e.n_kv_heads) * bph) {
+      const size_t at = (size_t)(id & 0xffff) * half + 16 * (nb & (bph - 1)) + 4 * g;
+#pragma unroll
+      for (int q4 = 0; q4 < 2; ++q4) {
+        in.c[q4] = *(const float4*)(e.rope_cos + at + 8 * q4);
+        in.s[q4] = *(const float4*)(e.rope_sin + at + 8 * q4);
+      }
+    }
+  } else if constexpr (EPI == EPI_RESID) {
+    const float* rs = e.resid_src + ((size_t)(id >> 16) * e.resid_seq_stride + (e.h_compact ? 0 : id & 0xffff)) * e.d_model +
+                      nb * 32 + 4 * g;
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) in.r[q4] = *(const float4*)(rs + 8 * q4);
+  }
+}
 
 template <int EPI, bool F16>
-__device__ inline void epilogue_tile(const GemmEpi& e, int nb, int slot, int id, int g,
-                                     const f32x16& acc) {
+__device__ __forceinline__ void epilogue_store(const GemmEpi& e, int nb, int slot, int id, int g,
+                                               const f32x16& acc, const EpiIn<EPI>& in) {
   const int b = id >> 16, pos = id & 0xffff;
   if constexpr (EPI == EPI_QKV) {
-    const int hd = e.head_dim, bph = hd >> 5;
+    const int hd = e.head_dim, bph = hd >> 5, bph_log = (hd >> 7) + 1;  // (hd is 64 or 128)
     const int nbq = e.n_q_heads * bph, nbk = e.n_kv_heads * bph;
     const size_t head_elems = (size_t)e.max_seq * hd;
     bf16_t* kvl = e.kv + (size_t)b * e.kv_stream_stride + e.kv_layer_off;
     if (nb < nbq + nbk) {
       // query or key block: rows 0..15 hold features f, rows 16..31 their rotary partners f + hd/2
       const bool isq = nb < nbq;
-      const int nbl = isq ? nb : nb - nbq, head = nbl / bph, sb = nbl % bph;
+      const int nbl = isq ? nb : nb - nbq, head = nbl >> bph_log, sb = nbl & (bph - 1);
       bf16_t* dst;
       int row;  // row of the fragment-ordered destination
       if (isq) {
@@ -88,8 +121,7 @@ __device__ inline void epilogue_tile(const GemmEpi& e, int nb, int slot, int id,
 #pragma unroll
       for (int q4 = 0; q4 < 2; ++q4) {
         const int f1 = 16 * sb + 8 * q4 + 4 * g;
-        const float4 c4 = *(const float4*)(e.rope_cos + (size_t)pos * (hd >> 1) + f1);
-        const float4 s4 = *(const float4*)(e.rope_sin + (size_t)pos * (hd >> 1) + f1);
+        const float4 c4 = in.c[q4], s4 = in.s[q4];
         const float cs[4] = {c4.x, c4.y, c4.z, c4.w}, sn[4] = {s4.x, s4.y, s4.z, s4.w};
         float o1[4], o2[4];
 #pragma unroll
@@ -107,7 +139,7 @@ __device__ inline void epilogue_tile(const GemmEpi& e, int nb, int slot, int id,
     } else {
       // value block -> the cache's V tile: per 32 positions and 32 features, the
       // operand of the P.V product (key order inside a tile follows the score tile)
-      const int nbl = nb - nbq - nbk, head = nbl / bph, ib = nbl % bph;
+      const int nbl = nb - nbq - nbk, head = nbl >> bph_log, ib = nbl & (bph - 1);
       const int pt = pos >> 5, pl = pos & 31, s = pl >> 4, r16 = pl & 15;
       const int gp = (r16 & 7) >> 2, ep = 4 * (r16 >> 3) + (r16 & 3);
       bf16_t* dst = kvl + (size_t)(e.n_kv_heads + head) * head_elems +
@@ -115,15 +147,18 @@ __device__ inline void epilogue_tile(const GemmEpi& e, int nb, int slot, int id,
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4)
 #pragma unroll
-        for (int k = 0; k < 4; ++k) dst[(8 * q4 + 4 * g + k) * 8] = f2op<F16>(acc[4 * q4 + k]);
+        for (int k = 0; k < 4; k += 2) {
+          const uint32_t two = pack_op2<F16>(acc[4 * q4 + k], acc[4 * q4 + k + 1]);
+          dst[(8 * q4 + 4 * g + k) * 8] = (bf16_t)two;
+          dst[(8 * q4 + 4 * g + k + 1) * 8] = (bf16_t)(two >> 16);
+        }
     }
   } else if constexpr (EPI == EPI_RESID) {
     const int hpos = e.h_compact ? 0 : pos;
-    const float* rs = e.resid_src + ((size_t)b * e.resid_seq_stride + hpos) * e.d_model + nb * 32 + 4 * g;
     float* hp = e.h + ((size_t)b * e.h_seq_stride + hpos) * e.d_model + nb * 32 + 4 * g;
 #pragma unroll
     for (int q4 = 0; q4 < 4; ++q4) {
-      float4 r = *(const float4*)(rs + 8 * q4);
+      float4 r = in.r[q4];
       r.x += acc[4 * q4]; r.y += acc[4 * q4 + 1]; r.z += acc[4 * q4 + 2]; r.w += acc[4 * q4 + 3];
       *(float4*)(hp + 8 * q4) = r;
     }
@@ -157,6 +192,13 @@ __device__ inline void epilogue_tile(const GemmEpi& e, int nb, int slot, int id,
       *(float4*)(out + 8 * q4) =
           make_float4(acc[4 * q4], acc[4 * q4 + 1], acc[4 * q4 + 2], acc[4 * q4 + 3]);
   }
+}
+
+template <int EPI, bool F16>
+__device__ __forceinline__ void epilogue_tile(const GemmEpi& e, int nb, int slot, int id, int g, const f32x16& acc) {
+  EpiIn<EPI> in;
+  epilogue_load<EPI>(e, nb, id, g, in);
+  epilogue_store<EPI, F16>(e, nb, slot, id, g, acc, in);
 }
 
 // gemm_tall.hip: the many-rows kernel with both operands through LDS (its plan: common.h).

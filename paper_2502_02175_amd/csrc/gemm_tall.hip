@@ -26,10 +26,18 @@
 //    of a k-tile are read while the MFMAs of the one before run, across the barrier as well.
 //  * The grid is one workgroup per CU; a workgroup runs its work items one after the other
 //    and copies the first stages of the next item during the last steps of the one before.
-//  * Row blocks of 192 or 128 rows (a wave owns 4 x 3 or 4 x 2 tiles), and K split in 2 or 3
+//  * Row blocks of 192 or 128 rows (a wave owns 4 x 3 or 4 x 2 tiles), and K split in up to 8
 //    parts in the projections with a residual (whose consumer, residual add + RMSNorm, adds
 //    the partial rows up), where that takes less time by the estimate of tall_plan, which
 //    kernel and consumer evaluate on the device from the actual row count.
+//  * Behind its last product an item has the CU to itself (one wave per SIMD), so what it does with its sums
+//    counts in full.  The sums stay in their registers until a tile's turn (copied out of them all at once
+//    behind the loop, they spilled 80 to 110 registers); what an epilogue reads is asked for ahead of the stores
+//    of the row tile before it; and where a lane's access would be a cache line of its own (residual rows, partial
+//    rows, rotary factors) the tile goes through 4 KiB of LDS, so that 4 or 8 lanes share a line.  What is left
+//    per item of 8 x 1057 tokens (7B; products 80 to 100 us): SwiGLU 4.5 us, QKV 10 (L2 requests), residual rows
+//    10.5 (memory).  Whole calls before and after: 8 x 1057 tokens of 7B 4853 -> 4659 us, 32 x 304 of grouped
+//    queries 2847 -> 2633, 601 tokens of 7B 1303 -> 1268.
 //  * Measured against this design and not kept: a 512-feature x 128-row item with the weight
 //    tiles fetched global -> registers by 8 waves (20 KiB per 64 MFMAs: 5 to 8 % slower at
 //    the 7B layer shape with 2700 to 8400 rows, equal at d_model 1536); rings of 4 stages
@@ -55,6 +63,7 @@ struct TallRing {
   static constexpr int YOUNGER = COPIES * (N - 2); // copies behind the stage a step waits for
   static_assert(YOUNGER <= 63, "the counter holds 63");
 };
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kTallLds = 160 * 1024;
 template <int N>
 __device__ inline void tall_wait() {
@@ -74,7 +83,7 @@ struct TallItem { int tile, s, mb; };
 // RING - 1 steps of this item copy its first stages instead of stages past the end).
 // prefilled: the copies of this item's first RING - 1 stages have been issued already (by
 // the item before) into the ring from `slot` on.  Returns the ring slot after the last stage.
-template <int FW, int RT, int NA, int EPI, bool F16>
+template <int FW, int RT, int NA, int EPI, bool F16, bool W8>
 __device__ __forceinline__ int tall_body(const GemmArgs& a, uint4* lds, TallItem it, TallItem nx, bool chain,
                                           bool prefilled, int slot, int n_rows, int S) {
   constexpr int RING = TallRing<FW, RT>::N, STAGE = TallRing<FW, RT>::STAGE, C = TallRing<FW, RT>::COPIES;
@@ -174,7 +183,8 @@ __device__ __forceinline__ int tall_body(const GemmArgs& a, uint4* lds, TallItem
 #pragma unroll
     for (int q = 0; q < FW + NA; ++q) read_one(lds + slot * STAGE + lane, q, W0, X0);
   }
-  for (int i = 0; i < n_steps; ++i) {
+  int i = 0;
+  do {  // (an item has at least one step; a loop that might have none would copy the sums behind it)
     const int slot_next = slot + 1 == RING ? 0 : slot + 1, slot_copy = slot == 0 ? RING - 1 : slot - 1;
     const uint4* cur = lds + slot * STAGE + lane;
     const uint4* nxt = lds + slot_next * STAGE + lane;
@@ -217,7 +227,7 @@ __device__ __forceinline__ int tall_body(const GemmArgs& a, uint4* lds, TallItem
       for (int q = FW * NX - 1; q < FW + NA; ++q) read_one(nxt, q, W0, X0);
     }
     slot = slot_next;
-  }
+  } while (++i < n_steps);
   if (!chain) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no copy outlives the item
     __syncthreads();                                  // (the next item's copies overwrite any slot)
@@ -225,49 +235,156 @@ __device__ __forceinline__ int tall_body(const GemmArgs& a, uint4* lds, TallItem
 
   if constexpr (NA > 0) {
     const int g = lane >> 5;
-    if (a.wscale) {  // weights expanded from e4m3 codes: the scale of every output feature
+    auto result = [&](int f, int m) __attribute__((always_inline)) {
+      // (pinned: else all 16 tiles are copied to the other half of the registers behind the loop, and spill there)
+      asm volatile("" : "+a"(acc[f][m]));
+      f32x16 t = acc[f][m];
+      if constexpr (W8) scale_tile(a.wscale, min(nb0 + FW * wi + f, a.NB - 1), g, t);
+      return t;
+    };
+    auto block = [&](int f) { return min(nb0 + FW * wi + f, a.NB - 1); };  // (for loads: past the end the last again)
+    // 4 KiB of the stage this item read last, in this wave's quarter of it: free until the wave itself copies
+    // a stage of the next item there.  [row of 32][chunk of 16 bytes, 8 of them], chunks swizzled by the row.
+    f32x4* tile = (f32x4*)(lds + (slot == 0 ? RING - 1 : slot - 1) * STAGE + w * (C * 64));
+    auto slot_of = [&](int m, int r) { return row0 + (2 * m + wj) * 32 + r; };
+    const int j = lane & 31;
+    if constexpr (EPI == EPI_RESID) {
+      // A lane of the products holds 4 features of a row of its own: stored like that, every lane of an access
+      // is a cache line of its own.  Turned round in LDS 8 lanes hold the 32 features of a row.
+      const int q = lane >> 3, c = lane & 7;  // a lane's rows are 8 r + q
+      auto turned = [&](int f, int m, f32x4(&v)[4]) __attribute__((always_inline)) {
+        const f32x16 t = result(f, m);
 #pragma unroll
-      for (int f = 0; f < FW; ++f)
-        if (nb0 + FW * wi + f < a.NB) {
+        for (int q4 = 0; q4 < 4; ++q4)
+          tile[j * 8 + ((2 * q4 + g) ^ (j & 7))] = (f32x4){t[4 * q4], t[4 * q4 + 1], t[4 * q4 + 2], t[4 * q4 + 3]};
 #pragma unroll
-          for (int m = 0; m < NA; ++m) scale_tile(a.wscale, nb0 + FW * wi + f, g, acc[f][m]);
-        }
-    }
-    if (EPI == EPI_RESID && S > 1) {
-      // split K: the partial rows [part][row][feature] are left to the row kernel that follows
-      // (residual add + RMSNorm), which adds the parts up in order
+        for (int r = 0; r < 4; ++r) v[r] = tile[(8 * r + q) * 8 + (c ^ q)];
+      };
+      if (S > 1) {
+        // split K: the partial rows [part][row][feature] are left to the row kernel that follows
+        // (residual add + RMSNorm), which adds the parts up in order
 #pragma unroll
-      for (int m = 0; m < NA; ++m) {
-        const int slot_r = row0 + (2 * m + wj) * 32 + (lane & 31);
-        if (slot_r < n_rows) {
+        for (int m = 0; m < NA; ++m) {
+          float* dp = a.e.rpart + ((size_t)it.s * a.e.rpart_rows + slot_of(m, q)) * a.e.d_model + (nb0 + FW * wi) * 32 + 4 * c;
 #pragma unroll
           for (int f = 0; f < FW; ++f)
             if (nb0 + FW * wi + f < a.NB) {
-              float* dp = a.e.rpart + ((size_t)it.s * a.e.rpart_rows + slot_r) * a.e.d_model + (nb0 + FW * wi + f) * 32 + 4 * g;
+              f32x4 v[4];
+              turned(f, m, v);
 #pragma unroll
-              for (int q4 = 0; q4 < 4; ++q4)
-                *(float4*)(dp + 8 * q4) = make_float4(acc[f][m][4 * q4], acc[f][m][4 * q4 + 1],
-                                                      acc[f][m][4 * q4 + 2], acc[f][m][4 * q4 + 3]);
+              for (int r = 0; r < 4; ++r)
+                if (slot_of(m, 8 * r + q) < n_rows) *(f32x4*)(dp + (size_t)(8 * r) * a.e.d_model + 32 * f) = v[r];
             }
         }
+      } else {
+        int ids[NA][4];
+#pragma unroll
+        for (int m = 0; m < NA; ++m)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) ids[m][r] = a.e.rows[(uint32_t)min(slot_of(m, 8 * r + q), n_rows - 1)];
+        f32x4 in[2][FW][4];  // residual rows, asked for ahead of the stores of the row tile before
+        auto ask = [&](int m) __attribute__((always_inline)) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int id = ids[m][r];
+            const float* rs = a.e.resid_src + ((size_t)(id >> 16) * a.e.resid_seq_stride + (id & 0xffff)) * a.e.d_model + 4 * c;
+#pragma unroll
+            for (int f = 0; f < FW; ++f)
+              in[m & 1][f][r] = *(const f32x4*)(rs + 32 * block(f));
+          }
+        };
+        ask(0);
+#pragma unroll
+        for (int m = 0; m < NA; ++m) {
+          if (m + 1 < NA) ask(m + 1);
+          __builtin_amdgcn_sched_barrier(0);
+          float* hp[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            hp[r] = a.e.h + ((size_t)(ids[m][r] >> 16) * a.e.h_seq_stride + (ids[m][r] & 0xffff)) * a.e.d_model +
+                    (nb0 + FW * wi) * 32 + 4 * c;
+#pragma unroll
+          for (int f = 0; f < FW; ++f)
+            if (nb0 + FW * wi + f < a.NB) {
+              f32x4 v[4];
+              turned(f, m, v);
+#pragma unroll
+              for (int r = 0; r < 4; ++r)
+                if (slot_of(m, 8 * r + q) < n_rows) *(f32x4*)(hp[r] + 32 * f) = in[m & 1][f][r] + v[r];
+            }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    } else if constexpr (EPI == EPI_QKV) {
+      // The rotary factors of a query or key block, 16 cosines and 16 sines per row, are asked for 4 lanes to a
+      // row, ahead of the stores of the row tile before, and reach the lanes that need them through LDS.
+      const int q = lane >> 2, c = lane & 3;  // a lane's rows are 16 p + q
+      auto chunk = [](int row, int k) { return row * 8 + (k ^ (((row & 1) << 2) | ((row >> 1) & 3))); };
+      const int bph = a.e.head_dim >> 5, nb_rot = (a.e.n_q_heads + a.e.n_kv_heads) * bph, half = a.e.head_dim >> 1;
+      int ids[NA], pos[NA][2];
+#pragma unroll
+      for (int m = 0; m < NA; ++m) {
+        ids[m] = a.e.rows[(uint32_t)min(slot_of(m, j), n_rows - 1)];
+#pragma unroll
+        for (int p = 0; p < 2; ++p) pos[m][p] = a.e.rows[(uint32_t)min(slot_of(m, 16 * p + q), n_rows - 1)] & 0xffff;
+      }
+      f32x4 in[2][FW][4];  // cosines, sines of rows 16 p + q
+      auto ask = [&](int m) __attribute__((always_inline)) {
+        if (nb0 + FW * wi < nb_rot) {  // (the last blocks of a wave may be value blocks: asked for all the same)
+#pragma unroll
+          for (int f = 0; f < FW; ++f)
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+              const uint32_t at = (uint32_t)(pos[m][p] * half + 16 * ((nb0 + FW * wi + f) & (bph - 1)) + 4 * c);
+              in[m & 1][f][p] = *(const f32x4*)(a.e.rope_cos + at);
+              in[m & 1][f][2 + p] = *(const f32x4*)(a.e.rope_sin + at);
+            }
+        }
+      };
+      ask(0);
+#pragma unroll
+      for (int m = 0; m < NA; ++m) {
+        if (m + 1 < NA) ask(m + 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int f = 0; f < FW; ++f) {
+          const int nb = nb0 + FW * wi + f;
+          EpiIn<EPI> mine = {};
+          if (nb < nb_rot) {
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+              tile[chunk(16 * p + q, c)] = in[m & 1][f][p];
+              tile[chunk(16 * p + q, 4 + c)] = in[m & 1][f][2 + p];
+            }
+#pragma unroll
+            for (int q4 = 0; q4 < 2; ++q4) {
+              const f32x4 x = tile[chunk(j, 2 * q4 + g)], y = tile[chunk(j, 4 + 2 * q4 + g)];
+              mine.c[q4] = make_float4(x[0], x[1], x[2], x[3]);
+              mine.s[q4] = make_float4(y[0], y[1], y[2], y[3]);
+            }
+          }
+          if (nb < a.NB) {
+            const f32x16 t = result(f, m);
+            if (slot_of(m, j) < n_rows) epilogue_store<EPI, F16>(a.e, nb, slot_of(m, j), ids[m], g, t, mine);
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
     } else {
 #pragma unroll
-      for (int m = 0; m < NA; ++m) {
-        const int slot_r = row0 + (2 * m + wj) * 32 + (lane & 31);
-        if (slot_r < n_rows) {
-          const int id = (EPI == EPI_LOGITS) ? 0 : a.e.rows[slot_r];
+      for (int m = 0; m < NA; ++m)
+        if (slot_of(m, j) < n_rows) {
 #pragma unroll
           for (int f = 0; f < FW; ++f)
-            if (nb0 + FW * wi + f < a.NB) epilogue_tile<EPI, F16>(a.e, nb0 + FW * wi + f, slot_r, id, g, acc[f][m]);
+            if (nb0 + FW * wi + f < a.NB)
+              epilogue_tile<EPI, F16>(a.e, nb0 + FW * wi + f, slot_of(m, j), 0, g, result(f, m));
         }
-      }
     }
   }
   return slot;
 }
 
-template <int FW, int RT, int EPI, bool F16>
+template <int FW, int RT, int EPI, bool F16, bool W8>
 __device__ __forceinline__ int tall_dispatch(const GemmArgs& a, uint4* lds, TallItem it, TallItem nx, bool chain,
                                               bool prefilled, int slot, int n_rows, int S) {
   // row tiles of this block, dealt to the two row halves alternately
@@ -276,13 +393,13 @@ __device__ __forceinline__ int tall_dispatch(const GemmArgs& a, uint4* lds, Tall
   const int na = (nt - wj + 1) >> 1;  // wave-uniform, 0 .. RT
 #define VLAC_TALL_CASE(N)                                                                                      \
   if constexpr (N < RT)                                                                                        \
-    if (na == N) return tall_body<FW, RT, N, EPI, F16>(a, lds, it, nx, chain, prefilled, slot, n_rows, S);
+    if (na == N) return tall_body<FW, RT, N, EPI, F16, W8>(a, lds, it, nx, chain, prefilled, slot, n_rows, S);
   VLAC_TALL_CASE(0) VLAC_TALL_CASE(1) VLAC_TALL_CASE(2) VLAC_TALL_CASE(3) VLAC_TALL_CASE(4)
 #undef VLAC_TALL_CASE
-  return tall_body<FW, RT, RT, EPI, F16>(a, lds, it, nx, chain, prefilled, slot, n_rows, S);
+  return tall_body<FW, RT, RT, EPI, F16, W8>(a, lds, it, nx, chain, prefilled, slot, n_rows, S);
 }
 
-template <int FW, int RT, int EPI, bool F16>
+template <int FW, int RT, int EPI, bool F16, bool W8>
 __device__ __forceinline__ void tall_items(const GemmArgs& a, uint4* lds, const TallPlan& pl, int n_rows) {
   // Work items are (weight tile, K part, row block) triples, listed with the row blocks of one
   // weight tile and part next to each other, and the list is cut into eight equal runs, one
@@ -300,6 +417,15 @@ __device__ __forceinline__ void tall_items(const GemmArgs& a, uint4* lds, const 
     t.mb = i - vt * pl.row_blocks;
     t.tile = vt / pl.S;
     t.s = vt - t.tile * pl.S;
+    if constexpr (EPI == EPI_QKV) {
+      // Every eighth weight tile, from both ends in turn: each XCD gets its share of the value blocks, whose
+      // results go to the cache in 2-byte pieces, and few of them at a time (a round of them at once kept an
+      // L2 busy for 16 us behind the products, all of them on three XCDs 28).
+      const int qt = pl.tiles >> 3, rt = pl.tiles & 7, far = t.tile - rt * (qt + 1);
+      const int x = far < 0 ? t.tile / (qt + 1) : rt + far / max(qt, 1), n = far < 0 ? qt + 1 : max(qt, 1);
+      const int k = far < 0 ? t.tile % (qt + 1) : far % max(qt, 1);
+      t.tile = 8 * (k & 1 ? n - 1 - (k >> 1) : k >> 1) + x;
+    }
     return t;
   };
   auto exists = [&](int j) { return j < per && x * per + j < items; };
@@ -314,7 +440,7 @@ __device__ __forceinline__ void tall_items(const GemmArgs& a, uint4* lds, const 
     const int jn = j + stride;
     const bool chain = can_chain && exists(jn);
     const TallItem nx = chain ? item_of(jn) : it;
-    slot = tall_dispatch<FW, RT, EPI, F16>(a, lds, it, nx, chain, prefilled, slot, n_rows, pl.S);
+    slot = tall_dispatch<FW, RT, EPI, F16, W8>(a, lds, it, nx, chain, prefilled, slot, n_rows, pl.S);
     if (!exists(jn)) break;
     prefilled = chain;
     it = item_of(jn);
@@ -325,7 +451,8 @@ __device__ __forceinline__ void tall_items(const GemmArgs& a, uint4* lds, const 
 
 // NARROW: items of 192 features are in the choice (a kernel of its own: their code beside the other
 // shapes' cost a whole prefill of thousands of rows, where it is never taken, 0.3 to 0.5 %)
-template <int EPI, bool F16, bool NARROW>
+// W8: weights expanded from e4m3 codes, whose scales (one per output feature) the results are multiplied by
+template <int EPI, bool F16, bool NARROW, bool W8>
 __global__ __launch_bounds__(256) void gemm_tall_kernel(GemmArgs a) {
   extern __shared__ uint4 lds[];  // TallRing<FW, RT>::N stages
   const int n_rows = a.n_rows_val >= 0 ? a.n_rows_val : *a.n_rows;
@@ -334,41 +461,53 @@ __global__ __launch_bounds__(256) void gemm_tall_kernel(GemmArgs a) {
   if constexpr (NARROW) {
     TallPlan p3;
     if (tall_plan_192(a.NB, n_rows, pl, &p3)) {
-      if (p3.rt == 5) tall_items<3, 5, EPI, F16>(a, lds, p3, n_rows);
-      else tall_items<3, 3, EPI, F16>(a, lds, p3, n_rows);
+      if (p3.rt == 5) tall_items<3, 5, EPI, F16, W8>(a, lds, p3, n_rows);
+      else tall_items<3, 3, EPI, F16, W8>(a, lds, p3, n_rows);
       return;
     }
   }
-  if (pl.rt == 4) tall_items<4, 4, EPI, F16>(a, lds, pl, n_rows);
-  else if (pl.rt == 3) tall_items<4, 3, EPI, F16>(a, lds, pl, n_rows);
-  else tall_items<4, 2, EPI, F16>(a, lds, pl, n_rows);
+  if (pl.rt == 4) tall_items<4, 4, EPI, F16, W8>(a, lds, pl, n_rows);
+  else if (pl.rt == 3) tall_items<4, 3, EPI, F16, W8>(a, lds, pl, n_rows);
+  else tall_items<4, 2, EPI, F16, W8>(a, lds, pl, n_rows);
 }
 
-template <int EPI, bool F16, bool NARROW = false>
+template <int EPI, bool F16, bool NARROW, bool W8>
 hipError_t set_lds() {
-  return hipFuncSetAttribute((const void*)gemm_tall_kernel<EPI, F16, NARROW>, hipFuncAttributeMaxDynamicSharedMemorySize,
+  return hipFuncSetAttribute((const void*)gemm_tall_kernel<EPI, F16, NARROW, W8>, hipFuncAttributeMaxDynamicSharedMemorySize,
                              kTallLds);
 }
+template <int EPI, bool F16, bool W8>
+hipError_t set_lds_both() {
+  const hipError_t e = set_lds<EPI, F16, false, W8>();
+  if constexpr (EPI == EPI_QKV || EPI == EPI_SWIGLU) return e != hipSuccess ? e : set_lds<EPI, F16, true, W8>();
+  return e;
+}
+template <bool F16, bool W8>
+hipError_t set_lds_all() {
+  hipError_t e = set_lds_both<EPI_QKV, F16, W8>();
+  if (e == hipSuccess) e = set_lds_both<EPI_SWIGLU, F16, W8>();
+  if (e == hipSuccess) e = set_lds_both<EPI_RESID, F16, W8>();
+  if (e == hipSuccess) e = set_lds_both<EPI_LOGITS, F16, W8>();
+  return e;
+}
 
-template <bool F16>
+template <bool F16, bool W8>
 void launch_tall_t(int epi, const GemmArgs& a, int grid, bool narrow, hipStream_t st) {
-  const size_t shm = kTallLds;
+#define VLAC_TALL_LAUNCH(EPI_, NARROW_) \
+  hipLaunchKernelGGL((gemm_tall_kernel<EPI_, F16, NARROW_, W8>), dim3(grid), dim3(256), kTallLds, st, a)
   switch (epi) {
     case EPI_QKV:
-      if (narrow) hipLaunchKernelGGL((gemm_tall_kernel<EPI_QKV, F16, true>), dim3(grid), dim3(256), shm, st, a);
-      else hipLaunchKernelGGL((gemm_tall_kernel<EPI_QKV, F16, false>), dim3(grid), dim3(256), shm, st, a);
+      if (narrow) VLAC_TALL_LAUNCH(EPI_QKV, true);
+      else VLAC_TALL_LAUNCH(EPI_QKV, false);
       break;
     case EPI_SWIGLU:
-      if (narrow) hipLaunchKernelGGL((gemm_tall_kernel<EPI_SWIGLU, F16, true>), dim3(grid), dim3(256), shm, st, a);
-      else hipLaunchKernelGGL((gemm_tall_kernel<EPI_SWIGLU, F16, false>), dim3(grid), dim3(256), shm, st, a);
+      if (narrow) VLAC_TALL_LAUNCH(EPI_SWIGLU, true);
+      else VLAC_TALL_LAUNCH(EPI_SWIGLU, false);
       break;
-    case EPI_RESID:
-      hipLaunchKernelGGL((gemm_tall_kernel<EPI_RESID, F16, false>), dim3(grid), dim3(256), shm, st, a);
-      break;
-    default:
-      hipLaunchKernelGGL((gemm_tall_kernel<EPI_LOGITS, F16, false>), dim3(grid), dim3(256), shm, st, a);
-      break;
+    case EPI_RESID: VLAC_TALL_LAUNCH(EPI_RESID, false); break;
+    default: VLAC_TALL_LAUNCH(EPI_LOGITS, false); break;
   }
+#undef VLAC_TALL_LAUNCH
 }
 
 __global__ __launch_bounds__(256) void expand_e4m3_kernel(const uint4* __restrict__ codes,
@@ -390,20 +529,10 @@ void launch_expand_e4m3(const uint4* codes, uint4* tiles, size_t n_slots, hipStr
 }
 
 int gemm_tall_init() {
-  hipError_t e;
-  if ((e = set_lds<EPI_QKV, true, true>()) != hipSuccess) return (int)e;
-  if ((e = set_lds<EPI_QKV, false, true>()) != hipSuccess) return (int)e;
-  if ((e = set_lds<EPI_SWIGLU, true, true>()) != hipSuccess) return (int)e;
-  if ((e = set_lds<EPI_SWIGLU, false, true>()) != hipSuccess) return (int)e;
-  if ((e = set_lds<EPI_QKV, true>()) != hipSuccess) return (int)e;
-  if ((e = set_lds<EPI_QKV, false>()) != hipSuccess) return (int)e;
-  if ((e = set_lds<EPI_SWIGLU, true>()) != hipSuccess) return (int)e;
-  if ((e = set_lds<EPI_SWIGLU, false>()) != hipSuccess) return (int)e;
-  if ((e = set_lds<EPI_RESID, true>()) != hipSuccess) return (int)e;
-  if ((e = set_lds<EPI_RESID, false>()) != hipSuccess) return (int)e;
-  if ((e = set_lds<EPI_LOGITS, true>()) != hipSuccess) return (int)e;
-  if ((e = set_lds<EPI_LOGITS, false>()) != hipSuccess) return (int)e;
-  return 0;
+  hipError_t e = set_lds_all<true, false>();
+  if (e == hipSuccess) e = set_lds_all<false, false>();
+  if (e == hipSuccess) e = set_lds_all<true, true>();
+  return (int)e;
 }
 
 void launch_gemm_tall(bool f16, int epi, GemmArgs& a, int rows_cap, int S_max, hipStream_t st) {
@@ -421,6 +550,7 @@ void launch_gemm_tall(bool f16, int epi, GemmArgs& a, int rows_cap, int S_max, h
     if (narrow && tall_plan_192(a.NB, std::min(n, rows_cap), pl, &p3)) most = std::max(most, p3.items());
   }
   const int grid = std::min(((most + 7) / 8) * 8, kTallGrid);
-  if (f16) launch_tall_t<true>(epi, a, grid, narrow, st);
-  else launch_tall_t<false>(epi, a, grid, narrow, st);
+  if (a.wscale) launch_tall_t<true, true>(epi, a, grid, narrow, st);
+  else if (f16) launch_tall_t<true, false>(epi, a, grid, narrow, st);
+  else launch_tall_t<false, false>(epi, a, grid, narrow, st);
 }
