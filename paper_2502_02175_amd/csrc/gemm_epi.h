@@ -61,10 +61,14 @@ __device__ __forceinline__ void read_epilogue_args(const GemmArgs& a) {
   else read_args(a.e.logits, a.e.logits_stride, a.e.best, a.e.vocab);
 }
 
-// x / (1 + e^-x) by the chip's reciprocal (1 ulp): the exponential before it is the larger error, and the result is
-// rounded to 16 bits.  (An IEEE division is ten instructions more, 1280 of the 3600 that a wave of the
-// many-rows kernel spent on a work item of 256 x 256 after its last product.)
-__device__ inline float silu_f(float x) { return x * __builtin_amdgcn_rcpf(1.f + __expf(-x)); }
+// x / (1 + e^-x): one step from x times the chip's reciprocal (1 ulp), whose remainder is exact, rounds as
+// the IEEE division does but for about one quotient in a million, and the fix-up treats infinities and NaN as it does
+// (denominators above 2^126: 0 for what is below 1e-36).  5 instructions instead of 11: the division was 1400 of
+// the 3600 that a wave of the many-rows kernel spent on a work item of 256 x 256 after its last product.
+__device__ inline float silu_f(float x) {
+  const float y = 1.f + __expf(-x), r = __builtin_amdgcn_rcpf(y), q = x * r;
+  return __builtin_amdgcn_div_fixupf(fmaf(fmaf(-y, q, x), r, q), y, x);
+}
 
 // What an epilogue reads from memory for one tile: rotary factors of a query or key block, residual rows of a
 // projection.  It is asked for apart from what is done with it: behind the stores of another tile the compiler
@@ -127,8 +131,10 @@ __device__ __forceinline__ void epilogue_store(const GemmEpi& e, int nb, int slo
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
           const float x1 = acc[4 * q4 + k], x2 = acc[4 * (q4 + 2) + k];
-          o1[k] = x1 * cs[k] - x2 * sn[k];
-          o2[k] = x2 * cs[k] + x1 * sn[k];
+          // (which product is rounded is written out: left to the compiler it changes with the code around it,
+          // and with it the last bits of every result)
+          o1[k] = fmaf(x1, cs[k], -(x2 * sn[k]));
+          o2[k] = fmaf(x2, cs[k], x1 * sn[k]);
         }
         const int f2 = f1 + (hd >> 1);
         *(uint2*)(dst + (size_t)(f1 >> 4) * 512 + ((row + (((f1 >> 3) & 1) << 5)) << 3) + (f1 & 7)) =
