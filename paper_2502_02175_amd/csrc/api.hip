@@ -238,6 +238,7 @@ int vlac_create(const vlac_model_cfg* cfg, vlac_ctx** out) {
   A_(errword, 1);
   A_(zero_tile, 512);
   A_(scratch_i, 64);
+  ctx->split = ctx->scratch_i;
 #undef A_
   if (e == hipSuccess) e = hipMemset(ctx->counters, 0, ctx->n_counters * sizeof(int));
   if (e == hipSuccess) e = hipMemset(ctx->stat_counters, 0, mb * sizeof(int));

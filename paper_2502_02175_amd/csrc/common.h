@@ -142,13 +142,13 @@ struct LayerW {
 };
 
 // What launch_resid_norm_rows needs to know of the GEMM whose partial rows it adds up, where
-// that GEMM chooses its split factor on the device (n_blocks == 0: the factor is S as given)
+// that GEMM chooses its split factor by the row count (neither split nor S_known: the factor is S as given)
 struct SplitAdapt {
-  const int* n_rows;  // device: the row count the GEMM ran with (n_rows_host >= 0: not read)
-  int n_rows_host, n_blocks, KS;  // the GEMM's feature blocks and 64-k steps
-  int S_tall;         // most splits the many-rows kernel may have used (tall_plan)
+  const int* split;   // device: the factor the many-rows kernel used (1: it completed the rows itself)
+  const int* n_rows;  // device: the row count the GEMM ran with
   int small_below;    // > 0: with fewer rows than this the one-stream kernel ran instead ...
   int S_small;        // ... and split K in this many parts (1: it completed the rows itself)
+  int S_known;        // > 0: the factor of a row count that the host knows (split is not read)
 };
 
 struct vlac_ctx {
@@ -209,6 +209,7 @@ struct vlac_ctx {
   bf16_t* zero_tile; // one operand tile of zeros
   int* errword;     // device error bits
   int* scratch_i;   // small int scratch
+  int* split;       // (there) split factor of the last many-rows GEMM with a residual
   uint8_t* filled;  // host: stream cache holds a prefill
   uint8_t* was_reset;
   // per-launch timing of one GEMM class (vlac_profile_select)
@@ -317,9 +318,7 @@ struct NormIn {
 // operands over its share of K; with K split also its partial rows, written once and read once
 // by the row kernel: 2 x 64 rt rows x 256 features x 4 bytes, counted twice, because they go
 // through memory where operand tiles are mostly shared in L2); ties go to the larger block
-// and the fewer parts.  KS: 64-k steps of the projection.  Both the GEMM and the row kernel
-// that consumes the partial rows call this function (32-bit arithmetic, divisions by
-// constants only).
+// and the fewer parts.  KS: 64-k steps of the projection.  (32-bit arithmetic, divisions by constants only.)
 struct TallPlan {
   int rt, tiles, row_blocks, S;  // row tiles per wave (4, 3 or 2), weight tiles of 256 features, row blocks, K parts
   __host__ __device__ int items() const { return tiles * S * row_blocks; }

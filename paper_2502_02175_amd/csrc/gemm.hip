@@ -801,16 +801,15 @@ static bool use_both(const vlac_ctx* c, int rows_cap, int n_rows_host) {
 }
 
 SplitAdapt gemm_resid_adapt(vlac_ctx* c, int n_blocks, int kpad, int rows_cap, const int* n_rows, int n_rows_host) {
-  SplitAdapt ad = {nullptr, -1, 0, 0, 0, 0, 0};
+  SplitAdapt ad = {nullptr, nullptr, 0, 0, 0};
   if (!use_tall(c, rows_cap)) return ad;
-  const int d_model = n_blocks * 32;
+  const int d_model = n_blocks * 32, S_max = tall_resid_smax(c, EPI_RESID, rows_cap, d_model);
   const bool both = use_both(c, rows_cap, n_rows_host);
-  ad.S_tall = tall_resid_smax(c, EPI_RESID, rows_cap, d_model);
-  if (ad.S_tall > 1 || both) {
+  if (n_rows_host >= 0) {
+    if (S_max > 1) ad.S_known = tall_plan((n_blocks + 7) >> 3, n_rows_host, S_max, kpad / 64).S;
+  } else if (both || S_max > 1) {
+    ad.split = c->split;
     ad.n_rows = n_rows;
-    ad.n_rows_host = n_rows_host;
-    ad.n_blocks = n_blocks;
-    ad.KS = kpad / 64;
     if (both) {
       ad.small_below = kSmallRows;
       ad.S_small = rows_kernel_splits(c, EPI_RESID, n_blocks, kpad / 64, rows_cap, d_model, kFewRows - 1, false);
@@ -903,6 +902,7 @@ int launch_gemm(vlac_ctx* c, int epi, const bf16_t* wp, const float* wscale, int
   if (norm) a.norm = *norm;
   a.partial = c->partial;
   a.counters = c->counters;
+  a.split = c->split;
   a.e = e;
   const int cls = rows_cap <= 32 ? 0 : 1;
   const bool timed = c->prof_kind == epi + 4 * cls && c->prof_n < c->prof_cap;

@@ -20,6 +20,7 @@ struct GemmArgs {
   const uint4* zero_tile;  // 1 KiB of zeros
   float* partial;
   int* counters;
+  int* split;         // many-rows GEMM with a residual: where it leaves the split factor it chose
   GemmEpi e;
   NormIn norm;        // fused RMSNorm of the input rows (few-rows kernel only)
 };

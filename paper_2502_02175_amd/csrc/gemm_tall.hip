@@ -458,6 +458,7 @@ __global__ __launch_bounds__(256) void gemm_tall_kernel(GemmArgs a) {
   const int n_rows = a.n_rows_val >= 0 ? a.n_rows_val : *a.n_rows;
   if (n_rows < a.rows_lo) return;  // the one-stream kernel's share
   const TallPlan pl = tall_plan((a.NB + 7) >> 3, n_rows, EPI == EPI_RESID ? a.S : 1, a.KS);
+  if (EPI == EPI_RESID && blockIdx.x == 0 && threadIdx.x == 0) *a.split = pl.S;
   if constexpr (NARROW) {
     TallPlan p3;
     if (tall_plan_192(a.NB, n_rows, pl, &p3)) {

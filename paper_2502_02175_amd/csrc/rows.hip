@@ -185,26 +185,27 @@ __global__ __launch_bounds__(256) void rmsnorm_rows_kernel(
     const int* __restrict__ n_rows, int n_rows_host, int decode_pos,
     const float* __restrict__ gain, float eps, int d, bf16_t* __restrict__ xp, int KC) {
   read_args(src, seq_stride, rows, decode_pos, gain, eps, d, xp, KC);
-  const int slot = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (slot >= (n_rows_host >= 0 ? n_rows_host : ld_scalar(n_rows))) return;
-  const int id = decode_pos >= 0 ? ((slot << 16) | decode_pos) : ld_scalar(rows + slot);
-  const float* x = src + ((size_t)(id >> 16) * seq_stride + (id & 0xffff)) * d;
-  float ss = 0.f;
-  for (int k = lane * 4; k < d; k += 256) {
-    const float4 v = *(const float4*)(x + k);
-    ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
-  }
-  ss = wave_sum(ss);
-  const float r = rsqrtf(ss / (float)d + eps);
-  for (int k = lane * 8; k < d; k += 512) {
-    const float4 a = *(const float4*)(x + k), b = *(const float4*)(x + k + 4);
-    const float4 ga = *(const float4*)(gain + k), gb = *(const float4*)(gain + k + 4);
-    uint4 o;
-    o.x = pack_op2<F16>(a.x * r * ga.x, a.y * r * ga.y);
-    o.y = pack_op2<F16>(a.z * r * ga.z, a.w * r * ga.w);
-    o.z = pack_op2<F16>(b.x * r * gb.x, b.y * r * gb.y);
-    o.w = pack_op2<F16>(b.z * r * gb.z, b.w * r * gb.w);
-    *(uint4*)(xp + frag_off(slot, k, KC)) = o;
+  const int lane = threadIdx.x & 63, n = n_rows_host >= 0 ? n_rows_host : ld_scalar(n_rows);
+  for (int slot = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); slot < n; slot += gridDim.x * 4) {
+    const int id = decode_pos >= 0 ? ((slot << 16) | decode_pos) : ld_scalar(rows + slot);
+    const float* x = src + ((size_t)(id >> 16) * seq_stride + (id & 0xffff)) * d;
+    float ss = 0.f;
+    for (int k = lane * 4; k < d; k += 256) {
+      const float4 v = *(const float4*)(x + k);
+      ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+    }
+    ss = wave_sum(ss);
+    const float r = rsqrtf(ss / (float)d + eps);
+    for (int k = lane * 8; k < d; k += 512) {
+      const float4 a = *(const float4*)(x + k), b = *(const float4*)(x + k + 4);
+      const float4 ga = *(const float4*)(gain + k), gb = *(const float4*)(gain + k + 4);
+      uint4 o;
+      o.x = pack_op2<F16>(a.x * r * ga.x, a.y * r * ga.y);
+      o.y = pack_op2<F16>(a.z * r * ga.z, a.w * r * ga.w);
+      o.z = pack_op2<F16>(b.x * r * gb.x, b.y * r * gb.y);
+      o.w = pack_op2<F16>(b.z * r * gb.z, b.w * r * gb.w);
+      *(uint4*)(xp + frag_off(slot, k, KC)) = o;
+    }
   }
 }
 
@@ -217,48 +218,194 @@ __global__ __launch_bounds__(256) void rmsnorm_rows_reg_kernel(
     const int* __restrict__ n_rows, int n_rows_host, int decode_pos,
     const float* __restrict__ gain, float eps, int d, bf16_t* __restrict__ xp, int KC) {
   read_args(src, seq_stride, rows, decode_pos, gain, eps, d, xp, KC);
-  const int slot = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (slot >= (n_rows_host >= 0 ? n_rows_host : ld_scalar(n_rows))) return;
-  const int id = decode_pos >= 0 ? ((slot << 16) | decode_pos) : ld_scalar(rows + slot);
-  const float* x = src + ((size_t)(id >> 16) * seq_stride + (id & 0xffff)) * d;
+  const int lane = threadIdx.x & 63, n = n_rows_host >= 0 ? n_rows_host : ld_scalar(n_rows);
   const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
-  float4 a[NI], b[NI], ga[NI], gb[NI];
+  int slot = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (slot >= n) return;
+  float4 ga[NI], gb[NI];
 #pragma unroll
   for (int i = 0; i < NI; ++i) {
     const int k = lane * 8 + i * 512;
-    a[i] = b[i] = ga[i] = gb[i] = zero;
+    ga[i] = gb[i] = zero;
     if (k < d) {
-      a[i] = *(const float4*)(x + k);
-      b[i] = *(const float4*)(x + k + 4);
       ga[i] = *(const float4*)(gain + k);
       gb[i] = *(const float4*)(gain + k + 4);
     }
   }
-  float ss = 0.f;
+  for (; slot < n; slot += gridDim.x * 4) {
+    const int id = decode_pos >= 0 ? ((slot << 16) | decode_pos) : ld_scalar(rows + slot);
+    const float* x = src + ((size_t)(id >> 16) * seq_stride + (id & 0xffff)) * d;
+    float4 a[NI], b[NI];
 #pragma unroll
-  for (int i = 0; i < NI; ++i)
-    ss += a[i].x * a[i].x + a[i].y * a[i].y + a[i].z * a[i].z + a[i].w * a[i].w +
-          (b[i].x * b[i].x + b[i].y * b[i].y + b[i].z * b[i].z + b[i].w * b[i].w);
-  ss = wave_sum(ss);
-  const float r = rsqrtf(ss / (float)d + eps);
+    for (int i = 0; i < NI; ++i) {
+      const int k = lane * 8 + i * 512;
+      a[i] = b[i] = zero;
+      if (k < d) {
+        a[i] = *(const float4*)(x + k);
+        b[i] = *(const float4*)(x + k + 4);
+      }
+    }
+    float ss = 0.f;
 #pragma unroll
-  for (int i = 0; i < NI; ++i) {
-    const int k = lane * 8 + i * 512;
-    if (k < d) {
-      uint4 o;
-      o.x = pack_op2<F16>(a[i].x * r * ga[i].x, a[i].y * r * ga[i].y);
-      o.y = pack_op2<F16>(a[i].z * r * ga[i].z, a[i].w * r * ga[i].w);
-      o.z = pack_op2<F16>(b[i].x * r * gb[i].x, b[i].y * r * gb[i].y);
-      o.w = pack_op2<F16>(b[i].z * r * gb[i].z, b[i].w * r * gb[i].w);
-      *(uint4*)(xp + frag_off(slot, k, KC)) = o;
+    for (int i = 0; i < NI; ++i)
+      ss += a[i].x * a[i].x + a[i].y * a[i].y + a[i].z * a[i].z + a[i].w * a[i].w +
+            (b[i].x * b[i].x + b[i].y * b[i].y + b[i].z * b[i].z + b[i].w * b[i].w);
+    ss = wave_sum(ss);
+    const float r = rsqrtf(ss / (float)d + eps);
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int k = lane * 8 + i * 512;
+      if (k < d) {
+        uint4 o;
+        o.x = pack_op2<F16>(a[i].x * r * ga[i].x, a[i].y * r * ga[i].y);
+        o.y = pack_op2<F16>(a[i].z * r * ga[i].z, a[i].w * r * ga[i].w);
+        o.z = pack_op2<F16>(b[i].x * r * gb[i].x, b[i].y * r * gb[i].y);
+        o.w = pack_op2<F16>(b[i].z * r * gb[i].z, b[i].w * r * gb[i].w);
+        *(uint4*)(xp + frag_off(slot, k, KC)) = o;
+      }
     }
   }
 }
 
+// Residual add with the split-K partial rows of the projection that came before, then
+// (optionally) the RMSNorm that comes next: h[row] = resid[row] + sum_s part[s][slot]
+// (in split order); xp[slot] = RMSNorm(h[row]) * gain.  One workgroup per row; the row
+// stays in registers (MAXI float4 per thread, d <= 1024 * MAXI), and all of a thread's
+// loads of the row and of its partial rows are in flight together: the work per row is all
+// latency.  gain == nullptr: no norm.
+struct RowArgs {
+  const float* resid; int resid_seq_stride;
+  const float* part; int part_rows;
+  float* h; int h_seq_stride;
+  const int *rows, *part_slot;  // part_slot: the slots that the rows had when the GEMM ran (nullptr: the same)
+  const float* gain; float eps; int d;
+  bf16_t* xp; int KC;
+  bool in_place;  // S == 0: h holds the sums already
+};
+
+template <bool F16, int MAXI, int S>
+__device__ __forceinline__ void resid_norm_body(const RowArgs& a, int n, float (&red)[2][4]) {
+  constexpr int SA = S * MAXI > 32 ? 4 : S;  // partial rows in flight at a time
+  const int tid = threadIdx.x, d = a.d;
+  const size_t pstride = (size_t)a.part_rows * d;
+  float4 g[MAXI];
+#pragma unroll
+  for (int i = 0; i < MAXI; ++i) {
+    const int k = tid * 4 + i * 1024;
+    g[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (a.gain && k < d) g[i] = *(const float4*)(a.gain + k);
+  }
+  // (the lists have room for every slot of the grid, and past the end of a list nothing is done with what
+  // they hold there)
+  int slot = blockIdx.x, id = ld_scalar(a.rows + slot), pslot = S > 0 && a.part_slot ? ld_scalar(a.part_slot + slot) : slot;
+  for (int turn = 0; slot < n; turn ^= 1) {
+    const int next = slot + gridDim.x;
+    int id_next = 0, pslot_next = next;
+    if (next < n) {
+      id_next = ld_scalar(a.rows + next);
+      if (S > 0 && a.part_slot) pslot_next = ld_scalar(a.part_slot + next);
+    }
+    float* y = a.h + ((size_t)(id >> 16) * a.h_seq_stride + (id & 0xffff)) * d;
+    const float* src = S == 0 && a.in_place ? y : a.resid + ((size_t)(id >> 16) * a.resid_seq_stride + (id & 0xffff)) * d;
+    const float* p0 = a.part + (size_t)pslot * d;
+    float4 v[MAXI], t[SA > 0 ? SA : 1][MAXI];
+#pragma unroll
+    for (int i = 0; i < MAXI; ++i) {
+      const int k = tid * 4 + i * 1024;
+      v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (k < d) v[i] = *(const float4*)(src + k);
+    }
+#pragma unroll
+    for (int s0 = 0; s0 < S; s0 += SA > 0 ? SA : 1) {  // fixed order
+#pragma unroll
+      for (int s = 0; s < SA; ++s)
+#pragma unroll
+        for (int i = 0; i < MAXI; ++i) {
+          const int k = tid * 4 + i * 1024;
+          t[s][i] = make_float4(0.f, 0.f, 0.f, 0.f);
+          if (s0 + s < S && k < d) t[s][i] = *(const float4*)(p0 + (s0 + s) * pstride + k);
+        }
+#pragma unroll
+      for (int s = 0; s < SA; ++s)
+        if (s0 + s < S) {
+#pragma unroll
+          for (int i = 0; i < MAXI; ++i) {
+            v[i].x += t[s][i].x; v[i].y += t[s][i].y;
+            v[i].z += t[s][i].z; v[i].w += t[s][i].w;
+          }
+        }
+    }
+    float ss = 0.f;
+#pragma unroll
+    for (int i = 0; i < MAXI; ++i) {
+      const int k = tid * 4 + i * 1024;
+      if (k < d && !(S == 0 && a.in_place)) *(float4*)(y + k) = v[i];
+      // (which product is rounded is written out: it would else change with the code around it)
+      ss += fmaf(v[i].w, v[i].w, fmaf(v[i].z, v[i].z, fmaf(v[i].x, v[i].x, v[i].y * v[i].y)));
+    }
+    if (a.gain) {
+      ss = wave_sum(ss);
+      if ((tid & 63) == 0) red[turn][tid >> 6] = ss;
+      __syncthreads();
+      const float rinv = rsqrtf((red[turn][0] + red[turn][1] + red[turn][2] + red[turn][3]) / (float)d + a.eps);
+#pragma unroll
+      for (int i = 0; i < MAXI; ++i) {
+        const int k = tid * 4 + i * 1024;
+        if (k < d)
+          *(uint2*)(a.xp + frag_off(slot, k, a.KC)) =
+              make_uint2(pack_op2<F16>(v[i].x * rinv * g[i].x, v[i].y * rinv * g[i].y),
+                         pack_op2<F16>(v[i].z * rinv * g[i].z, v[i].w * rinv * g[i].w));
+      }
+    }
+    slot = next;
+    id = id_next;
+    pslot = pslot_next;
+  }
+}
+
+// The partial rows of a launch are asked for exactly as many as there are: the split factor chooses the body.  (All
+// that the instance has room for, the last one again past the end, brought 8 of them for 3 at 519 rows.)  A factor
+// that the GEMM chose on the device is read, not worked out once more by every workgroup; a workgroup takes
+// every kRowGrid-th row and keeps the gains.  2712 rows of 4096 values, unsplit: 26.3 -> 24 us; 519 rows in 3 parts
+// 15.9 -> 13.2; grouped queries, 32 x 304 tokens, 23.4 -> 20.9 on average.  (The next row's loads ahead of the sum
+// of this one's squares: 208 registers instead of 124, and slower.)
+template <bool F16, int MAXI, int NS>
+__global__ __launch_bounds__(256, MAXI == 8 ? 1 : NS == 8 ? 2 : 4) void resid_norm_rows_kernel(RowArgs a, int S, const int* __restrict__ n_rows,
+                                                              int n_rows_host, SplitAdapt adapt) {
+  __shared__ float red[2][4];
+  read_args(a.resid, a.resid_seq_stride, a.part, a.part_rows, a.h, a.h_seq_stride, a.rows, a.part_slot, a.gain, a.eps, a.d,
+            a.xp, a.KC, S, n_rows, n_rows_host, adapt.n_rows, adapt.split, adapt.small_below, adapt.S_small, adapt.S_known);
+  const int n = n_rows_host >= 0 ? n_rows_host : ld_scalar(n_rows);
+  if (adapt.S_known > 0) S = adapt.S_known;
+  if (adapt.split) {
+    const int n_g = adapt.small_below > 0 ? ld_scalar(adapt.n_rows) : 0, told = ld_scalar(adapt.split);
+    S = n_g < adapt.small_below ? adapt.S_small : told;
+  }
+  // (unsplit the GEMM has added to the residual stream itself and left no partial rows)
+  if ((adapt.split || adapt.S_known > 0) && S == 1) {
+    S = 0;
+    a.in_place = true;
+  }
+  if ((int)blockIdx.x >= n) return;
+  switch (S) {
+    case 0: resid_norm_body<F16, MAXI, 0>(a, n, red); break;
+    case 1: resid_norm_body<F16, MAXI, 1>(a, n, red); break;
+    case 2: resid_norm_body<F16, MAXI, 2>(a, n, red); break;
+    case 3: resid_norm_body<F16, MAXI, 3>(a, n, red); break;
+    case 4: resid_norm_body<F16, MAXI, 4>(a, n, red); break;
+    case 5: if constexpr (NS > 4) resid_norm_body<F16, MAXI, 5>(a, n, red); break;
+    case 6: if constexpr (NS > 4) resid_norm_body<F16, MAXI, 6>(a, n, red); break;
+    case 7: if constexpr (NS > 4) resid_norm_body<F16, MAXI, 7>(a, n, red); break;
+    case 8: if constexpr (NS > 4) resid_norm_body<F16, MAXI, 8>(a, n, red); break;
+  }
+}
+
+static const int kRowGrid = 1024;  // workgroups of a row kernel at most: 4 per CU
+
 void launch_rmsnorm_rows(bool f16, const float* src, int seq_stride, const int* rows,
                          const int* n_rows, int n_rows_host, int decode_pos, int max_rows,
                          const float* gain, float eps, int d, bf16_t* xp, int KC, hipStream_t st) {
-  const dim3 grid((max_rows + 3) / 4), block(256);
+  const dim3 grid(std::min((max_rows + 3) / 4, kRowGrid)), block(256);
 #define VLAC_NORM_ARGS src, seq_stride, rows, n_rows, n_rows_host, decode_pos, gain, eps, d, xp, KC
   if (d <= 2048) {
     if (f16) hipLaunchKernelGGL((rmsnorm_rows_reg_kernel<true, 4>), grid, block, 0, st, VLAC_NORM_ARGS);
@@ -271,99 +418,6 @@ void launch_rmsnorm_rows(bool f16, const float* src, int seq_stride, const int* 
     else hipLaunchKernelGGL(rmsnorm_rows_kernel<false>, grid, block, 0, st, VLAC_NORM_ARGS);
   }
 #undef VLAC_NORM_ARGS
-}
-
-// Residual add with the split-K partial rows of the projection that came before, then
-// (optionally) the RMSNorm that comes next: h[row] = resid[row] + sum_s part[s][slot]
-// (in split order); xp[slot] = RMSNorm(h[row]) * gain.  One workgroup per row; the row
-// stays in registers (MAXI float4 per thread, d <= 1024 * MAXI), and all of a thread's
-// loads of the row and of two splits are in flight together: the work per row is all
-// latency.  gain == nullptr: no norm.
-template <bool F16, int MAXI, int NS>
-__global__ __launch_bounds__(256) void resid_norm_rows_kernel(
-    const float* __restrict__ resid, int resid_seq_stride, const float* __restrict__ part, int S,
-    int part_rows, float* __restrict__ h, int h_seq_stride, const int* __restrict__ rows,
-    const int* __restrict__ part_slot, const int* __restrict__ n_rows, int n_rows_host,
-    const float* __restrict__ gain, float eps, int d, bf16_t* __restrict__ xp, int KC, SplitAdapt adapt) {
-  __shared__ float red[4];
-  read_args(resid, resid_seq_stride, part, S, part_rows, h, h_seq_stride, rows, part_slot, n_rows, n_rows_host, gain, eps, d,
-            xp, KC, adapt.n_rows, adapt.n_rows_host, adapt.n_blocks, adapt.KS, adapt.S_tall, adapt.small_below, adapt.S_small);
-  // (asked for together; the lists have room for every slot of the grid, and past the end of
-  // a list nothing is done with what they hold there)
-  const int slot = blockIdx.x, tid = threadIdx.x;
-  const int n = n_rows_host >= 0 ? n_rows_host : ld_scalar(n_rows), id = ld_scalar(rows + slot);
-  // the partial rows are indexed by the slot the row had when the GEMM ran
-  const int pslot = part_slot ? ld_scalar(part_slot + slot) : slot;
-  // the GEMM's row count, where that is what its split factor followed from
-  const int n_g = adapt.n_blocks > 0 && adapt.n_rows_host < 0 ? ld_scalar(adapt.n_rows) : adapt.n_rows_host;
-  read_args(n, id, pslot, n_g);
-  if (slot >= n) return;
-  const float* r = resid + ((size_t)(id >> 16) * resid_seq_stride + (id & 0xffff)) * d;
-  float* y = h + ((size_t)(id >> 16) * h_seq_stride + (id & 0xffff)) * d;
-  if (adapt.n_blocks > 0) {
-    // the GEMM chose its split factor from its row count; unsplit, it added to the
-    // residual stream itself and left no partial rows
-    S = n_g < adapt.small_below ? adapt.S_small : tall_plan((adapt.n_blocks + 7) >> 3, n_g, adapt.S_tall, adapt.KS).S;
-    if (S == 1) {
-      S = 0;
-      r = y;
-    }
-  }
-  const float* p0 = part + (size_t)pslot * d;
-  const size_t pstride = (size_t)part_rows * d;
-  const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
-  // NS splits are in flight at a time (all 8 for rows of up to 4096 elements where the GEMM
-  // may have split that far; 4 where it splits less, which leaves registers for more rows
-  // per CU): a split past the last one is loaded from the last (a valid address, no branch)
-  // and not added
-  float4 v[MAXI], g[MAXI], t[NS][MAXI];
-#pragma unroll
-  for (int i = 0; i < MAXI; ++i) {
-    const int k = tid * 4 + i * 1024;
-    v[i] = g[i] = zero;
-    if (k < d) {
-      v[i] = *(const float4*)(r + k);
-      if (gain) g[i] = *(const float4*)(gain + k);
-    }
-  }
-  for (int s = 0; s < S; s += NS) {  // fixed order
-#pragma unroll
-    for (int u = 0; u < NS; ++u)
-#pragma unroll
-      for (int i = 0; i < MAXI; ++i) {
-        const int k = tid * 4 + i * 1024;
-        t[u][i] = zero;
-        if (k < d) t[u][i] = *(const float4*)(p0 + (size_t)min(s + u, S - 1) * pstride + k);
-      }
-#pragma unroll
-    for (int u = 0; u < NS; ++u)
-#pragma unroll
-      for (int i = 0; i < MAXI; ++i) {
-        const float on = s + u < S ? 1.f : 0.f;
-        v[i].x += on * t[u][i].x; v[i].y += on * t[u][i].y;
-        v[i].z += on * t[u][i].z; v[i].w += on * t[u][i].w;
-      }
-  }
-  float ss = 0.f;
-#pragma unroll
-  for (int i = 0; i < MAXI; ++i) {
-    const int k = tid * 4 + i * 1024;
-    if (k < d && (S > 0 || r != y)) *(float4*)(y + k) = v[i];  // (unsplit in place: h holds it already)
-    ss += v[i].x * v[i].x + v[i].y * v[i].y + v[i].z * v[i].z + v[i].w * v[i].w;
-  }
-  if (!gain) return;
-  ss = wave_sum(ss);
-  if ((tid & 63) == 0) red[tid >> 6] = ss;
-  __syncthreads();
-  const float rinv = rsqrtf((red[0] + red[1] + red[2] + red[3]) / (float)d + eps);
-#pragma unroll
-  for (int i = 0; i < MAXI; ++i) {
-    const int k = tid * 4 + i * 1024;
-    if (k < d)
-      *(uint2*)(xp + frag_off(slot, k, KC)) =
-          make_uint2(pack_op2<F16>(v[i].x * rinv * g[i].x, v[i].y * rinv * g[i].y),
-                     pack_op2<F16>(v[i].z * rinv * g[i].z, v[i].w * rinv * g[i].w));
-  }
 }
 
 // Rows longer than 8192: the row is re-read instead of kept (a thread re-reads only what
@@ -410,12 +464,10 @@ void launch_resid_norm_rows(bool f16, const float* resid, int resid_seq_stride, 
                             const int* part_slot, const int* n_rows, int n_rows_host, int max_rows,
                             const float* gain, float eps, int d, bf16_t* xp, int KC,
                             hipStream_t st, const SplitAdapt* adapt) {
-  SplitAdapt ad = {nullptr, -1, 0, 0, 0, 0, 0};
+  SplitAdapt ad = {nullptr, nullptr, 0, 0, 0};
   if (adapt) ad = *adapt;  // (never given for rows longer than 8192)
-#define VLAC_RN(K)                                                                               \
-  hipLaunchKernelGGL(K, dim3(max_rows), dim3(256), 0, st, resid, resid_seq_stride, part, S,      \
-                     part_rows, h, h_seq_stride, rows, part_slot, n_rows, n_rows_host, gain, eps, \
-                     d, xp, KC, ad)
+  const RowArgs a = {resid, resid_seq_stride, part, part_rows, h, h_seq_stride, rows, part_slot, gain, eps, d, xp, KC, false};
+#define VLAC_RN(K) hipLaunchKernelGGL(K, dim3(std::min(max_rows, kRowGrid)), dim3(256), 0, st, a, S, n_rows, n_rows_host, ad)
   if (d <= 4096 && S <= 4) {
     if (f16) VLAC_RN((resid_norm_rows_kernel<true, 4, 4>));
     else VLAC_RN((resid_norm_rows_kernel<false, 4, 4>));
@@ -423,8 +475,8 @@ void launch_resid_norm_rows(bool f16, const float* resid, int resid_seq_stride, 
     if (f16) VLAC_RN((resid_norm_rows_kernel<true, 4, 8>));
     else VLAC_RN((resid_norm_rows_kernel<false, 4, 8>));
   } else if (d <= 8192) {
-    if (f16) VLAC_RN((resid_norm_rows_kernel<true, 8, 4>));
-    else VLAC_RN((resid_norm_rows_kernel<false, 8, 4>));
+    if (f16) VLAC_RN((resid_norm_rows_kernel<true, 8, 8>));
+    else VLAC_RN((resid_norm_rows_kernel<false, 8, 8>));
   } else {
 #undef VLAC_RN
 #define VLAC_RN(K)                                                                               \
