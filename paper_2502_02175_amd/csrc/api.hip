@@ -701,14 +701,18 @@ int vlac_sparse_prefill(vlac_ctx* ctx, const float* embeds, int B, int L_v, int 
               ctx->prev_slot + (size_t)l * ctx->max_rows, (bf16_t*)kv_cache, out_attn_mean, &pending,
               st);
   }
-  if (pending)  // the last FFN's partial rows still have to reach the residual stream
+  // the last FFN's partial rows still have to reach the residual stream; the final norm of the hidden states is made
+  // on the way, while the row is in registers
+  const bool hidden_too = pending && out_hidden && m.d_model <= 8192;
+  if (pending)
     launch_resid_norm_rows(ctx->f16, ctx->h, m.max_seq, ctx->rpart, pending, rows_cap, ctx->h,
                            m.max_seq, ctx->rows + (size_t)(nl - 1) * ctx->max_rows, nullptr,
-                           ctx->n_rows + (nl - 1), n_host, rows_cap, nullptr, m.rms_eps, m.d_model,
-                           ctx->xa, ctx->kpad_d / 16, st, &ctx->pending_adapt);
+                           ctx->n_rows + (nl - 1), n_host, rows_cap, hidden_too ? ctx->g_final : nullptr, m.rms_eps,
+                           m.d_model, ctx->xa, ctx->kpad_d / 16, st, &ctx->pending_adapt,
+                           hidden_too ? out_hidden : nullptr, L);
   if (out_attn_mean && attention_defers_stats(ctx, B, L_v, L_t))
     launch_stats_reduce(ctx, B, L_v, L_t, out_attn_mean, st);
-  if (out_hidden)
+  if (out_hidden && !hidden_too)
     launch_final_hidden(ctx->h, m.max_seq, ctx->rows + (size_t)(nl - 1) * ctx->max_rows,
                         ctx->n_rows + (nl - 1), rows_cap, ctx->g_final, m.rms_eps, m.d_model,
                         out_hidden, L, st);

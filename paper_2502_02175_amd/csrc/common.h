@@ -249,12 +249,13 @@ void launch_decode_plan(vlac_ctx* c, int B, int L, int n_new, hipStream_t st);
 void launch_rmsnorm_rows(bool f16, const float* src, int seq_stride, const int* rows,
                          const int* n_rows, int n_rows_host, int decode_pos, int max_rows, const float* gain, float eps, int d,
                          bf16_t* xp, int KC, hipStream_t st);
-// h[row] = resid[row] + sum of the S partial rows; optionally RMSNorm(h[row]) -> operand xp
+// h[row] = resid[row] + sum of the S partial rows; optionally RMSNorm(h[row]) -> operand xp, or (rows of at most
+// 8192 elements) -> fp32 rows of out [B, out_L, d]
 void launch_resid_norm_rows(bool f16, const float* resid, int resid_seq_stride, const float* part,
                             int S, int part_rows, float* h, int h_seq_stride, const int* rows,
                             const int* part_slot, const int* n_rows, int n_rows_host, int max_rows,
                             const float* gain, float eps, int d, bf16_t* xp, int KC,
-                            hipStream_t st, const SplitAdapt* adapt = nullptr);
+                            hipStream_t st, const SplitAdapt* adapt = nullptr, float* out = nullptr, int out_L = 0);
 void launch_final_hidden(const float* src, int seq_stride, const int* rows, const int* n_rows,
                          int max_rows, const float* gain, float eps, int d, float* out, int L,
                          hipStream_t st);

@@ -137,10 +137,96 @@ __global__ __launch_bounds__(256) void plan_rows_kernel(
   }
 }
 
+// The plan of a single stream in one launch: grid (n_layers + 1), a workgroup ranks the stream's reuse order for
+// itself (in LDS) and works out its layer's count.  (Two launches of 5 us each that wait for one another: all latency.)
+constexpr int kPlanOneLv = 4096;
+__global__ __launch_bounds__(256) void plan_one_kernel(int L_v, int L_t, int n_layers, int max_rows, int max_batch,
+                                                       const int32_t* __restrict__ reuse_order,
+                                                       const int32_t* __restrict__ reuse_count, int stride,
+                                                       const int32_t* __restrict__ layer_count, int* __restrict__ rows,
+                                                       int* __restrict__ n_rows, int* __restrict__ slot_off,
+                                                       int* __restrict__ prev_slot, int* __restrict__ errword) {
+  __shared__ int rk[kPlanOneLv];
+  __shared__ int wsum[4], wsum_p[4], wmax[4], wmax_p[4];
+  read_args(L_v, L_t, n_layers, max_rows, max_batch, reuse_order, reuse_count, stride, layer_count, rows, n_rows, slot_off,
+            prev_slot, errword);
+  const int l = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6, L = L_v + L_t;
+  if (l == n_layers) {
+    if (tid == 0) {
+      rows[(size_t)l * max_rows] = L - 1;
+      slot_off[(size_t)l * (max_batch + 1)] = 0;
+      slot_off[(size_t)l * (max_batch + 1) + 1] = 1;
+      n_rows[l] = 1;
+    }
+    return;
+  }
+  int cnt = 0;
+  if (reuse_order) {
+    cnt = ld_scalar(reuse_count);
+    if (cnt < 0 || cnt > stride) {
+      if (tid == 0 && l == 0) atomicOr(errword, VLAC_ERR_BAD_INDEX);
+      cnt = cnt < 0 ? 0 : stride;
+    }
+  }
+  // m: how many entries of the reuse order layer l reuses (clamped, non-decreasing over l), m_p: the layer before
+  int m = 0, m_p = 0;
+  for (int k = tid; k <= l; k += 256) {
+    const int x = layer_count ? min(max(layer_count[k], 0), cnt) : cnt;
+    m = max(m, x);
+    if (k < l) m_p = max(m_p, x);
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    m = max(m, __shfl_xor(m, o));
+    m_p = max(m_p, __shfl_xor(m_p, o));
+  }
+  if (lane == 0) { wmax[w] = m; wmax_p[w] = m_p; }
+  for (int v = tid; v < L_v; v += 256) rk[v] = 0x7fffffff;
+  __syncthreads();
+  m = max(max(wmax[0], wmax[1]), max(wmax[2], wmax[3]));
+  m_p = max(max(wmax_p[0], wmax_p[1]), max(wmax_p[2], wmax_p[3]));
+  for (int i = tid; i < cnt; i += 256) {
+    const int v = reuse_order[i];
+    const bool ok = v >= 0 && v < L_v;
+    if (!ok || atomicMin(&rk[v], i) != 0x7fffffff) {  // out of range, or a repeated entry
+      if (l == 0) atomicOr(errword, VLAC_ERR_BAD_INDEX);
+    }
+  }
+  __syncthreads();
+  int base = 0, base_p = 0;
+  for (int c0 = 0; c0 < L; c0 += 256) {
+    const int p = c0 + tid, r = p < L_v ? rk[p] : 0x7fffffff;
+    const int keep = p < L && r >= m, keep_p = p < L && r >= m_p;  // (the row of the layer before: a superset)
+    const unsigned long long bal = __ballot(keep), bal_p = __ballot(keep_p), below = (1ull << lane) - 1ull;
+    if (lane == 0) { wsum[w] = __popcll(bal); wsum_p[w] = __popcll(bal_p); }
+    __syncthreads();
+    int o = base, o_p = base_p;
+    for (int k = 0; k < w; ++k) { o += wsum[k]; o_p += wsum_p[k]; }
+    if (keep) {
+      const int slot = o + __popcll(bal & below);
+      rows[(size_t)l * max_rows + slot] = p;
+      prev_slot[(size_t)l * max_rows + slot] = l > 0 ? o_p + __popcll(bal_p & below) : slot;
+    }
+    base += wsum[0] + wsum[1] + wsum[2] + wsum[3];
+    base_p += wsum_p[0] + wsum_p[1] + wsum_p[2] + wsum_p[3];
+    __syncthreads();
+  }
+  if (tid == 0) {
+    slot_off[(size_t)l * (max_batch + 1)] = 0;
+    slot_off[(size_t)l * (max_batch + 1) + 1] = base;
+    n_rows[l] = base;
+  }
+}
+
 void launch_plan(vlac_ctx* c, int B, int L_v, int L_t, const int32_t* reuse_order,
                  const int32_t* reuse_count, int stride, const int32_t* layer_count,
                  hipStream_t st) {
   const int nl = c->cfg.n_layers;
+  if (B == 1 && L_v <= kPlanOneLv) {
+    hipLaunchKernelGGL(plan_one_kernel, dim3(nl + 1), dim3(256), 0, st, L_v, L_t, nl, c->max_rows, c->cfg.max_batch,
+                       reuse_order, reuse_count, stride, layer_count, c->rows, c->n_rows, c->slot_off, c->prev_slot,
+                       c->errword);
+    return;
+  }
   hipLaunchKernelGGL(plan_counts_kernel, dim3(B), dim3(256), 0, st, L_v, L_t, nl, c->cfg.max_seq,
                      reuse_order, reuse_count, stride, layer_count, c->rank, c->m_layer,
                      c->n_rows_bl, B, c->errword);
@@ -281,9 +367,10 @@ struct RowArgs {
   const float* gain; float eps; int d;
   bf16_t* xp; int KC;
   bool in_place;  // S == 0: h holds the sums already
+  float* out; int out_L;  // fp32 rows [b][out_L][d] in place of xp (the final norm)
 };
 
-template <bool F16, int MAXI, int S>
+template <bool F16, int MAXI, int S, bool OUT>
 __device__ __forceinline__ void resid_norm_body(const RowArgs& a, int n, float (&red)[2][4]) {
   constexpr int SA = S * MAXI > 32 ? 4 : S;  // partial rows in flight at a time
   const int tid = threadIdx.x, d = a.d;
@@ -351,10 +438,10 @@ __device__ __forceinline__ void resid_norm_body(const RowArgs& a, int n, float (
 #pragma unroll
       for (int i = 0; i < MAXI; ++i) {
         const int k = tid * 4 + i * 1024;
-        if (k < d)
-          *(uint2*)(a.xp + frag_off(slot, k, a.KC)) =
-              make_uint2(pack_op2<F16>(v[i].x * rinv * g[i].x, v[i].y * rinv * g[i].y),
-                         pack_op2<F16>(v[i].z * rinv * g[i].z, v[i].w * rinv * g[i].w));
+        if (k >= d) continue;
+        const float4 x = make_float4(v[i].x * rinv * g[i].x, v[i].y * rinv * g[i].y, v[i].z * rinv * g[i].z, v[i].w * rinv * g[i].w);
+        if constexpr (OUT) *(float4*)(a.out + ((size_t)(id >> 16) * a.out_L + (id & 0xffff)) * d + k) = x;
+        else *(uint2*)(a.xp + frag_off(slot, k, a.KC)) = make_uint2(pack_op2<F16>(x.x, x.y), pack_op2<F16>(x.z, x.w));
       }
     }
     slot = next;
@@ -369,12 +456,13 @@ __device__ __forceinline__ void resid_norm_body(const RowArgs& a, int n, float (
 // every kRowGrid-th row and keeps the gains.  2712 rows of 4096 values, unsplit: 26.3 -> 24 us; 519 rows in 3 parts
 // 15.9 -> 13.2; grouped queries, 32 x 304 tokens, 23.4 -> 20.9 on average.  (The next row's loads ahead of the sum
 // of this one's squares: 208 registers instead of 124, and slower.)
-template <bool F16, int MAXI, int NS>
+// OUT: the norm goes to fp32 rows of out.
+template <bool F16, int MAXI, int NS, bool OUT = false>
 __global__ __launch_bounds__(256, MAXI == 8 ? 1 : NS == 8 ? 2 : 4) void resid_norm_rows_kernel(RowArgs a, int S, const int* __restrict__ n_rows,
                                                               int n_rows_host, SplitAdapt adapt) {
   __shared__ float red[2][4];
   read_args(a.resid, a.resid_seq_stride, a.part, a.part_rows, a.h, a.h_seq_stride, a.rows, a.part_slot, a.gain, a.eps, a.d,
-            a.xp, a.KC, S, n_rows, n_rows_host, adapt.n_rows, adapt.split, adapt.small_below, adapt.S_small, adapt.S_known);
+            a.xp, a.KC, a.out, a.out_L, S, n_rows, n_rows_host, adapt.n_rows, adapt.split, adapt.small_below, adapt.S_small, adapt.S_known);
   const int n = n_rows_host >= 0 ? n_rows_host : ld_scalar(n_rows);
   if (adapt.S_known > 0) S = adapt.S_known;
   if (adapt.split) {
@@ -388,15 +476,15 @@ __global__ __launch_bounds__(256, MAXI == 8 ? 1 : NS == 8 ? 2 : 4) void resid_no
   }
   if ((int)blockIdx.x >= n) return;
   switch (S) {
-    case 0: resid_norm_body<F16, MAXI, 0>(a, n, red); break;
-    case 1: resid_norm_body<F16, MAXI, 1>(a, n, red); break;
-    case 2: resid_norm_body<F16, MAXI, 2>(a, n, red); break;
-    case 3: resid_norm_body<F16, MAXI, 3>(a, n, red); break;
-    case 4: resid_norm_body<F16, MAXI, 4>(a, n, red); break;
-    case 5: if constexpr (NS > 4) resid_norm_body<F16, MAXI, 5>(a, n, red); break;
-    case 6: if constexpr (NS > 4) resid_norm_body<F16, MAXI, 6>(a, n, red); break;
-    case 7: if constexpr (NS > 4) resid_norm_body<F16, MAXI, 7>(a, n, red); break;
-    case 8: if constexpr (NS > 4) resid_norm_body<F16, MAXI, 8>(a, n, red); break;
+    case 0: resid_norm_body<F16, MAXI, 0, OUT>(a, n, red); break;
+    case 1: resid_norm_body<F16, MAXI, 1, OUT>(a, n, red); break;
+    case 2: resid_norm_body<F16, MAXI, 2, OUT>(a, n, red); break;
+    case 3: resid_norm_body<F16, MAXI, 3, OUT>(a, n, red); break;
+    case 4: resid_norm_body<F16, MAXI, 4, OUT>(a, n, red); break;
+    case 5: if constexpr (NS > 4) resid_norm_body<F16, MAXI, 5, OUT>(a, n, red); break;
+    case 6: if constexpr (NS > 4) resid_norm_body<F16, MAXI, 6, OUT>(a, n, red); break;
+    case 7: if constexpr (NS > 4) resid_norm_body<F16, MAXI, 7, OUT>(a, n, red); break;
+    case 8: if constexpr (NS > 4) resid_norm_body<F16, MAXI, 8, OUT>(a, n, red); break;
   }
 }
 
@@ -463,12 +551,16 @@ void launch_resid_norm_rows(bool f16, const float* resid, int resid_seq_stride, 
                             int S, int part_rows, float* h, int h_seq_stride, const int* rows,
                             const int* part_slot, const int* n_rows, int n_rows_host, int max_rows,
                             const float* gain, float eps, int d, bf16_t* xp, int KC,
-                            hipStream_t st, const SplitAdapt* adapt) {
+                            hipStream_t st, const SplitAdapt* adapt, float* out, int out_L) {
   SplitAdapt ad = {nullptr, nullptr, 0, 0, 0};
   if (adapt) ad = *adapt;  // (never given for rows longer than 8192)
-  const RowArgs a = {resid, resid_seq_stride, part, part_rows, h, h_seq_stride, rows, part_slot, gain, eps, d, xp, KC, false};
+  const RowArgs a = {resid, resid_seq_stride, part, part_rows, h, h_seq_stride, rows, part_slot, gain, eps, d, xp, KC, false, out, out_L};
 #define VLAC_RN(K) hipLaunchKernelGGL(K, dim3(std::min(max_rows, kRowGrid)), dim3(256), 0, st, a, S, n_rows, n_rows_host, ad)
-  if (d <= 4096 && S <= 4) {
+  if (out) {
+    if (d <= 4096 && S <= 4) VLAC_RN((resid_norm_rows_kernel<true, 4, 4, true>));
+    else if (d <= 4096) VLAC_RN((resid_norm_rows_kernel<true, 4, 8, true>));
+    else VLAC_RN((resid_norm_rows_kernel<true, 8, 8, true>));
+  } else if (d <= 4096 && S <= 4) {
     if (f16) VLAC_RN((resid_norm_rows_kernel<true, 4, 4>));
     else VLAC_RN((resid_norm_rows_kernel<false, 4, 4>));
   } else if (d <= 4096) {
