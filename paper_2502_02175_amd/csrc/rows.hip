@@ -256,6 +256,20 @@ void launch_decode_plan(vlac_ctx* c, int B, int L, int n_new, hipStream_t st) {
                      slot_off);
 }
 
+// The operand rows that these kernels write lie in fragment order: 16 bytes of each of 8 rows make a cache line.
+// So 8 neighbouring rows go to workgroups of one XCD (workgroup id % 8), whose L2 puts the line together; dealt to
+// the XCDs row by row, every line left eight L2s in pieces of 16 bytes (residual + norm of 2712 rows of 4096 values 21.9 -> 15.8 us, 9728 rows
+// and fewer of 1536 values 20.9 -> 14.3 on average, 288 rows 8.6 -> 7.9, 32 rows 4.1 -> 3.5).  Grids are a multiple of 64 / PER workgroups of
+// PER rows.  -> the first row of workgroup w.
+template <int PER>
+__device__ __forceinline__ int first_row(int w) {
+  constexpr int G = 8 / PER;  // workgroups per line
+  const int x = w & 7, y = w >> 3;
+  return ((y / G * 8 + x) * G + y % G) * PER;
+}
+static const int kRowGrid = 1024;  // workgroups of a row kernel at most: 4 per CU
+static int row_grid(int rows, int per) { return std::min(round_up((rows + per - 1) / per, 64 / per), kRowGrid); }
+
 // ---------------------------------------------------------------------------
 // RMSNorm of the recomputed rows.  One wave per row: x * rsqrt(mean(x^2) + eps) * g,
 // statistics in fp32, output bf16 in fragment order (slot = row of the operand).
@@ -272,7 +286,7 @@ __global__ __launch_bounds__(256) void rmsnorm_rows_kernel(
     const float* __restrict__ gain, float eps, int d, bf16_t* __restrict__ xp, int KC) {
   read_args(src, seq_stride, rows, decode_pos, gain, eps, d, xp, KC);
   const int lane = threadIdx.x & 63, n = n_rows_host >= 0 ? n_rows_host : ld_scalar(n_rows);
-  for (int slot = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); slot < n; slot += gridDim.x * 4) {
+  for (int slot = first_row<4>(blockIdx.x) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); slot < n; slot += gridDim.x * 4) {
     const int id = decode_pos >= 0 ? ((slot << 16) | decode_pos) : ld_scalar(rows + slot);
     const float* x = src + ((size_t)(id >> 16) * seq_stride + (id & 0xffff)) * d;
     float ss = 0.f;
@@ -306,7 +320,7 @@ __global__ __launch_bounds__(256) void rmsnorm_rows_reg_kernel(
   read_args(src, seq_stride, rows, decode_pos, gain, eps, d, xp, KC);
   const int lane = threadIdx.x & 63, n = n_rows_host >= 0 ? n_rows_host : ld_scalar(n_rows);
   const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
-  int slot = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int slot = first_row<4>(blockIdx.x) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (slot >= n) return;
   float4 ga[NI], gb[NI];
 #pragma unroll
@@ -382,9 +396,7 @@ __device__ __forceinline__ void resid_norm_body(const RowArgs& a, int n, float (
     g[i] = make_float4(0.f, 0.f, 0.f, 0.f);
     if (a.gain && k < d) g[i] = *(const float4*)(a.gain + k);
   }
-  // (the lists have room for every slot of the grid, and past the end of a list nothing is done with what
-  // they hold there)
-  int slot = blockIdx.x, id = ld_scalar(a.rows + slot), pslot = S > 0 && a.part_slot ? ld_scalar(a.part_slot + slot) : slot;
+  int slot = first_row<1>(blockIdx.x), id = ld_scalar(a.rows + slot), pslot = S > 0 && a.part_slot ? ld_scalar(a.part_slot + slot) : slot;
   for (int turn = 0; slot < n; turn ^= 1) {
     const int next = slot + gridDim.x;
     int id_next = 0, pslot_next = next;
@@ -453,8 +465,8 @@ __device__ __forceinline__ void resid_norm_body(const RowArgs& a, int n, float (
 // The partial rows of a launch are asked for exactly as many as there are: the split factor chooses the body.  (All
 // that the instance has room for, the last one again past the end, brought 8 of them for 3 at 519 rows.)  A factor
 // that the GEMM chose on the device is read, not worked out once more by every workgroup; a workgroup takes
-// every kRowGrid-th row and keeps the gains.  2712 rows of 4096 values, unsplit: 26.3 -> 24 us; 519 rows in 3 parts
-// 15.9 -> 13.2; grouped queries, 32 x 304 tokens, 23.4 -> 20.9 on average.  (The next row's loads ahead of the sum
+// every kRowGrid-th row and keeps the gains.  2712 rows of 4096 values, unsplit: 24.4 -> 21.9 us on average;
+// 519 rows in 3 parts 15.9 -> 13.2; grouped queries, 32 x 304 tokens, 23.4 -> 20.9 (and then first_row).  (The next row's loads ahead of the sum
 // of this one's squares: 208 registers instead of 124, and slower.)
 // OUT: the norm goes to fp32 rows of out.
 template <bool F16, int MAXI, int NS, bool OUT = false>
@@ -474,7 +486,7 @@ __global__ __launch_bounds__(256, MAXI == 8 ? 1 : NS == 8 ? 2 : 4) void resid_no
     S = 0;
     a.in_place = true;
   }
-  if ((int)blockIdx.x >= n) return;
+  if (first_row<1>(blockIdx.x) >= n) return;
   switch (S) {
     case 0: resid_norm_body<F16, MAXI, 0, OUT>(a, n, red); break;
     case 1: resid_norm_body<F16, MAXI, 1, OUT>(a, n, red); break;
@@ -488,12 +500,10 @@ __global__ __launch_bounds__(256, MAXI == 8 ? 1 : NS == 8 ? 2 : 4) void resid_no
   }
 }
 
-static const int kRowGrid = 1024;  // workgroups of a row kernel at most: 4 per CU
-
 void launch_rmsnorm_rows(bool f16, const float* src, int seq_stride, const int* rows,
                          const int* n_rows, int n_rows_host, int decode_pos, int max_rows,
                          const float* gain, float eps, int d, bf16_t* xp, int KC, hipStream_t st) {
-  const dim3 grid(std::min((max_rows + 3) / 4, kRowGrid)), block(256);
+  const dim3 grid(row_grid(max_rows, 4)), block(256);
 #define VLAC_NORM_ARGS src, seq_stride, rows, n_rows, n_rows_host, decode_pos, gain, eps, d, xp, KC
   if (d <= 2048) {
     if (f16) hipLaunchKernelGGL((rmsnorm_rows_reg_kernel<true, 4>), grid, block, 0, st, VLAC_NORM_ARGS);
@@ -555,7 +565,7 @@ void launch_resid_norm_rows(bool f16, const float* resid, int resid_seq_stride, 
   SplitAdapt ad = {nullptr, nullptr, 0, 0, 0};
   if (adapt) ad = *adapt;  // (never given for rows longer than 8192)
   const RowArgs a = {resid, resid_seq_stride, part, part_rows, h, h_seq_stride, rows, part_slot, gain, eps, d, xp, KC, false, out, out_L};
-#define VLAC_RN(K) hipLaunchKernelGGL(K, dim3(std::min(max_rows, kRowGrid)), dim3(256), 0, st, a, S, n_rows, n_rows_host, ad)
+#define VLAC_RN(K) hipLaunchKernelGGL(K, dim3(row_grid(max_rows, 1)), dim3(256), 0, st, a, S, n_rows, n_rows_host, ad)
   if (out) {
     if (d <= 4096 && S <= 4) VLAC_RN((resid_norm_rows_kernel<true, 4, 4, true>));
     else if (d <= 4096) VLAC_RN((resid_norm_rows_kernel<true, 4, 8, true>));
