@@ -28,8 +28,8 @@
 //    and copies the first stages of the next item during the last steps of the one before.
 //  * Row blocks of 192 or 128 rows (a wave owns 4 x 3 or 4 x 2 tiles), and K split in up to 8
 //    parts in the projections with a residual (whose consumer, residual add + RMSNorm, adds
-//    the partial rows up), where that takes less time by the estimate of tall_plan, which
-//    kernel and consumer evaluate on the device from the actual row count.
+//    the partial rows up), where that takes less time by the estimate of tall_plan, which the kernel
+//    evaluates on the device from the actual row count; it leaves the K parts for the consumer to read.
 //  * Behind its last product an item has the CU to itself (one wave per SIMD), so what it does with its sums
 //    counts in full.  The sums stay in their registers until a tile's turn (copied out of them all at once
 //    behind the loop, they spilled 80 to 110 registers); what an epilogue reads is asked for ahead of the stores
