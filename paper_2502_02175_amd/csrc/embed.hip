@@ -17,7 +17,8 @@
 #include "common.h"
 
 // list[b][0 .. n_live[b]) = the patches of stream b that are NOT among the first m reuse
-// entries, ascending.  One workgroup per stream.  For the wide form only, whose workgroups would each spend 2 us on it.
+// entries, ascending.  One workgroup per stream.  For calls of many workgroups, which would each spend 2 us on it
+// (emb_own).
 __global__ __launch_bounds__(256) void embed_mark_kernel(const int32_t* __restrict__ reuse_order,
                                                          const int32_t* __restrict__ reuse_count,
                                                          int stride, const int32_t* __restrict__ layer_count,
@@ -59,8 +60,9 @@ __global__ __launch_bounds__(256) void embed_mark_kernel(const int32_t* __restri
 struct EmbedReuse { const int32_t *order, *count; int stride; const int32_t* layer_count; int n_layers; };
 
 // The patches [g0, g0 + PB) of that list, worked out by the workgroup itself; returns the list's length.  flags:
-// L_v bytes of LDS that are used for nothing else until then.  (Few patches: one launch less, 2.3 us of the GPU and 4
-// of the host; a front end of 256 patches, whose launches the host queues no faster than the GPU runs them, 42 -> 39.5 us; 8 streams of 63 patches 41 -> 37.7.)
+// L_v bytes of LDS that are used for nothing else until then.  (One round of workgroups: one launch less, 2.3 us of the
+// GPU and 4 of the host; a front end of 256 patches, whose launches the host queues no faster than the GPU runs them,
+// 40.0 -> 37.2 us.)
 template <int PB>
 __device__ __forceinline__ int embed_group(const EmbedReuse& r, int b, int L_v, int g0, uint8_t* flags, int* group) {
   __shared__ int wsum[2][4];
@@ -115,26 +117,26 @@ typedef uint32_t u32x4_u __attribute__((ext_vector_type(4), aligned(1)));
 // staging 13 us, products 28, output 15 of the 67 at 8 x 1024.
 // (EMB_D k-tiles of weights in flight per wave: with 2 row tiles only 2, so that a
 // second workgroup fits the CU: 85 -> 72 us per call at 8 x 1024 patches)
-template <int RT, int KS, bool VEC, bool TWO>
-__global__ __launch_bounds__(256, 2) void embed_patches_kernel(const uint8_t* __restrict__ frame, int H, int W,
-                                                            int patch, const bf16_t* __restrict__ w_proj,
-                                                            int d, const int* __restrict__ list,
-                                                            const int* __restrict__ n_live, EmbedReuse reuse,
-                                                            float* __restrict__ embeds, int L) {
+// OWN: the workgroup works the list out for itself, list and n_live are not read.
+template <int RT, int KS, bool VEC, bool TWO, bool OWN>
+__device__ __forceinline__ void embed_patches(const uint8_t* __restrict__ frame, int H, int W, int patch,
+                                              const bf16_t* __restrict__ w_proj, int d, const int* __restrict__ list,
+                                              const int* __restrict__ n_live, const EmbedReuse& reuse,
+                                              float* __restrict__ embeds, int L) {
   extern __shared__ uint4 px[];  // [RT][k-tiles][64]; KS = 4: then, per row tile, the waves' sums
-  __shared__ int group[KS == 1 ? 1 : 32 * RT];  // KS = 4: the group's patches
   constexpr int PB = 32 * RT, EMB_D = RT == 2 ? 2 : 4;
   const int gw = W / patch, dp = 3 * patch * patch, prow = 3 * patch, n_kt = (dp + 15) >> 4;
   const int b = blockIdx.z, g0 = blockIdx.y * PB, tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   int nl;
   const int* mine;
-  if constexpr (KS == 1) {
-    nl = n_live[b];
-    mine = list + (size_t)b * 4096 + g0;
-  } else {
+  if constexpr (OWN) {
+    __shared__ int group[PB];
     nl = embed_group<PB>(reuse, b, gw * (H / patch), g0, (uint8_t*)px, group);
     mine = group;
+  } else {
+    nl = n_live[b];
+    mine = list + (size_t)b * 4096 + g0;
   }
   if (g0 >= nl) return;
   const int cnt = min(PB, nl - g0);
@@ -362,6 +364,23 @@ __global__ __launch_bounds__(256, 2) void embed_patches_kernel(const uint8_t* __
   }
 }
 
+template <int RT, int KS, bool VEC, bool TWO>
+__global__ __launch_bounds__(256, 2) void embed_patches_kernel(const uint8_t* __restrict__ frame, int H, int W, int patch,
+                                                               const bf16_t* __restrict__ w_proj, int d,
+                                                               const int* __restrict__ list, const int* __restrict__ n_live,
+                                                               EmbedReuse reuse, float* __restrict__ embeds, int L) {
+  embed_patches<RT, KS, VEC, TWO, KS == 4>(frame, H, W, patch, w_proj, d, list, n_live, reuse, embeds, L);
+}
+
+// the form of few patches with the list of embed_mark_kernel
+template <bool VEC, bool TWO>
+__global__ __launch_bounds__(256, 2) void embed_listed_kernel(const uint8_t* __restrict__ frame, int H, int W, int patch,
+                                                              const bf16_t* __restrict__ w_proj, int d,
+                                                              const int* __restrict__ list, const int* __restrict__ n_live,
+                                                              float* __restrict__ embeds, int L) {
+  embed_patches<1, 4, VEC, TWO, false>(frame, H, W, patch, w_proj, d, list, n_live, EmbedReuse{}, embeds, L);
+}
+
 // LDS: the pixel operands of the group; KS = 4: or the four waves' sums of one row tile
 static size_t embed_lds(int RT, int KS, int dp) {
   return std::max((size_t)RT * ((dp + 15) / 16) * 1024, KS == 1 ? (size_t)0 : (size_t)65536);
@@ -375,6 +394,9 @@ int embed_init() {
   VLAC_EMB_SET(1, 4, true, true) VLAC_EMB_SET(1, 4, false, true) VLAC_EMB_SET(1, 4, true, false)
   VLAC_EMB_SET(1, 4, false, false) VLAC_EMB_SET(2, 1, true, false) VLAC_EMB_SET(2, 1, false, false)
 #undef VLAC_EMB_SET
+  for (const void* k : {(const void*)embed_listed_kernel<true, true>, (const void*)embed_listed_kernel<false, true>,
+                        (const void*)embed_listed_kernel<true, false>, (const void*)embed_listed_kernel<false, false>})
+    if ((e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 159 * 1024)) != hipSuccess) return (int)e;
   return 0;
 }
 
@@ -384,6 +406,14 @@ int embed_init() {
 // 128 such workgroups (4 x 256 patches, d_model 4096) 29 us against 22 with KS = 4, at 256 (2 x
 // 1024) 33 against 38, at 1024 (8 x 1024) 85 against 117.
 static const long long kEmbWide = 256;
+// Workgroups of 128 features and 32 patches work the list of live patches out for themselves up to a round and a half of
+// them where two fit a CU (patches of up to 20 x 20 pixels), up to two rounds where one does; more of them read it from
+// embed_mark_kernel.  Front end, list by the launch and by the workgroups, us: 256 workgroups (1 x 256 patches, d_model
+// 4096) 39.2 and 36.6; 512 (8 x 63) 43.0 and 41.0; 640 (1 x 625) 71.0 and 69.2; 768 (3 x 256) 43.2 and 41.7, (12 x 1024 of
+// 16 x 16 pixels, d_model 256) 73.0 and 72.5; 1024 (4 x 256) 43.6 and 45.2; 1152 (12 x 90) 51.2 and 53.8; 1536 (6 x 256)
+// 53.3 and 54.3; 8192 (8 x 1024 of 16 x 16) 172 and 193; 32768 (32 x 1024) 607 and 700.  26 x 26 pixels: 576 workgroups (1
+// x 576) 86.4 and 85.1; 768 (12 x 1024, d_model 256) 133 and 136; 1024 (1 x 1024) 123 and 127.
+static long long emb_own(size_t lds) { return lds <= 80 * 1024 ? 768 : 512; }
 
 void launch_embed_patches(vlac_ctx* c, const uint8_t* frame, int B, int H, int W, int patch,
                           const bf16_t* w_proj, const int32_t* reuse_order, const int32_t* reuse_count,
@@ -391,20 +421,30 @@ void launch_embed_patches(vlac_ctx* c, const uint8_t* frame, int B, int H, int W
   const int L_v = (H / patch) * (W / patch), d = c->cfg.d_model, dp = 3 * patch * patch;
   const EmbedReuse reuse = {reuse_order, reuse_count, stride, layer_count, c->cfg.n_layers};
   const bool wide = (long long)((d + 511) / 512) * ((L_v + 63) / 64) * B >= kEmbWide && embed_lds(2, 1, dp) <= 80 * 1024;
+  const bool own = !wide && (long long)((d + 127) / 128) * ((L_v + 31) / 32) * B <= emb_own(embed_lds(1, 4, dp));
   // (8-byte weight loads and 16-byte stores where the caller's buffers allow them)
   const bool vec = (uintptr_t)w_proj % 8 == 0 && (uintptr_t)embeds % 16 == 0;
-#define VLAC_EMB(RT_, KS_, VEC_, TWO_)                                                                     \
-  hipLaunchKernelGGL((embed_patches_kernel<RT_, KS_, VEC_, TWO_>),                                         \
-                     dim3((d + 512 / KS_ - 1) / (512 / KS_), (L_v + 32 * RT_ - 1) / (32 * RT_), B), dim3(256), \
-                     embed_lds(RT_, KS_, dp), st, frame, H, W, patch, w_proj, d, c->embed_list, c->embed_n, reuse, embeds, L)
-  if (wide) {
+  const bool two = (patch & 1) == 0 && ((uintptr_t)frame & 1) == 0;
+  if (!own)
     hipLaunchKernelGGL(embed_mark_kernel, dim3(B), dim3(256), 0, st, reuse_order, reuse_count, stride,
                        layer_count, c->cfg.n_layers, L_v, c->flags, c->embed_list, c->embed_n);
+#define VLAC_EMB_GRID(RT_, KS_) \
+  dim3((d + 512 / KS_ - 1) / (512 / KS_), (L_v + 32 * RT_ - 1) / (32 * RT_), B), dim3(256), embed_lds(RT_, KS_, dp), st
+#define VLAC_EMB(RT_, KS_, VEC_, TWO_)                                                                                \
+  hipLaunchKernelGGL((embed_patches_kernel<RT_, KS_, VEC_, TWO_>), VLAC_EMB_GRID(RT_, KS_), frame, H, W, patch, w_proj, \
+                     d, c->embed_list, c->embed_n, reuse, embeds, L)
+#define VLAC_EMB_FEW(VEC_, TWO_)                                                                                     \
+  if (own) VLAC_EMB(1, 4, VEC_, TWO_);                                                                               \
+  else hipLaunchKernelGGL((embed_listed_kernel<VEC_, TWO_>), VLAC_EMB_GRID(1, 4), frame, H, W, patch, w_proj, d,      \
+                          c->embed_list, c->embed_n, embeds, L)
+  if (wide) {
     if (vec) VLAC_EMB(2, 1, true, false); else VLAC_EMB(2, 1, false, false);
-  } else if ((patch & 1) == 0 && ((uintptr_t)frame & 1) == 0) {
-    if (vec) VLAC_EMB(1, 4, true, true); else VLAC_EMB(1, 4, false, true);
+  } else if (two) {
+    if (vec) { VLAC_EMB_FEW(true, true); } else { VLAC_EMB_FEW(false, true); }
   } else {
-    if (vec) VLAC_EMB(1, 4, true, false); else VLAC_EMB(1, 4, false, false);
+    if (vec) { VLAC_EMB_FEW(true, false); } else { VLAC_EMB_FEW(false, false); }
   }
+#undef VLAC_EMB_FEW
+#undef VLAC_EMB_GRID
 #undef VLAC_EMB
 }

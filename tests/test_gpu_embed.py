@@ -175,3 +175,46 @@ def test_embed_feeds_the_sparse_prefill():
         assert np.isfinite(got1["logits"]).all()
     finally:
         gm.close()
+
+
+@pytest.mark.parametrize("B,H,W,patch,skew", [
+    (12, 16 * 32, 16 * 32, 16, 0),  # 768 workgroups of 128 features and 32 patches: the last that list for themselves
+    (13, 16 * 32, 16 * 32, 16, 0),  # one stream more: the list of the launch before
+    (13, 16 * 32, 16 * 32, 16, 1),
+    (97, 13 * 11, 13 * 11, 13, 0),  # the same with odd patches, a last group of 25 and less
+    (8, 26 * 32, 26 * 32, 26, 0),   # one workgroup per CU: 512 of them
+    (9, 26 * 32, 26 * 32, 26, 0),
+])
+def test_who_lists_the_live_patches(B, H, W, patch, skew):
+    """Reuse lists of every length, shuffled and clamped by the layer count, on both sides of the limit; the sums are exact
+    but for the fp32 rounding of 3 patch^2 terms (as above)."""
+    import torch
+    cfg = synth.CONFIGS["tiny"]
+    gm = GpuModel(cfg, seed=0, max_batch=B, max_seq=32)
+    try:
+        V, dev = gm.V, gm.device
+        rng = np.random.default_rng(B)
+        L_v, d = (H // patch) * (W // patch), cfg.d_model
+        frames = rng.integers(0, 256, size=(B, H, W, 3), dtype=np.uint8)
+        w = synth.round_bf16(synth.projection_matrix(d, patch, 9))
+        n = [L_v * b // (B - 1) for b in range(B)]
+        order = np.stack([rng.permutation(L_v) for _ in range(B)]).astype(np.int32)
+        lc = np.full((B, cfg.n_layers), L_v, np.int32)
+        lc[1::3, 0] = 7
+        fbuf = torch.zeros(frames.size + 8, dtype=torch.uint8, device=dev)[skew:skew + frames.size].view(frames.shape)
+        fbuf.copy_(torch.tensor(frames))
+        out = torch.full((B, L_v, d), -7.0, device=dev)
+        V.vlac_embed_patches(gm.ctx, fbuf, B, H, W, patch, torch.tensor(w, device=dev).to(torch.bfloat16),
+                             torch.tensor(order, device=dev), torch.tensor(n, dtype=torch.int32, device=dev), L_v,
+                             torch.tensor(lc, device=dev), out, L_v)
+        got = out.cpu().numpy()
+        for b in range(B):
+            m = min(n[b], lc[b, 0])
+            keep = np.ones(L_v, bool)
+            keep[order[b, :m]] = False
+            assert np.array_equal(got[b, :, 0] != -7.0, keep), b
+            if b % 4 == 0 or b == B - 1:
+                want = O.embed_patches(frames[b], patch, w, order[b, :m].tolist())
+                assert not keep.any() or np.abs(got[b][keep] - want[keep]).max() <= 1e-5
+    finally:
+        gm.close()
