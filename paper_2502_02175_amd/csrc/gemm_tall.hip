@@ -73,6 +73,13 @@ __device__ inline void tall_wait() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 #endif
 }
+// Between a wave's stores to LDS and its reads of what other lanes stored (and between those reads and the next stores):
+// the compiler, which sees one lane, may else move one past the other.  No instruction: a wave's LDS accesses are worked
+// off in order.
+__device__ __forceinline__ void lanes_exchange() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+}
 constexpr int kTallGrid = 256;          // one workgroup per CU (a workgroup takes all of a CU's LDS)
 
 // A work item: weight tile, K part, row block
@@ -254,9 +261,11 @@ __device__ __forceinline__ int tall_body(const GemmArgs& a, uint4* lds, TallItem
       const int q = lane >> 3, c = lane & 7;  // a lane's rows are 8 r + q
       auto turned = [&](int f, int m, f32x4(&v)[4]) __attribute__((always_inline)) {
         const f32x16 t = result(f, m);
+        lanes_exchange();
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4)
           tile[j * 8 + ((2 * q4 + g) ^ (j & 7))] = (f32x4){t[4 * q4], t[4 * q4 + 1], t[4 * q4 + 2], t[4 * q4 + 3]};
+        lanes_exchange();
 #pragma unroll
         for (int r = 0; r < 4; ++r) v[r] = tile[(8 * r + q) * 8 + (c ^ q)];
       };
@@ -351,11 +360,13 @@ __device__ __forceinline__ int tall_body(const GemmArgs& a, uint4* lds, TallItem
           const int nb = nb0 + FW * wi + f;
           EpiIn<EPI> mine = {};
           if (nb < nb_rot) {
+            lanes_exchange();
 #pragma unroll
             for (int p = 0; p < 2; ++p) {
               tile[chunk(16 * p + q, c)] = in[m & 1][f][p];
               tile[chunk(16 * p + q, 4 + c)] = in[m & 1][f][2 + p];
             }
+            lanes_exchange();
 #pragma unroll
             for (int q4 = 0; q4 < 2; ++q4) {
               const f32x4 x = tile[chunk(j, 2 * q4 + g)], y = tile[chunk(j, 4 + 2 * q4 + g)];
