@@ -53,3 +53,21 @@ def test_the_embedding_of_many_workgroups_reads_its_list():
     assert len(mine) == 4
     for n, k in mine.items():
         assert k[".group_segment_fixed_size"] == 0 and k[".vgpr_spill_count"] == 0 and k[".vgpr_count"] <= 224, n
+
+
+def test_the_many_rows_gemm_keeps_its_sums_in_registers():
+    """Copied behind the loop, out of the half of the registers that the products leave them in, they spill by 80 to 110
+    registers; what holds them there is one empty instruction that a compiler may take otherwise.  (Output head:
+    two words of addresses, outside the loop.)"""
+    mine = {n: k for n, k in kernels().items() if "gemm_tall_kernel" in n}
+    assert len(mine) == 18  # epilogues, items of 192 features, operand types
+    for n, k in mine.items():
+        head = "gemm_tall_kernelILi3E" in n
+        assert k[".private_segment_fixed_size"] <= (8 if head else 0) and k[".vgpr_spill_count"] <= (1 if head else 0), n
+
+
+def test_the_few_rows_gemm_of_several_feature_blocks_does_not_spill():
+    mine = {n: k for n, k in kernels().items() if "gemm_few_wide_kernel" in n}
+    assert len(mine) == 27  # two and three blocks (head: and four), epilogues, operand types
+    for n, k in mine.items():
+        assert k[".private_segment_fixed_size"] == 0 and k[".vgpr_spill_count"] == 0, n
