@@ -654,7 +654,8 @@ __global__ __launch_bounds__(256, XMODE == X_NORM8 ? 2 : 3) void gemm_few_kernel
   }
 }
 
-// The same for more rows than have their norm made here (5 to 32), with FB feature blocks per workgroup: the
+// The same for rows that do not have their norm made here (5 to 32 of them, and any number in the projections with a
+// residual), with FB feature blocks per workgroup: the
 // operand rows, as many bytes per k-tile as a weight tile when there are 32 of them, come from L2 once for
 // all FB blocks, and FB is what gives the chip whole rounds of workgroups (few_blocks).  K is dealt to the
 // workgroups and waves, and their sums added, as in gemm_few_kernel: the results are the same bits.
@@ -758,19 +759,33 @@ __global__ __launch_bounds__(256, FB == 3 ? 1 : 2) void gemm_few_wide_kernel(Gem
   }
 }
 
-// Feature blocks per workgroup of the kernels for up to 32 rows (1: gemm_few_kernel): the least rounds of 256
-// workgroups x what a workgroup fetches per k-tile, in 32nds of a KiB (a weight tile of 16-bit operands is 32, as are
-// 32 operand rows).  A hand-over between workgroups (K split, no residual) is made by gemm_few_kernel only.
-// The head's 1000 blocks make several rounds, which even out what the memory gives to the CUs: one round of long runs
-// pays only where the operand rows weigh (7B, FB = 4 against 1: 32 rows 48.0 and 51.7 us, 24 rows 47.7 and 46.8, 8 rows
-// 47.3 and 44.6; 8-bit weights, 8 rows 30.0 and 25.0; K = 1536: 6 rows 18.4 and 19.5).
+// Feature blocks per workgroup of the kernels for up to 32 rows (1: gemm_few_kernel).  Taken is the least estimate of
+// rounds of 256 workgroups x what a workgroup fetches per k-tile, in 32nds of a KiB: a weight tile of 16-bit operands is
+// 32; the operand rows, which come from L2, count a sixth of their bytes.  A last round that is not full costs half of what
+// is missing (one block per workgroup, three workgroups to a CU: three quarters); 32 rounds' worth of start and end.
+// An even number of blocks pays for weights whose workgroups' runs start a multiple of 256 KiB apart: all of them
+// ask the same few channels, above all with a power of two between two blocks.  (The K parts of the projections with a
+// residual start apart.)  A hand-over between workgroups (K split, no residual) is made by gemm_few_kernel only.
+// Measured over 6400 launches of 7 to 340 us (K 256 to 17920, 32 to 4752 blocks, 1 to 32 rows, 16- and 8-bit weights): on
+// average 4.8 % faster than one block each, 1.2 % of them more than 5 % slower (at most 18 %: K 512, 1344 blocks, 32 rows 18.9
+// and 22.3 us).  One block against several, us: K 2048, 512 blocks, 8 rows 15.7 and 17.9 (one is taken), 4008 blocks 88
+// and 105 (one); K 4096, 896 blocks, 16 rows 43.8 and 48.3 (one), 688 blocks, 8 rows 33.5 and 32.8 (three), 384 blocks, 32
+// rows 26.3 and 23.7 (two); K 1536, 1000 blocks, 32 rows 25.9 and 21.1 (four); K 2560, 1000 blocks, 8-bit weights, 8 rows
+// 20.8 and 19.4 (four).  The projections with a residual come here with 1 to 4 rows too: K 8960, 48 blocks in 6
+// parts, 1 row 12.0 and 11.7 (two).  QKV with few k-tiles to a wave, K 512, 480 blocks, 32 rows 10.6 and 11.7 (one).
 static int few_blocks(int epi, int n_blocks, int KS, int S, int rows, bool w8) {
+  const int KC = 4 * KS;
   if (S > 1 && epi != EPI_RESID) return 1;
-  if (epi == EPI_LOGITS && KS > 32 && (rows <= 24 || w8)) return 1;
-  int best = 1, least = 0x7fffffff;
+  if (epi == EPI_QKV && KC < (w8 ? 64 : 48)) return 1;
+  int best = 1;
+  double least = 0;
   for (int fb = 1; fb <= (epi == EPI_LOGITS ? 4 : 3); ++fb) {
-    const int cost = ((n_blocks + fb - 1) / fb * S + 255) / 256 * (fb * (w8 ? 16 : 32) + rows);
-    if (cost < least) { least = cost; best = fb; }
+    const int n = (n_blocks + fb - 1) / fb * S, full = (n + 255) / 256 * 256, weight = fb * (w8 ? 16 : 32);
+    const bool same = epi != EPI_RESID && fb % 2 == 0 && KC * weight % 8192 == 0, most = (KC & (KC - 1)) == 0 && n_blocks >= 512;
+    const double rounds = fb == 1 ? 0.25 * n + 0.75 * full : 0.5 * (n + full);
+    const double fetch = weight * (!same ? 1. : most ? 1.25 : 1.03) + rows / 6. + 0.4;
+    const double cost = (rounds * fetch + 32 * 256) * (fb == 1 ? 1. : fb == 3 ? 1.035 : 1.015);  // (3: one workgroup per CU)
+    if (fb == 1 || cost < least) { least = cost; best = fb; }
   }
   return best;
 }
