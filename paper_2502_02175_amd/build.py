@@ -25,7 +25,8 @@ def _run(cmd):
 
 # The sources that place waits for compiler-invisible copies by hand; libvlac_safe.so is the
 # same library with those sources compiled with -DVLAC_SAFE_WAITS (every such wait is for all
-# outstanding loads): a checking aid that a GPU test compares with libvlac.so bit for bit.
+# outstanding loads, and the few-rows GEMM takes one feature block to a workgroup): a checking aid
+# that GPU tests compare with libvlac.so bit for bit.
 HAND_WAITS = ["gemm.hip", "gemm_tall.hip", "attn.hip"]
 CHECKS = ["convert_check.hip"]  # kernels that only tests call: linked into libvlac_safe.so
 LIB_SAFE = os.path.join(HERE, "libvlac_safe.so")

@@ -774,6 +774,9 @@ __global__ __launch_bounds__(256, FB == 3 ? 1 : 2) void gemm_few_wide_kernel(Gem
 // 20.8 and 19.4 (four).  The projections with a residual come here with 1 to 4 rows too: K 8960, 48 blocks in 6
 // parts, 1 row 12.0 and 11.7 (two).  QKV with few k-tiles to a wave, K 512, 480 blocks, 32 rows 10.6 and 11.7 (one).
 static int few_blocks(int epi, int n_blocks, int KS, int S, int rows, bool w8) {
+#ifdef VLAC_SAFE_WAITS
+  return 1;  // (gemm_few_wide_kernel adds in the same order: a test compares the two libraries bit for bit)
+#endif
   const int KC = 4 * KS;
   if (S > 1 && epi != EPI_RESID) return 1;
   if (epi == EPI_QKV && KC < (w8 ? 64 : 48)) return 1;
