@@ -1,6 +1,7 @@
-// The fp32 -> 16-bit conversions of common.h as a kernel of their own, for a test that compares them with the
-// integer definition over chosen bit patterns.  Linked into libvlac_safe.so only.
+// The fp32 -> 16-bit conversions of common.h and the SwiGLU quotient of gemm_epi.h as kernels of their own, for tests
+// that compare them with the integer definition and with the division.  Linked into libvlac_safe.so only.
 #include "common.h"
+#include "gemm_epi.h"
 
 __global__ __launch_bounds__(256) void convert_check_kernel(const float* __restrict__ x, int n, uint16_t* __restrict__ bf,
                                                             uint16_t* __restrict__ h, uint32_t* __restrict__ bf2,
@@ -20,5 +21,27 @@ extern "C" int vlac_convert_check(const float* x, int n, uint16_t* bf, uint16_t*
   if (!x || !bf || !h || !bf2 || !h2) return VLAC_E_NULL;
   if (n < 1) return VLAC_E_RANGE;
   hipLaunchKernelGGL(convert_check_kernel, dim3((n + 255) / 256), dim3(256), 0, (hipStream_t)stream, x, n, bf, h, bf2, h2);
+  return hipGetLastError() == hipSuccess ? VLAC_OK : VLAC_E_HIP;
+}
+
+__global__ __launch_bounds__(256) void silu_check_kernel(uint32_t first, int n, float* __restrict__ denominator,
+                                                         float* __restrict__ got, uint32_t* __restrict__ differ) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  const float x = __uint_as_float(first + (uint32_t)i), y = 1.f + __expf(-x), a = silu_f(x), b = x / y;
+  if (denominator) denominator[i] = y;
+  if (got) got[i] = a;
+  if (__float_as_uint(a) != __float_as_uint(b) && !(a != a && b != b)) {
+    atomicAdd(differ, 1u);
+    atomicMin(differ + 1, first + (uint32_t)i);
+  }
+}
+
+// The n fp32 values whose bits are first, first + 1, ...: differ[0] += those whose silu_f is not x / (1 + e^-x) by the
+// IEEE division, bit for bit (two NaN are alike), differ[1] = the least bits of one; denominator, got: device fp32 [n] or NULL
+extern "C" int vlac_silu_check(uint32_t first, int n, float* denominator, float* got, uint32_t* differ, void* stream) {
+  if (!differ) return VLAC_E_NULL;
+  if (n < 1 || n > (1 << 30)) return VLAC_E_RANGE;
+  hipLaunchKernelGGL(silu_check_kernel, dim3((n + 255) / 256), dim3(256), 0, (hipStream_t)stream, first, n, denominator, got, differ);
   return hipGetLastError() == hipSuccess ? VLAC_OK : VLAC_E_HIP;
 }

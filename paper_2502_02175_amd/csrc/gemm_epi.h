@@ -62,12 +62,13 @@ __device__ __forceinline__ void read_epilogue_args(const GemmArgs& a) {
   else read_args(a.e.logits, a.e.logits_stride, a.e.best, a.e.vocab);
 }
 
-// x / (1 + e^-x): one step from x times the chip's reciprocal (1 ulp), whose remainder is exact, rounds as
-// the IEEE division does (84 million values over +-80: no difference), and the fix-up treats infinities and NaN as it does
-// (denominators above 2^126: 0 for what is below 1e-36).  5 instructions instead of 11: the division was 1400 of
-// the 3600 that a wave of the many-rows kernel spent on a work item of 256 x 256 after its last product.
+// x / (1 + e^-x): one step from x times the chip's reciprocal (1 ulp) gives the bits of the IEEE division (for every
+// fp32 value, which a test runs through); the reciprocal is taken of a quarter, because the chip flushes subnormal ones
+// (denominators above 2^126), and the fix-up treats infinities and NaN as the division does.  7 instructions instead of
+// 11: the division was 1400 of the 3600 that a wave of the many-rows kernel spent on a work item of 256 x 256 after
+// its last product.
 __device__ inline float silu_f(float x) {
-  const float y = 1.f + __expf(-x), r = __builtin_amdgcn_rcpf(y), q = x * r;
+  const float e = __expf(-x), y = 1.f + e, r = 0.25f * __builtin_amdgcn_rcpf(fmaf(e, 0.25f, 0.25f)), q = x * r;
   return __builtin_amdgcn_div_fixupf(fmaf(fmaf(-y, q, x), r, q), y, x);
 }
 

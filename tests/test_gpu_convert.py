@@ -63,6 +63,37 @@ def test_conversions_bit_for_bit():
         assert np.array_equal(pair >> 16, want[::-1])
 
 
+@pytest.mark.gpu
+def test_the_swiglu_quotient_is_the_division_for_every_value():
+    """x / (1 + e^-x) by the chip's reciprocal and one step from it, over all 2^32 fp32 patterns (signed zeros, subnormals,
+    denominators up to infinity, infinities, NaN), against the compiler's IEEE division in the same kernel; and that
+    division against numpy's, over every 4099th value and all of the denominators above 2^126."""
+    import torch
+    f = C.CDLL(SAFE).vlac_silu_check
+    f.restype = C.c_int
+    differ = torch.tensor([0, -1], dtype=torch.int32, device="cuda:0")
+    n = 1 << 28
+    y, got = (torch.empty(n, dtype=torch.float32, device="cuda:0") for _ in range(2))
+    kept = []
+    for part in range(16):
+        first = part * n
+        assert f(C.c_uint32(first), C.c_int(n), C.c_void_p(y.data_ptr()), C.c_void_p(got.data_ptr()),
+                 C.c_void_p(differ.data_ptr()), C.c_void_p(0)) == 0
+        torch.cuda.synchronize()
+        i = torch.arange(0, n, 4099, device="cuda:0")
+        if first <= 0xc2ae0000 < first + n:  # -87 .. -89: e^-x of 2^125.5 .. infinity
+            i = torch.cat([i, torch.arange(0xc2ae0000 - first, 0xc2b20000 - first, device="cuda:0")])
+        kept.append(((i + first).cpu().numpy().astype(np.uint32), y[i].cpu().numpy(), got[i].cpu().numpy()))
+    count, least = (int(v) & 0xffffffff for v in differ.cpu())
+    x, y, got = (np.concatenate(k) for k in zip(*kept))
+    x = x.view(np.float32)
+    with np.errstate(all="ignore"):
+        want = x / y
+    bad = (got.view(np.uint32) != want.view(np.uint32)) & ~(np.isnan(got) & np.isnan(want))
+    assert count == 0, (count, hex(least), float(np.array([least], np.uint32).view(np.float32)[0]))
+    assert not bad.any(), (x[bad][:4], y[bad][:4], got[bad][:4], want[bad][:4])
+
+
 def test_the_integer_definitions_are_numpy_s():
     rng = np.random.default_rng(1)
     u = rng.integers(0, 2 ** 32, 400000, dtype=np.uint64).astype(np.uint32)
