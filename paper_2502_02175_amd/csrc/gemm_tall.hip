@@ -80,6 +80,10 @@ __device__ __forceinline__ void lanes_exchange() {
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
   __builtin_amdgcn_wave_barrier();
 }
+// Waits here for a load that not every path goes on to use.  Left open it would be waited for where its register is
+// written next, in the loop of the item after: with every copy that is younger, at each of its steps.
+template <class T>
+__device__ __forceinline__ void arrived(const T& v) { asm volatile("" ::"v"(v)); }
 constexpr int kTallGrid = 256;          // one workgroup per CU (a workgroup takes all of a CU's LDS)
 
 // A work item: weight tile, K part, row block
@@ -307,6 +311,10 @@ __device__ __forceinline__ int tall_body(const GemmArgs& a, uint4* lds, TallItem
         for (int m = 0; m < NA; ++m) {
           if (m + 1 < NA) ask(m + 1);
           __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int f = 0; f < FW; ++f)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) arrived(in[m & 1][f][r]);
           float* hp[4];
 #pragma unroll
           for (int r = 0; r < 4; ++r)
@@ -350,11 +358,23 @@ __device__ __forceinline__ int tall_body(const GemmArgs& a, uint4* lds, TallItem
             }
         }
       };
+#pragma unroll
+      for (int m = 0; m < NA; ++m) {
+        arrived(ids[m]);
+        arrived(pos[m][0]);
+        arrived(pos[m][1]);
+      }
       ask(0);
 #pragma unroll
       for (int m = 0; m < NA; ++m) {
         if (m + 1 < NA) ask(m + 1);
         __builtin_amdgcn_sched_barrier(0);
+        if (nb0 + FW * wi < nb_rot) {
+#pragma unroll
+          for (int f = 0; f < FW; ++f)
+#pragma unroll
+            for (int p = 0; p < 4; ++p) arrived(in[m & 1][f][p]);
+        }
 #pragma unroll
         for (int f = 0; f < FW; ++f) {
           const int nb = nb0 + FW * wi + f;
