@@ -28,17 +28,19 @@ __global__ __launch_bounds__(256) void silu_check_kernel(uint32_t first, int n, 
                                                          float* __restrict__ got, uint32_t* __restrict__ differ) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i >= n) return;
-  const float x = __uint_as_float(first + (uint32_t)i), y = 1.f + __expf(-x), a = silu_f(x), b = x / y;
+  const uint32_t u = first + (uint32_t)i;
+  const float x = __uint_as_float(u), y = 1.f + __expf(-x), b = x / y, a = fabsf(x) > kFarGate ? b : silu_quick(x);
   if (denominator) denominator[i] = y;
   if (got) got[i] = a;
   if (__float_as_uint(a) != __float_as_uint(b) && !(a != a && b != b)) {
     atomicAdd(differ, 1u);
-    atomicMin(differ + 1, first + (uint32_t)i);
+    atomicMin(differ + 1, u);
   }
 }
 
-// The n fp32 values whose bits are first, first + 1, ...: differ[0] += those whose silu_f is not x / (1 + e^-x) by the
-// IEEE division, bit for bit (two NaN are alike), differ[1] = the least bits of one; denominator, got: device fp32 [n] or NULL
+// The n fp32 values whose bits are first, first + 1, ...: differ[0] += those whose quotient as the epilogues make it is not
+// x / (1 + e^-x) by the IEEE division, bit for bit (two NaN are alike), differ[1] = the least bits of one; denominator, got:
+// device fp32 [n] or NULL
 extern "C" int vlac_silu_check(uint32_t first, int n, float* denominator, float* got, uint32_t* differ, void* stream) {
   if (!differ) return VLAC_E_NULL;
   if (n < 1 || n > (1 << 30)) return VLAC_E_RANGE;

@@ -303,6 +303,7 @@ __device__ __forceinline__ void rows_body(const GemmArgs& a, uint4* lds, RowsWei
 #pragma unroll
     for (int m = 0; m < NA; ++m) ids[m] = a.e.rows[min((rt0 + m) * 32 + (lane & 31), row_end - 1)];
   }
+  [[maybe_unused]] float gates = 0.f;
 #pragma unroll
   for (int m = 0; m < NA; ++m) {
     if (KP == 2 && (m >= (NA + 1) / 2) != (part == 1)) continue;
@@ -319,9 +320,21 @@ __device__ __forceinline__ void rows_body(const GemmArgs& a, uint4* lds, RowsWei
         *(float4*)(dst + 8 * q4) =
             make_float4(acc[m][4 * q4], acc[m][4 * q4 + 1], acc[m][4 * q4 + 2], acc[m][4 * q4 + 3]);
     } else {
-      epilogue_tile<EPI, F16>(a.e, nb, row, ids[m], g, acc[m]);
+      EpiIn<EPI> in;
+      epilogue_load<EPI>(a.e, nb, ids[m], g, in);
+      epilogue_store<EPI, F16>(a.e, nb, row, ids[m], g, acc[m], in);
+      if constexpr (EPI == EPI_SWIGLU) gates = largest_gate(acc[m], gates);
     }
   }
+  if constexpr (EPI == EPI_SWIGLU)
+    if (__builtin_expect(__any(gates > kFarGate), 0)) {
+#pragma unroll
+      for (int m = 0; m < NA; ++m) {
+        const int row = (rt0 + m) * 32 + (lane & 31);
+        if ((KP == 2 && (m >= (NA + 1) / 2) != (part == 1)) || row >= row_end) continue;
+        epilogue_store<EPI, F16, true>(a.e, nb, row, ids[m], g, acc[m], {});
+      }
+    }
 }
 
 // How a row count (in tiles of 32, at most 32 of them) is cut: feature blocks per workgroup and row
@@ -891,10 +904,10 @@ bool gemm_can_fuse_norm(int n_rows_host, int decode_pos, int kpad) {
 // 1069 and 941 us, 448 rows 1211 and 1154, 500 rows 1376 and 1323; grouped queries, 380 rows 589
 // and 472, 500 rows 636 and 578.  Decode passes of many streams, four layers, two tokens of 7B: 353 streams 3404 and 2960,
 // 400 streams 3708 and 3427, 500 streams 4260 and 4077; three tokens of grouped queries: 353 streams
-// 1918 and 1492, 500 streams 2157 and 1933.  (Weights stored as e4m3 codes: the many-rows kernel has
-// no variant for them; up to 1023 rows stay with the one-stream kernel, from 1024 rows on
-// the matrix is expanded to fp16 before every launch, 3 bytes of traffic per weight
-// against the 2 rows flops per weight that such a launch spends on it.)
+// 1918 and 1492, 500 streams 2157 and 1933.  (Weights stored as e4m3 codes: the many-rows kernel
+// multiplies fp16 operands, its instances for such weights only apply the scales to the results; up to 1023 rows stay with
+// the one-stream kernel, from 1024 rows on the matrix is expanded to fp16 before every launch, 3 bytes of traffic per
+// weight against the 2 rows flops per weight that such a launch spends on it.)
 static const int kTallRows = 512;
 static bool use_tall(const vlac_ctx* c, int rows_cap) {
   return c->w8 ? rows_cap >= 1024 && c->wdeq : rows_cap >= kTallRows;

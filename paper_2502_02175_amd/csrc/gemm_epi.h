@@ -62,14 +62,24 @@ __device__ __forceinline__ void read_epilogue_args(const GemmArgs& a) {
   else read_args(a.e.logits, a.e.logits_stride, a.e.best, a.e.vocab);
 }
 
-// x / (1 + e^-x): one step from x times the chip's reciprocal (1 ulp) gives the bits of the IEEE division (for every
-// fp32 value, which a test runs through); the reciprocal is taken of a quarter, because the chip flushes subnormal ones
-// (denominators above 2^126), and the fix-up treats infinities and NaN as the division does.  7 instructions instead of
-// 11: the division was 1400 of the 3600 that a wave of the many-rows kernel spent on a work item of 256 x 256 after
-// its last product.
-__device__ inline float silu_f(float x) {
-  const float e = __expf(-x), y = 1.f + e, r = 0.25f * __builtin_amdgcn_rcpf(fmaf(e, 0.25f, 0.25f)), q = x * r;
-  return __builtin_amdgcn_div_fixupf(fmaf(fmaf(-y, q, x), r, q), y, x);
+// x / (1 + e^-x): one step from x times the chip's reciprocal (1 ulp), whose remainder is exact, gives the bits of the
+// IEEE division for every fp32 value up to kFarGate (a test runs through all of them; the sign of the remainder is such that a
+// negative zero stays one).  Beyond, the reciprocal gets subnormal, which the chip makes 0, and infinities begin.  4
+// instructions instead of 11: the division was 1400 of the 3600 that a wave of the many-rows kernel spent on a work item
+// of 256 x 256 after its last product.
+__device__ inline float silu_quick(float x) {
+  const float y = 1.f + __expf(-x), r = __builtin_amdgcn_rcpf(y), q = x * r;
+  return fmaf(-fmaf(y, q, -x), r, q);
+}
+// The largest gate of a tile is looked for beside the quick quotients (1 instruction for two gates; asm, because fmaxf makes
+// its operands quiet first), and where it is beyond kFarGate the stores are made again with the division.  (A
+// reciprocal of a quarter of the denominator, which serves them too, is 2 instructions more for all: gate/up of grouped
+// queries, 32 x 304 tokens, 1 % slower; a branch ahead of every tile's quotients 3 %.)
+constexpr float kFarGate = 87.f;
+__device__ __forceinline__ float largest_gate(const f32x16& acc, float most = 0.f) {
+#pragma unroll
+  for (int k = 0; k < 8; k += 2) asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(most) : "v"(acc[k]), "v"(acc[k + 1]));
+  return most;
 }
 
 // What an epilogue reads from memory for one tile: rotary factors of a query or key block, residual rows of a
@@ -102,7 +112,8 @@ __device__ __forceinline__ void epilogue_load(const GemmEpi& e, int nb, int id, 
   }
 }
 
-template <int EPI, bool F16>
+// FAR (SwiGLU): with the division
+template <int EPI, bool F16, bool FAR = false>
 __device__ __forceinline__ void epilogue_store(const GemmEpi& e, int nb, int slot, int id, int g,
                                                const f32x16& acc, const EpiIn<EPI>& in) {
   const int b = id >> 16, pos = id & 0xffff;
@@ -177,7 +188,10 @@ __device__ __forceinline__ void epilogue_store(const GemmEpi& e, int nb, int slo
       const int ff = 16 * nb + 8 * q4 + 4 * g;
       float o[4];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) o[k] = silu_f(acc[4 * q4 + k]) * acc[4 * (q4 + 2) + k];
+      for (int k = 0; k < 4; ++k) {
+        const float x = acc[4 * q4 + k];
+        o[k] = (FAR ? x / (1.f + __expf(-x)) : silu_quick(x)) * acc[4 * (q4 + 2) + k];
+      }
       *(uint2*)(e.xf + frag_off(slot, ff, e.kc_f)) =
           make_uint2(pack_op2<F16>(o[0], o[1]), pack_op2<F16>(o[2], o[3]));
     }
@@ -207,6 +221,8 @@ __device__ __forceinline__ void epilogue_tile(const GemmEpi& e, int nb, int slot
   EpiIn<EPI> in;
   epilogue_load<EPI>(e, nb, id, g, in);
   epilogue_store<EPI, F16>(e, nb, slot, id, g, acc, in);
+  if constexpr (EPI == EPI_SWIGLU)
+    if (__builtin_expect(__any(largest_gate(acc) > kFarGate), 0)) epilogue_store<EPI, F16, true>(e, nb, slot, id, g, acc, in);
 }
 
 // gemm_tall.hip: the many-rows kernel with both operands through LDS (its plan: common.h).

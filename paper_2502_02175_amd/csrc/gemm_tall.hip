@@ -402,14 +402,24 @@ __device__ __forceinline__ int tall_body(const GemmArgs& a, uint4* lds, TallItem
         __builtin_amdgcn_sched_barrier(0);
       }
     } else {
+      [[maybe_unused]] float gates = 0.f;
+      auto store = [&](auto far) __attribute__((always_inline)) {
 #pragma unroll
-      for (int m = 0; m < NA; ++m)
-        if (slot_of(m, j) < n_rows) {
+        for (int m = 0; m < NA; ++m)
+          if (slot_of(m, j) < n_rows) {
 #pragma unroll
-          for (int f = 0; f < FW; ++f)
-            if (nb0 + FW * wi + f < a.NB)
-              epilogue_tile<EPI, F16>(a.e, nb0 + FW * wi + f, slot_of(m, j), 0, g, result(f, m));
-        }
+            for (int f = 0; f < FW; ++f)
+              if (nb0 + FW * wi + f < a.NB) {
+                const f32x16 t = result(f, m);
+                if constexpr (EPI == EPI_SWIGLU && !far.value) gates = largest_gate(t, gates);
+                epilogue_store<EPI, F16, far.value>(a.e, nb0 + FW * wi + f, slot_of(m, j), 0, g, t, {});
+              }
+          }
+      };
+      store(std::false_type{});
+      if constexpr (EPI == EPI_SWIGLU)
+        // (one branch per item: between the tiles it would part them)
+        if (__builtin_expect(__any(gates > kFarGate), 0)) store(std::true_type{});
     }
   }
   return slot;
