@@ -29,16 +29,17 @@ __global__ __launch_bounds__(256) void silu_check_kernel(uint32_t first, int n, 
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i >= n) return;
   const uint32_t u = first + (uint32_t)i;
-  const float x = __uint_as_float(u), y = 1.f + __expf(-x), b = x / y, a = fabsf(x) > kFarGate ? b : silu_quick(x);
+  const float x = __uint_as_float(u), y = 1.f + __expf(-x), b = x / y, any = silu_any(x), a = fabsf(x) > kFarGate ? any : silu_quick(x);
   if (denominator) denominator[i] = y;
   if (got) got[i] = a;
-  if (__float_as_uint(a) != __float_as_uint(b) && !(a != a && b != b)) {
+  auto other = [&](float v) { return __float_as_uint(v) != __float_as_uint(b) && !(v != v && b != b); };
+  if (other(a) || other(any)) {
     atomicAdd(differ, 1u);
     atomicMin(differ + 1, u);
   }
 }
 
-// The n fp32 values whose bits are first, first + 1, ...: differ[0] += those whose quotient as the epilogues make it is not
+// The n fp32 values whose bits are first, first + 1, ...: differ[0] += those where a quotient as the epilogues make it is not
 // x / (1 + e^-x) by the IEEE division, bit for bit (two NaN are alike), differ[1] = the least bits of one; denominator, got:
 // device fp32 [n] or NULL
 extern "C" int vlac_silu_check(uint32_t first, int n, float* denominator, float* got, uint32_t* differ, void* stream) {

@@ -65,7 +65,7 @@ def test_conversions_bit_for_bit():
 
 @pytest.mark.gpu
 def test_the_swiglu_quotient_is_the_division_for_every_value():
-    """x / (1 + e^-x) by the chip's reciprocal and one step from it, or by division beyond +-87, over all 2^32 fp32 patterns
+    """x / (1 + e^-x) by the chip's reciprocal and one step from it, with a scaled one beyond +-87, over all 2^32 fp32 patterns
     (signed zeros, subnormals, denominators up to infinity, infinities, NaN), against the compiler's IEEE division in the same kernel; and that
     division against numpy's, over every 4099th value and all of the denominators above 2^126."""
     import torch

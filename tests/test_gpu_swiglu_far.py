@@ -1,5 +1,5 @@
-"""SwiGLU where many gates lie beyond +-87, so that the quick quotient does not serve and the stores are made again with the
-division, and others are small or zero: every kernel with that epilogue (up to 32 rows with one and with several
+"""SwiGLU where many gates lie beyond +-87, so that the quick quotient does not serve and the stores are made again, and
+others are small or zero: every kernel with that epilogue (up to 32 rows with one and with several
 feature blocks, one-stream, many-rows), against the oracle and bit for bit against the build with full waits."""
 import os
 
