@@ -53,7 +53,7 @@ def test_gates_beyond_87(B, L, F, decode, operand):
     finally:
         V.use_library(None)
     assert np.array_equal(hidden, safe[0]) and np.array_equal(logits, safe[1])
-    tol = 2e-2 if operand == "f16" else 1.2e-1  # (activations of 300 instead of 3 x weights of 1 / 32: as elsewhere, and half as much)
+    tol = 2e-2 if operand == "f16" else 8e-2
     for b in range(B):
         cache = O.new_cache(cfg, L + 8)
         want = O.dense_forward(om, emb[b], L - N_TXT, cache)
